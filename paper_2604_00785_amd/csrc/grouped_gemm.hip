@@ -50,6 +50,8 @@
 #include <type_traits>
 #include <utility>
 #include "common.h"
+#include "gemm.h"
+#include "small_gemm.h"
 
 namespace {
 
@@ -1289,16 +1291,25 @@ extern "C" size_t moe_workspace_bytes(int T, int E, int k, int d, int f) {
   return m;
 }
 
-namespace {
 // xp grouped rows, or (row_token not null) the token rows themselves, gathered by the GEMM's loads
-int gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets, const moe_bf16* Wg,
-             const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* g, moe_bf16* u,
-             moe_bf16* h, moe_bf16* yp, void* stream) {
+int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets, const moe_bf16* Wg,
+                 const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* g,
+                 moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
   if (!xp || !expert_offsets || !Wg || !Wu || !Wd || !g || !u || !h || !yp) return MOE_ERR_INVALID;
   if (bad_gemm_dims(E, R_cap, d, f)) return MOE_ERR_INVALID;
   const void* ptrs[] = {xp, expert_offsets, Wg, Wu, Wd, g, u, h, yp};
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  if (rows <= static_cast<long long>(STREAM_ROWS) * E) {
+    StreamFwdArgs p{};
+    p.A = U16(xp); p.row_token = row_token; p.row_weight = row_weight; p.offsets = expert_offsets;
+    p.B0 = U16(Wg); p.B1 = U16(Wu); p.O0 = g; p.O1 = u; p.O2 = h; p.E = E; p.K = d; p.N = f;
+    const int rc = moe_stream_gate_up(p, R_cap, rows, s);
+    if (rc != MOE_OK) return rc;
+    StreamFwdArgs q{};
+    q.A = U16(h); q.offsets = expert_offsets; q.B0 = U16(Wd); q.O0 = yp; q.E = E; q.K = f; q.N = d;
+    return moe_stream_down(q, R_cap, rows, s);
+  }
   const int m_tiles = R_cap / BM + E;
 
   GemmArgs a{};
@@ -1316,6 +1327,7 @@ int gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weig
   return launch_gemm<DOWN>(b, static_cast<long long>(b.n_tiles) * m_tiles, s, "gemm_down");
 }
 
+namespace {
 // byte offsets of gathered rows are 32-bit lane offsets from the start of x (T*width*2 bytes just under 4 GiB at most)
 bool bad_gather(const moe_bf16* x, int T, const int32_t* row_token, int width) {
   return !x || !row_token || T <= 0 || !moe_aligned16(row_token) ||
@@ -1323,35 +1335,46 @@ bool bad_gather(const moe_bf16* x, int T, const int32_t* row_token, int width) {
 }
 }  // namespace
 
+// x, row_token: rows gathered; row_weight (or null): gate weights folded into h.  No expert has more rows than
+// there are tokens, since a token's experts are distinct.
+int moe_gemm_fwd_gather(const moe_bf16* x, int T, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets,
+                        const moe_bf16* Wg, const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int d,
+                        int f, moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
+  if (bad_gather(x, T, row_token, d)) return MOE_ERR_INVALID;
+  const long long most = static_cast<long long>(T) * E;
+  return moe_gemm_fwd(x, row_token, row_weight, expert_offsets, Wg, Wu, Wd, E, R_cap, rows < most ? rows : most, d, f, g, u,
+                      h, yp, stream);
+}
+
 extern "C" int moe_grouped_gemm_fwd(const moe_bf16* xp, const int32_t* expert_offsets, const moe_bf16* Wg,
                                     const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f,
                                     moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
-  return gemm_fwd(xp, nullptr, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, g, u, h, yp, stream);
+  return moe_gemm_fwd(xp, nullptr, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, g, u, h, yp, stream);
 }
 
 extern "C" int moe_grouped_gemm_fwd_gather(const moe_bf16* x, int T, const int32_t* row_token,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
                                            const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* g,
                                            moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
-  if (bad_gather(x, T, row_token, d)) return MOE_ERR_INVALID;
-  return gemm_fwd(x, row_token, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, g, u, h, yp, stream);
+  return moe_gemm_fwd_gather(x, T, row_token, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, g, u, h, yp, stream);
 }
 
 extern "C" int moe_grouped_gemm_fwd_folded(const moe_bf16* x, int T, const int32_t* row_token, const float* row_weight,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
                                            const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* g,
                                            moe_bf16* u, moe_bf16* hw, moe_bf16* ypw, void* stream) {
-  if (bad_gather(x, T, row_token, d) || !row_weight || !moe_aligned16(row_weight)) return MOE_ERR_INVALID;
-  return gemm_fwd(x, row_token, row_weight, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, g, u, hw, ypw, stream);
+  if (!row_weight || !moe_aligned16(row_weight)) return MOE_ERR_INVALID;
+  return moe_gemm_fwd_gather(x, T, row_token, row_weight, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, g, u, hw, ypw,
+                             stream);
 }
 
-namespace {
 // xp grouped rows, or (row_token not null) the token rows themselves, gathered by the loads of the
 // two weight-gradient products that read them
-int gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
-             const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-             const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp, moe_bf16* dWg, moe_bf16* dWu,
-             moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream) {
+int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
+                 const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
+                 const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
+                 moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream) {
+  if (row_token != nullptr && bad_gather(xp, T, row_token, d)) return MOE_ERR_INVALID;
   if (!dyp || !xp || !g || !u || !h || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws)
     return MOE_ERR_INVALID;
   if (bad_gemm_dims(E, R_cap, d, f)) return MOE_ERR_INVALID;
@@ -1394,15 +1417,14 @@ int gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, const int32_t* row_token, 
   if (row_token != nullptr) return launch_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, tiles, s, "gemm_wgrad_gate_up+dgrad_x");
   return launch_gemm_pair<DGRAD_X, WGRAD>(b, w, tiles, s, "gemm_wgrad_gate_up+dgrad_x");
 }
-}  // namespace
 
 extern "C" int moe_grouped_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, const moe_bf16* g, const moe_bf16* u,
                                     const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg,
                                     const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f,
                                     moe_bf16* dxp, moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws,
                                     size_t ws_bytes, void* stream) {
-  return gemm_bwd(dyp, xp, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd, ws,
-                  ws_bytes, stream);
+  return moe_gemm_bwd(dyp, xp, 0, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
+                      ws, ws_bytes, stream);
 }
 
 extern "C" int moe_grouped_gemm_bwd_gather(const moe_bf16* dyp, const moe_bf16* x, int T, const int32_t* row_token,
@@ -1411,9 +1433,9 @@ extern "C" int moe_grouped_gemm_bwd_gather(const moe_bf16* dyp, const moe_bf16* 
                                            const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes,
                                            void* stream) {
-  if (bad_gather(x, T, row_token, d)) return MOE_ERR_INVALID;
-  return gemm_bwd(dyp, x, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd, ws,
-                  ws_bytes, stream);
+  if (row_token == nullptr) return MOE_ERR_INVALID;
+  return moe_gemm_bwd(dyp, x, T, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
+                      ws, ws_bytes, stream);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1444,11 +1466,11 @@ extern "C" size_t moe_grouped_gemm_bwd_folded_workspace_bytes(int R_cap, int f) 
   return moe_grouped_gemm_bwd_workspace_bytes(R_cap, f) + folded_part_bytes(R_cap, f);
 }
 
-extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
+int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
                                            const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-                                           const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
+                                           const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
   if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !dgate ||
@@ -1504,4 +1526,15 @@ extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16*
   // kernel streams its rows with non-temporal loads it no longer depends on that.)
   return launch_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, 2ll * w.n_tiles * w.m_tiles_cap * E + static_cast<long long>(b.n_tiles) * m_tiles,
                                                  s, "gemm_wgrad_gate_up+dgrad_x");
+}
+
+extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
+                                           const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
+                                           const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
+                                           const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
+                                           const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
+                                           moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
+                                           size_t ws_bytes, void* stream) {
+  return moe_gemm_bwd_folded(dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, expert_offsets, Wg, Wu, Wd, E, R_cap,
+                             R_cap, d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
 }
