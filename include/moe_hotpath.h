@@ -326,6 +326,36 @@ int moe_router_bwd(const moe_bf16* x, const float* Wr, const float* dlogits, int
                    moe_bf16* dx, float* dWr, void* ws, size_t ws_bytes, void* stream);
 
 /*
+ * Several stages of one layer with one call: the calls above in the layer's order, on buffers that the caller
+ * laid out once, so that a small step does not spend its time crossing a language boundary a dozen times.
+ * `what` is a sum of MOE_LAYER_ROUTER (moe_router_fwd into logits), MOE_LAYER_FWD (Stages 1-5), MOE_LAYER_BWD
+ * (their derivatives; the forward call's buffers must be as it left them) and MOE_LAYER_ROUTER_BWD (moe_route_bwd,
+ * moe_router_bwd).  `path` chooses the calls: MOE_LAYER_PLAIN (xp is materialised, dyp is used), MOE_LAYER_GATHER
+ * (rows gathered by the products, no xp), MOE_LAYER_FOLD (gate weights folded: h and yp hold hw and ypw; no xp, no
+ * dyp, row_weight is used).  Sizes, buffers and errors are those of the calls; pointers that the chosen stages and
+ * path do not use may be NULL.  A stage that fails leaves the stages before it enqueued.
+ */
+enum { MOE_LAYER_PLAIN = 0, MOE_LAYER_GATHER = 1, MOE_LAYER_FOLD = 2 };
+enum { MOE_LAYER_ROUTER = 1, MOE_LAYER_FWD = 2, MOE_LAYER_BWD = 4, MOE_LAYER_ROUTER_BWD = 8 };
+typedef struct moe_layer {
+  int32_t T, d, E, k, f, e_begin, e_count, renormalize, path, reserved;
+  const moe_bf16 *x, *dout, *Wg, *Wu, *Wd;
+  const float* Wr;
+  float* logits;                  /* read by MOE_LAYER_FWD, written by MOE_LAYER_ROUTER */
+  float *dlogits, *dWr;
+  int32_t* topk_idx;
+  float* topk_w;
+  int32_t *expert_offsets, *row_token, *slot_row;
+  float* row_weight;
+  moe_bf16 *xp, *g, *u, *h, *yp, *out, *dyp, *dxp, *dx;
+  float* dgate;
+  moe_bf16 *dWg, *dWu, *dWd;
+  void* ws;
+  size_t ws_bytes;
+} moe_layer;
+int moe_layer_run(const moe_layer* layer, int what, void* stream);
+
+/*
  * Per-kernel timing for benchmarks (not part of the paper's method).  While
  * enabled, every kernel the library launches is bracketed by two HIP events
  * recorded on the launch stream.  moe_prof_read synchronises on the recorded

@@ -1,0 +1,55 @@
+// The whole layer in one call: what a program would otherwise enqueue through five to twelve calls of the C ABI.
+// Host code only; it adds two things to the calls it makes: one argument check per call instead of one crossing of
+// the language boundary per stage, and the number of experts of the whole layer, from which the expected number of
+// local rows follows (the grouped products by themselves only know the bound T * k).
+#include "gemm.h"
+
+extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
+  if (!L || (what & ~(MOE_LAYER_ROUTER | MOE_LAYER_FWD | MOE_LAYER_BWD | MOE_LAYER_ROUTER_BWD))) return MOE_ERR_INVALID;
+  if (L->path < MOE_LAYER_PLAIN || L->path > MOE_LAYER_FOLD) return MOE_ERR_INVALID;
+  if (L->T <= 0 || L->k <= 0 || L->E <= 0 || L->e_count <= 0 || static_cast<long long>(L->T) * L->k > 0x7FFFFFFFll / 2)
+    return MOE_ERR_INVALID;
+  const int T = L->T, d = L->d, E = L->E, k = L->k, f = L->f, nl = L->e_count, R_cap = T * k;
+  const long long rows = (static_cast<long long>(R_cap) * nl + E - 1) / E;
+  const bool fold = L->path == MOE_LAYER_FOLD, plain = L->path == MOE_LAYER_PLAIN;
+  int rc = MOE_OK;
+  if (what & MOE_LAYER_ROUTER) {
+    if ((rc = moe_router_fwd(L->x, L->Wr, T, d, E, L->logits, stream)) != MOE_OK) return rc;
+  }
+  if (what & MOE_LAYER_FWD) {
+    rc = moe_route_permute(L->logits, plain ? L->x : nullptr, T, d, E, k, L->renormalize, L->e_begin, nl, L->topk_idx, L->topk_w,
+                           L->expert_offsets, L->row_token, L->slot_row, fold ? L->row_weight : nullptr,
+                           plain ? L->xp : nullptr, L->ws, L->ws_bytes, stream);
+    if (rc != MOE_OK) return rc;
+    if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
+    if (plain)
+      rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->g, L->u, L->h,
+                        L->yp, stream);
+    else
+      rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
+                               R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
+    if (rc != MOE_OK) return rc;
+    rc = fold ? moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream)
+              : moe_unpermute_combine(L->yp, L->slot_row, L->topk_w, T, k, d, L->out, stream);
+    if (rc != MOE_OK) return rc;
+  }
+  if (what & MOE_LAYER_BWD) {
+    if (fold) {
+      rc = moe_gemm_bwd_folded(L->dout, L->x, T, k, L->row_token, L->row_weight, L->slot_row, L->g, L->u, L->h,
+                               L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
+                               L->dgate, L->ws, L->ws_bytes, stream);
+    } else {
+      rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
+      if (rc != MOE_OK) return rc;
+      rc = moe_gemm_bwd(L->dyp, plain ? L->xp : L->x, T, plain ? nullptr : L->row_token, L->g, L->u, L->h, L->expert_offsets,
+                        L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
+    }
+    if (rc != MOE_OK) return rc;
+    if ((rc = moe_permute_bwd(L->dxp, L->slot_row, T, k, d, L->dx, stream)) != MOE_OK) return rc;
+  }
+  if (what & MOE_LAYER_ROUTER_BWD) {
+    if ((rc = moe_route_bwd(L->logits, L->topk_idx, L->dgate, T, E, k, L->renormalize, L->dlogits, stream)) != MOE_OK) return rc;
+    rc = moe_router_bwd(L->x, L->Wr, L->dlogits, T, d, E, L->dx, L->dWr, L->ws, L->ws_bytes, stream);
+  }
+  return rc;
+}
