@@ -61,3 +61,11 @@ inline int perm_max_chunks(int e_count) {
 bool moe_launch_route_count(const float* logits, int T, int E, int k, int renormalize, int e_begin, int e_count,
                             int nbits, int32_t* topk_idx, float* topk_w, int32_t* hist, size_t hist_cells, int* chunk,
                             int* nblocks, hipStream_t s);
+
+// Stages 1-3 of a call with at most RS_PAIRS (token, slot) pairs in one launch of one workgroup (route.hip).  Returns
+// false if the call has more pairs, or more tokens than two passes of the workgroup route: then the workgroups of
+// the two-launch form are quicker.
+constexpr int RS_PAIRS = 1024;
+bool moe_launch_route_small(const float* logits, int T, int E, int k, int renormalize, int e_begin, int e_count, int nbits,
+                            int32_t* topk_idx, float* topk_w, int32_t* expert_offsets, int32_t* row_token,
+                            int32_t* slot_row, float* row_weight, hipStream_t s);

@@ -297,6 +297,11 @@ extern "C" int moe_route_permute(const float* logits, const moe_bf16* x, int T, 
   if (bad != MOE_OK) return bad;
   hipStream_t s = static_cast<hipStream_t>(stream);
   const int n = T * k, nbits = expert_bits(e_count);
+  if (moe_launch_route_small(logits, T, E_total, k, renormalize != 0, e_begin, e_count, nbits, topk_idx, topk_w,
+                             expert_offsets, row_token, slot_row, row_weight, s)) {
+    if (xp) launch_rows(x, slot_row, T, d, k, xp, s);
+    return moe_check_launch();
+  }
   int32_t* hist = static_cast<int32_t*>(ws);
   int chunk = 0, nb = 0;
   if (!moe_launch_route_count(logits, T, E_total, k, renormalize != 0, e_begin, e_count, nbits, topk_idx, topk_w, hist,

@@ -50,6 +50,63 @@ template <int G> __device__ __forceinline__ uint64_t group_max_u64(uint64_t best
   return best;
 }
 
+// Selection and gates of one token by a group of G lanes (gl: lane inside the group): val[j] is the logit of expert
+// gl + j G.  Winner i ends up in lane i % G, slot i / G: my_idx its expert, my_w its gate.
+template <int G, int VPL>
+__device__ __forceinline__ void route_token(const float (&val)[VPL], int gl, int E, int k, int renormalize, int (&my_idx)[VPL],
+                                            float (&my_w)[VPL]) {
+  uint64_t key[VPL];
+#pragma unroll
+  for (int j = 0; j < VPL; ++j) {
+    const int e = gl + j * G;
+    // padding keys lie below every real key (real keys have a non-zero low word or high bit)
+    key[j] = e < E ? (static_cast<uint64_t>(ordered_bits(val[j])) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(e)) : 0;
+  }
+  float my_val[VPL];
+#pragma unroll
+  for (int j = 0; j < VPL; ++j) { my_idx[j] = 0; my_val[j] = 0.f; }
+  // full-softmax denominator pieces need the row maximum, which is winner 0
+  float row_max = 0.f;
+  for (int i = 0; i < k; ++i) {
+    uint64_t best = key[0];
+#pragma unroll
+    for (int j = 1; j < VPL; ++j) best = key[j] > best ? key[j] : best;
+    best = group_max_u64<G>(best);
+    const int e = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(best));
+    // the owner retires the key and publishes the value
+    float v = 0.f;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+      if (gl + j * G == e) { v = val[j]; key[j] = 0; }
+    }
+    // exactly one lane of the group holds v != 0-initialised; share it
+    const int owner = e % G;
+    v = __shfl(v, static_cast<int>(threadIdx.x) / G * G % MOE_WAVE + owner, MOE_WAVE);
+    if (i == 0) row_max = v;
+    if (gl == i % G) {
+#pragma unroll
+      for (int j = 0; j < VPL; ++j)
+        if (j == i / G) { my_idx[j] = e; my_val[j] = v; }
+    }
+  }
+  // denominator
+  float part = 0.f;
+  if (renormalize) {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+      if (gl + j * G < k) part += expf(my_val[j] - row_max);
+  } else {
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+      if (gl + j * G < E) part += expf(val[j] - row_max);
+  }
+#pragma unroll
+  for (int m = 1; m < G; m <<= 1) part += __shfl_xor(part, m, MOE_WAVE);
+  const float inv = 1.0f / part;
+#pragma unroll
+  for (int j = 0; j < VPL; ++j) my_w[j] = expf(my_val[j] - row_max) * inv;
+}
+
 // COUNT: also write hist[blockIdx.x][local expert] = winners of this workgroup's tokens per local expert.
 template <int G, int VPL, bool COUNT>
 __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ logits, int T, int E, int k,
@@ -83,61 +140,13 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
   for (int pass = 0; pass < passes; ++pass) {
     const int t = (blockIdx.x * passes + pass) * GROUPS_PER_BLOCK + tid / G;
     const bool live = t < T;
-    uint64_t key[VPL];
     float val[VPL];
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) {
-      const int e = gl + j * G;
-      val[j] = nxt[j];
-      // padding keys lie below every real key (real keys have a non-zero low word or high bit)
-      key[j] = e < E ? (static_cast<uint64_t>(ordered_bits(val[j])) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(e)) : 0;
-    }
+    for (int j = 0; j < VPL; ++j) val[j] = nxt[j];
     if (pass + 1 < passes) load_row(pass + 1, nxt);   // the next pass's logits arrive during this pass's selection
-
-    // full-softmax denominator pieces need the row maximum, which is winner 0
-    int my_idx[VPL];   // winner i is kept by lane i % G in slot i / G
-    float my_val[VPL];
-#pragma unroll
-    for (int j = 0; j < VPL; ++j) { my_idx[j] = 0; my_val[j] = 0.f; }
-    float row_max = 0.f;
-
-    for (int i = 0; i < k; ++i) {
-      uint64_t best = key[0];
-#pragma unroll
-      for (int j = 1; j < VPL; ++j) best = key[j] > best ? key[j] : best;
-      best = group_max_u64<G>(best);
-      const int e = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(best));
-      // the owner retires the key and publishes the value
-      float v = 0.f;
-#pragma unroll
-      for (int j = 0; j < VPL; ++j) {
-        if (gl + j * G == e) { v = val[j]; key[j] = 0; }
-      }
-      // exactly one lane of the group holds v != 0-initialised; share it
-      const int owner = e % G;
-      v = __shfl(v, (tid / G) * G % MOE_WAVE + owner, MOE_WAVE);
-      if (i == 0) row_max = v;
-      if (gl == i % G) {
-#pragma unroll
-        for (int j = 0; j < VPL; ++j)
-          if (j == i / G) { my_idx[j] = e; my_val[j] = v; }
-      }
-    }
-
-    // denominator
-    float part = 0.f;
-    if (renormalize) {
-#pragma unroll
-      for (int j = 0; j < VPL; ++j)
-        if (gl + j * G < k) part += expf(my_val[j] - row_max);
-    } else {
-#pragma unroll
-      for (int j = 0; j < VPL; ++j)
-        if (gl + j * G < E) part += expf(val[j] - row_max);
-    }
-#pragma unroll
-    for (int m = 1; m < G; m <<= 1) part += __shfl_xor(part, m, MOE_WAVE);
-    const float inv = 1.0f / part;
+    int my_idx[VPL];
+    float my_w[VPL];
+    route_token<G, VPL>(val, gl, E, k, renormalize, my_idx, my_w);
 
 #pragma unroll
     for (int j = 0; j < VPL; ++j) {
@@ -145,7 +154,7 @@ __global__ __launch_bounds__(256) void route_kernel(const float* __restrict__ lo
       if (i < k) {
         if (live) {
           topk_idx[static_cast<size_t>(t) * k + i] = my_idx[j];
-          topk_w[static_cast<size_t>(t) * k + i] = expf(my_val[j] - row_max) * inv;
+          topk_w[static_cast<size_t>(t) * k + i] = my_w[j];
         }
       }
     }
@@ -208,6 +217,96 @@ bool launch_route_count(const float* logits, int T, int E, int k, int renorm, in
   return true;
 }
 
+// Stages 1-3 of a call with few tokens in ONE workgroup and launch: routes all tokens, keeps the pairs' local
+// experts in LDS and sorts them there.  Wave w owns pairs 64 w .. 64 w + 63 (at most RS_PAIRS in all): it counts
+// them per expert with the ballots of the counting sort, one thread per expert turns the waves' counts into first
+// rows, and every pair finds its row as permute_place does.  Results are those of the two launches, bit for bit.
+constexpr int RS_THREADS = 1024, RS_WAVES = RS_THREADS / MOE_WAVE;
+template <int G, int VPL>
+__global__ __launch_bounds__(RS_THREADS) void route_small_kernel(const float* __restrict__ logits, int T, int E, int k,
+                                                                int renormalize, int e_begin, int e_count, int nbits,
+                                                                int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
+                                                                int32_t* __restrict__ expert_offsets,
+                                                                int32_t* __restrict__ row_token, int32_t* __restrict__ slot_row,
+                                                                float* __restrict__ row_weight) {
+  constexpr int GROUPS = RS_THREADS / G;
+  __shared__ int s_e[RS_PAIRS];
+  __shared__ float s_w[RS_PAIRS];
+  __shared__ int s_sum[MOE_MAX_EXPERTS / MOE_WAVE];
+  extern __shared__ int s_cnt[];              // [used waves][e_count]
+  const int tid = threadIdx.x, lane = tid % MOE_WAVE, w = tid / MOE_WAVE;
+  const int n = T * k, waves = (n + MOE_WAVE - 1) / MOE_WAVE;
+  const int gl = tid % G;
+  for (int i = tid; i < waves * e_count; i += RS_THREADS) s_cnt[i] = 0;
+  for (int t0 = 0; t0 < T; t0 += GROUPS) {
+    const int t = t0 + tid / G;
+    if (t0 + w * (MOE_WAVE / G) >= T) break;          // the whole wave is past the last token
+    const int tt = t < T ? t : T - 1;
+    float val[VPL];
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+      const int e = gl + j * G;
+      val[j] = e < E ? logits[static_cast<size_t>(tt) * E + e] : 0.f;
+    }
+    int my_idx[VPL];
+    float my_w[VPL];
+    route_token<G, VPL>(val, gl, E, k, renormalize, my_idx, my_w);
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+      const int i = gl + j * G;
+      if (i < k && t < T) {
+        const int p = t * k + i;
+        topk_idx[p] = my_idx[j];
+        topk_w[p] = my_w[j];
+        const int le = my_idx[j] - e_begin;
+        s_e[p] = le < 0 || le >= e_count ? -1 : le;
+        s_w[p] = my_w[j];
+      }
+    }
+  }
+  __syncthreads();
+  // counts of the wave's 64 pairs per expert
+  const int e = tid < n ? s_e[tid] : -1;
+  const uint64_t m = w < waves ? same_expert_mask(e, nbits) : 0;
+  if (m != 0 && lane == __builtin_ctzll(m)) s_cnt[w * e_count + e] = __builtin_popcountll(m);
+  __syncthreads();
+  // thread x < e_count: rows of expert x in front of each wave, and the scan over the experts
+  int total = 0;
+  if (tid < e_count) {
+    for (int v = 0; v < waves; ++v) {
+      const int c = s_cnt[v * e_count + tid];
+      s_cnt[v * e_count + tid] = total;
+      total += c;
+    }
+  }
+  int inc = total;
+#pragma unroll
+  for (int d = 1; d < MOE_WAVE; d <<= 1) {
+    const int o = __shfl_up(inc, d, MOE_WAVE);
+    if (lane >= d) inc += o;
+  }
+  if (lane == MOE_WAVE - 1 && w < MOE_MAX_EXPERTS / MOE_WAVE) s_sum[w] = inc;
+  __syncthreads();
+  if (tid < e_count) {
+    int base = 0;
+    for (int v = 0; v < w; ++v) base += s_sum[v];
+    const int first = base + inc - total;
+    expert_offsets[tid] = first;
+    if (tid == e_count - 1) expert_offsets[e_count] = first + total;
+    for (int v = 0; v < waves; ++v) s_cnt[v * e_count + tid] += first;
+  }
+  __syncthreads();
+  if (tid < n) {
+    int row = -1;
+    if (m != 0) {
+      row = s_cnt[w * e_count + e] + __builtin_popcountll(m & lanemask_lt());
+      row_token[row] = tid / k;
+      if (row_weight != nullptr) row_weight[row] = s_w[tid];
+    }
+    slot_row[tid] = row;
+  }
+}
+
 }  // namespace
 
 bool moe_launch_route_count(const float* logits, int T, int E, int k, int renormalize, int e_begin, int e_count,
@@ -227,6 +326,28 @@ bool moe_launch_route_count(const float* logits, int T, int E, int k, int renorm
   if (E <= 256) return MOE_ROUTE_COUNT(32, 8);
   return MOE_ROUTE_COUNT(64, 8);
 #undef MOE_ROUTE_COUNT
+}
+
+bool moe_launch_route_small(const float* logits, int T, int E, int k, int renormalize, int e_begin, int e_count, int nbits,
+                            int32_t* topk_idx, float* topk_w, int32_t* expert_offsets, int32_t* row_token,
+                            int32_t* slot_row, float* row_weight, hipStream_t s) {
+  if (E > MOE_MAX_EXPERTS || static_cast<long long>(T) * k > RS_PAIRS) return false;
+  // the lane groups of the plain launch (same bits)
+  const int G = E <= 64 ? 8 : E <= 128 ? 16 : E <= 256 ? 32 : 64;
+  if (T > 2 * (RS_THREADS / G)) return false;
+  const size_t lds = static_cast<size_t>((T * k + MOE_WAVE - 1) / MOE_WAVE) * e_count * sizeof(int);
+#define MOE_ROUTE_SMALL(G, VPL)                                                                                            \
+  MOE_LAUNCH("route_small", (route_small_kernel<G, VPL>), dim3(1), dim3(RS_THREADS), lds, s, logits, T, E, k, renormalize, \
+             e_begin, e_count, nbits, topk_idx, topk_w, expert_offsets, row_token, slot_row, row_weight)
+  if (E <= 8) MOE_ROUTE_SMALL(8, 1);
+  else if (E <= 16) MOE_ROUTE_SMALL(8, 2);
+  else if (E <= 32) MOE_ROUTE_SMALL(8, 4);
+  else if (E <= 64) MOE_ROUTE_SMALL(8, 8);
+  else if (E <= 128) MOE_ROUTE_SMALL(16, 8);
+  else if (E <= 256) MOE_ROUTE_SMALL(32, 8);
+  else MOE_ROUTE_SMALL(64, 8);
+#undef MOE_ROUTE_SMALL
+  return true;
 }
 
 extern "C" int moe_route(const float* logits, int T, int E, int k, int renormalize, int32_t* topk_idx,
