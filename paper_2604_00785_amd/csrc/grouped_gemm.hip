@@ -302,7 +302,9 @@ __device__ __forceinline__ const char* scalarize(const char* p) {
 // K steps it has.
 struct TileState {
   int e, m0, m_end, nt, n0;     // expert, first output row, end of the valid rows, column tile, first output column
-  int nv;                       // 32-row groups of this wave's 128 rows that hold a valid row
+  int r0;                       // first of this wave's rows inside the tile
+  int m_wave;                   // end of the valid rows that are this wave's
+  int nv;                       // 32-row groups of this wave's rows that hold a valid row (the others issue no MFMA)
   bool second;                  // tile of the second weight gradient of a pair
   int nk, nk_phase;             // K steps in total / in the first K phase
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
@@ -389,14 +391,20 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   m_end = __builtin_amdgcn_readfirstlane(m_end);
   const int n0 = nt * (MODE == GATE_UP ? BN / 2 : BN);
   t.e = e; t.m0 = m0; t.m_end = m_end; t.nt = nt; t.n0 = n0; t.second = second;
-  // 32-row groups of this wave's 128 rows that hold at least one valid row (the others issue no MFMA)
-  int nv = 4;
+  // The tile's 32-row groups that hold a valid row are shared out evenly: the upper waves take the larger half, so
+  // that a ragged tile keeps both pairs of waves busy for half the time instead of one for all of it.
+  int nv = 4, r0 = wm * 128, m_wave = m_end;
   if constexpr (!is_wgrad(MODE)) {
-    nv = (m_end - m0 - wm * 128 + 31) >> 5;
-    nv = nv < 0 ? 0 : (nv > 4 ? 4 : nv);
-    nv = __builtin_amdgcn_readfirstlane(nv);
+    int groups = (m_end - m0 + 31) >> 5;
+    groups = groups > 8 ? 8 : groups;
+    const int upper = (groups + 1) >> 1;
+    nv = __builtin_amdgcn_readfirstlane(wm == 0 ? upper : groups - upper);
+    r0 = wm * 32 * upper;
+    m_wave = m_end < m0 + r0 + 32 * nv ? m_end : m0 + r0 + 32 * nv;
+    r0 = __builtin_amdgcn_readfirstlane(r0);
+    m_wave = __builtin_amdgcn_readfirstlane(m_wave);
   }
-  t.nv = nv;
+  t.nv = nv; t.r0 = r0; t.m_wave = m_wave;
 
   // ---------------- operand sources -------------------------------------------
   // Per K step and operand tile a wave issues eight direct-to-LDS loads of 1 KB each:
@@ -624,6 +632,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   //    16 g .. 16 g + 15 take k rows 8 g .. of the sub-step.  The k-row swizzle XORs bits 1-2 of the block
   //    number, so the address of block b is base[b / 2] + 32 (b & 1); the second half of a fragment lies
   //    4 k rows = 2048 bytes further, sub-step 1 32 k rows = 16384 bytes further.
+  // The addresses of a row-grouped A operand carry the wave's first row r0, which depends on the tile (a multiple of 32,
+  // so the rotation of the pieces does not see it).
   uint32_t fa_base[3][4], fb_base[3][4];
 #pragma unroll
   for (int st = 0; st < 3; ++st) {
@@ -633,7 +643,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       const int i16 = lane & 15;
       // [row][k]
       const int pc = ((x & 1) * 4 + (lane >> 4) + (lane & 7)) & 7;   // sub-step x & 1; the block is an immediate offset
-      const uint32_t kc_a = org + (wm * 128 + i16) * 128 + pc * 16;
+      const uint32_t kc_a = org + i16 * 128 + pc * 16;   // + 128 r0 of the tile, see main_loop
       const uint32_t kc_b = org + (wn * 128 + i16) * 128 + pc * 16;
       // [k][n]
       const int krow = (lane >> 4) * 8 + (i16 >> 2);
@@ -645,6 +655,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       fb_base[st][x] = B_KN ? kn_b : kc_b;
     }
   }
+  int fa_r0 = 0;                 // the r0 that the A addresses carry
 
   // ---------------- main loop ----------------------------------------------------
   f32x4_t acc[8][8];
@@ -809,6 +820,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
   auto main_loop = [&](TileState& t, auto nv_tag) __attribute__((always_inline)) {
     if (t.nk <= 0) return;
+    if constexpr (!A_KN) {
+#pragma unroll
+      for (int st = 0; st < 3; ++st) {
+        fa_base[st][0] += (t.r0 - fa_r0) * 128;
+        fa_base[st][1] += (t.r0 - fa_r0) * 128;
+      }
+      fa_r0 = t.r0;
+    }
     const int p0 = t.p0, nmain = t.nmain;
     // The tile's first loads are awaited; those of step 1 may stay in flight (the stores of the epilogue before
     // are older than all of them, and loads complete in order among themselves).
@@ -885,7 +904,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   auto fetch_row_weights = [&](const TileState& t, const float* rw) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      int r = t.m0 + wm * 128 + i * 16 + (lane & 15);  if (r > t.m_end - 1) r = t.m_end - 1;
+      int r = t.m0 + t.r0 + i * 16 + (lane & 15);  if (r > t.m_end - 1) r = t.m_end - 1;
       const float* ptr = rw + r;
       asm volatile("global_load_dword %0, %1, off" : "=v"(wv[i]) : "v"(ptr) : "memory");
     }
@@ -896,8 +915,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     int tid = tid0;                           // laundered as in setup_tile
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
-    const int m0 = t.m0, m_end = t.m_end, n0 = t.n0;
-    const int grow0 = m0 + wm * 128;                                     // wave's first output row
+    const int m_end = t.m_wave, n0 = t.n0;                               // end of the wave's valid rows
+    const int grow0 = t.m0 + t.r0;                                       // wave's first output row
     const int gcol0 = n0 + wn * (MODE == GATE_UP ? 64 : 128);            // wave's first output column
     char* stage = lds + wave * 8192;
     // address of the 8 bytes of columns 4 lq .. + 3 of 16-column block `blk` in staged row `row`
@@ -969,6 +988,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       char* hstage = stage + 16 * 256;
       static_for<8>([&](auto i_tag) {
         constexpr int i = decltype(i_tag)::value;
+        if (grow0 + i * 16 >= m_end) return;      // no valid row
         const int row = l16;
         const float w = weighted ? wv[i] : 1.f;
         static_for<4>([&](auto j_tag) {
@@ -1004,11 +1024,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       constexpr bool GATE = (MODE == DGRAD_H_GATE);
       constexpr int GU_PASSES = 4;   // 16 rows x 16 pieces = 256 pieces of 16 bytes, 64 per pass
       constexpr int UOFF = 4096;
+      // read once, in front of the branches below
+      const int ncol = ae->N;
+      const uint16_t* const gsrc = ae->G;
+      const uint16_t* const usrc = ae->U;
+      uint16_t* const dgout = ae->O0;
+      uint16_t* const duout = ae->O1;
       u32x4 pg[GU_PASSES], pu[GU_PASSES];
       auto gu_load = [&](int part) __attribute__((always_inline)) {
-        const int ncol = ae->N;
-        const uint16_t* gsrc = ae->G;
-        const uint16_t* usrc = ae->U;
         const int r0 = grow0 + part * 16;
         if (r0 + 16 <= m_end && gcol0 + 128 <= ncol) {   // wave-uniform: the whole part exists, nothing to clamp
           const size_t o = static_cast<size_t>(r0 + (lane >> 4)) * ncol + gcol0 + (lane & 15) * 8;
@@ -1048,10 +1071,12 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
 #pragma unroll
         for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
       }
+      float dpart[8][2];
+      // (All eight parts, also those without a valid row: any branch around them, tried in three forms, made the launch
+      // 6-15 % slower, whole tiles included.)
       gu_load(0);
       gu_stage(bufs[0]);
       gu_load(1);
-      float dpart[8][2];
       static_for<8>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
         const int first = grow0 + part * 16;
@@ -1112,21 +1137,21 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         __builtin_amdgcn_wave_barrier();
         if constexpr (part + 1 < 8) gu_stage(bufs[(part + 1) & 1]);   // awaits the loads of part + 1
         __builtin_amdgcn_wave_barrier();
-        flush(IC<0>{}, buf, IC<256>{}, ae->O0, ae->N, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ae->N);
-        flush(IC<0>{}, buf + UOFF, IC<256>{}, ae->O1, ae->N, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ae->N);
+        flush(IC<0>{}, buf, IC<256>{}, dgout, ncol, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ncol);
+        flush(IC<0>{}, buf + UOFF, IC<256>{}, duout, ncol, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ncol);
         __builtin_amdgcn_wave_barrier();
         if constexpr (part + 2 < 8) gu_load(part + 2);
       });
       if constexpr (GATE) {
         // the strips' shares of the gate gradient, stored behind everything else (a store in the middle of a
         // part would be one more thing the next wait for loads has to sit out)
-        const int strips = ae->N >> 6;
+        const int strips = ncol >> 6;
         static_for<8>([&](auto part_tag) {
           constexpr int part = decltype(part_tag)::value;
           const int r = grow0 + part * 16 + l16;
 #pragma unroll
           for (int s2 = 0; s2 < 2; ++s2) {
-            if (gcol0 + s2 * 64 < ae->N) {     // a strip past the last column holds repeated columns: no share
+            if (gcol0 + s2 * 64 < ncol) {     // a strip past the last column holds repeated columns: no share
               float* part_out = ae->dgate_part + ((gcol0 >> 6) + s2);
               if (lq == 0 && r < m_end) part_out[static_cast<size_t>(r) * strips] = dpart[part][s2];
             }
@@ -1139,6 +1164,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // four parts of 32 rows
       static_for<4>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
+        if (!is_wgrad(MODE) && grow0 + part * 32 >= m_end) return;   // no valid row
         static_for<2>([&](auto i2_tag) {
           constexpr int i2 = decltype(i2_tag)::value;
           static_for<8>([&](auto j_tag) { put_quad(i2 * 16 + l16, decltype(j_tag)::value, accq(IC<part * 2 + i2>{}, j_tag)); });
@@ -1152,10 +1178,28 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
 
   // ---------------- the tile loop ------------------------------------------------
+  // A workgroup that always took the same place of an XCD's run would meet the same row tile of every expert whose
+  // number of row tiles divides the run, the whole one or the ragged one; so the places move on by one each round
+  // (inside a run, where runs are whole: the list stays covered once).
   int tile = first_tile;
+  // Where experts have few row tiles (three or fewer on average) the launch waits for weights, and an expert with one row
+  // tile needs far more of them per operation than one with many.  The list has the experts with many tiles in
+  // front, so its runs are then taken from its two ends in turn: every round asks memory for about the same (zipf-like
+  // load over 96 experts: gate_up 337 -> 305 us, dgrad_h 418 -> 395 us).  Not with reductions under 16 steps: there the
+  // experts that straddle two runs, fetched twice when the runs are far apart in time, weigh more (down of 128 experts
+  // with 250 rows and 8 steps: 116 -> 124 us), nor with more row tiles (no difference).
+  bool mix = false;
+  if constexpr (!is_wgrad(MODE)) mix = a.K * (MODE == DGRAD_X ? 2 : 1) >= 16 * BK && total <= 3 * a.E * a.n_tiles;
+  auto list_entry = [&](int at) __attribute__((always_inline)) {
+    const int run = static_cast<int>(gridDim.x >> 3);
+    const int b = at / run, whole = total / run;
+    if (b >= whole) return at;
+    const int c = mix ? ((b & 1) ? whole - 1 - (b >> 1) : (b >> 1)) : b;
+    return c * run + (at - b * run + at / static_cast<int>(gridDim.x)) % run;
+  };
   if (tile < total) {
     TileState cur;
-    setup_tile(tile, cur);
+    setup_tile(list_entry(tile), cur);
     first_loads(cur);
     for (;;) {
 #pragma unroll
@@ -1174,7 +1218,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // a wave stages in, and loads into, its own 8 KB of a slot only: no barrier between epilogue and loads
       tile += gridDim.x;
       if (tile >= total) break;
-      setup_tile(tile, cur);
+      setup_tile(list_entry(tile), cur);
       first_loads(cur);
     }
   }
