@@ -929,52 +929,49 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       o.y = pack_bf16(v[2], v[3]);
       *reinterpret_cast<u32x2*>(quad_addr(row, blk)) = o;
     };
-    // Stores ROWS staged rows of RB bytes (pieces swizzled by row & (RB / 16 - 1); region at `base`) to out rows
-    // first_row .. (row stride ld): each row's PIECES 16-byte pieces from piece PIECE0 on go to columns
-    // col0 + 8 piece.  The LDS reads of up to eight passes are issued together, then their stores (one wave per
-    // SIMD: nothing else would cover the latency of a read-then-store chain).  When every row and column of the
-    // block exists (a wave-uniform test) the stores are unconditional and their addresses one add apart;
-    // otherwise each is masked by its row and column.  NT: the output is not read again soon (g and u: not before
-    // the backward pass; dWg and dWu: not by this layer at all), so its stores are marked non-temporal and leave the
-    // caches to what the next kernels read (measured: 0.4-0.6 % of the step, most of it in the kernels that follow).
-    auto flush = [&](auto nt_tag, const char* base, auto rb_tag, uint16_t* out, size_t ld, int first_row, auto rows_tag, auto piece0_tag,
-                     auto pieces_tag, int col0, int ncols) __attribute__((always_inline)) {
-      constexpr int RB = decltype(rb_tag)::value, ROWS = decltype(rows_tag)::value;
-      constexpr bool NT = decltype(nt_tag)::value != 0;
-      typedef unsigned int u32x4_nt __attribute__((ext_vector_type(4)));
-      auto put = [&](char* p, const u32x4& v) __attribute__((always_inline)) {
-        if constexpr (NT) { u32x4_nt w = {v.x, v.y, v.z, v.w}; __builtin_nontemporal_store(w, reinterpret_cast<u32x4_nt*>(p)); }
-        else *reinterpret_cast<u32x4*>(p) = v;
-      };
-      constexpr int PIECE0 = decltype(piece0_tag)::value, PIECES = decltype(pieces_tag)::value;
-      constexpr int RPP = 64 / PIECES, PASSES = ROWS / RPP, SWZ = RB / 16 - 1;
-      const int prow = lane / PIECES, piece = lane % PIECES;
-      const int gc = col0 + piece * 8;
-      const bool whole = first_row + ROWS <= m_end && col0 + PIECES * 8 <= ncols;
-      char* const p0 = reinterpret_cast<char*>(out + static_cast<size_t>(first_row + prow) * ld + gc);
-      const size_t pass_bytes = static_cast<size_t>(RPP) * ld * 2;
-      static_for<(PASSES + 7) / 8>([&](auto b_tag) {
-        constexpr int P0 = decltype(b_tag)::value * 8;
-        constexpr int NB = PASSES - P0 < 8 ? PASSES - P0 : 8;
-        u32x4 v[NB];
+    // Rows are stored (and g, u loaded) through buffer resources that end with the wave's last valid row: what lies past it
+    // is dropped (reads as zero) by the hardware's range check, and a lane whose columns do not exist carries an offset
+    // past every end (the row is part of the lane's offset, which is what the check looks at).  So the whole epilogue is straight-line code, ragged or not.
+    const int ncol = ae->N;
+    int rows = m_end - grow0;
+    rows = rows < 0 ? 0 : (rows > 128 ? 128 : rows);
+    auto rows_of = [&](const void* base, int ld_bytes) __attribute__((always_inline)) {
+      const char* first = scalarize(static_cast<const char*>(base) + static_cast<size_t>(grow0) * ld_bytes);
+      return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, __builtin_amdgcn_readfirstlane(rows * ld_bytes), 0x00020000);
+    };
+    typedef decltype(rows_of(nullptr, 0)) Rsrc;
+    constexpr int PAST = 0x40000000;
+    // PASSES staged passes of 64 / PIECES rows of RB bytes each (16-byte pieces swizzled by row & (RB / 16 - 1), region at
+    // `base`), the PIECES pieces from PIECE0 on of each row: read into registers, and stored from there (first row
+    // `first`, counted from the wave's first) to columns col0 + 8 piece.  NT: the output is not read again soon (g and u: not
+    // before the backward pass; dWg and dWu: not by this layer at all), so its stores are marked non-temporal and leave
+    // the caches to what the next kernels read (measured: 0.4-0.6 % of the step, most of it in the kernels that follow).
+    auto read_staged = [&](u32x4* v, const char* base, auto rb_tag, auto passes_tag, auto piece0_tag, auto pieces_tag)
+        __attribute__((always_inline)) {
+      constexpr int RB = decltype(rb_tag)::value, PASSES = decltype(passes_tag)::value, PIECES = decltype(pieces_tag)::value;
+      constexpr int RPP = 64 / PIECES, SWZ = RB / 16 - 1;
 #pragma unroll
-        for (int k = 0; k < NB; ++k) {
-          const int row = (P0 + k) * RPP + prow;
-          v[k] = *reinterpret_cast<const u32x4*>(base + row * RB + (((PIECE0 + piece) ^ (row & SWZ)) << 4));
-        }
-        if (whole) {
+      for (int k = 0; k < PASSES; ++k) {
+        const int row = k * RPP + lane / PIECES;
+        v[k] = *reinterpret_cast<const u32x4*>(base + row * RB + (((decltype(piece0_tag)::value + lane % PIECES) ^ (row & SWZ)) << 4));
+      }
+    };
+    auto store_rows = [&](auto nt_tag, const u32x4* v, Rsrc out, int first, auto passes_tag, auto pieces_tag)
+        __attribute__((always_inline)) {
+      constexpr int PASSES = decltype(passes_tag)::value, PIECES = decltype(pieces_tag)::value, RPP = 64 / PIECES;
+      const int gc = gcol0 + lane % PIECES * 8;
+      const int off = gc < ncol ? (lane / PIECES * ncol + gc) * 2 : PAST;
 #pragma unroll
-          for (int k = 0; k < NB; ++k) put(p0 + (P0 + k) * pass_bytes, v[k]);
-        } else {
-#pragma unroll
-          for (int k = 0; k < NB; ++k) {
-            const int gr = first_row + (P0 + k) * RPP + prow;
-            if (gr < m_end && gc < ncols) put(p0 + (P0 + k) * pass_bytes, v[k]);
-          }
-        }
-      });
+      for (int k = 0; k < PASSES; ++k)
+        __builtin_amdgcn_raw_buffer_store_b128(v[k], out, off + (first + k * RPP) * ncol * 2, 0, decltype(nt_tag)::value ? 2 : 0);
     };
 
+    // A wave with 96 rows or fewer takes a second copy, which tests in front of every part whether it has a row: the tests
+    // end the overlap, but the parts left out are worth more.
+    // Measured against masked stores issued part by part: gate_up 470 -> 459 us and the launch of dgrad_h 575 -> 560 us at
+    // 65536 rows, d 2048, f 1024, 64 experts; 17 -> 13 and 25 -> 17 us where experts have 56 rows (d 128, f 512).
+    // In every form a part's rows are read back from LDS as soon as they are staged and stored behind the arithmetic of the
+    // part after it: with one wave per SIMD nothing else covers the round trip through LDS.
     if constexpr (MODE == GATE_UP) {
       // blocks 0-3 are g, blocks 4-7 the same columns of u.  Eight parts of 16 rows: g in pieces 0-7 and u in
       // pieces 8-15 of 256-byte rows, h = silu(g) * u (from the fp32 accumulators, times the row's gate weight if
@@ -986,9 +983,18 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
       }
       char* hstage = stage + 16 * 256;
+      const Rsrc go = rows_of(ae->O0, ncol * 2), uo = rows_of(ae->O1, ncol * 2), ho = rows_of(ae->O2, ncol * 2);
+      u32x4 v[6];
+      auto store_part = [&](int part) __attribute__((always_inline)) {
+        store_rows(IC<1>{}, v, go, part * 16, IC<2>{}, IC<8>{});
+        store_rows(IC<1>{}, v + 2, uo, part * 16, IC<2>{}, IC<8>{});
+        store_rows(IC<0>{}, v + 4, ho, part * 16, IC<2>{}, IC<8>{});
+      };
+      auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
+      constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
       static_for<8>([&](auto i_tag) {
         constexpr int i = decltype(i_tag)::value;
-        if (grow0 + i * 16 >= m_end) return;      // no valid row
+        if constexpr (RAGGED) { if (i * 16 >= rows) return; }
         const int row = l16;
         const float w = weighted ? wv[i] : 1.f;
         static_for<4>([&](auto j_tag) {
@@ -1006,51 +1012,34 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
           *reinterpret_cast<u32x2*>(hstage + row * 128 + (((2 * j + (lq >> 1)) ^ (row & 7)) << 4) + (lq & 1) * 8) = o;
         });
         __builtin_amdgcn_wave_barrier();
-        flush(IC<1>{}, stage, IC<256>{}, ae->O0, ae->N, grow0 + i * 16, IC<16>{}, IC<0>{}, IC<8>{}, gcol0, ae->N);
-        flush(IC<1>{}, stage, IC<256>{}, ae->O1, ae->N, grow0 + i * 16, IC<16>{}, IC<8>{}, IC<8>{}, gcol0, ae->N);
-        flush(IC<0>{}, hstage, IC<128>{}, ae->O2, ae->N, grow0 + i * 16, IC<16>{}, IC<0>{}, IC<8>{}, gcol0, ae->N);
+        if constexpr (!RAGGED && i > 0) store_part(i - 1);
+        read_staged(v, stage, IC<256>{}, IC<2>{}, IC<0>{}, IC<8>{});
+        read_staged(v + 2, stage, IC<256>{}, IC<2>{}, IC<8>{}, IC<8>{});
+        read_staged(v + 4, hstage, IC<128>{}, IC<2>{}, IC<0>{}, IC<8>{});
         __builtin_amdgcn_wave_barrier();
+        if constexpr (RAGGED) store_part(i);
       });
+      if constexpr (!RAGGED) store_part(7);
+      };
+      if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
     } else if constexpr (is_dgrad_h(MODE)) {
       // In eight parts of 16 rows, staged alternately in the wave's share of the first and of the second ring
       // slot: g rows at [0, 4K), u rows at [4K, 8K) of the part's buffer, overwritten in place by dg and du.
-      // Order of the memory operations of part p: compute p; await the g/u rows of part p+1 and stage them;
-      // store part p; request the g/u rows of part p+2.  Waiting for loads also waits for every store issued
-      // before them (stores and loads share a counter and complete in no fixed order), so the wait is placed
-      // where the youngest stores are a whole part old, never right behind a part's own stores.
       // DGRAD_H_GATE: the accumulators hold dh0 = dout[token] . Wd; the row's gate weight w turns them into
       // dh = w dh0, and the sum over a 64-column strip of dh0 * silu(g) * u is the strip's share of the
       // gradient of w (a lane holds 16 of the strip's columns of its row, lanes ^ 16, ^ 32 the others).
       constexpr bool GATE = (MODE == DGRAD_H_GATE);
       constexpr int GU_PASSES = 4;   // 16 rows x 16 pieces = 256 pieces of 16 bytes, 64 per pass
       constexpr int UOFF = 4096;
-      // read once, in front of the branches below
-      const int ncol = ae->N;
-      const uint16_t* const gsrc = ae->G;
-      const uint16_t* const usrc = ae->U;
-      uint16_t* const dgout = ae->O0;
-      uint16_t* const duout = ae->O1;
+      const Rsrc gi = rows_of(ae->G, ncol * 2), ui = rows_of(ae->U, ncol * 2);
+      const Rsrc dgo = rows_of(ae->O0, ncol * 2), duo = rows_of(ae->O1, ncol * 2);
       u32x4 pg[GU_PASSES], pu[GU_PASSES];
+      const int gu_off = gcol0 + (lane & 15) * 8 < ncol ? ((lane >> 4) * ncol + gcol0 + (lane & 15) * 8) * 2 : PAST;
       auto gu_load = [&](int part) __attribute__((always_inline)) {
-        const int r0 = grow0 + part * 16;
-        if (r0 + 16 <= m_end && gcol0 + 128 <= ncol) {   // wave-uniform: the whole part exists, nothing to clamp
-          const size_t o = static_cast<size_t>(r0 + (lane >> 4)) * ncol + gcol0 + (lane & 15) * 8;
-          const size_t pass = static_cast<size_t>(4) * ncol;
-#pragma unroll
-          for (int p = 0; p < GU_PASSES; ++p) {
-            pg[p] = *reinterpret_cast<const u32x4*>(gsrc + o + p * pass);
-            pu[p] = *reinterpret_cast<const u32x4*>(usrc + o + p * pass);
-          }
-          return;
-        }
 #pragma unroll
         for (int p = 0; p < GU_PASSES; ++p) {
-          const int row = p * 4 + (lane >> 4), piece = lane & 15;
-          int gr = r0 + row;  if (gr > m_end - 1) gr = m_end - 1;
-          int gc = gcol0 + piece * 8;  if (gc > ncol - 8) gc = ncol - 8;
-          const size_t o = static_cast<size_t>(gr) * ncol + gc;
-          pg[p] = *reinterpret_cast<const u32x4*>(gsrc + o);
-          pu[p] = *reinterpret_cast<const u32x4*>(usrc + o);
+          pg[p] = __builtin_amdgcn_raw_buffer_load_b128(gi, gu_off + (part * 16 + p * 4) * ncol * 2, 0, 0);
+          pu[p] = __builtin_amdgcn_raw_buffer_load_b128(ui, gu_off + (part * 16 + p * 4) * ncol * 2, 0, 0);
         }
       };
       auto gu_stage = [&](char* buf) __attribute__((always_inline)) {
@@ -1071,15 +1060,20 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
 #pragma unroll
         for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
       }
+      u32x4 v[8];
+      auto store_part = [&](int part) __attribute__((always_inline)) {
+        store_rows(IC<0>{}, v, dgo, part * 16, IC<4>{}, IC<16>{});
+        store_rows(IC<0>{}, v + 4, duo, part * 16, IC<4>{}, IC<16>{});
+      };
       float dpart[8][2];
-      // (All eight parts, also those without a valid row: any branch around them, tried in three forms, made the launch
-      // 6-15 % slower, whole tiles included.)
+      auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
+      constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
       gu_load(0);
       gu_stage(bufs[0]);
       gu_load(1);
       static_for<8>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
-        const int first = grow0 + part * 16;
+        if constexpr (RAGGED) { if (part * 16 >= rows) return; }
         char* const buf = bufs[part & 1];
         const float wrow = GATE ? wv[part] : 1.f;
         float dsum[2] = {0.f, 0.f};
@@ -1137,42 +1131,57 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         __builtin_amdgcn_wave_barrier();
         if constexpr (part + 1 < 8) gu_stage(bufs[(part + 1) & 1]);   // awaits the loads of part + 1
         __builtin_amdgcn_wave_barrier();
-        flush(IC<0>{}, buf, IC<256>{}, dgout, ncol, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ncol);
-        flush(IC<0>{}, buf + UOFF, IC<256>{}, duout, ncol, first, IC<16>{}, IC<0>{}, IC<16>{}, gcol0, ncol);
+        if constexpr (!RAGGED && part > 0) store_part(part - 1);
+        read_staged(v, buf, IC<256>{}, IC<4>{}, IC<0>{}, IC<16>{});
+        read_staged(v + 4, buf + UOFF, IC<256>{}, IC<4>{}, IC<0>{}, IC<16>{});
         __builtin_amdgcn_wave_barrier();
+        if constexpr (RAGGED) store_part(part);
         if constexpr (part + 2 < 8) gu_load(part + 2);
       });
+      if constexpr (!RAGGED) store_part(7);
+      };
+      if (rows > 96) parts(IC<0>{}); else if (rows > 0) parts(IC<1>{});
       if constexpr (GATE) {
-        // the strips' shares of the gate gradient, stored behind everything else (a store in the middle of a
-        // part would be one more thing the next wait for loads has to sit out)
+        // the strips' shares of the gate gradient, stored behind everything else
         const int strips = ncol >> 6;
-        static_for<8>([&](auto part_tag) {
-          constexpr int part = decltype(part_tag)::value;
-          const int r = grow0 + part * 16 + l16;
+        const Rsrc dpo = rows_of(ae->dgate_part, strips * 4);
 #pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2) {
-            if (gcol0 + s2 * 64 < ncol) {     // a strip past the last column holds repeated columns: no share
-              float* part_out = ae->dgate_part + ((gcol0 >> 6) + s2);
-              if (lq == 0 && r < m_end) part_out[static_cast<size_t>(r) * strips] = dpart[part][s2];
-            }
-          }
-        });
+        for (int s2 = 0; s2 < 2; ++s2) {
+          // a strip past the last column has no share
+          const int off = lq == 0 && gcol0 + s2 * 64 < ncol ? (l16 * strips + (gcol0 >> 6) + s2) * 4 : PAST;
+          static_for<8>([&](auto part_tag) {
+            constexpr int part = decltype(part_tag)::value;
+            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dpart[part][s2]), dpo, off + part * 16 * strips * 4, 0, 0);
+          });
+        }
       }
     } else {
       uint16_t* out = t.second ? ae->O1 : ae->O0;
-      if constexpr (is_wgrad(MODE)) out += static_cast<size_t>(t.e) * ae->M * ae->N;
+      if constexpr (is_wgrad(MODE)) out += static_cast<size_t>(t.e) * ae->M * ncol;
+      const Rsrc oo = rows_of(out, ncol * 2);
+      u32x4 v[8];
       // four parts of 32 rows
+      auto store_part = [&](int part) __attribute__((always_inline)) {
+        store_rows(IC<(MODE == WGRAD_GATHER) ? 1 : 0>{}, v, oo, part * 32, IC<8>{}, IC<16>{});
+      };
+      auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
+      constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
       static_for<4>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
-        if (!is_wgrad(MODE) && grow0 + part * 32 >= m_end) return;   // no valid row
+        if constexpr (RAGGED) { if (part * 32 >= rows) return; }
         static_for<2>([&](auto i2_tag) {
           constexpr int i2 = decltype(i2_tag)::value;
           static_for<8>([&](auto j_tag) { put_quad(i2 * 16 + l16, decltype(j_tag)::value, accq(IC<part * 2 + i2>{}, j_tag)); });
         });
         __builtin_amdgcn_wave_barrier();
-        flush(IC<(MODE == WGRAD_GATHER) ? 1 : 0>{}, stage, IC<256>{}, out, ae->N, grow0 + part * 32, IC<32>{}, IC<0>{}, IC<16>{}, gcol0, ae->N);
+        if constexpr (!RAGGED && part > 0) store_part(part - 1);
+        read_staged(v, stage, IC<256>{}, IC<8>{}, IC<0>{}, IC<16>{});
         __builtin_amdgcn_wave_barrier();
+        if constexpr (RAGGED) store_part(part);
       });
+      if constexpr (!RAGGED) store_part(3);
+      };
+      if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wave's staging reads are done
   };
@@ -1190,16 +1199,16 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // with 250 rows and 8 steps: 116 -> 124 us), nor with more row tiles (no difference).
   bool mix = false;
   if constexpr (!is_wgrad(MODE)) mix = a.K * (MODE == DGRAD_X ? 2 : 1) >= 16 * BK && total <= 3 * a.E * a.n_tiles;
-  auto list_entry = [&](int at) __attribute__((always_inline)) {
-    const int run = static_cast<int>(gridDim.x >> 3);
-    const int b = at / run, whole = total / run;
-    if (b >= whole) return at;
-    const int c = mix ? ((b & 1) ? whole - 1 - (b >> 1) : (b >> 1)) : b;
-    return c * run + (at - b * run + at / static_cast<int>(gridDim.x)) % run;
+  const int run = static_cast<int>(gridDim.x >> 3);
+  const int whole_runs = total / run;
+  int block = first_tile / run, place = first_tile - block * run;
+  auto list_entry = [&]() __attribute__((always_inline)) {
+    if (block >= whole_runs) return tile;
+    return (mix ? ((block & 1) ? whole_runs - 1 - (block >> 1) : (block >> 1)) : block) * run + place;
   };
   if (tile < total) {
     TileState cur;
-    setup_tile(list_entry(tile), cur);
+    setup_tile(list_entry(), cur);
     first_loads(cur);
     for (;;) {
 #pragma unroll
@@ -1218,7 +1227,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // a wave stages in, and loads into, its own 8 KB of a slot only: no barrier between epilogue and loads
       tile += gridDim.x;
       if (tile >= total) break;
-      setup_tile(list_entry(tile), cur);
+      block += 8;
+      place = place + 1 == run ? 0 : place + 1;
+      setup_tile(list_entry(), cur);
       first_loads(cur);
     }
   }
