@@ -312,7 +312,7 @@ struct TileState {
   bool last_partial;            // weight gradients: the last step holds fewer than 64 rows
   uint32_t voa[8], vob[8];      // lane offsets of the eight loads per operand tile, in bytes
   uint32_t vcb[8];              // gathered operand: lane offset of a load without its token row
-  int tokn[8], tokn1[8];        // gathered operand: tokens of the lane's eight reduction rows of coming steps
+  int tokn[8];                  // gathered operand: tokens of the lane's eight reduction rows of a coming step
   const char* sa_next;          // scalar bases of the next A / B tile to load (LOAD_BIAS low)
   const char* sb_next;
   const char* sa_phase1;        // DGRAD_X: bases of the second K phase
@@ -425,7 +425,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   const int32_t* row_tok = nullptr;     // GATHER_A/B: token of the expert's first reduction row onwards
   uint32_t (&vcb)[8] = t.vcb;           // GATHER_A/B: lane offset of a load without its token row
 #pragma unroll
-  for (int i = 0; i < 8; ++i) { t.vcb[i] = 0; t.tokn[i] = 0; t.tokn1[i] = 0; }
+  for (int i = 0; i < 8; ++i) { t.vcb[i] = 0; t.tokn[i] = 0; }
   int nk, nk_phase;                     // steps in total / in the first K phase
 
   if constexpr (is_wgrad(MODE)) {
@@ -765,58 +765,67 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     lds_wait<0>();
   };
 
-  // The first loads of a tile: steps 0 and 1 into the slots of phases p0 and p0 + 1; awaited when the tile's
-  // main loop starts.  (Requesting them before the epilogue of the tile before, with the epilogue staged in the
-  // one slot they leave free, was built and measured: the loads' latency disappears, 3.5 us per tile, and the
-  // step takes as long as before, because the chip is power-limited and the main loops slow down by what the
-  // idle phases no longer give back.)
+  // The first loads of a tile: steps 0 and 1 into the slots of phases p0 and p0 + 1.  They are requested BEFORE the epilogue
+  // of the tile before, which is staged in the slot that they leave free (spare_slot; the SwiGLU derivative needs two, so
+  // that B(1) waits until it is done), and awaited when the tile's main loop starts.
+  // What a tile waits for between main loops counts where tiles are short: a training step of 2048 tokens (d 2048, f 1024, 64
+  // experts, 4 steps per weight gradient) 885 -> 868 us, the forward of 4001 tokens over 128 experts of f 512 328 -> 322 us;
+  // at 1024 rows per expert and more the chip is power-limited and the step takes as long as before (0-1.5 % less).
+  auto spare_slot = [&](const TileState& t) __attribute__((always_inline)) { return (2 * t.p0 + 4) % NSLOT; };
+  auto slot_m0 = [&](const TileState& t, int unit) __attribute__((always_inline)) {   // units 0..3: A(0), B(0), A(1), B(1)
+    return lds_fill + ((2 * t.p0 + unit) % NSLOT) * TILE_BYTES;
+  };
+  auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
+    set_m0_rt(slot_m0(t, 2 * kt));
+    asm volatile("s_nop 0" ::: "memory");
+    static_for<8>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
+    a_end(t, kt);
+  };
+  auto b_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
+    set_m0_rt(slot_m0(t, 2 * kt + 1));
+    asm volatile("s_nop 0" ::: "memory");
+    static_for<8>([&](auto i) { b_part(t, kt, i, IC<2>{}); });
+    b_end(t, kt);
+  };
   auto first_loads = [&](TileState& t) __attribute__((always_inline)) {
     if (t.nk <= 0) return;
-    const int p0 = t.p0;
-    const int p1 = (p0 + 1) % NSLOT;
-    const uint32_t m_a0 = lds_fill + ((2 * p0) % NSLOT) * TILE_BYTES, m_b0 = lds_fill + ((2 * p0 + 1) % NSLOT) * TILE_BYTES;
-    const uint32_t m_a1 = lds_fill + ((2 * p1) % NSLOT) * TILE_BYTES, m_b1 = lds_fill + ((2 * p1 + 1) % NSLOT) * TILE_BYTES;
-    auto a_unit = [&](int kt, uint32_t m) __attribute__((always_inline)) {
-      set_m0_rt(m);
-      asm volatile("s_nop 0" ::: "memory");
-      static_for<8>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
-      a_end(t, kt);
-    };
-    auto b_unit = [&](int kt, uint32_t m) __attribute__((always_inline)) {
-      set_m0_rt(m);
-      asm volatile("s_nop 0" ::: "memory");
-      static_for<8>([&](auto i) { b_part(t, kt, i, IC<2>{}); });
-      b_end(t, kt);
-    };
-    if constexpr (GATHER_B) {
-      // the tokens of steps 0 and 1 are requested first and are older than the loads of A(0), A(1): one wait for both
-      fetch_tok(t, 0, t.tokn);
-      if (t.nk > 1) fetch_tok(t, 1, t.tokn1);
-      a_unit(0, m_a0);
-      if (t.nk > 1) { a_unit(1, m_a1); wait_vm<16>(); } else { wait_vm<8>(); }
-      apply_tok(t, t.tokn);
-      b_unit(0, m_b0);
-      if (t.nk > 1) { apply_tok(t, t.tokn1); b_unit(1, m_b1); }
-    } else if constexpr (GATHER_A) {
-      fetch_tok(t, 0, t.tokn);
-      if (t.nk > 1) fetch_tok(t, 1, t.tokn1);
-      b_unit(0, m_b0);
-      if (t.nk > 1) { b_unit(1, m_b1); wait_vm<16>(); } else { wait_vm<8>(); }
-      apply_tok(t, t.tokn);
-      a_unit(0, m_a0);
-      if (t.nk > 1) {
-        apply_tok(t, t.tokn1);
-        if (t.nk > 2) fetch_tok(t, 2, t.tokn);   // applied at the start of step 0: older than the loads of A(1)
-        a_unit(1, m_a1);
-      }
+    if constexpr (GATHER_A || GATHER_B) {
+      // The tokens of steps 0, 1 and 2 are requested first, older than the loads of the other operand, and are here before
+      // the epilogue starts: no register that a load has yet to write lives across it.  Rows past the expert's end, and
+      // steps that do not exist, repeat its last row.
+      int tk[3][8];
+      const int last = t.k_hi - t.k_lo - 1;
+      static_for<3>([&](auto s_tag) {
+        constexpr int s = decltype(s_tag)::value;
+        static_for<8>([&](auto i_tag) {
+          constexpr int i = decltype(i_tag)::value;
+          int r = s * BK + (wave * 8 + i) * 2 + (lane >> 5);
+          if (r > last) r = last;
+          tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, t.row_tok);
+        });
+      });
+      if constexpr (GATHER_B) a_unit(t, 0); else b_unit(t, 0);
+      wait_vm<8>();                             // on every path, behind no branch: the compiler does not know of these loads
+#pragma unroll
+      for (int i = 0; i < 24; ++i) asm volatile("" : "+v"(tk[i / 8][i % 8]));
+      if (t.nk > 1) { if constexpr (GATHER_B) a_unit(t, 1); else b_unit(t, 1); }
+      apply_tok(t, tk[0]);
+      if constexpr (GATHER_B) b_unit(t, 0); else a_unit(t, 0);
+      apply_tok(t, tk[1]);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) t.tokn[i] = tk[2][i];
+      if (t.nk > 1) { if constexpr (GATHER_B) b_unit(t, 1); else a_unit(t, 1); }
     } else {
-      b_unit(0, m_b0);
-      a_unit(0, m_a0);
-      if (t.nk > 1) { b_unit(1, m_b1); a_unit(1, m_a1); }
+      b_unit(t, 0);
+      a_unit(t, 0);
+      if (t.nk > 1) {
+        if constexpr (!is_dgrad_h(MODE)) b_unit(t, 1);
+        a_unit(t, 1);
+      }
     }
-    if constexpr (GATHER_B) {
-      if (t.nk > 2) fetch_tok(t, 2, t.tokn);   // applied behind step 0's barrier, whose wait covers it
-    }
+  };
+  auto last_first_loads = [&](TileState& t) __attribute__((always_inline)) {
+    if constexpr (is_dgrad_h(MODE)) { if (t.nk > 1) b_unit(t, 1); }
   };
   auto main_loop = [&](TileState& t, auto nv_tag) __attribute__((always_inline)) {
     if (t.nk <= 0) return;
@@ -829,9 +838,10 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       fa_r0 = t.r0;
     }
     const int p0 = t.p0, nmain = t.nmain;
-    // The tile's first loads are awaited; those of step 1 may stay in flight (the stores of the epilogue before
-    // are older than all of them, and loads complete in order among themselves).
-    if (GATHER_A || GATHER_B || t.nk <= 1) wait_vm<0>(); else wait_vm<16>();
+    // The tile's first loads are awaited; those of step 1 may stay in flight (the last of a gathered operand only: both
+    // steps of the other one come first).  Stores of the epilogue before are in flight too; as loads complete in order
+    // among themselves, the waits here and in the steps hold wherever the stores lie between them.
+    if (t.nk <= 1) wait_vm<0>(); else if (GATHER_A || GATHER_B) wait_vm<8>(); else wait_vm<16>();
     wg_barrier();
     // ---- first fragments: sub-step 0 of step 0, from the slots of phase p0
     constexpr int NV = decltype(nv_tag)::value;
@@ -883,7 +893,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
   // ---------------- epilogue -----------------------------------------------------
   // acc[i][j][c] is the wave's element (row, col) with row = 16 i + (lane & 15) and col = 16 j + 4 (lane / 16) + c.
-  // The wave stages bf16 rows of 256 bytes in 8 KB of LDS of its own (its share of ring slot 0; 16-byte pieces
+  // The wave stages bf16 rows of 256 bytes in 8 KB of LDS of its own (its share of a ring slot; 16-byte pieces
   // swizzled by the row), a few rows at a time, and stores 16 bytes per lane in full row segments.
   // The accumulators are read out of the accumulation registers at the point of use, by hand: left to the
   // compiler they are moved (and spilled) in bulk where the copies of the main loop join.
@@ -898,19 +908,22 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(c3));  v[3] = x;
     return v;
   };
-  // GATE_UP with gate weights folded into h, DGRAD_H_GATE: the weights of the lane's eight rows, requested by
-  // hand right behind the main loop and awaited by hand where the epilogue first needs them.
-  float wv[8];
+  // GATE_UP with gate weights folded into h, DGRAD_H_GATE: the weights of the lane's eight rows, requested
+  // right behind the main loop and awaited before the next tile's first loads are requested.
+  float wv[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
   auto fetch_row_weights = [&](const TileState& t, const float* rw) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       int r = t.m0 + t.r0 + i * 16 + (lane & 15);  if (r > t.m_end - 1) r = t.m_end - 1;
-      const float* ptr = rw + r;
-      asm volatile("global_load_dword %0, %1, off" : "=v"(wv[i]) : "v"(ptr) : "memory");
+      wv[i] = rw[r];
     }
+    asm volatile("" ::: "memory");            // requested here, not where they are used
   };
 
-  auto epilogue = [&](const TileState& t) __attribute__((always_inline)) {
+  // what the epilogue needs of a tile whose successor is set up already (and its first loads in flight: slot, and for the
+  // SwiGLU derivative the one before it, is what they leave free)
+  struct Finished { int e, m0, n0, r0, m_wave, slot; bool second; };
+  auto epilogue = [&](const Finished& t) __attribute__((always_inline)) {
     const ArgPtr ae = reload_args<ARG>();     // the epilogue reads its arguments afresh
     int tid = tid0;                           // laundered as in setup_tile
     asm volatile("" : "+v"(tid));
@@ -918,7 +931,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     const int m_end = t.m_wave, n0 = t.n0;                               // end of the wave's valid rows
     const int grow0 = t.m0 + t.r0;                                       // wave's first output row
     const int gcol0 = n0 + wn * (MODE == GATE_UP ? 64 : 128);            // wave's first output column
-    char* stage = lds + wave * 8192;
+    char* stage = lds + t.slot * TILE_BYTES + wave * 8192;
     // address of the 8 bytes of columns 4 lq .. + 3 of 16-column block `blk` in staged row `row`
     auto quad_addr = [&](int row, int blk) __attribute__((always_inline)) -> char* {
       return stage + row * 256 + (((2 * blk + (lq >> 1)) ^ (row & 15)) << 4) + (lq & 1) * 8;
@@ -977,11 +990,6 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // pieces 8-15 of 256-byte rows, h = silu(g) * u (from the fp32 accumulators, times the row's gate weight if
       // the caller folds the weights into h) in 128-byte rows behind them.
       const bool weighted = ae->row_weight != nullptr;
-      if (weighted) {
-        wait_vm<0>();
-#pragma unroll
-        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
-      }
       char* hstage = stage + 16 * 256;
       const Rsrc go = rows_of(ae->O0, ncol * 2), uo = rows_of(ae->O1, ncol * 2), ho = rows_of(ae->O2, ncol * 2);
       u32x4 v[6];
@@ -1023,8 +1031,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       };
       if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
     } else if constexpr (is_dgrad_h(MODE)) {
-      // In eight parts of 16 rows, staged alternately in the wave's share of the first and of the second ring
-      // slot: g rows at [0, 4K), u rows at [4K, 8K) of the part's buffer, overwritten in place by dg and du.
+      // In eight parts of 16 rows, staged alternately in the wave's share of two ring slots: g rows at [0, 4K), u rows at [4K, 8K) of the part's buffer, overwritten in place by dg and du.
       // DGRAD_H_GATE: the accumulators hold dh0 = dout[token] . Wd; the row's gate weight w turns them into
       // dh = w dh0, and the sum over a 64-column strip of dh0 * silu(g) * u is the strip's share of the
       // gradient of w (a lane holds 16 of the strip's columns of its row, lanes ^ 16, ^ 32 the others).
@@ -1051,15 +1058,10 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
           *reinterpret_cast<u32x4*>(buf + UOFF + so) = pu[p];
         }
       };
-      char* const bufs[2] = {stage, stage + TILE_BYTES};
+      char* const bufs[2] = {stage, lds + (t.slot + NSLOT - 1) % NSLOT * TILE_BYTES + wave * 8192};
       int qoff[8];                  // offsets of the lane's quads in a part's buffer: the same for every part
 #pragma unroll
       for (int j = 0; j < 8; ++j) qoff[j] = static_cast<int>(quad_addr(l16, j) - stage);
-      if constexpr (GATE) {
-        wait_vm<0>();               // the row weights requested behind the main loop
-#pragma unroll
-        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
-      }
       u32x4 v[8];
       auto store_part = [&](int part) __attribute__((always_inline)) {
         store_rows(IC<0>{}, v, dgo, part * 16, IC<4>{}, IC<16>{});
@@ -1211,6 +1213,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     setup_tile(list_entry(), cur);
     first_loads(cur);
     for (;;) {
+      last_first_loads(cur);
 #pragma unroll
       for (int i = 0; i < 8; ++i)
 #pragma unroll
@@ -1219,18 +1222,29 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
           for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
       run_main(cur);
       wg_barrier();                             // every wave is done with the operand tiles
-      if constexpr (MODE == GATE_UP) {
-        if (a.row_weight != nullptr) fetch_row_weights(cur, a.row_weight);
+      bool weighted = (MODE == DGRAD_H_GATE);
+      if constexpr (MODE == GATE_UP) weighted = a.row_weight != nullptr;
+      if constexpr (MODE == GATE_UP || MODE == DGRAD_H_GATE) {
+        if (weighted) fetch_row_weights(cur, a.row_weight);
       }
-      if constexpr (MODE == DGRAD_H_GATE) fetch_row_weights(cur, a.row_weight);
-      epilogue(cur);
-      // a wave stages in, and loads into, its own 8 KB of a slot only: no barrier between epilogue and loads
+      Finished done{cur.e, cur.m0, cur.n0, cur.r0, cur.m_wave, 0, cur.second};
       tile += gridDim.x;
-      if (tile >= total) break;
-      block += 8;
-      place = place + 1 == run ? 0 : place + 1;
-      setup_tile(list_entry(), cur);
-      first_loads(cur);
+      const bool more = tile < total;
+      if (more) {
+        block += 8;
+        place = place + 1 == run ? 0 : place + 1;
+        setup_tile(list_entry(), cur);
+        done.slot = __builtin_amdgcn_readfirstlane(spare_slot(cur));
+      }
+      if constexpr (MODE == GATE_UP || MODE == DGRAD_H_GATE) {
+        // (a use that the compiler sees: left to the epilogue, its wait would cover the first loads too)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
+      }
+      if (more) first_loads(cur);
+      epilogue(done);
+      // a wave stages in, and loads into, its own 8 KB of a slot only: no barrier between epilogue and later loads
+      if (!more) break;
     }
   }
   return tile - total;
