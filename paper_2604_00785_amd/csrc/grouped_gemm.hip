@@ -46,7 +46,8 @@
 // Tiles of the row-grouped products are found on the device from expert_offsets: every wave
 // turns the tile number into (expert, first row, column tile); inside an expert the row tiles are
 // innermost; experts without rows own no tile; rows past an expert's end are clamped on load and
-// masked on store, and 32-row groups without a valid row issue no MFMA.
+// dropped on store by the range check of buffer resources, and 32-row groups without a valid row issue no MFMA.
+#include <climits>
 #include <type_traits>
 #include <utility>
 #include "common.h"
@@ -944,7 +945,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     };
     // Rows are stored (and g, u loaded) through buffer resources that end with the wave's last valid row: what lies past it
     // is dropped (reads as zero) by the hardware's range check, and a lane whose columns do not exist carries an offset
-    // past every end (the row is part of the lane's offset, which is what the check looks at).  So the whole epilogue is straight-line code, ragged or not.
+    // past every end (the row is part of the lane's offset, which is what the check looks at).  So the whole epilogue is
+    // straight-line code, ragged or not.
     const int ncol = ae->N;
     int rows = m_end - grow0;
     rows = rows < 0 ? 0 : (rows > 128 ? 128 : rows);
@@ -953,7 +955,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, __builtin_amdgcn_readfirstlane(rows * ld_bytes), 0x00020000);
     };
     typedef decltype(rows_of(nullptr, 0)) Rsrc;
-    constexpr int PAST = 0x40000000;
+    // as unsigned 2^31: not before the end of 128 rows of any width for which the loads' 32-bit lane offsets suffice, and
+    // still past it with the row of a part added
+    constexpr int PAST = INT_MIN;
     // PASSES staged passes of 64 / PIECES rows of RB bytes each (16-byte pieces swizzled by row & (RB / 16 - 1), region at
     // `base`), the PIECES pieces from PIECE0 on of each row: read into registers, and stored from there (first row
     // `first`, counted from the wave's first) to columns col0 + 8 piece.  NT: the output is not read again soon (g and u: not
@@ -1031,7 +1035,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       };
       if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
     } else if constexpr (is_dgrad_h(MODE)) {
-      // In eight parts of 16 rows, staged alternately in the wave's share of two ring slots: g rows at [0, 4K), u rows at [4K, 8K) of the part's buffer, overwritten in place by dg and du.
+      // In eight parts of 16 rows, staged alternately in the wave's share of two ring slots: g rows at [0, 4K), u rows at
+      // [4K, 8K) of the part's buffer, overwritten in place by dg and du.
       // DGRAD_H_GATE: the accumulators hold dh0 = dout[token] . Wd; the row's gate weight w turns them into
       // dh = w dh0, and the sum over a 64-column strip of dh0 * silu(g) * u is the strip's share of the
       // gradient of w (a lane holds 16 of the strip's columns of its row, lanes ^ 16, ^ 32 the others).
