@@ -479,51 +479,82 @@ class MoELayerBuffers:
         # one workspace for every call of the layer (the router's backward included)
         self.ws = torch.zeros(max(moe_workspace_bytes(T, E, k, d, f), 256), dtype=torch.uint8, device=dev)
         self.logits = self.dlogits = self.dWr = None      # of run_block_fwd_bwd, created on its first call
-        self._bound = self._blob = None
+        if dev.type == "cuda":                            # so that the first pass is like the others
+            for what in (self._FWD, self._FWD + self._BWD):
+                self._plan(what)
 
     # What moe_layer_run reads (struct moe_layer): ten 32-bit sizes, then pointers in this order, then the workspace's
     # size.  The first seven come with the call, the others are the layer's own.
     _ROUTER, _FWD, _BWD, _ROUTER_BWD = 1, 2, 4, 8
-    _SIZES, _ARGS, _OWN = struct.Struct("=10i"), struct.Struct("=7Q"), struct.Struct("=21Q")
+    _SIZES, _ARGS, _OWN = struct.Struct("=10i"), struct.Struct("=7Q"), struct.Struct("=22Q")
+    _ORDER = ("dlogits", "dWr", "topk_idx", "topk_w", "expert_offsets", "row_token", "slot_row", "row_weight", "xp", "g", "u", "h",
+              "yp", "out", "dyp", "dxp", "dx", "dgate", "dWg", "dWu", "dWd", "ws")
 
-    def _own(self):
-        """The layer's sizes and the addresses of its buffers, as they are now."""
-        P = torch.Tensor.data_ptr
-        o = lambda t: 0 if t is None else P(t)
-        return (self.T, self.d, self.E, self.k, self.f, self.e_begin, self.e_count, self.renormalize, self.fold, self.gather,
-                o(self.dlogits), o(self.dWr), P(self.topk_idx), P(self.topk_w), P(self.expert_offsets), P(self.row_token),
-                P(self.slot_row), o(self.row_weight), o(self.xp), P(self.g), P(self.u), P(self.h), P(self.yp), P(self.out),
-                o(self.dyp), P(self.dxp), P(self.dx), P(self.dgate), P(self.dWg), P(self.dWu), P(self.dWd), P(self.ws))
+    # A size or a buffer that is set or taken away: what was checked and written down before no longer counts.
+    def __setattr__(self, name, value):
+        object.__setattr__(self, name, value)
+        if name != "_x":
+            self.__dict__["_plans"] = {}
 
-    def _bind(self, own) -> None:
-        """Check the layer's own buffers and write them down for moe_layer_run: once, and again when one was replaced."""
+    def __delattr__(self, name):
+        object.__delattr__(self, name)
+        self.__dict__["_plans"] = {}
+
+    def _needs(self, what: int) -> set:
+        """The layer's own buffers that these stages read or write; the others may be missing."""
+        n = set()
+        if what & self._ROUTER:
+            n |= {"logits"}
+        if what & self._FWD:
+            n |= {"topk_idx", "topk_w", "expert_offsets", "row_token", "slot_row", "g", "u", "h", "yp", "out", "ws"}
+        if what & self._BWD:
+            n |= {"expert_offsets", "slot_row", "g", "u", "h", "dxp", "dx", "dgate", "dWg", "dWu", "dWd", "ws"}
+            n |= {"row_token"} if self.gather else set()
+            n |= set() if self.fold else {"topk_w", "yp", "dyp"}
+        if what & (self._FWD | self._BWD):
+            n |= {"row_weight"} if self.fold else set()
+            n |= set() if self.gather else {"xp"}
+        if what & self._ROUTER_BWD:
+            n |= {"logits", "topk_idx", "dgate", "dlogits", "dx", "dWr", "ws"}
+        return n
+
+    def _plan(self, what: int):
+        """Check the buffers that these stages use and write them down for moe_layer_run (about 30 us).  Done once for
+        each sum of stages, and again after a buffer was replaced (see __setattr__), moved or resized (see _run)."""
         T, d, E, k, f, nl = self.T, self.d, self.E, self.k, self.f, self.e_count
         R, i32, f32 = T * k, torch.int32, torch.float32
-        want = [("topk_idx", i32, (T, k)), ("topk_w", f32, (T, k)), ("expert_offsets", i32, (nl + 1,)), ("row_token", i32, (R,)),
-                ("slot_row", i32, (T, k)), ("g", BF16, (R, f)), ("u", BF16, (R, f)), ("h", BF16, (R, f)), ("yp", BF16, (R, d)),
-                ("out", BF16, (T, d)), ("dxp", BF16, (R, d)), ("dx", BF16, (T, d)), ("dgate", f32, (T, k)),
-                ("dWg", BF16, (nl, f, d)), ("dWu", BF16, (nl, f, d)), ("dWd", BF16, (nl, d, f)), ("ws", None, None)]
-        want += [("row_weight", f32, (R,))] if self.fold else [("dyp", BF16, (R, d))]
-        want += [] if self.gather else [("xp", BF16, (R, d))]
-        want += [] if self.dWr is None else [("logits", f32, (T, E)), ("dlogits", f32, (T, E)), ("dWr", f32, (E, d))]
-        for name, dtype, shape in want:
-            t = getattr(self, name)
-            if dtype is not None:
-                _want(t, dtype, shape, name)
-            _p(t)
-        s, a = self._SIZES, self._ARGS
-        blob = ctypes.create_string_buffer(s.size + a.size + self._OWN.size + 8 + 8)
-        s.pack_into(blob, 0, T, d, E, k, f, self.e_begin, nl, self.renormalize, 2 if self.fold else 1 if self.gather else 0, 0)
-        # struct order: the call's seven pointers, dlogits, dWr, and so on to dgate, the weight gradients, ws
-        self._OWN.pack_into(blob, s.size + a.size, *own[10:31])
-        struct.pack_into("=QQ", blob, s.size + a.size + self._OWN.size, own[31], self.ws.numel() * self.ws.element_size())
-        self._blob, self._bound = blob, own
-        self._blob_at = ctypes.addressof(blob)
+        want = {"topk_idx": (i32, (T, k)), "topk_w": (f32, (T, k)), "expert_offsets": (i32, (nl + 1,)), "row_token": (i32, (R,)),
+                "slot_row": (i32, (T, k)), "row_weight": (f32, (R,)), "xp": (BF16, (R, d)), "g": (BF16, (R, f)),
+                "u": (BF16, (R, f)), "h": (BF16, (R, f)), "yp": (BF16, (R, d)), "out": (BF16, (T, d)), "dyp": (BF16, (R, d)),
+                "dxp": (BF16, (R, d)), "dx": (BF16, (T, d)), "dgate": (f32, (T, k)), "dWg": (BF16, (nl, f, d)),
+                "dWu": (BF16, (nl, f, d)), "dWd": (BF16, (nl, d, f)), "logits": (f32, (T, E)), "dlogits": (f32, (T, E)),
+                "dWr": (f32, (E, d))}
+        bufs = {name: getattr(self, name) for name in self._needs(what)}
+        for name, t in bufs.items():
+            if name != "ws" and (t.dtype is not want[name][0] or t.shape != want[name][1]):
+                _want(t, *want[name], name)
+            if not t.is_cuda or not t.is_contiguous():
+                _p(t)
+        blob = ctypes.create_string_buffer(self._SIZES.size + self._ARGS.size + self._OWN.size + 8)
+        self._SIZES.pack_into(blob, 0, T, d, E, k, f, self.e_begin, nl, self.renormalize,
+                              2 if self.fold else 1 if self.gather else 0, 0)
+        ws = bufs.get("ws")
+        self._OWN.pack_into(blob, self._SIZES.size + self._ARGS.size,
+                            *[bufs[n].data_ptr() if n in bufs else 0 for n in self._ORDER])
+        ctypes.c_size_t.from_buffer(blob, len(blob) - 8).value = 0 if ws is None else ws.numel() * ws.element_size()
+        ts = list(bufs.values())
+        plan = self._plans[what] = (blob, ctypes.addressof(blob), ts, self._state(ts))
+        return plan
+
+    @staticmethod
+    def _state(ts):
+        return [*map(torch.Tensor.data_ptr, ts), *map(torch.Tensor.numel, ts)]
 
     def _run(self, what: int, x, logits, dout, Wg, Wu, Wd, Wr) -> None:
-        own = self._own()
-        if own != self._bound:
-            self._bind(own)
+        plan = self._plans.get(what)
+        if plan is None or self._state(plan[2]) != plan[3]:
+            plan = self._plan(what)
+        blob, blob_at = plan[0], plan[1]
         T, d, nl, f = self.T, self.d, self.e_count, self.f
         at = [0, 0, 0, 0, 0, 0, 0]
         for i, t, dtype, shape, name in ((0, x, BF16, (T, d), "x"), (1, dout, BF16, (T, d), "dout"), (2, Wg, BF16, (nl, f, d), "Wg"),
@@ -536,8 +567,8 @@ class MoELayerBuffers:
                 if not t.is_cuda or not t.is_contiguous():
                     _p(t)
                 at[i] = t.data_ptr()
-        self._ARGS.pack_into(self._blob, 40, *at)
-        rc = load().moe_layer_run(self._blob_at, what, _stream())
+        self._ARGS.pack_into(blob, 40, *at)
+        rc = load().moe_layer_run(blob_at, what, _stream())
         if rc != 0:
             _check(rc, "moe_layer_run")
 
