@@ -520,7 +520,7 @@ class MoELayerBuffers:
 
     def _plan(self, what: int):
         """Check the buffers that these stages use and write them down for moe_layer_run (about 30 us).  Done once for
-        each sum of stages, and again after a buffer was replaced (see __setattr__), moved or resized (see _run)."""
+        each sum of stages, and again after a buffer was replaced (see __setattr__) or changed in place (see _state)."""
         T, d, E, k, f, nl = self.T, self.d, self.E, self.k, self.f, self.e_count
         R, i32, f32 = T * k, torch.int32, torch.float32
         want = {"topk_idx": (i32, (T, k)), "topk_w": (f32, (T, k)), "expert_offsets": (i32, (nl + 1,)), "row_token": (i32, (R,)),
@@ -546,9 +546,13 @@ class MoELayerBuffers:
         plan = self._plans[what] = (blob, ctypes.addressof(blob), ts, self._state(ts))
         return plan
 
-    @staticmethod
-    def _state(ts):
-        return [*map(torch.Tensor.data_ptr, ts), *map(torch.Tensor.numel, ts)]
+    # All that a check of these buffers looks at: t_() and a resize_ to another shape keep address and element count, an
+    # assignment to .data may keep both and change the type (11 us for the 22 buffers of a training step).
+    _shape, _dtype = torch.Tensor.shape.__get__, torch.Tensor.dtype.__get__
+
+    @classmethod
+    def _state(cls, ts):
+        return [*map(torch.Tensor.data_ptr, ts), *map(torch.Tensor.is_contiguous, ts), *map(cls._shape, ts), *map(cls._dtype, ts)]
 
     def _run(self, what: int, x, logits, dout, Wg, Wu, Wd, Wr) -> None:
         plan = self._plans.get(what)

@@ -40,6 +40,18 @@ def test_replaced_buffers(path):
     with pytest.raises(B.MoeError):
         step()
     m.h.resize_(shape)
+    # refused, though address and element count are the same: other strides, another shape
+    for name in ("out", "dxp", "topk_w"):
+        t = getattr(m, name)
+        shape = t.shape
+        t.t_()
+        with pytest.raises(B.MoeError):
+            step()
+        t.t_()
+        t.resize_(shape[1], shape[0])
+        with pytest.raises(B.MoeError):
+            step()
+        t.resize_(shape)
     # a new buffer is the one that is written
     old = m.out
     old.fill_(7.0)
