@@ -34,6 +34,7 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if (rc != MOE_OK) return rc;
   }
   if (what & MOE_LAYER_BWD) {
+    if (!plain && !L->row_token) return MOE_ERR_INVALID;   // without it moe_gemm_bwd would take x for T * k grouped rows
     if (fold) {
       rc = moe_gemm_bwd_folded(L->dout, L->x, T, k, L->row_token, L->row_weight, L->slot_row, L->g, L->u, L->h,
                                L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,

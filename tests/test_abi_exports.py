@@ -118,3 +118,38 @@ def test_moe_workspace_bytes_covers_every_call():
         assert total == max(parts.values())
     assert B.moe_workspace_bytes(8192, 64, 8, 2048, 1024) == B.moe_grouped_gemm_bwd_folded_workspace_bytes(65536, 1024)
     assert B.moe_workspace_bytes(8192, 64, 1, 4096, 64) == B.moe_router_bwd_workspace_bytes(8192, 4096, 64)
+
+
+def test_layer_run_refuses_bad_arguments_on_the_host():
+    """``moe_layer_run`` returns before it launches anything: NULL layer, unknown stages, unknown path, bad sizes, and
+    every buffer that the first call of a stage needs.  (The addresses are made up; nothing reads them.)"""
+    import ctypes
+    L = B.MoELayerBuffers
+    args = ["x", "dout", "Wg", "Wu", "Wd", "Wr", "logits"]
+    names = args + list(L._ORDER)
+
+    def run(what, path=0, missing=(), T=64, d=64, E=8, k=2, f=64, nl=8, ws_bytes=1 << 20):
+        at = [0 if n in missing else 4096 * (i + 1) for i, n in enumerate(names)]
+        blob = ctypes.create_string_buffer(L._SIZES.pack(T, d, E, k, f, 0, nl, 1, path, 0) + L._ARGS.pack(*at[:7]) +
+                                           L._OWN.pack(*at[7:]) + ws_bytes.to_bytes(8, "little"))
+        return B.load().moe_layer_run(ctypes.addressof(blob), what, None)
+
+    assert B.load().moe_layer_run(None, 2, None) == -1
+    assert run(16) == -1 and run(-1) == -1
+    assert run(2, path=-1) == -1 and run(2, path=3) == -1
+    for bad in (dict(T=0), dict(k=0), dict(E=0), dict(nl=0), dict(T=1 << 30, k=4), dict(nl=9)):
+        assert run(2, **bad) == -1, bad
+    for n in ("x", "Wr", "logits"):
+        assert run(1, missing=[n]) == -1, n
+    for path in (0, 1, 2):
+        for n in ("logits", "topk_idx", "topk_w", "expert_offsets", "row_token", "slot_row", "ws"):
+            assert run(2, path, [n]) == -1, (path, n)
+    for path, need in ((0, ("dout", "yp", "slot_row", "topk_w", "dyp", "dgate")),
+                       (1, ("dout", "yp", "slot_row", "topk_w", "dyp", "dgate", "row_token")),
+                       (2, ("dout", "x", "row_token", "row_weight", "slot_row", "g", "u", "h", "expert_offsets", "Wg", "Wu", "Wd",
+                            "dxp", "dWg", "dWu", "dWd", "dgate", "ws"))):
+        for n in need:
+            assert run(4, path, [n]) == -1, (path, n)
+    for n in ("logits", "topk_idx", "dgate", "dlogits"):
+        assert run(8, missing=[n]) == -1, n
+    assert run(4, 2, ws_bytes=256) == -2
