@@ -500,6 +500,13 @@ class MoELayerBuffers:
         object.__delattr__(self, name)
         self.__dict__["_plans"] = {}
 
+    # A plan holds the address of its own memory: a copy, or a layer read from a file, starts without any.
+    def __getstate__(self):
+        return {n: v for n, v in self.__dict__.items() if n != "_plans"}
+
+    def __setstate__(self, state):
+        self.__dict__.update(state, _plans={})
+
     def _needs(self, what: int) -> set:
         """The layer's own buffers that these stages read or write; the others may be missing."""
         n = set()

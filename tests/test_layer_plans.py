@@ -1,4 +1,7 @@
 """What MoELayerBuffers writes down about its buffers, as far as that shows without a GPU."""
+import copy
+import pickle
+
 import pytest
 import torch
 
@@ -19,3 +22,14 @@ def test_in_place_changes_are_seen(change):
     change(ts[1])
     assert ts[1].data_ptr() == at
     assert B.MoELayerBuffers._state(ts) != before
+
+
+@pytest.mark.parametrize("again", [copy.copy, copy.deepcopy, lambda m: pickle.loads(pickle.dumps(m))])
+def test_copies_start_without_plans(again):
+    m = B.MoELayerBuffers(8, 64, 4, 2, 64, device="cpu")
+    m._plans[2] = ("memory", 4096, [], [])
+    c = again(m)
+    assert c._plans == {} and m._plans[2][1] == 4096
+    assert torch.equal(c.out, m.out) and c.k == 2
+    c.out = torch.ones(8, 64)
+    assert m._plans and not torch.equal(c.out, m.out)
