@@ -478,10 +478,11 @@ class MoELayerBuffers:
         self.dWg, self.dWu, self.dWd = z(nl, f, d), z(nl, f, d), z(nl, d, f)
         # one workspace for every call of the layer (the router's backward included)
         self.ws = torch.zeros(max(moe_workspace_bytes(T, E, k, d, f), 256), dtype=torch.uint8, device=dev)
-        self.logits = self.dlogits = self.dWr = None      # of run_block_fwd_bwd, created on its first call
         if dev.type == "cuda":                            # so that the first pass is like the others
             for what in (self._FWD, self._FWD + self._BWD):
                 self._plan(what)
+
+    logits = dlogits = dWr = None      # of run_block_fwd_bwd: created on its first call, and again after a del
 
     # What moe_layer_run reads (struct moe_layer): ten 32-bit sizes, then pointers in this order, then the workspace's
     # size.  The first seven come with the call, the others are the layer's own.

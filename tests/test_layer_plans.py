@@ -33,3 +33,15 @@ def test_copies_start_without_plans(again):
     assert torch.equal(c.out, m.out) and c.k == 2
     c.out = torch.ones(8, 64)
     assert m._plans and not torch.equal(c.out, m.out)
+
+
+def test_block_buffers_come_back_after_a_del():
+    """The logits of the drop-in block are created where there are none: in a new layer, after a ``del``, and in a layer
+    whose pickle predates them.  (The call itself is refused on host tensors.)"""
+    m = B.MoELayerBuffers(8, 64, 4, 2, 64, device="cpu")
+    x = torch.zeros(8, 64, dtype=torch.bfloat16)
+    for _ in range(2):
+        with pytest.raises(B.MoeError):
+            m.run_block_fwd_bwd(x, torch.zeros(4, 64), x, m.dWg, m.dWu, m.dWd)
+        assert m.logits.shape == (8, 4) and m.dlogits.shape == (8, 4) and m.dWr.shape == (4, 64)
+        del m.logits
