@@ -584,16 +584,22 @@ class MoELayerBuffers:
         if rc != 0:
             _check(rc, "moe_layer_run")
 
+    def _keep(self, x) -> None:
+        """The backward of the gathered and folded forms reads the input of the last pass again; the plain form has its
+        rows in xp and does not keep the caller's tensor alive."""
+        if self.gather:
+            self._x = x
+
     def run_fwd(self, x, logits, Wg, Wu, Wd) -> None:
-        self._x = x              # the backward of the gathered and folded forms reads the layer input again
         self._run(self._FWD, x, logits, None, Wg, Wu, Wd, None)
+        self._keep(x)
 
     def run_bwd(self, dout, Wg, Wu, Wd) -> None:
         self._run(self._BWD, self._x if self.gather else None, None, dout, Wg, Wu, Wd, None)
 
     def run_fwd_bwd(self, x, logits, dout, Wg, Wu, Wd) -> None:
-        self._x = x
         self._run(self._FWD + self._BWD, x, logits, dout, Wg, Wu, Wd, None)
+        self._keep(x)
 
     def run_block_fwd_bwd(self, x, Wr, dout, Wg, Wu, Wd) -> None:
         """The layer as a drop-in block: the router's Linear layer in front (logits from ``x`` and
@@ -605,9 +611,9 @@ class MoELayerBuffers:
             self.logits = torch.zeros(self.T, self.E, dtype=torch.float32, device=dev)
             self.dlogits = torch.zeros(self.T, self.E, dtype=torch.float32, device=dev)
             self.dWr = torch.zeros(self.E, self.d, dtype=torch.float32, device=dev)
-        self._x = x
         # the layer's one workspace is free again when the router's backward uses it
         self._run(self._ROUTER + self._FWD + self._BWD + self._ROUTER_BWD, x, self.logits, dout, Wg, Wu, Wd, Wr)
+        self._keep(x)
 
     def capture_fwd_bwd(self, x, logits, dout, Wg, Wu, Wd) -> "torch.cuda.CUDAGraph":
         """Record ``run_fwd_bwd`` on these buffers and arguments into a HIP graph.

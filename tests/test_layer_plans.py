@@ -45,3 +45,24 @@ def test_block_buffers_come_back_after_a_del():
             m.run_block_fwd_bwd(x, torch.zeros(4, 64), x, m.dWg, m.dWu, m.dWd)
         assert m.logits.shape == (8, 4) and m.dlogits.shape == (8, 4) and m.dWr.shape == (4, 64)
         del m.logits
+
+
+@pytest.mark.parametrize("form", ["plain", "gather", "fold"])
+def test_input_is_kept_only_for_a_backward_that_reads_it(form, monkeypatch):
+    m = B.MoELayerBuffers(8, 64, 4, 2, 64, device="cpu", gather=form == "gather", fold=form == "fold")
+    ran = []
+    monkeypatch.setattr(B.MoELayerBuffers, "_run", lambda self, *a: ran.append(a[1]))
+    x = [torch.zeros(8, 64, dtype=torch.bfloat16) for _ in range(3)]
+    w = m.dWg, m.dWu, m.dWd
+    for step in (lambda: m.run_fwd(x[0], None, *w), lambda: m.run_fwd_bwd(x[1], None, x[0], *w),
+                 lambda: m.run_block_fwd_bwd(x[2], None, x[0], *w)):
+        step()
+        m.run_bwd(x[0], *w)
+        assert ran[-1] is (None if form == "plain" else ran[-2])
+    # a pass that is refused leaves the input of the pass before
+    def refuse(self, *a):
+        raise B.MoeError("refused")
+    monkeypatch.setattr(B.MoELayerBuffers, "_run", refuse)
+    with pytest.raises(B.MoeError):
+        m.run_fwd(x[0], None, *w)
+    assert getattr(m, "_x", None) is (None if form == "plain" else x[2])
