@@ -544,8 +544,6 @@ class MoELayerBuffers:
             if not t.is_cuda or not t.is_contiguous():
                 _p(t)
         blob = ctypes.create_string_buffer(self._SIZES.size + self._ARGS.size + self._OWN.size + 8)
-        self._SIZES.pack_into(blob, 0, T, d, E, k, f, self.e_begin, nl, self.renormalize,
-                              2 if self.fold else 1 if self.gather else 0, 0)
         ws = bufs.get("ws")
         self._OWN.pack_into(blob, self._SIZES.size + self._ARGS.size,
                             *[bufs[n].data_ptr() if n in bufs else 0 for n in self._ORDER])
@@ -558,6 +556,9 @@ class MoELayerBuffers:
     # assignment to .data may keep both and change the type (11 us for the 22 buffers of a training step).
     _shape, _dtype = torch.Tensor.shape.__get__, torch.Tensor.dtype.__get__
 
+    def _path(self) -> int:
+        return 2 if self.fold else 1 if self.gather else 0
+
     @classmethod
     def _state(cls, ts):
         return [*map(torch.Tensor.data_ptr, ts), *map(torch.Tensor.is_contiguous, ts), *map(cls._shape, ts), *map(cls._dtype, ts)]
@@ -567,18 +568,28 @@ class MoELayerBuffers:
         if plan is None or self._state(plan[2]) != plan[3]:
             plan = self._plan(what)
         blob, blob_at = plan[0], plan[1]
-        T, d, nl, f = self.T, self.d, self.e_count, self.f
+        T, d, nl, f, E = self.T, self.d, self.e_count, self.f, self.E
+        router = what & (self._ROUTER | self._ROUTER_BWD)
+        # Where no other buffer has to match them, x may have rows behind the T that are used (a batch in a larger buffer),
+        # and the logits more or fewer columns than the E that the workspace was laid out for (moe_layer_run checks them).
+        if x is not None and not router and not (self.fold and what & self._BWD) and x.dim() == 2 and x.shape[0] > T:
+            x_shape = (x.shape[0], d)
+        else:
+            x_shape = (T, d)
+        if logits is not None and not router and logits.dim() == 2:
+            E = logits.shape[1]
         at = [0, 0, 0, 0, 0, 0, 0]
-        for i, t, dtype, shape, name in ((0, x, BF16, (T, d), "x"), (1, dout, BF16, (T, d), "dout"), (2, Wg, BF16, (nl, f, d), "Wg"),
+        for i, t, dtype, shape, name in ((0, x, BF16, x_shape, "x"), (1, dout, BF16, (T, d), "dout"), (2, Wg, BF16, (nl, f, d), "Wg"),
                                          (3, Wu, BF16, (nl, f, d), "Wu"), (4, Wd, BF16, (nl, d, f), "Wd"),
-                                         (5, Wr, torch.float32, (self.E, d), "Wr"),
-                                         (6, logits, torch.float32, (T, self.E), "logits")):
+                                         (5, Wr, torch.float32, (E, d), "Wr"),
+                                         (6, logits, torch.float32, (T, E), "logits")):
             if t is not None:
                 if t.dtype is not dtype or t.shape != shape:
                     _want(t, dtype, shape, name)
                 if not t.is_cuda or not t.is_contiguous():
                     _p(t)
                 at[i] = t.data_ptr()
+        self._SIZES.pack_into(blob, 0, T, d, E, self.k, f, self.e_begin, nl, self.renormalize, self._path(), 0)
         self._ARGS.pack_into(blob, 40, *at)
         rc = load().moe_layer_run(blob_at, what, _stream())
         if rc != 0:

@@ -66,3 +66,32 @@ def test_replaced_buffers(path):
     m.out.zero_()
     m.run_fwd(a["x"], a["logits"], *w)
     assert torch.equal(m.out, want["out"])
+
+
+@pytest.mark.parametrize("path", ["plain", "gather", "fold"])
+def test_wider_arguments(path):
+    """x may lie in front of other rows, and the logits may have columns that the layer was not laid out for, where no other
+    buffer has to match them; fewer rows of x than tokens are refused."""
+    m, a, w = _layer(path)
+    m.run_fwd(a["x"], a["logits"], *w)
+    want = {n: getattr(m, n).clone() for n in ("topk_idx", "topk_w", "out")}
+    longer = torch.cat([a["x"], torch.full_like(a["x"][:5], float("nan"))])
+    wider = torch.cat([a["logits"], torch.full_like(a["logits"][:, :3], -1e30)], 1)
+    m.out.zero_()
+    m.run_fwd(longer, wider, *w)
+    for n, t in want.items():
+        assert torch.equal(getattr(m, n), t), n
+    if path == "fold":                   # its backward reads dout by the token too, and wants both of one size
+        with pytest.raises(B.MoeError):
+            m.run_bwd(a["dout"], *w)
+    else:
+        m.run_fwd_bwd(a["x"], a["logits"], a["dout"], *w)
+        grads = {n: getattr(m, n).clone() for n in ("dx", "dgate", "dWg", "dWu", "dWd")}
+        m.run_fwd_bwd(longer, wider, a["dout"], *w)
+        for n, t in grads.items():
+            assert torch.equal(getattr(m, n), t), n
+    for x, lg in ((a["x"][:-1], a["logits"]), (longer[:, :-8].contiguous(), a["logits"]), (a["x"], a["logits"][:-1]), (a["x"][0], a["logits"])):
+        with pytest.raises(B.MoeError):
+            m.run_fwd(x, lg, *w)
+    with pytest.raises(B.MoeError):
+        m.run_block_fwd_bwd(longer, torch.zeros(m.E, m.d, device="cuda:0"), a["dout"], *w)
