@@ -108,6 +108,8 @@ struct GemmArgs {
   int N;                // output columns (per half for GATE_UP)
   int n_tiles;          // column tiles
   int m_tiles_cap;      // upper bound on row tiles (row-grouped products); row tiles of one dW (WGRAD)
+  int stream_rows;      // GATE_UP, DOWN: nothing is done where there are at most this many rows (0: always): a launch of
+                        // the streaming kernel in front has done it
   // WGRAD: out[e][M][N] = sum over the expert's rows of A[r][M] * B[r][N]
   int M;
 };
@@ -350,6 +352,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     total = a.E * a.m_tiles_cap * a.n_tiles * wpair;
   } else {
     total = count_row_tiles(a.offsets, a.E, tid0 & 63) * a.n_tiles;
+    if constexpr (MODE == GATE_UP || MODE == DOWN) {
+      if (a.stream_rows > 0 && a.offsets[a.E] <= a.stream_rows) total = 0;
+    }
     if (a.E <= LANE_EXPERTS_MAX) {
       const int e0 = tid0 & 63, e1 = 64 + (tid0 & 63);
       if (e0 < a.E) { lo0 = a.offsets[e0]; hi0 = a.offsets[e0 + 1]; }
@@ -1367,22 +1372,26 @@ extern "C" size_t moe_workspace_bytes(int T, int E, int k, int d, int f) {
 
 // xp grouped rows, or (row_token not null) the token rows themselves, gathered by the GEMM's loads
 int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets, const moe_bf16* Wg,
-                 const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* g,
-                 moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
+                 const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int most, int d, int f,
+                 moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
   if (!xp || !expert_offsets || !Wg || !Wu || !Wd || !g || !u || !h || !yp) return MOE_ERR_INVALID;
   if (bad_gemm_dims(E, R_cap, d, f)) return MOE_ERR_INVALID;
   const void* ptrs[] = {xp, expert_offsets, Wg, Wu, Wd, g, u, h, yp};
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (rows <= static_cast<long long>(STREAM_ROWS) * E) {
-    StreamFwdArgs p{};
+  // Few rows for certain: the streaming kernels.  Few rows expected, but not for certain (a rank's share of the experts): both,
+  // and on the device one of the two finds that the rows are not for it (see small_gemm.h).
+  const int few = STREAM_ROWS * E;
+  const bool streamed = R_cap <= few || most <= STREAM_TOKENS, either = !streamed && rows <= few;
+  int rc = MOE_OK;
+  StreamFwdArgs p{}, q{};
+  if (streamed || either) {
     p.A = U16(xp); p.row_token = row_token; p.row_weight = row_weight; p.offsets = expert_offsets;
     p.B0 = U16(Wg); p.B1 = U16(Wu); p.O0 = g; p.O1 = u; p.O2 = h; p.E = E; p.K = d; p.N = f;
-    const int rc = moe_stream_gate_up(p, R_cap, rows, s);
-    if (rc != MOE_OK) return rc;
-    StreamFwdArgs q{};
     q.A = U16(h); q.offsets = expert_offsets; q.B0 = U16(Wd); q.O0 = yp; q.E = E; q.K = f; q.N = d;
-    return moe_stream_down(q, R_cap, rows, s);
+    p.max_rows = q.max_rows = either ? few : R_cap;
+    if ((rc = moe_stream_gate_up(p, rows, s)) != MOE_OK) return rc;
+    if (streamed) return moe_stream_down(q, rows, s);
   }
   const int m_tiles = R_cap / BM + E;
 
@@ -1391,13 +1400,16 @@ int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_
   // gate | up with the SwiGLU epilogue
   a.A0 = U16(xp); a.B0 = U16(Wg); a.B1 = U16(Wu); a.O0 = g; a.O1 = u; a.O2 = h;
   a.K = d; a.N = f; a.n_tiles = (f + BN / 2 - 1) / (BN / 2);
-  int rc = launch_gemm<GATE_UP>(a, static_cast<long long>(a.n_tiles) * m_tiles, s, "gemm_gate_up");
+  a.stream_rows = either ? few : 0;
+  rc = launch_gemm<GATE_UP>(a, static_cast<long long>(a.n_tiles) * m_tiles, s, "gemm_gate_up");
   if (rc != MOE_OK) return rc;
   // down
+  if (either && (rc = moe_stream_down(q, rows, s)) != MOE_OK) return rc;
   GemmArgs b{};
   b.offsets = expert_offsets; b.E = E; b.m_tiles_cap = m_tiles;
   b.A0 = U16(h); b.B0 = U16(Wd); b.O0 = yp;
   b.K = f; b.N = d; b.n_tiles = (d + BN - 1) / BN;
+  b.stream_rows = a.stream_rows;
   return launch_gemm<DOWN>(b, static_cast<long long>(b.n_tiles) * m_tiles, s, "gemm_down");
 }
 
@@ -1415,15 +1427,13 @@ int moe_gemm_fwd_gather(const moe_bf16* x, int T, const int32_t* row_token, cons
                         const moe_bf16* Wg, const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int d,
                         int f, moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
   if (bad_gather(x, T, row_token, d)) return MOE_ERR_INVALID;
-  const long long most = static_cast<long long>(T) * E;
-  return moe_gemm_fwd(x, row_token, row_weight, expert_offsets, Wg, Wu, Wd, E, R_cap, rows < most ? rows : most, d, f, g, u,
-                      h, yp, stream);
+  return moe_gemm_fwd(x, row_token, row_weight, expert_offsets, Wg, Wu, Wd, E, R_cap, rows, T, d, f, g, u, h, yp, stream);
 }
 
 extern "C" int moe_grouped_gemm_fwd(const moe_bf16* xp, const int32_t* expert_offsets, const moe_bf16* Wg,
                                     const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f,
                                     moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
-  return moe_gemm_fwd(xp, nullptr, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, g, u, h, yp, stream);
+  return moe_gemm_fwd(xp, nullptr, nullptr, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, R_cap, d, f, g, u, h, yp, stream);
 }
 
 extern "C" int moe_grouped_gemm_fwd_gather(const moe_bf16* x, int T, const int32_t* row_token,
@@ -1446,7 +1456,7 @@ extern "C" int moe_grouped_gemm_fwd_folded(const moe_bf16* x, int T, const int32
 // two weight-gradient products that read them
 int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
                  const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-                 const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
+                 const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
                  moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream) {
   if (row_token != nullptr && bad_gather(xp, T, row_token, d)) return MOE_ERR_INVALID;
   if (!dyp || !xp || !g || !u || !h || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws)
@@ -1497,7 +1507,7 @@ extern "C" int moe_grouped_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, con
                                     const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f,
                                     moe_bf16* dxp, moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws,
                                     size_t ws_bytes, void* stream) {
-  return moe_gemm_bwd(dyp, xp, 0, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
+  return moe_gemm_bwd(dyp, xp, 0, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd,
                       ws, ws_bytes, stream);
 }
 
@@ -1508,7 +1518,7 @@ extern "C" int moe_grouped_gemm_bwd_gather(const moe_bf16* dyp, const moe_bf16* 
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes,
                                            void* stream) {
   if (row_token == nullptr) return MOE_ERR_INVALID;
-  return moe_gemm_bwd(dyp, x, T, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
+  return moe_gemm_bwd(dyp, x, T, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd,
                       ws, ws_bytes, stream);
 }
 
@@ -1544,7 +1554,7 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
                                            const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-                                           const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp,
+                                           const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
   if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !dgate ||
@@ -1610,5 +1620,5 @@ extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16*
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
   return moe_gemm_bwd_folded(dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, expert_offsets, Wg, Wu, Wd, E, R_cap,
-                             R_cap, d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
+                             d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
 }

@@ -1,7 +1,7 @@
 // The whole layer in one call: what a program would otherwise enqueue through five to twelve calls of the C ABI.
 // Host code only; it adds two things to the calls it makes: one argument check per call instead of one crossing of
-// the language boundary per stage, and the number of experts of the whole layer, from which the expected number of
-// local rows follows (the grouped products by themselves only know the bound T * k).
+// the language boundary per stage, and what the grouped products by themselves do not know: the number of experts of the
+// whole layer, from which the expected number of local rows follows, and of tokens, which no expert's rows exceed.
 #include "gemm.h"
 
 extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
@@ -23,7 +23,7 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if (rc != MOE_OK) return rc;
     if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
     if (plain)
-      rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->g, L->u, L->h,
+      rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, T, d, f, L->g, L->u, L->h,
                         L->yp, stream);
     else
       rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
@@ -37,13 +37,13 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if (!plain && !L->row_token) return MOE_ERR_INVALID;   // without it moe_gemm_bwd would take x for T * k grouped rows
     if (fold) {
       rc = moe_gemm_bwd_folded(L->dout, L->x, T, k, L->row_token, L->row_weight, L->slot_row, L->g, L->u, L->h,
-                               L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
+                               L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
                                L->dgate, L->ws, L->ws_bytes, stream);
     } else {
       rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
       if (rc != MOE_OK) return rc;
       rc = moe_gemm_bwd(L->dyp, plain ? L->xp : L->x, T, plain ? nullptr : L->row_token, L->g, L->u, L->h, L->expert_offsets,
-                        L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
+                        L->Wg, L->Wu, L->Wd, nl, R_cap, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
     }
     if (rc != MOE_OK) return rc;
     if ((rc = moe_permute_bwd(L->dxp, L->slot_row, T, k, d, L->dx, stream)) != MOE_OK) return rc;

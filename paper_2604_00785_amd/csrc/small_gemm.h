@@ -2,10 +2,24 @@
 #pragma once
 #include "common.h"
 
-// Rows per expert, on average, up to which the forward products take the streaming kernels.  Measured at d 2048, f 1024,
-// 64 experts: 12 rows 114 + 63 us against 137 + 64 us in the tiled kernel, 19 rows 119 + 66 against 116-128 + 64, 25 rows
-// 126 + 71 against 118-139 + 64.
-constexpr int STREAM_ROWS = 20;
+// The forward products take the streaming kernels where a load of any skew leaves few 16-row tiles per expert, so that its
+// weights are not fetched again and again: at most STREAM_ROWS rows per expert, or no expert with more than STREAM_TOKENS
+// rows (a token's experts are distinct, so no expert has more rows than there are tokens).  A rank's share may hold the
+// large experts: where R_cap allows more rows and only the expected number is small, both kernels are launched and look
+// at the number of rows on the device; the one that it is not for ends at once.
+// Forward pass, tiled / streaming, in us, other weights in every pass:
+//                                             rows per expert  even load    zipf load
+//   d 2048, f 1024, 64 experts, 8 per token           4          182 / 167    164 / 130
+//                                                     8          184 / 172    171 / 161
+//                                                    10          186 / 186    174 / 178
+//   d 1088, f 576, 96 experts, 4 per token            8          106 /  89     80 /  75
+//   d 512, f 256, 128 experts, 8 per token            8           57 /  52     57 /  51
+//   d 1024, f 512, 128 experts, 2 per token           6          109 /  95     70 /  63
+//   d 2048, f 1024, 64 experts, 1 per token           6          169 / 159     95 / 101
+//   d 2048, f 1024, the 20 of 240 experts that zipf makes the largest, 8 per token: 32 tokens 93 / 81; the same weights in
+//   every pass: 32 tokens 67 / 67, 48 tokens 70 / 83, 128 tokens 78 / 134
+constexpr int STREAM_ROWS = 8, STREAM_TOKENS = 32;
+
 // One grouped product out[r] = act[r] . W[e]^T (weights [N][K], K contiguous), or the pair gate/up with the
 // SwiGLU epilogue.  E, K, N as in GemmArgs; row_token / row_weight may be null.
 struct StreamFwdArgs {
@@ -19,8 +33,9 @@ struct StreamFwdArgs {
   uint16_t* O1;                 // u
   uint16_t* O2;                 // h
   int E, K, N;
+  int max_rows;                 // nothing is done where there are more rows
 };
 
-// R_cap: row capacity, rows: rows to expect (both only shape the launch)
-int moe_stream_gate_up(const StreamFwdArgs& a, int R_cap, long long rows, hipStream_t s);
-int moe_stream_down(const StreamFwdArgs& a, int R_cap, long long rows, hipStream_t s);
+// rows: rows to expect (only shapes the launch, not the results)
+int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s);
+int moe_stream_down(const StreamFwdArgs& a, long long rows, hipStream_t s);

@@ -188,15 +188,16 @@ __device__ __forceinline__ void st_fwd_tile(const StreamFwdArgs& a, const StTile
 template <bool GATE_UP, int FR, int PIECES>
 __global__ __launch_bounds__(256 / FR, 4) void stream_fwd_kernel(StreamFwdArgs a) {
   __shared__ f32x4_t part[4 * 64];
+  const int rows = a.offsets[a.E];
   StTile t;
-  if (!st_find_tile(a.offsets, a.E, a.N / (GATE_UP ? 32 : 64), t)) return;
+  if (!st_find_tile(a.offsets, a.E, a.N / (GATE_UP ? 32 : 64), t) || rows > a.max_rows) return;
   st_fwd_tile<GATE_UP, FR, PIECES>(a, t, part);
 }
 
 template <bool GATE_UP, int FR, int PIECES>
-int launch_fwd(const StreamFwdArgs& a, int R_cap, hipStream_t s, const char* name) {
+int launch_fwd(const StreamFwdArgs& a, hipStream_t s, const char* name) {
   const int ncol = a.N / (GATE_UP ? 32 : 64);
-  const long long row_tiles = R_cap / ST_ROWS + (a.E < R_cap ? a.E : R_cap);
+  const long long row_tiles = a.max_rows / ST_ROWS + (a.E < a.max_rows ? a.E : a.max_rows);
   const long long tiles = (row_tiles * ncol + 7) & ~7ll;
   if (tiles > 0x7FFFFFFFll) return MOE_ERR_INVALID;
   MOE_LAUNCH(name, (stream_fwd_kernel<GATE_UP, FR, PIECES>), dim3(static_cast<unsigned>(tiles)), dim3(256 / FR), 0, s, a);
@@ -209,14 +210,14 @@ int launch_fwd(const StreamFwdArgs& a, int R_cap, hipStream_t s, const char* nam
 //   384 tiles (d 4096) 72 / 66 / 77; 512 tiles (two tokens, d 2048) 56 / 53 / 58
 //   1130 tiles (d 1088, 24 tokens) 67 / 64 / 64; 2050 tiles (64 tokens, d 2048) 186 / 179 / 172
 template <bool GATE_UP>
-int launch_fwd_any(const StreamFwdArgs& a, int R_cap, long long rows, hipStream_t s, const char* name) {
+int launch_fwd_any(const StreamFwdArgs& a, long long rows, hipStream_t s, const char* name) {
   const long long tiles = rows * a.E / (rows + a.E) * (a.N / (GATE_UP ? 32 : 64));
-  if (tiles < 256) return launch_fwd<GATE_UP, 2, 2>(a, R_cap, s, name);
-  if (tiles <= 512) return launch_fwd<GATE_UP, 2, 1>(a, R_cap, s, name);
-  return launch_fwd<GATE_UP, 4, 1>(a, R_cap, s, name);
+  if (tiles < 256) return launch_fwd<GATE_UP, 2, 2>(a, s, name);
+  if (tiles <= 512) return launch_fwd<GATE_UP, 2, 1>(a, s, name);
+  return launch_fwd<GATE_UP, 4, 1>(a, s, name);
 }
 
 }  // namespace
 
-int moe_stream_gate_up(const StreamFwdArgs& a, int R_cap, long long rows, hipStream_t s) { return launch_fwd_any<true>(a, R_cap, rows, s, "gemm_gate_up"); }
-int moe_stream_down(const StreamFwdArgs& a, int R_cap, long long rows, hipStream_t s) { return launch_fwd_any<false>(a, R_cap, rows, s, "gemm_down"); }
+int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s) { return launch_fwd_any<true>(a, rows, s, "gemm_gate_up"); }
+int moe_stream_down(const StreamFwdArgs& a, long long rows, hipStream_t s) { return launch_fwd_any<false>(a, rows, s, "gemm_down"); }

@@ -95,3 +95,55 @@ def test_wider_arguments(path):
             m.run_fwd(x, lg, *w)
     with pytest.raises(B.MoeError):
         m.run_block_fwd_bwd(longer, torch.zeros(m.E, m.d, device="cuda:0"), a["dout"], *w)
+
+
+def _stage_calls(m, path, x, logits, dout, Wg, Wu, Wd):
+    """What run_fwd_bwd does in one native call, through the calls of the single stages."""
+    fold, plain = path == "fold", path == "plain"
+    B.moe_route_permute(logits, x if plain else None, m.k, m.renormalize, m.e_begin, m.e_count, m.topk_idx, m.topk_w,
+                        m.expert_offsets, m.row_token, m.slot_row, m.row_weight, m.xp, m.ws)
+    if fold:
+        B.moe_grouped_gemm_fwd_folded(x, m.row_token, m.row_weight, m.expert_offsets, Wg, Wu, Wd, m.g, m.u, m.h, m.yp)
+        B.moe_unpermute_sum(m.yp, m.slot_row, m.out)
+        B.moe_grouped_gemm_bwd_folded(dout, x, m.row_token, m.row_weight, m.slot_row, m.g, m.u, m.h, m.expert_offsets, Wg, Wu, Wd,
+                                      m.dxp, m.dWg, m.dWu, m.dWd, m.dgate, m.ws)
+    else:
+        if plain:
+            B.moe_grouped_gemm_fwd(m.xp, m.expert_offsets, Wg, Wu, Wd, m.g, m.u, m.h, m.yp)
+        else:
+            B.moe_grouped_gemm_fwd_gather(x, m.row_token, m.expert_offsets, Wg, Wu, Wd, m.g, m.u, m.h, m.yp)
+        B.moe_unpermute_combine(m.yp, m.slot_row, m.topk_w, m.out)
+        B.moe_unpermute_combine_bwd(dout, m.yp, m.slot_row, m.topk_w, m.dyp, m.dgate)
+        if plain:
+            B.moe_grouped_gemm_bwd(m.dyp, m.xp, m.g, m.u, m.h, m.expert_offsets, Wg, Wu, Wd, m.dxp, m.dWg, m.dWu, m.dWd, m.ws)
+        else:
+            B.moe_grouped_gemm_bwd_gather(m.dyp, x, m.row_token, m.g, m.u, m.h, m.expert_offsets, Wg, Wu, Wd, m.dxp, m.dWg, m.dWu,
+                                          m.dWd, m.ws)
+    B.moe_permute_bwd(m.dxp, m.slot_row, m.dx)
+
+
+# tiled products with ragged tiles; streamed products of few rows; a rank's share; one whose expected rows are few, so that the
+# number of rows decides on the device between the two (the stage calls, which know only T * k, take the tiled ones)
+@pytest.mark.parametrize("T,d,E,k,f,eb,ec,hot", [
+    (500, 192, 6, 3, 320, 0, 6, 0), (24, 320, 40, 4, 192, 0, 40, 0), (300, 128, 16, 4, 64, 4, 5, 0),
+    (70, 320, 64, 4, 192, 8, 4, 0), (70, 320, 64, 4, 192, 8, 4, 30), (70, 320, 64, 4, 192, 8, 4, -30)])
+@pytest.mark.parametrize("path", ["plain", "gather", "fold"])
+def test_one_call_equals_the_stage_calls(path, T, d, E, k, f, eb, ec, hot):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(T)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda:0")
+    x, dout, logits = r(T, d).bfloat16(), r(T, d).bfloat16(), r(T, E)
+    logits[:, eb:eb + ec] += hot
+    w = [r(ec, *s).mul_(0.05).bfloat16() for s in ((f, d), (f, d), (d, f))]
+    layers = [B.MoELayerBuffers(T, d, E, k, f, eb, ec, 1, gather=path == "gather", fold=path == "fold") for _ in range(2)]
+    layers[0].run_fwd_bwd(x, logits, dout, *w)
+    _stage_calls(layers[1], path, x, logits, dout, *w)
+    one, stages = (m.results() for m in layers)
+    rows = int(one["expert_offsets"][-1])
+    if T == 70:
+        assert rows == {0: rows, 30: T * k, -30: 0}[hot] and (rows <= 8 * ec) == (hot <= 0)
+    for n, t in one.items():
+        a, b = t, stages[n]
+        if n in ("row_token", "row_weight", "xp", "g", "u", "h", "yp", "hw", "ypw", "dyp", "dxp"):     # T * k rows, not all local
+            a, b = a[:rows], b[:rows]
+        assert torch.equal(a, b), n
