@@ -1204,11 +1204,16 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // (inside a run, where runs are whole: the list stays covered once).
   int tile = first_tile;
   // Where experts have few row tiles (three or fewer on average) the launch waits for weights, and an expert with one row
-  // tile needs far more of them per operation than one with many.  The list has the experts with many tiles in
-  // front, so its runs are then taken from its two ends in turn: every round asks memory for about the same (zipf-like
-  // load over 96 experts: gate_up 337 -> 305 us, dgrad_h 418 -> 395 us).  Not with reductions under 16 steps: there the
-  // experts that straddle two runs, fetched twice when the runs are far apart in time, weigh more (down of 128 experts
-  // with 250 rows and 8 steps: 116 -> 124 us), nor with more row tiles (no difference).
+  // tile needs far more of them per operation than one with many.  The runs are then taken from the two ends of the list in
+  // turn, so that a round asks memory for two stretches of experts instead of one.  What they hold depends on the load: inside
+  // a class the list is in index order.  Forward and backward pass, in us, list from the front / from both ends, zipf-like
+  // load with the experts sorted by size, reversed, in two random orders, and an even load:
+  //   64 experts, 2048 tokens, d 2048   949/909  994/980  965/956  983/961  959/942
+  //   128 experts, 3000 tokens, d 1024  918/905  902/892  978/947  987/963  770/763
+  //   96 experts, 4099 tokens, d 2048   1651/1607  1677/1687  1709/1702  1628/1657  1503/1501
+  // (Listing the experts by their tile counts first changed this by -3 to +3 %, on average by nothing.)  Not with reductions
+  // under 16 steps: there the experts that straddle two runs, fetched twice when the runs are far apart in time, weigh more
+  // (down of 128 experts with 250 rows and 8 steps: 116 -> 124 us), nor with more row tiles (no difference).
   bool mix = false;
   if constexpr (!is_wgrad(MODE)) mix = a.K * (MODE == DGRAD_X ? 2 : 1) >= 16 * BK && total <= 3 * a.E * a.n_tiles;
   const int run = static_cast<int>(gridDim.x >> 3);

@@ -1,5 +1,6 @@
 """GPU parity of the variants that calls with few rows take, at the sizes where a tile, a lane group or a wave's share
 ends.  Same oracle, inputs and tolerances as the tests they reuse."""
+import numpy as np
 import pytest
 import torch
 
@@ -86,6 +87,17 @@ def test_streamed_products_have_the_bits_of_the_tiled(T, d, E, k, f, form):
         pytest.skip("a call that knows no number of tokens takes the tiled products")
     for n, a, b in zip("guhy", few, tiled):
         assert torch.equal(a, b), n
+
+
+# A list of many tiles whose experts' sizes are in no order: several rounds of runs taken from both ends, and (more than 128
+# experts) in index order
+@pytest.mark.parametrize("E,d,f", [(96, 1024, 1024), (72, 512, 2048), (140, 1024, 512)])
+def test_many_rounds_of_uneven_experts(E, d, f):
+    rng = np.random.default_rng(E)
+    counts = np.concatenate([[1100, 520, 513, 300, 257, 256, 255, 0, 0, 0], rng.integers(1, 30, E - 10)])
+    rng.shuffle(counts)
+    assert 256 * 2 < sum(-(-c // 256) for c in counts) * (f // 128) and sum(-(-c // 256) for c in counts) <= 3 * E
+    P.test_grouped_gemm_fwd_bwd_isolated([int(c) for c in counts], d, f)
 
 
 # Stages 1-3 in one workgroup: at most 1024 pairs
