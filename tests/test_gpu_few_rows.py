@@ -100,7 +100,17 @@ def test_many_rounds_of_uneven_experts(E, d, f):
     P.test_grouped_gemm_fwd_bwd_isolated([int(c) for c in counts], d, f)
 
 
-# Stages 1-3 in one workgroup: at most 1024 pairs
+# Stages 1-3 in one workgroup: at most 1024 pairs, two passes of the workgroup's 128 (up to 64 experts), 64 (128), 32 (256) or 16
+# lane groups; the odd sizes here take the first call of the two launches
+@pytest.mark.parametrize("T,E,k,eb,ec", [
+    (128, 12, 4, 0, 12), (129, 12, 4, 2, 9), (256, 24, 4, 0, 24), (257, 24, 3, 0, 24), (64, 100, 8, 0, 100), (65, 100, 8, 7, 90),
+    (128, 100, 8, 0, 100), (129, 100, 7, 0, 100), (32, 200, 9, 0, 200), (33, 200, 9, 150, 50), (64, 200, 16, 0, 200), (65, 200, 15, 0, 200)])
+@pytest.mark.parametrize("renorm,gate", [(0, False), (1, True)])
+def test_one_launch_routing_passes(T, E, k, eb, ec, renorm, gate):
+    P.test_route_permute_one_call(T, E, k, eb, ec, renorm, gate)
+
+
+# both sides of the rule for one workgroup: at most 1024 pairs and two passes
 @pytest.mark.parametrize("T,E,k,eb,ec", [
     (128, 64, 8, 0, 64), (129, 64, 8, 3, 50),         # the last call of one launch, the first of two
     (65, 8, 1, 0, 8), (256, 33, 4, 1, 31), (257, 33, 3, 0, 33), (100, 130, 10, 0, 130), (14, 512, 70, 0, 512), (17, 300, 3, 299, 1)])
