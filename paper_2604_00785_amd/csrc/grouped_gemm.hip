@@ -20,6 +20,10 @@
 //     of the step, and a tile enters the ring of LDS slots at the phase that puts those three on
 //     phases 0, 1 and 2.
 //
+// The whole of it exists a second time with tiles of 128x128: four waves of 64x64 pieces = 4x4 accumulators, 80 KB of LDS and
+// less than 256 registers, so that two workgroups share a compute unit.  The sums run in the same order and give the same
+// bits; which size a launch takes is a rule on its expected tiles (TileCost).  What is said here in numbers is about the large tiles.
+//
 // The two operand tiles of a step (32 KB each) live in a ring of five LDS slots (160 KB, all
 // there is): A(t) in slot 2t mod 5, B(t) in slot (2t+1) mod 5, so two and a half steps are
 // resident.  Step t loads A(t+2) during its first 32-deep sub-step, into the slot B(t-1) left;
@@ -56,11 +60,25 @@
 
 namespace {
 
-constexpr int BM = 256, BN = 256, BK = 64;
+constexpr int BK = 64;
 constexpr int GEMM_THREADS = 256;
-constexpr int TILE_BYTES = BM * BK * 2;               // one operand tile (32 KB)
 constexpr int NSLOT = 5;                              // ring of operand tile slots
-constexpr int LDS_BYTES = NSLOT * TILE_BYTES;         // 160 KB: everything a workgroup can have
+// What follows from the edge S of the output tile, 256 or 128 (see tile_edge()).  Four waves as 2 x 2 in either case.
+template <int S> struct Tile {
+  static_assert(S == 256 || S == 128);
+  static constexpr int BYTES = S * BK * 2;            // one operand tile: 32 or 16 KB
+  static constexpr int LDS = NSLOT * BYTES;           // 160 KB, everything a compute unit has; or 80 KB, two workgroups on it
+  static constexpr int PER_CU = 256 / S;              // workgroups per compute unit
+  static constexpr int HALF = S / 2;                  // rows and columns of a wave's piece
+  static constexpr int NB = S / 32;                   // 16 x 16 blocks along each side of it
+  static constexpr int NL = S / 32;                   // direct-to-LDS loads (1 KB each) per wave and operand tile
+  static constexpr int SHARE = BYTES / 4;             // a wave's share of a slot: what it fills, and stages in
+  static constexpr int KN_ROW = S * 2;                // bytes of a row of a [64 k][S n] tile
+  static constexpr int KN_PIECES = S / 8;             // 16-byte pieces of it
+  static constexpr int KN_RPL = 64 / KN_PIECES;       // rows of it that one load fills
+  static constexpr int SLOTS_PER_SET = 65536 / BYTES; // slots that an LDS read's immediate offset reaches
+  static constexpr int SETS = (NSLOT + SLOTS_PER_SET - 1) / SLOTS_PER_SET;
+};
 constexpr int LOAD_BIAS = 4096;                       // see dma16_imm
 constexpr int slot_of_a(int p) { return (2 * p) % NSLOT; }       // p = ring phase of the step
 constexpr int slot_of_b(int p) { return (2 * p + 1) % NSLOT; }
@@ -122,7 +140,7 @@ __device__ __attribute__((aligned(512))) uint32_t g_zero_block[128];
 // cycles per CU, as a linear read does; XOR-ing the piece with (row ^ row >> 3) & 7 costs 8.9, no swizzle 16.
 // This is the inverse: which logical piece a fill has to fetch for physical piece `phys`.
 __device__ __forceinline__ int kc_logical_piece(int row, int phys) { return (phys - row) & 7; }
-// [64 k][256 n] tile: 16-byte pieces of a k row are XOR-swizzled with 4*(k & 3), which spreads the
+// [64 k][S n] tile: 16-byte pieces of a k row are XOR-swizzled with 4*(k & 3), which spreads the
 // four k rows that 16 lanes of a transposing read touch over four different 64-byte bank groups.
 __device__ __forceinline__ int kn_piece(int krow, int piece) { return piece ^ ((krow & 3) << 2); }
 
@@ -182,7 +200,7 @@ __device__ __forceinline__ float sigmoid_f(float g) {
 }
 __device__ __forceinline__ float silu_f(float g) { return g * sigmoid_f(g); }
 
-// Row tiles of the grouped products: expert e owns ceil(rows_e / 256) consecutive tile numbers.
+// Row tiles of the grouped products: expert e owns ceil(rows_e / S) consecutive tile numbers (S: the tile's edge).
 // Both functions are evaluated by a whole wave (64 experts per pass) and return wave-uniform values.
 __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
 #pragma unroll
@@ -192,12 +210,12 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   }
   return v;
 }
-__device__ __forceinline__ int count_row_tiles(const int32_t* offsets, int E, int lane) {
+template <int S> __device__ __forceinline__ int count_row_tiles(const int32_t* offsets, int E, int lane) {
   int total = 0;
   for (int e0 = 0; e0 < E; e0 += 64) {
     const int ee = e0 + lane;
     const int rows = ee < E ? offsets[ee + 1] - offsets[ee] : 0;
-    total += __shfl(wave_incl_scan((rows + BM - 1) / BM, lane), 63, 64);
+    total += __shfl(wave_incl_scan((rows + S - 1) / S, lane), 63, 64);
   }
   return __builtin_amdgcn_readfirstlane(total);
 }
@@ -236,9 +254,10 @@ __device__ __forceinline__ void sorted_first_tiles(int tiles0, int tiles1, int r
 }
 constexpr int LANE_EXPERTS_MAX = 128;
 // One half (experts 64 h .. 64 h + 63, one per lane) of the register-resident lookup.
+template <int S>
 __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first, int n_tiles, int tile, int& e, int& m0,
                                                int& m_end, int& nt) {
-  const int row_tiles = (hi - lo + BM - 1) / BM;
+  const int row_tiles = (hi - lo + S - 1) / S;
   const int tiles = row_tiles * n_tiles;
   const unsigned long long hit = __ballot(tiles > 0 && first <= tile && tile < first + tiles);
   if (!hit) return false;
@@ -247,23 +266,24 @@ __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first,
   const int q = tile - __shfl(first, l, 64);
   const int rt = __shfl(row_tiles, l, 64);
   nt = q / rt;
-  m0 = __shfl(lo, l, 64) + (q - nt * rt) * BM;
+  m0 = __shfl(lo, l, 64) + (q - nt * rt) * S;
   m_end = __shfl(hi, l, 64);
   return true;
 }
+template <int S>
 __device__ __forceinline__ void find_tile(const int32_t* offsets, int E, int lo0, int hi0, int first0, int lo1, int hi1,
                                           int first1, int n_tiles, int tile, int lane, int& e, int& m0, int& m_end, int& nt) {
   e = 0; m0 = 0; m_end = 0; nt = 0;
   if (E <= LANE_EXPERTS_MAX) {
-    if (find_tile_half(0, lo0, hi0, first0, n_tiles, tile, e, m0, m_end, nt)) return;
-    find_tile_half(1, lo1, hi1, first1, n_tiles, tile, e, m0, m_end, nt);
+    if (find_tile_half<S>(0, lo0, hi0, first0, n_tiles, tile, e, m0, m_end, nt)) return;
+    find_tile_half<S>(1, lo1, hi1, first1, n_tiles, tile, e, m0, m_end, nt);
     return;
   }
   int base = 0;
   for (int e0 = 0; e0 < E; e0 += 64) {
     const int ee = e0 + lane;
     const int lo = ee < E ? offsets[ee] : 0, hi = ee < E ? offsets[ee + 1] : 0;
-    const int row_tiles = (hi - lo + BM - 1) / BM;
+    const int row_tiles = (hi - lo + S - 1) / S;
     const int tiles = row_tiles * n_tiles;
     const int inc = wave_incl_scan(tiles, lane);
     const int excl = base + inc - tiles;
@@ -274,7 +294,7 @@ __device__ __forceinline__ void find_tile(const int32_t* offsets, int E, int lo0
       const int q = tile - __shfl(excl, l, 64);
       const int rt = __shfl(row_tiles, l, 64);
       nt = q / rt;
-      m0 = __shfl(lo, l, 64) + (q - nt * rt) * BM;
+      m0 = __shfl(lo, l, 64) + (q - nt * rt) * S;
       m_end = __shfl(hi, l, 64);
       return;
     }
@@ -303,6 +323,7 @@ __device__ __forceinline__ const char* scalarize(const char* p) {
 
 // What a workgroup knows about one tile: where it lies, where its operand loads come from, how many
 // K steps it has.
+template <int S>
 struct TileState {
   int e, m0, m_end, nt, n0;     // expert, first output row, end of the valid rows, column tile, first output column
   int r0;                       // first of this wave's rows inside the tile
@@ -313,9 +334,9 @@ struct TileState {
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
   int k_lo, k_hi;               // weight gradients: the expert's row range is the reduction
   bool last_partial;            // weight gradients: the last step holds fewer than 64 rows
-  uint32_t voa[8], vob[8];      // lane offsets of the eight loads per operand tile, in bytes
-  uint32_t vcb[8];              // gathered operand: lane offset of a load without its token row
-  int tokn[8];                  // gathered operand: tokens of the lane's eight reduction rows of a coming step
+  uint32_t voa[Tile<S>::NL], vob[Tile<S>::NL];   // lane offsets of a wave's loads per operand tile, in bytes
+  uint32_t vcb[Tile<S>::NL];    // gathered operand: lane offset of a load without its token row
+  int tokn[Tile<S>::NL];        // gathered operand: tokens of the lane's reduction rows of a coming step
   const char* sa_next;          // scalar bases of the next A / B tile to load (LOAD_BIAS low)
   const char* sb_next;
   const char* sa_phase1;        // DGRAD_X: bases of the second K phase
@@ -327,8 +348,11 @@ struct TileState {
 // One product's tile list, walked by this workgroup from list position first_tile in steps of
 // gridDim.x.  Returns the position at which the workgroup left the list, counted from its end:
 // where it enters a list that follows in the same launch.
-template <int MODE, int ARG>
+template <int MODE, int S, int ARG>
 __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile) {
+  using TL = Tile<S>;
+  using TileState = TileState<S>;
+  constexpr int NL = TL::NL, NB = TL::NB, HALF = TL::HALF, TILE_BYTES = TL::BYTES;
   extern __shared__ __attribute__((aligned(16))) char lds[];
   const int tid0 = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid0 >> 6);
@@ -351,7 +375,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   if constexpr (is_wgrad(MODE)) {
     total = a.E * a.m_tiles_cap * a.n_tiles * wpair;
   } else {
-    total = count_row_tiles(a.offsets, a.E, tid0 & 63) * a.n_tiles;
+    total = count_row_tiles<S>(a.offsets, a.E, tid0 & 63) * a.n_tiles;
     if constexpr (MODE == GATE_UP || MODE == DOWN) {
       if (a.stream_rows > 0 && a.offsets[a.E] <= a.stream_rows) total = 0;
     }
@@ -359,15 +383,17 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       const int e0 = tid0 & 63, e1 = 64 + (tid0 & 63);
       if (e0 < a.E) { lo0 = a.offsets[e0]; hi0 = a.offsets[e0 + 1]; }
       if (e1 < a.E) { lo1 = a.offsets[e1]; hi1 = a.offsets[e1 + 1]; }
-      sorted_first_tiles((hi0 - lo0 + BM - 1) / BM * a.n_tiles, (hi1 - lo1 + BM - 1) / BM * a.n_tiles, gridDim.x >> 3,
+      sorted_first_tiles((hi0 - lo0 + S - 1) / S * a.n_tiles, (hi1 - lo1 + S - 1) / S * a.n_tiles, gridDim.x >> 3,
                          tid0 & 63, first0, first1);
     }
   }
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<size_t>(LDS_PTR(lds)));
-  // M0 base of this wave's loads: the middle of its 8 KB share of tile slot 0 (immediates reach -4096 .. +3072)
-  const uint32_t lds_fill = __builtin_amdgcn_readfirstlane(lds0 + wave * 8192 + 4096);
+  // M0 base of this wave's loads: the middle of its share of tile slot 0 (immediates reach -4096 .. +3072)
+  const uint32_t lds_fill = __builtin_amdgcn_readfirstlane(lds0 + wave * TL::SHARE + NL / 2 * 1024);
 
   const int lane = tid0 & 63;
+  // k row (of a [64 k][S n] tile) that load i of this wave fills from this lane
+  auto kn_load_row = [&](int i, int lane) __attribute__((always_inline)) { return (wave * NL + i) * TL::KN_RPL + lane / TL::KN_PIECES; };
   // Everything about tile number `tile` of the list that does not depend on the K step.
   auto setup_tile = [&](int tile, TileState& t) __attribute__((always_inline)) {
   // the thread id is laundered per tile so that the lane-dependent pieces of the load offsets are recomputed for
@@ -384,10 +410,10 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     e = rest / per_expert;
     int mi = rest % per_expert;
     if (mi >= a.m_tiles_cap) { mi -= a.m_tiles_cap; second = true; }
-    m0 = mi * BM;                       // output row of dW
+    m0 = mi * S;                        // output row of dW
     m_end = a.M;
   } else {
-    find_tile(a.offsets, a.E, lo0, hi0, first0, lo1, hi1, first1, a.n_tiles, tile, lane, e, m0, m_end, nt);
+    find_tile<S>(a.offsets, a.E, lo0, hi0, first0, lo1, hi1, first1, a.n_tiles, tile, lane, e, m0, m_end, nt);
     nt = __builtin_amdgcn_readfirstlane(nt);
   }
   // tile coordinates are wave-uniform: keep them in scalar registers, so that everything derived
@@ -395,14 +421,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   e = __builtin_amdgcn_readfirstlane(e);
   m0 = __builtin_amdgcn_readfirstlane(m0);
   m_end = __builtin_amdgcn_readfirstlane(m_end);
-  const int n0 = nt * (MODE == GATE_UP ? BN / 2 : BN);
+  const int n0 = nt * (MODE == GATE_UP ? HALF : S);
   t.e = e; t.m0 = m0; t.m_end = m_end; t.nt = nt; t.n0 = n0; t.second = second;
   // The tile's 32-row groups that hold a valid row are shared out evenly: the upper waves take the larger half, so
   // that a ragged tile keeps both pairs of waves busy for half the time instead of one for all of it.
-  int nv = 4, r0 = wm * 128, m_wave = m_end;
+  int nv = HALF / 32, r0 = wm * HALF, m_wave = m_end;
   if constexpr (!is_wgrad(MODE)) {
     int groups = (m_end - m0 + 31) >> 5;
-    groups = groups > 8 ? 8 : groups;
+    groups = groups > S / 32 ? S / 32 : groups;
     const int upper = (groups + 1) >> 1;
     nv = __builtin_amdgcn_readfirstlane(wm == 0 ? upper : groups - upper);
     r0 = wm * 32 * upper;
@@ -413,25 +439,25 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   t.nv = nv; t.r0 = r0; t.m_wave = m_wave;
 
   // ---------------- operand sources -------------------------------------------
-  // Per K step and operand tile a wave issues eight direct-to-LDS loads of 1 KB each:
-  //  K-contiguous source ([row][k]): load i of wave w fills tile rows 64 w + 8 i .. + 8;
+  // Per K step and operand tile a wave issues NL direct-to-LDS loads of 1 KB each:
+  //  K-contiguous source ([row][k]): load i of wave w fills tile rows 8 (NL w + i) .. + 8;
   //    lane l -> row + l/8, physical piece l%8, i.e. logical piece kc_logical_piece(row, l%8).
   //    The base advances by 64 elements per step.
-  //  n-contiguous source ([k][n]): load i of wave w fills k rows 2 (8 w + i), + 1;
-  //    lane l -> k row + l/32, physical piece l%32 = logical piece kn_piece(k row, l%32).
+  //  n-contiguous source ([k][n]): load i of wave w fills the KN_RPL (2 or 4) k rows from KN_RPL (NL w + i) on;
+  //    with P = KN_PIECES (32 or 16) lane l -> k row + l/P, physical piece l%P = logical piece kn_piece(k row, l%P).
   //    The base advances by 64 rows per step.
-  // Lane offsets carry LOAD_BIAS - (i - 4) * 1024 (see dma16_imm); the scalar bases lie LOAD_BIAS low.
-  uint32_t (&voa)[8] = t.voa;           // lane offsets in bytes
-  uint32_t (&vob)[8] = t.vob;
+  // Lane offsets carry LOAD_BIAS - (i - NL / 2) * 1024 (see dma16_imm); the scalar bases lie LOAD_BIAS low.
+  uint32_t (&voa)[NL] = t.voa;          // lane offsets in bytes
+  uint32_t (&vob)[NL] = t.vob;
   const char* abase;                    // step 0 of phase 0, without the bias
   const char* bbase;
   ptrdiff_t a_phase = 0, b_phase = 0;   // byte offset of the second K phase (DGRAD_X)
   size_t a_step, b_step;                // bytes per step
   int k_lo = 0, k_hi = 0;               // WGRAD: the expert's row range is the reduction
   const int32_t* row_tok = nullptr;     // GATHER_A/B: token of the expert's first reduction row onwards
-  uint32_t (&vcb)[8] = t.vcb;           // GATHER_A/B: lane offset of a load without its token row
+  uint32_t (&vcb)[NL] = t.vcb;          // GATHER_A/B: lane offset of a load without its token row
 #pragma unroll
-  for (int i = 0; i < 8; ++i) { t.vcb[i] = 0; t.tokn[i] = 0; }
+  for (int i = 0; i < NL; ++i) { t.vcb[i] = 0; t.tokn[i] = 0; }
   int nk, nk_phase;                     // steps in total / in the first K phase
 
   if constexpr (is_wgrad(MODE)) {
@@ -457,12 +483,12 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       b_step = static_cast<size_t>(BK) * a.N * 2;
     }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int krow = (wave * 8 + i) * 2 + (lane >> 5);
-      const int piece = kn_piece(krow, lane & 31);
+    for (int i = 0; i < NL; ++i) {
+      const int krow = kn_load_row(i, lane);
+      const int piece = kn_piece(krow, lane % TL::KN_PIECES);
       int ca = piece * 8;  if (m0 + ca > a.M - 8) ca = a.M - 8 - m0;
       int cb = piece * 8;  if (n0 + cb > a.N - 8) cb = a.N - 8 - n0;
-      const uint32_t fix = static_cast<uint32_t>(LOAD_BIAS - (i - 4) * 1024);
+      const uint32_t fix = static_cast<uint32_t>(LOAD_BIAS - (i - NL / 2) * 1024);
       voa[i] = static_cast<uint32_t>((krow * a.M + ca) * 2) + fix;
       vob[i] = static_cast<uint32_t>((krow * a.N + cb) * 2) + fix;
       if constexpr (GATHER_B) vcb[i] = static_cast<uint32_t>(cb * 2) + fix;
@@ -478,45 +504,45 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     if constexpr (MODE == DGRAD_H_GATE) gathered = true;
     if (gathered) abase = reinterpret_cast<const char*>(a.A0);   // lane offsets carry the token row
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = (wave * 8 + i) * 8 + (lane >> 3);
+    for (int i = 0; i < NL; ++i) {
+      const int row = (wave * NL + i) * 8 + (lane >> 3);
       const int chunk = kc_logical_piece(row, lane & 7);
       int r = row;
       if (m0 + r > m_end - 1) r = m_end - 1 - m0;
-      const uint32_t fix = static_cast<uint32_t>(LOAD_BIAS - (i - 4) * 1024);
+      const uint32_t fix = static_cast<uint32_t>(LOAD_BIAS - (i - NL / 2) * 1024);
       if (gathered) voa[i] = (static_cast<uint32_t>(a.row_token[m0 + r]) * a.K + chunk * 8) * 2u + fix;
       else voa[i] = static_cast<uint32_t>((r * a.K + chunk * 8) * 2) + fix;
     }
     if constexpr (MODE == DGRAD_X) { a_phase = (a.A1 - a.A0) * 2; nk *= 2; }
     const size_t wsz = static_cast<size_t>(a.N) * a.K;
     if constexpr (!B_KN) {
-      // GATE_UP: a wave's 128 tile rows are 64 rows of Wg and the same 64 rows of Wu: tile rows
-      // [0,64) Wg n0.., [64,128) Wu n0.., [128,192) Wg n0+64.., [192,256) Wu n0+64.. (wave w fills its own 64)
+      // GATE_UP: with Q = S / 4 a wave's 2 Q tile rows are Q rows of Wg and the same Q rows of Wu: tile rows
+      // [0,Q) Wg n0.., [Q,2Q) Wu n0.., [2Q,3Q) Wg n0+Q.., [3Q,4Q) Wu n0+Q.. (wave w fills rows Q w .. of them)
       const uint16_t* w = a.B0;
-      int first_col = wave * 64;
+      int first_col = wave * (S / 4);
       if constexpr (MODE == GATE_UP) {
         if (wave & 1) w = a.B1;
-        first_col = (wave >> 1) * 64;
+        first_col = (wave >> 1) * (S / 4);
       }
       bbase = reinterpret_cast<const char*>(w + static_cast<size_t>(e) * wsz + static_cast<size_t>(n0) * a.K);
       b_step = BK * 2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int row = (wave * 8 + i) * 8 + (lane >> 3);   // LDS row of the B tile
+      for (int i = 0; i < NL; ++i) {
+        const int row = (wave * NL + i) * 8 + (lane >> 3);   // LDS row of the B tile
         const int chunk = kc_logical_piece(row, lane & 7);
         int col = first_col + i * 8 + (lane >> 3);
         if (n0 + col > a.N - 1) col = a.N - 1 - n0;
-        vob[i] = static_cast<uint32_t>((col * a.K + chunk * 8) * 2) + static_cast<uint32_t>(LOAD_BIAS - (i - 4) * 1024);
+        vob[i] = static_cast<uint32_t>((col * a.K + chunk * 8) * 2) + static_cast<uint32_t>(LOAD_BIAS - (i - NL / 2) * 1024);
       }
     } else {  // DGRAD_H / DGRAD_X: weights stored [K][N]
       bbase = reinterpret_cast<const char*>(a.B0 + static_cast<size_t>(e) * wsz + n0);
       b_step = static_cast<size_t>(BK) * a.N * 2;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int krow = (wave * 8 + i) * 2 + (lane >> 5);
-        int cb = kn_piece(krow, lane & 31) * 8;
+      for (int i = 0; i < NL; ++i) {
+        const int krow = kn_load_row(i, lane);
+        int cb = kn_piece(krow, lane % TL::KN_PIECES) * 8;
         if (n0 + cb > a.N - 8) cb = a.N - 8 - n0;
-        vob[i] = static_cast<uint32_t>((krow * a.N + cb) * 2) + static_cast<uint32_t>(LOAD_BIAS - (i - 4) * 1024);
+        vob[i] = static_cast<uint32_t>((krow * a.N + cb) * 2) + static_cast<uint32_t>(LOAD_BIAS - (i - NL / 2) * 1024);
       }
       if constexpr (MODE == DGRAD_X) b_phase = (a.B1 - a.B0) * 2;
     }
@@ -545,12 +571,12 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // SP 0: the step is known to be whole; 1: known to be the partial one; 2: look (first loads of a tile).
   auto a_part = [&](TileState& t, int kt, auto i_tag, auto sp_tag) __attribute__((always_inline)) {
     constexpr int i = decltype(i_tag)::value, SP = decltype(sp_tag)::value;
-    constexpr int OFF = (i - 4) * 1024;
+    constexpr int OFF = (i - NL / 2) * 1024;
     if constexpr (is_wgrad(MODE) && !GATHER_A && SP != 0) {
       if (SP == 1 || (t.last_partial && kt == t.nk - 1)) {
-        const int krow = t.k_lo + kt * BK + (wave * 8 + i) * 2 + (lane >> 5);
+        const int krow = t.k_lo + kt * BK + kn_load_row(i, lane);
         dma16_lane_imm<OFF>(krow < t.k_hi ? t.sa_next + t.voa[i]
-                                        : reinterpret_cast<const char*>(g_zero_block) + (lane & 31) * 16 - OFF);
+                                        : reinterpret_cast<const char*>(g_zero_block) + lane % TL::KN_PIECES * 16 - OFF);
         return;
       }
     }
@@ -558,14 +584,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
   auto b_part = [&](TileState& t, int kt, auto i_tag, auto sp_tag) __attribute__((always_inline)) {
     constexpr int i = decltype(i_tag)::value, SP = decltype(sp_tag)::value;
-    constexpr int OFF = (i - 4) * 1024;
+    constexpr int OFF = (i - NL / 2) * 1024;
     if constexpr ((GATHER_A || MODE == WGRAD) && SP != 0) {
       if (SP == 1 || (t.last_partial && kt == t.nk - 1)) {
-        const int krow = t.k_lo + kt * BK + (wave * 8 + i) * 2 + (lane >> 5);
+        const int krow = t.k_lo + kt * BK + kn_load_row(i, lane);
         if constexpr (GATHER_A) {
           // the gathered operand repeats the expert's last row past its end: this one reads zeros there
           dma16_lane_imm<OFF>(krow < t.k_hi ? t.sb_next + t.vob[i]
-                                          : reinterpret_cast<const char*>(g_zero_block) + (lane & 31) * 16 - OFF);
+                                          : reinterpret_cast<const char*>(g_zero_block) + lane % TL::KN_PIECES * 16 - OFF);
         } else {
           // ... and the other operand reads its last valid row there, so that zero times it is zero
           dma16_lane_imm<OFF>(t.sb_next + t.vob[i] - (krow < t.k_hi ? 0 : static_cast<size_t>(krow - (t.k_hi - 1)) * a.N * 2));
@@ -587,39 +613,35 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       if (kt + 1 == t.nk_phase) t.sb_next = t.sb_phase1;
     }
   };
-  // GATHER_A/B: the tokens of the lane's eight reduction rows of step kt (rows 2 (8 w + i) + lane / 32), loaded
+  // GATHER_A/B: the tokens of the lane's NL reduction rows of step kt (kn_load_row), loaded
   // without any vector-ALU work except in an expert's last, partial step (rows past its end repeat its last
   // row: the other operand is zero there), and their turn into lane offsets of the gathered operand's loads.
   // The loads are asynchronous: apply_tok may only run after a wait that covers them.
-  const uint32_t tok_voff = static_cast<uint32_t>(((wave * 8) * 2 + (lane >> 5)) * 4);   // row of load 0; load i: + 2 i rows
-  auto fetch_tok = [&](TileState& t, int kt, int (&tk)[8]) __attribute__((always_inline)) {
+  const uint32_t tok_voff = static_cast<uint32_t>(kn_load_row(0, lane) * 4);   // row of load 0; load i: + KN_RPL i rows
+  auto fetch_tok = [&](TileState& t, int kt, int (&tk)[NL]) __attribute__((always_inline)) {
     if constexpr (GATHER_B || GATHER_A) {
       if (t.k_lo + (kt + 1) * BK > t.k_hi) {
         const int last = t.k_hi - t.k_lo - 1;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          int r = kt * BK + (wave * 8 + i) * 2 + (lane >> 5);
+        for (int i = 0; i < NL; ++i) {
+          int r = kt * BK + kn_load_row(i, lane);
           if (r > last) r = last;
           tk[i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, t.row_tok);
         }
       } else {
         const int32_t* base = t.row_tok + static_cast<size_t>(kt) * BK;
-        tk[0] = load_i32<0>(tok_voff, base);
-        tk[1] = load_i32<8>(tok_voff, base);
-        tk[2] = load_i32<16>(tok_voff, base);
-        tk[3] = load_i32<24>(tok_voff, base);
-        tk[4] = load_i32<32>(tok_voff, base);
-        tk[5] = load_i32<40>(tok_voff, base);
-        tk[6] = load_i32<48>(tok_voff, base);
-        tk[7] = load_i32<56>(tok_voff, base);
+        static_for<NL>([&](auto i_tag) {
+          constexpr int i = decltype(i_tag)::value;
+          tk[i] = load_i32<i * TL::KN_RPL * 4>(tok_voff, base);
+        });
       }
     }
   };
-  auto apply_tok = [&](TileState& t, int (&tk)[8]) __attribute__((always_inline)) {
+  auto apply_tok = [&](TileState& t, int (&tk)[NL]) __attribute__((always_inline)) {
     if constexpr (GATHER_B || GATHER_A) {
       const uint32_t row_bytes = static_cast<uint32_t>(GATHER_B ? a.N : a.M) * 2u;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < NL; ++i) {
         asm volatile("" : "+v"(tk[i]));   // not before the wait that precedes this call
         const uint32_t off = static_cast<uint32_t>(tk[i]) * row_bytes + t.vcb[i];
         if constexpr (GATHER_B) t.vob[i] = off; else t.voa[i] = off;
@@ -628,35 +650,35 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
 
   // ---------------- fragment addresses ------------------------------------------
-  // Slot, block and sub-step are immediate offsets of the LDS reads, which reach 64 KB: one set of
-  // per-lane addresses serves slots 0-1, one slots 2-3, one slot 4; four addresses per set and operand.
+  // Slot, block and sub-step are immediate offsets of the LDS reads, which reach 64 KB: one set of per-lane addresses
+  // serves slots 0-1, one slots 2-3, one slot 4 (S = 128: slots 0-3, slot 4); up to four addresses per set and operand.
   //  [row][k] tile: block b = rows 16 b + (lane & 15), sub-step s (32 k) = logical piece 4 s + lane / 16.
   //    The row's share of the swizzle is lane & 7 whatever the block, so the address of (b, s) is
   //    base[s] + 2048 b.
   //  [k][n] tile: block b = columns 16 b + (lane & 15); within 16 lanes, lane i supplies the address of four
   //    consecutive n of k row i / 4, n group i % 4, and lane l receives k rows 0..3 of column l; lanes
   //    16 g .. 16 g + 15 take k rows 8 g .. of the sub-step.  The k-row swizzle XORs bits 1-2 of the block
-  //    number, so the address of block b is base[b / 2] + 32 (b & 1); the second half of a fragment lies
-  //    4 k rows = 2048 bytes further, sub-step 1 32 k rows = 16384 bytes further.
+  //    number (counted over the whole row), so the address of block b is base[b / 2] + 32 (b & 1); the second half of a
+  //    fragment lies 4 k rows further, sub-step 1 32 k rows.
   // The addresses of a row-grouped A operand carry the wave's first row r0, which depends on the tile (a multiple of 32,
   // so the rotation of the pieces does not see it).
-  uint32_t fa_base[3][4], fb_base[3][4];
+  uint32_t fa_base[TL::SETS][4], fb_base[TL::SETS][4];
 #pragma unroll
-  for (int st = 0; st < 3; ++st) {
-    const uint32_t org = lds0 + st * 2 * TILE_BYTES;
+  for (int st = 0; st < TL::SETS; ++st) {
+    const uint32_t org = lds0 + st * TL::SLOTS_PER_SET * TILE_BYTES;
 #pragma unroll
     for (int x = 0; x < 4; ++x) {
       const int i16 = lane & 15;
       // [row][k]
       const int pc = ((x & 1) * 4 + (lane >> 4) + (lane & 7)) & 7;   // sub-step x & 1; the block is an immediate offset
       const uint32_t kc_a = org + i16 * 128 + pc * 16;   // + 128 r0 of the tile, see main_loop
-      const uint32_t kc_b = org + (wn * 128 + i16) * 128 + pc * 16;
+      const uint32_t kc_b = org + (wn * HALF + i16) * 128 + pc * 16;
       // [k][n]
       const int krow = (lane >> 4) * 8 + (i16 >> 2);
       const int sw = krow & 3;
-      const uint32_t kn_lane = krow * 512 + ((x ^ sw) << 6) + ((i16 >> 1) & 1) * 16 + (i16 & 1) * 8;
-      const uint32_t kn_a = org + wm * 256 + kn_lane;
-      const uint32_t kn_b = org + wn * 256 + kn_lane;
+      const uint32_t kn_lane = org + krow * TL::KN_ROW + ((i16 >> 1) & 1) * 16 + (i16 & 1) * 8;
+      const uint32_t kn_a = kn_lane + (((wm * (NB / 2) + x) ^ sw) << 6);   // 64-byte group of block 2 x in the row
+      const uint32_t kn_b = kn_lane + (((wn * (NB / 2) + x) ^ sw) << 6);
       fa_base[st][x] = A_KN ? kn_a : kc_a;
       fb_base[st][x] = B_KN ? kn_b : kc_b;
     }
@@ -664,32 +686,32 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   int fa_r0 = 0;                 // the r0 that the A addresses carry
 
   // ---------------- main loop ----------------------------------------------------
-  f32x4_t acc[8][8];
+  f32x4_t acc[NB][NB];
 
   // two fragment sets: one feeds the MFMAs while the other is being read
-  KnFrag fa[2][8], fb[2][8];
-  constexpr int A_OPS_PER_BLK = A_KN ? 2 : 1, B_OPS_PER_BLK = B_KN ? 2 : 1;
+  KnFrag fa[2][NB], fb[2][NB];
+  constexpr int A_OPS_PER_BLK = A_KN ? 2 : 1, B_OPS_PER_BLK = B_KN ? 2 : 1, SPS = TL::SLOTS_PER_SET;
   // Read instruction number `op` of a sub-step: the A blocks first (only the live ones), then the B blocks.
   auto read_op = [&](auto slot_a_tag, auto slot_b_tag, auto s_tag, auto set_tag, auto nv_tag, auto op_tag) __attribute__((always_inline)) {
-    constexpr int SA = decltype(slot_a_tag)::value, SB = decltype(slot_b_tag)::value, S = decltype(s_tag)::value;
+    constexpr int SA = decltype(slot_a_tag)::value, SB = decltype(slot_b_tag)::value, SUB = decltype(s_tag)::value;
     constexpr int SET = decltype(set_tag)::value, NV = decltype(nv_tag)::value, OP = decltype(op_tag)::value;
     constexpr int A_OPS = 2 * NV * A_OPS_PER_BLK;
     if constexpr (OP < A_OPS) {
       constexpr int blk = OP / A_OPS_PER_BLK;
       if constexpr (A_KN) {
         constexpr int half = OP % 2;
-        fa[SET][blk].h[half] = lds_read_tr_b64<(SA & 1) * TILE_BYTES + S * 16384 + half * 2048 + (blk & 1) * 32>(fa_base[SA >> 1][blk >> 1]);
+        fa[SET][blk].h[half] = lds_read_tr_b64<SA % SPS * TILE_BYTES + SUB * 32 * TL::KN_ROW + half * 4 * TL::KN_ROW + (blk & 1) * 32>(fa_base[SA / SPS][blk >> 1]);
       } else {
-        fa[SET][blk].v = lds_read_b128<(SA & 1) * TILE_BYTES + blk * 2048>(fa_base[SA >> 1][S]);
+        fa[SET][blk].v = lds_read_b128<SA % SPS * TILE_BYTES + blk * 2048>(fa_base[SA / SPS][SUB]);
       }
     } else {
       constexpr int OB = OP - A_OPS;
       constexpr int blk = OB / B_OPS_PER_BLK;
       if constexpr (B_KN) {
         constexpr int half = OB % 2;
-        fb[SET][blk].h[half] = lds_read_tr_b64<(SB & 1) * TILE_BYTES + S * 16384 + half * 2048 + (blk & 1) * 32>(fb_base[SB >> 1][blk >> 1]);
+        fb[SET][blk].h[half] = lds_read_tr_b64<SB % SPS * TILE_BYTES + SUB * 32 * TL::KN_ROW + half * 4 * TL::KN_ROW + (blk & 1) * 32>(fb_base[SB / SPS][blk >> 1]);
       } else {
-        fb[SET][blk].v = lds_read_b128<(SB & 1) * TILE_BYTES + blk * 2048>(fb_base[SB >> 1][S]);
+        fb[SET][blk].v = lds_read_b128<SB % SPS * TILE_BYTES + blk * 2048>(fb_base[SB / SPS][SUB]);
       }
     }
   };
@@ -703,26 +725,27 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
 
   // One 32-deep sub-step: the live MFMAs of fragment set SET, and between them (one per gap) the read
-  // instructions of the next sub-step and, in a step that loads (LOADS), the wave's eight loads of one
-  // tile.  Gap g is the place after MFMA g: reads take the even gaps 0, 2, .. (every gap when both operands
-  // need two reads per block), M0 is set in gap 1, loads take gaps 3, 7, .., 31; what does not fit behind
+  // instructions of the next sub-step and, in a step that loads (LOADS), the wave's NL loads of one
+  // tile.  Gap g is the place after MFMA g: reads take the even gaps 0, 2, .. (every gap when they would not fit
+  // otherwise), M0 is set in gap 1, loads take gaps 3, 7, .., 4 NL - 1; what does not fit behind
   // the last live MFMA follows it.
   auto sub_step = [&](auto set_tag, auto nv_tag, auto nreads_tag, auto reader, auto loads_tag, auto set_m0_fn, auto loader)
       __attribute__((always_inline)) {
     constexpr int SET = decltype(set_tag)::value, NV = decltype(nv_tag)::value;
     constexpr int NREADS = decltype(nreads_tag)::value;
     constexpr bool LOADS = decltype(loads_tag)::value != 0;
-    constexpr int ML = 16 * NV;                         // live MFMAs: blocks i < 2 NV, all j
-    constexpr int RSTRIDE = NREADS > 32 ? 1 : 2;
-    constexpr int LAST_GAP = (NREADS - 1) * RSTRIDE > 31 ? (NREADS - 1) * RSTRIDE : 31;
+    constexpr int ML = 2 * NB * NV;                     // live MFMAs: blocks i < 2 NV, all j
+    constexpr int RSTRIDE = 2 * NREADS > NB * NB ? 1 : 2;
+    constexpr int LAST_LOAD = 4 * NL - 1;
+    constexpr int LAST_GAP = (NREADS - 1) * RSTRIDE > LAST_LOAD ? (NREADS - 1) * RSTRIDE : LAST_LOAD;
     constexpr int SLOTS = ML > LAST_GAP + 1 ? ML : LAST_GAP + 1;
     static_for<SLOTS>([&](auto g_tag) {
       constexpr int g = decltype(g_tag)::value;
-      if constexpr (g < ML) mma(IC<SET>{}, IC<g / 8>{}, IC<g % 8>{});
+      if constexpr (g < ML) mma(IC<SET>{}, IC<g / NB>{}, IC<g % NB>{});
       if constexpr (g % RSTRIDE == 0 && g / RSTRIDE < NREADS) reader(IC<g / RSTRIDE>{});
       if constexpr (LOADS) {
         if constexpr (g == 1) set_m0_fn();
-        if constexpr (g >= 3 && g <= 31 && (g - 3) % 4 == 0) loader(IC<(g - 3) / 4>{});
+        if constexpr (g >= 3 && g <= LAST_LOAD && (g - 3) % 4 == 0) loader(IC<(g - 3) / 4>{});
       }
     });
   };
@@ -734,10 +757,10 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     constexpr int P = decltype(phase_tag)::value, KIND = decltype(kind_tag)::value, NV = decltype(nv_tag)::value;
     using SA = IC<slot_of_a(P)>;
     using SB = IC<slot_of_b(P)>;
-    using NA = IC<slot_of_a((P + 1) % NSLOT)>;
-    using NB = IC<slot_of_b((P + 1) % NSLOT)>;
+    using NextA = IC<slot_of_a((P + 1) % NSLOT)>;
+    using NextB = IC<slot_of_b((P + 1) % NSLOT)>;
     constexpr int LA = slot_of_a((P + 2) % NSLOT);
-    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + 8 * B_OPS_PER_BLK;
+    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
     if constexpr (KIND == 2 && GATHER_A) {
       // the tokens of A(kt+2) were fetched a step ago and are covered by that step's wait; those of A(kt+3)
       // are requested before the loads of A(kt+2), the only ones this step's wait leaves in flight
@@ -752,12 +775,12 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     if constexpr (KIND == 2) a_end(t, kt + 2);
     lds_wait<0>();
     if constexpr (KIND >= 1) {
-      if constexpr (KIND == 2) wait_vm<8>(); else wait_vm<0>();   // this wave's loads of A(kt+2) may stay in flight
+      if constexpr (KIND == 2) wait_vm<NL>(); else wait_vm<0>();   // this wave's loads of A(kt+2) may stay in flight
       wg_barrier();
     }
     if constexpr (KIND == 2 && GATHER_B) apply_tok(t, t.tokn);   // fetched a step ago, older than the loads of A(kt+2)
     sub_step(IC<1>{}, nv_tag, IC<KIND >= 1 ? NREADS : 0>{},
-             [&](auto op) __attribute__((always_inline)) { read_op(NA{}, NB{}, IC<0>{}, IC<0>{}, nv_tag, op); },
+             [&](auto op) __attribute__((always_inline)) { read_op(NextA{}, NextB{}, IC<0>{}, IC<0>{}, nv_tag, op); },
              IC<KIND == 2 ? 1 : 0>{},
              [&]() __attribute__((always_inline)) { set_m0<SA::value * TILE_BYTES>(lds_fill); },
              [&](auto i) __attribute__((always_inline)) { b_part(t, kt + 2, i, sp_tag); });
@@ -784,13 +807,13 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
     set_m0_rt(slot_m0(t, 2 * kt));
     asm volatile("s_nop 0" ::: "memory");
-    static_for<8>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
+    static_for<NL>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
     a_end(t, kt);
   };
   auto b_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
     set_m0_rt(slot_m0(t, 2 * kt + 1));
     asm volatile("s_nop 0" ::: "memory");
-    static_for<8>([&](auto i) { b_part(t, kt, i, IC<2>{}); });
+    static_for<NL>([&](auto i) { b_part(t, kt, i, IC<2>{}); });
     b_end(t, kt);
   };
   auto first_loads = [&](TileState& t) __attribute__((always_inline)) {
@@ -799,27 +822,27 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // The tokens of steps 0, 1 and 2 are requested first, older than the loads of the other operand, and are here before
       // the epilogue starts: no register that a load has yet to write lives across it.  Rows past the expert's end, and
       // steps that do not exist, repeat its last row.
-      int tk[3][8];
+      int tk[3][NL];
       const int last = t.k_hi - t.k_lo - 1;
       static_for<3>([&](auto s_tag) {
         constexpr int s = decltype(s_tag)::value;
-        static_for<8>([&](auto i_tag) {
+        static_for<NL>([&](auto i_tag) {
           constexpr int i = decltype(i_tag)::value;
-          int r = s * BK + (wave * 8 + i) * 2 + (lane >> 5);
+          int r = s * BK + kn_load_row(i, lane);
           if (r > last) r = last;
           tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, t.row_tok);
         });
       });
       if constexpr (GATHER_B) a_unit(t, 0); else b_unit(t, 0);
-      wait_vm<8>();                             // on every path, behind no branch: the compiler does not know of these loads
+      wait_vm<NL>();                            // on every path, behind no branch: the compiler does not know of these loads
 #pragma unroll
-      for (int i = 0; i < 24; ++i) asm volatile("" : "+v"(tk[i / 8][i % 8]));
+      for (int i = 0; i < 3 * NL; ++i) asm volatile("" : "+v"(tk[i / NL][i % NL]));
       if (t.nk > 1) { if constexpr (GATHER_B) a_unit(t, 1); else b_unit(t, 1); }
       apply_tok(t, tk[0]);
       if constexpr (GATHER_B) b_unit(t, 0); else a_unit(t, 0);
       apply_tok(t, tk[1]);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) t.tokn[i] = tk[2][i];
+      for (int i = 0; i < NL; ++i) t.tokn[i] = tk[2][i];
       if (t.nk > 1) { if constexpr (GATHER_B) b_unit(t, 1); else a_unit(t, 1); }
     } else {
       b_unit(t, 0);
@@ -837,7 +860,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     if (t.nk <= 0) return;
     if constexpr (!A_KN) {
 #pragma unroll
-      for (int st = 0; st < 3; ++st) {
+      for (int st = 0; st < TL::SETS; ++st) {
         fa_base[st][0] += (t.r0 - fa_r0) * 128;
         fa_base[st][1] += (t.r0 - fa_r0) * 128;
       }
@@ -847,11 +870,11 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     // The tile's first loads are awaited; those of step 1 may stay in flight (the last of a gathered operand only: both
     // steps of the other one come first).  Stores of the epilogue before are in flight too; as loads complete in order
     // among themselves, the waits here and in the steps hold wherever the stores lie between them.
-    if (t.nk <= 1) wait_vm<0>(); else if (GATHER_A || GATHER_B) wait_vm<8>(); else wait_vm<16>();
+    if (t.nk <= 1) wait_vm<0>(); else if (GATHER_A || GATHER_B) wait_vm<NL>(); else wait_vm<2 * NL>();
     wg_barrier();
     // ---- first fragments: sub-step 0 of step 0, from the slots of phase p0
     constexpr int NV = decltype(nv_tag)::value;
-    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + 8 * B_OPS_PER_BLK;
+    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
     auto first_reads = [&](auto phase_tag) __attribute__((always_inline)) {
       constexpr int P = decltype(phase_tag)::value;
       static_for<NREADS>([&](auto op) { read_op(IC<slot_of_a(P)>{}, IC<slot_of_b(P)>{}, IC<0>{}, IC<0>{}, nv_tag, op); });
@@ -886,7 +909,13 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // expert's end only keeps the loads and barriers going
   auto run_main = [&](TileState& t) __attribute__((always_inline)) {
     if constexpr (is_wgrad(MODE)) {
-      main_loop(t, IC<4>{});
+      main_loop(t, IC<HALF / 32>{});
+    } else if constexpr (S == 128) {
+      switch (t.nv) {
+        case 2: main_loop(t, IC<2>{}); break;
+        case 1: main_loop(t, IC<1>{}); break;
+        default: main_loop(t, IC<0>{}); break;
+      }
     } else {
       switch (t.nv) {
         case 4: main_loop(t, IC<4>{}); break;
@@ -899,7 +928,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
   // ---------------- epilogue -----------------------------------------------------
   // acc[i][j][c] is the wave's element (row, col) with row = 16 i + (lane & 15) and col = 16 j + 4 (lane / 16) + c.
-  // The wave stages bf16 rows of 256 bytes in 8 KB of LDS of its own (its share of a ring slot; 16-byte pieces
+  // The wave stages its bf16 rows of S bytes in LDS of its own (its share of a ring slot; 16-byte pieces
   // swizzled by the row), a few rows at a time, and stores 16 bytes per lane in full row segments.
   // The accumulators are read out of the accumulation registers at the point of use, by hand: left to the
   // compiler they are moved (and spilled) in bulk where the copies of the main loop join.
@@ -914,12 +943,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(x) : "a"(c3));  v[3] = x;
     return v;
   };
-  // GATE_UP with gate weights folded into h, DGRAD_H_GATE: the weights of the lane's eight rows, requested
+  // GATE_UP with gate weights folded into h, DGRAD_H_GATE: the weights of the lane's NB rows, requested
   // right behind the main loop and awaited before the next tile's first loads are requested.
-  float wv[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+  float wv[NB];
+#pragma unroll
+  for (int i = 0; i < NB; ++i) wv[i] = 1.f;
   auto fetch_row_weights = [&](const TileState& t, const float* rw) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < NB; ++i) {
       int r = t.m0 + t.r0 + i * 16 + (lane & 15);  if (r > t.m_end - 1) r = t.m_end - 1;
       wv[i] = rw[r];
     }
@@ -936,11 +967,12 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     const int lane = tid & 63, l16 = lane & 15, lq = lane >> 4;
     const int m_end = t.m_wave, n0 = t.n0;                               // end of the wave's valid rows
     const int grow0 = t.m0 + t.r0;                                       // wave's first output row
-    const int gcol0 = n0 + wn * (MODE == GATE_UP ? 64 : 128);            // wave's first output column
-    char* stage = lds + t.slot * TILE_BYTES + wave * 8192;
+    const int gcol0 = n0 + wn * (MODE == GATE_UP ? S / 4 : HALF);        // wave's first output column
+    constexpr int RB = S, RP = S / 16;          // bytes and 16-byte pieces of a staged row of all the wave's columns
+    char* stage = lds + t.slot * TILE_BYTES + wave * TL::SHARE;
     // address of the 8 bytes of columns 4 lq .. + 3 of 16-column block `blk` in staged row `row`
     auto quad_addr = [&](int row, int blk) __attribute__((always_inline)) -> char* {
-      return stage + row * 256 + (((2 * blk + (lq >> 1)) ^ (row & 15)) << 4) + (lq & 1) * 8;
+      return stage + row * RB + (((2 * blk + (lq >> 1)) ^ (row & (RP - 1))) << 4) + (lq & 1) * 8;
     };
     auto put_quad = [&](int row, int blk, const f32x4_t& v) __attribute__((always_inline)) {
       u32x2 o;
@@ -954,7 +986,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     // straight-line code, ragged or not.
     const int ncol = ae->N;
     int rows = m_end - grow0;
-    rows = rows < 0 ? 0 : (rows > 128 ? 128 : rows);
+    rows = rows < 0 ? 0 : (rows > HALF ? HALF : rows);
     auto rows_of = [&](const void* base, int ld_bytes) __attribute__((always_inline)) {
       const char* first = scalarize(static_cast<const char*>(base) + static_cast<size_t>(grow0) * ld_bytes);
       return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(first), 0, __builtin_amdgcn_readfirstlane(rows * ld_bytes), 0x00020000);
@@ -988,117 +1020,120 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         __builtin_amdgcn_raw_buffer_store_b128(v[k], out, off + (first + k * RPP) * ncol * 2, 0, decltype(nt_tag)::value ? 2 : 0);
     };
 
-    // A wave with 96 rows or fewer takes a second copy, which tests in front of every part whether it has a row: the tests
+    // A wave with HALF - 32 rows or fewer takes a second copy, which tests in front of every part whether it has a row: the tests
     // end the overlap, but the parts left out are worth more.
     // Measured against masked stores issued part by part: gate_up 470 -> 459 us and the launch of dgrad_h 575 -> 560 us at
     // 65536 rows, d 2048, f 1024, 64 experts; 17 -> 13 and 25 -> 17 us where experts have 56 rows (d 128, f 512).
     // In every form a part's rows are read back from LDS as soon as they are staged and stored behind the arithmetic of the
     // part after it: with one wave per SIMD nothing else covers the round trip through LDS.
     if constexpr (MODE == GATE_UP) {
-      // blocks 0-3 are g, blocks 4-7 the same columns of u.  Eight parts of 16 rows: g in pieces 0-7 and u in
-      // pieces 8-15 of 256-byte rows, h = silu(g) * u (from the fp32 accumulators, times the row's gate weight if
-      // the caller folds the weights into h) in 128-byte rows behind them.
+      // The first half of the blocks are g, the other half the same columns of u.  Parts of 16 rows: g in the first and u in
+      // the second half of the staged rows, h = silu(g) * u (from the fp32 accumulators, times the row's gate weight if
+      // the caller folds the weights into h) in rows of half their length behind them.
       const bool weighted = ae->row_weight != nullptr;
-      char* hstage = stage + 16 * 256;
+      constexpr int HP = RP / 2, GP = 16 * HP / 64;   // pieces of a row of g, u or h; passes of 64 pieces over 16 rows
+      char* hstage = stage + 16 * RB;
       const Rsrc go = rows_of(ae->O0, ncol * 2), uo = rows_of(ae->O1, ncol * 2), ho = rows_of(ae->O2, ncol * 2);
-      u32x4 v[6];
+      u32x4 v[3 * GP];
       auto store_part = [&](int part) __attribute__((always_inline)) {
-        store_rows(IC<1>{}, v, go, part * 16, IC<2>{}, IC<8>{});
-        store_rows(IC<1>{}, v + 2, uo, part * 16, IC<2>{}, IC<8>{});
-        store_rows(IC<0>{}, v + 4, ho, part * 16, IC<2>{}, IC<8>{});
+        store_rows(IC<1>{}, v, go, part * 16, IC<GP>{}, IC<HP>{});
+        store_rows(IC<1>{}, v + GP, uo, part * 16, IC<GP>{}, IC<HP>{});
+        store_rows(IC<0>{}, v + 2 * GP, ho, part * 16, IC<GP>{}, IC<HP>{});
       };
       auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
       constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
-      static_for<8>([&](auto i_tag) {
+      static_for<NB>([&](auto i_tag) {
         constexpr int i = decltype(i_tag)::value;
         if constexpr (RAGGED) { if (i * 16 >= rows) return; }
         const int row = l16;
         const float w = weighted ? wv[i] : 1.f;
-        static_for<4>([&](auto j_tag) {
+        static_for<NB / 2>([&](auto j_tag) {
           constexpr int j = decltype(j_tag)::value;
           const f32x4_t gv = accq(i_tag, IC<j>{});
-          const f32x4_t uv = accq(i_tag, IC<j + 4>{});
+          const f32x4_t uv = accq(i_tag, IC<j + NB / 2>{});
           put_quad(row, j, gv);
-          put_quad(row, j + 4, uv);
+          put_quad(row, j + NB / 2, uv);
           u32x2 o;
           float h[4];
 #pragma unroll
           for (int c = 0; c < 4; ++c) h[c] = silu_f(gv[c]) * uv[c] * w;
           o.x = pack_bf16(h[0], h[1]);
           o.y = pack_bf16(h[2], h[3]);
-          *reinterpret_cast<u32x2*>(hstage + row * 128 + (((2 * j + (lq >> 1)) ^ (row & 7)) << 4) + (lq & 1) * 8) = o;
+          *reinterpret_cast<u32x2*>(hstage + row * (RB / 2) + (((2 * j + (lq >> 1)) ^ (row & (HP - 1))) << 4) + (lq & 1) * 8) = o;
         });
         __builtin_amdgcn_wave_barrier();
         if constexpr (!RAGGED && i > 0) store_part(i - 1);
-        read_staged(v, stage, IC<256>{}, IC<2>{}, IC<0>{}, IC<8>{});
-        read_staged(v + 2, stage, IC<256>{}, IC<2>{}, IC<8>{}, IC<8>{});
-        read_staged(v + 4, hstage, IC<128>{}, IC<2>{}, IC<0>{}, IC<8>{});
+        read_staged(v, stage, IC<RB>{}, IC<GP>{}, IC<0>{}, IC<HP>{});
+        read_staged(v + GP, stage, IC<RB>{}, IC<GP>{}, IC<HP>{}, IC<HP>{});
+        read_staged(v + 2 * GP, hstage, IC<RB / 2>{}, IC<GP>{}, IC<0>{}, IC<HP>{});
         __builtin_amdgcn_wave_barrier();
         if constexpr (RAGGED) store_part(i);
       });
-      if constexpr (!RAGGED) store_part(7);
+      if constexpr (!RAGGED) store_part(NB - 1);
       };
-      if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
+      if (rows > HALF - 32) parts(IC<0>{}); else parts(IC<1>{});
     } else if constexpr (is_dgrad_h(MODE)) {
-      // In eight parts of 16 rows, staged alternately in the wave's share of two ring slots: g rows at [0, 4K), u rows at
-      // [4K, 8K) of the part's buffer, overwritten in place by dg and du.
+      // In parts of 16 rows, staged alternately in the wave's share of two ring slots: g rows in the first half, u rows in
+      // the second half of the part's buffer, overwritten in place by dg and du.
       // DGRAD_H_GATE: the accumulators hold dh0 = dout[token] . Wd; the row's gate weight w turns them into
       // dh = w dh0, and the sum over a 64-column strip of dh0 * silu(g) * u is the strip's share of the
       // gradient of w (a lane holds 16 of the strip's columns of its row, lanes ^ 16, ^ 32 the others).
       constexpr bool GATE = (MODE == DGRAD_H_GATE);
-      constexpr int GU_PASSES = 4;   // 16 rows x 16 pieces = 256 pieces of 16 bytes, 64 per pass
-      constexpr int UOFF = 4096;
+      constexpr int GU_PASSES = 16 * RP / 64;   // 16 rows of RP pieces of 16 bytes, 64 per pass
+      constexpr int GU_ROWS = 64 / RP;          // rows of a pass
+      constexpr int UOFF = TL::SHARE / 2;
       const Rsrc gi = rows_of(ae->G, ncol * 2), ui = rows_of(ae->U, ncol * 2);
       const Rsrc dgo = rows_of(ae->O0, ncol * 2), duo = rows_of(ae->O1, ncol * 2);
       u32x4 pg[GU_PASSES], pu[GU_PASSES];
-      const int gu_off = gcol0 + (lane & 15) * 8 < ncol ? ((lane >> 4) * ncol + gcol0 + (lane & 15) * 8) * 2 : PAST;
+      const int gu_off = gcol0 + lane % RP * 8 < ncol ? (lane / RP * ncol + gcol0 + lane % RP * 8) * 2 : PAST;
       auto gu_load = [&](int part) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < GU_PASSES; ++p) {
-          pg[p] = __builtin_amdgcn_raw_buffer_load_b128(gi, gu_off + (part * 16 + p * 4) * ncol * 2, 0, 0);
-          pu[p] = __builtin_amdgcn_raw_buffer_load_b128(ui, gu_off + (part * 16 + p * 4) * ncol * 2, 0, 0);
+          pg[p] = __builtin_amdgcn_raw_buffer_load_b128(gi, gu_off + (part * 16 + p * GU_ROWS) * ncol * 2, 0, 0);
+          pu[p] = __builtin_amdgcn_raw_buffer_load_b128(ui, gu_off + (part * 16 + p * GU_ROWS) * ncol * 2, 0, 0);
         }
       };
       auto gu_stage = [&](char* buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int p = 0; p < GU_PASSES; ++p) {
-          const int row = p * 4 + (lane >> 4), piece = lane & 15;
-          const int so = row * 256 + ((piece ^ (row & 15)) << 4);
+          const int row = p * GU_ROWS + lane / RP, piece = lane % RP;
+          const int so = row * RB + ((piece ^ (row & (RP - 1))) << 4);
           *reinterpret_cast<u32x4*>(buf + so) = pg[p];
           *reinterpret_cast<u32x4*>(buf + UOFF + so) = pu[p];
         }
       };
-      char* const bufs[2] = {stage, lds + (t.slot + NSLOT - 1) % NSLOT * TILE_BYTES + wave * 8192};
-      int qoff[8];                  // offsets of the lane's quads in a part's buffer: the same for every part
+      char* const bufs[2] = {stage, lds + (t.slot + NSLOT - 1) % NSLOT * TILE_BYTES + wave * TL::SHARE};
+      int qoff[NB];                 // offsets of the lane's quads in a part's buffer: the same for every part
 #pragma unroll
-      for (int j = 0; j < 8; ++j) qoff[j] = static_cast<int>(quad_addr(l16, j) - stage);
-      u32x4 v[8];
+      for (int j = 0; j < NB; ++j) qoff[j] = static_cast<int>(quad_addr(l16, j) - stage);
+      u32x4 v[2 * GU_PASSES];
       auto store_part = [&](int part) __attribute__((always_inline)) {
-        store_rows(IC<0>{}, v, dgo, part * 16, IC<4>{}, IC<16>{});
-        store_rows(IC<0>{}, v + 4, duo, part * 16, IC<4>{}, IC<16>{});
+        store_rows(IC<0>{}, v, dgo, part * 16, IC<GU_PASSES>{}, IC<RP>{});
+        store_rows(IC<0>{}, v + GU_PASSES, duo, part * 16, IC<GU_PASSES>{}, IC<RP>{});
       };
-      float dpart[8][2];
+      constexpr int STRIPS = HALF / 64;         // 64-column strips of the wave's piece
+      float dpart[NB][STRIPS];
       auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
       constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
       gu_load(0);
       gu_stage(bufs[0]);
       gu_load(1);
-      static_for<8>([&](auto part_tag) {
+      static_for<NB>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
         if constexpr (RAGGED) { if (part * 16 >= rows) return; }
         char* const buf = bufs[part & 1];
         const float wrow = GATE ? wv[part] : 1.f;
-        float dsum[2] = {0.f, 0.f};
+        float dsum[STRIPS] = {};
         __builtin_amdgcn_wave_barrier();
-        // the lane's eight g and u quads of the part, read in one go: the quads are overwritten in place below, so
+        // the lane's g and u quads of the part, read in one go: the quads are overwritten in place below, so
         // reads issued one by one would each wait behind the previous quad's write
-        u32x2 gqs[8], uqs[8];
+        u32x2 gqs[NB], uqs[NB];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NB; ++j) {
           gqs[j] = *reinterpret_cast<const u32x2*>(buf + qoff[j]);
           uqs[j] = *reinterpret_cast<const u32x2*>(buf + qoff[j] + UOFF);
         }
-        static_for<8>([&](auto j_tag) {
+        static_for<NB>([&](auto j_tag) {
           constexpr int j = decltype(j_tag)::value;
           const f32x4_t dhv = accq(part_tag, j_tag);
           char* ga = buf + qoff[j];
@@ -1115,7 +1150,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
               const float dh0 = dhv[c];
               const float sl = g4[c] * sg;                 // silu(g)
               const float t0 = dh0 * u4[c];
-              dsum[j >> 2] = __builtin_fmaf(t0, sl, dsum[j >> 2]);
+              dsum[j >> 2] = __builtin_fmaf(t0, sl, dsum[j >> 2]);   // 4 blocks to a strip
               du[c] = (dh0 * wrow) * sl;
               dg[c] = (t0 * wrow) * (sg * __builtin_fmaf(g4[c], 1.0f - sg, 1.0f));
             } else {
@@ -1133,7 +1168,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         });
         if constexpr (GATE) {
 #pragma unroll
-          for (int s2 = 0; s2 < 2; ++s2) {
+          for (int s2 = 0; s2 < STRIPS; ++s2) {
             float x = dsum[s2];
             x += __shfl_xor(x, 16, 64);
             x += __shfl_xor(x, 32, 64);
@@ -1141,27 +1176,27 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
           }
         }
         __builtin_amdgcn_wave_barrier();
-        if constexpr (part + 1 < 8) gu_stage(bufs[(part + 1) & 1]);   // awaits the loads of part + 1
+        if constexpr (part + 1 < NB) gu_stage(bufs[(part + 1) & 1]);   // awaits the loads of part + 1
         __builtin_amdgcn_wave_barrier();
         if constexpr (!RAGGED && part > 0) store_part(part - 1);
-        read_staged(v, buf, IC<256>{}, IC<4>{}, IC<0>{}, IC<16>{});
-        read_staged(v + 4, buf + UOFF, IC<256>{}, IC<4>{}, IC<0>{}, IC<16>{});
+        read_staged(v, buf, IC<RB>{}, IC<GU_PASSES>{}, IC<0>{}, IC<RP>{});
+        read_staged(v + GU_PASSES, buf + UOFF, IC<RB>{}, IC<GU_PASSES>{}, IC<0>{}, IC<RP>{});
         __builtin_amdgcn_wave_barrier();
         if constexpr (RAGGED) store_part(part);
-        if constexpr (part + 2 < 8) gu_load(part + 2);
+        if constexpr (part + 2 < NB) gu_load(part + 2);
       });
-      if constexpr (!RAGGED) store_part(7);
+      if constexpr (!RAGGED) store_part(NB - 1);
       };
-      if (rows > 96) parts(IC<0>{}); else if (rows > 0) parts(IC<1>{});
+      if (rows > HALF - 32) parts(IC<0>{}); else if (rows > 0) parts(IC<1>{});
       if constexpr (GATE) {
         // the strips' shares of the gate gradient, stored behind everything else
         const int strips = ncol >> 6;
         const Rsrc dpo = rows_of(ae->dgate_part, strips * 4);
 #pragma unroll
-        for (int s2 = 0; s2 < 2; ++s2) {
+        for (int s2 = 0; s2 < STRIPS; ++s2) {
           // a strip past the last column has no share
           const int off = lq == 0 && gcol0 + s2 * 64 < ncol ? (l16 * strips + (gcol0 >> 6) + s2) * 4 : PAST;
-          static_for<8>([&](auto part_tag) {
+          static_for<NB>([&](auto part_tag) {
             constexpr int part = decltype(part_tag)::value;
             __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dpart[part][s2]), dpo, off + part * 16 * strips * 4, 0, 0);
           });
@@ -1171,29 +1206,30 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       uint16_t* out = t.second ? ae->O1 : ae->O0;
       if constexpr (is_wgrad(MODE)) out += static_cast<size_t>(t.e) * ae->M * ncol;
       const Rsrc oo = rows_of(out, ncol * 2);
-      u32x4 v[8];
-      // four parts of 32 rows
+      constexpr int PASSES = 32 * RP / 64;
+      u32x4 v[PASSES];
+      // parts of 32 rows
       auto store_part = [&](int part) __attribute__((always_inline)) {
-        store_rows(IC<(MODE == WGRAD_GATHER) ? 1 : 0>{}, v, oo, part * 32, IC<8>{}, IC<16>{});
+        store_rows(IC<(MODE == WGRAD_GATHER) ? 1 : 0>{}, v, oo, part * 32, IC<PASSES>{}, IC<RP>{});
       };
       auto parts = [&](auto ragged_tag) __attribute__((always_inline)) {
       constexpr bool RAGGED = decltype(ragged_tag)::value != 0;
-      static_for<4>([&](auto part_tag) {
+      static_for<HALF / 32>([&](auto part_tag) {
         constexpr int part = decltype(part_tag)::value;
         if constexpr (RAGGED) { if (part * 32 >= rows) return; }
         static_for<2>([&](auto i2_tag) {
           constexpr int i2 = decltype(i2_tag)::value;
-          static_for<8>([&](auto j_tag) { put_quad(i2 * 16 + l16, decltype(j_tag)::value, accq(IC<part * 2 + i2>{}, j_tag)); });
+          static_for<NB>([&](auto j_tag) { put_quad(i2 * 16 + l16, decltype(j_tag)::value, accq(IC<part * 2 + i2>{}, j_tag)); });
         });
         __builtin_amdgcn_wave_barrier();
         if constexpr (!RAGGED && part > 0) store_part(part - 1);
-        read_staged(v, stage, IC<256>{}, IC<8>{}, IC<0>{}, IC<16>{});
+        read_staged(v, stage, IC<RB>{}, IC<PASSES>{}, IC<0>{}, IC<RP>{});
         __builtin_amdgcn_wave_barrier();
         if constexpr (RAGGED) store_part(part);
       });
-      if constexpr (!RAGGED) store_part(3);
+      if constexpr (!RAGGED) store_part(HALF / 32 - 1);
       };
-      if (rows > 96) parts(IC<0>{}); else parts(IC<1>{});
+      if (rows > HALF - 32) parts(IC<0>{}); else parts(IC<1>{});
     }
     __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0): this wave's staging reads are done
   };
@@ -1230,9 +1266,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     for (;;) {
       last_first_loads(cur);
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
+      for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
           for (int r = 0; r < 4; ++r) acc[i][j][r] = 0.f;
       run_main(cur);
@@ -1254,11 +1290,11 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       if constexpr (MODE == GATE_UP || MODE == DGRAD_H_GATE) {
         // (a use that the compiler sees: left to the epilogue, its wait would cover the first loads too)
 #pragma unroll
-        for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(wv[i]));
+        for (int i = 0; i < NB; ++i) asm volatile("" : "+v"(wv[i]));
       }
       if (more) first_loads(cur);
       epilogue(done);
-      // a wave stages in, and loads into, its own 8 KB of a slot only: no barrier between epilogue and later loads
+      // a wave stages in, and loads into, its own share of a slot only: no barrier between epilogue and later loads
       if (!more) break;
     }
   }
@@ -1274,18 +1310,18 @@ __device__ __forceinline__ int first_list_position() {
   return (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
 }
 
-template <int MODE>
-__global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_kernel(GemmArgs a) {
-  gemm_tile_list<MODE, 0>(a, first_list_position());
+template <int MODE, int S>
+__global__ __launch_bounds__(GEMM_THREADS, Tile<S>::PER_CU) void grouped_gemm_kernel(GemmArgs a) {
+  gemm_tile_list<MODE, S, 0>(a, first_list_position());
 }
 
 // Two products that do not depend on each other in one launch: the tile list of the second follows
 // that of the first, so the workgroups that run out of tiles of the first go on with the second
 // instead of idling until the next launch (one tail and one start-up instead of two).
-template <int MODE_A, int MODE_B>
-__global__ __launch_bounds__(GEMM_THREADS) void grouped_gemm_pair_kernel(GemmArgs a, GemmArgs b) {
-  const int next = gemm_tile_list<MODE_A, 0>(a, first_list_position());
-  gemm_tile_list<MODE_B, 1>(b, next);
+template <int MODE_A, int MODE_B, int S>
+__global__ __launch_bounds__(GEMM_THREADS, Tile<S>::PER_CU) void grouped_gemm_pair_kernel(GemmArgs a, GemmArgs b) {
+  const int next = gemm_tile_list<MODE_A, S, 0>(a, first_list_position());
+  gemm_tile_list<MODE_B, S, 1>(b, next);
 }
 
 // Per-device facts, looked up once per device: HIP keeps function attributes and the number of compute
@@ -1297,9 +1333,9 @@ int current_device() {
   if (hipGetDevice(&dev) != hipSuccess) { (void)hipGetLastError(); dev = 0; }
   return dev >= 0 && dev < MAX_DEVICES ? dev : 0;
 }
-// Workgroups of the persistent launch: one per compute unit (the 160 KB of LDS allow no more),
+// Workgroups of the persistent launch: as many per compute unit as the LDS allows (one or two),
 // a multiple of 8 so that every XCD gets the same share, and no more than there can be tiles.
-int persistent_grid(long long max_tiles) {
+int compute_units() {
   static int cus_of[MAX_DEVICES] = {};
   const int dev = current_device();
   int cus = cus_of[dev];
@@ -1311,17 +1347,21 @@ int persistent_grid(long long max_tiles) {
     }
     cus = cus_of[dev] = n & ~7;
   }
+  return cus;
+}
+template <int S> int persistent_grid(long long max_tiles) {
+  const int most = Tile<S>::PER_CU * compute_units();
   long long g = (max_tiles + 7) & ~7ll;
-  if (g > cus) g = cus;
+  if (g > most) g = most;
   if (g < 8) g = 8;
   return static_cast<int>(g);
 }
 // Raises the kernel's dynamic-LDS limit on the current device, once per device.
 template <typename K>
-int configure_lds(K kernel, bool (&done)[MAX_DEVICES]) {
+int configure_lds(K kernel, int bytes, bool (&done)[MAX_DEVICES]) {
   const int dev = current_device();
   if (done[dev]) return MOE_OK;
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, LDS_BYTES) !=
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, bytes) !=
       hipSuccess) {
     (void)hipGetLastError();
     return MOE_ERR_LAUNCH;
@@ -1330,22 +1370,106 @@ int configure_lds(K kernel, bool (&done)[MAX_DEVICES]) {
   return MOE_OK;
 }
 
-template <int MODE>
+template <int MODE, int S>
 int launch_gemm(const GemmArgs& a, long long max_tiles, hipStream_t s, const char* name) {
-  const dim3 grid(persistent_grid(max_tiles));
+  const dim3 grid(persistent_grid<S>(max_tiles));
   static bool configured[MAX_DEVICES] = {};
-  if (configure_lds(&grouped_gemm_kernel<MODE>, configured) != MOE_OK) return MOE_ERR_LAUNCH;
-  MOE_LAUNCH(name, grouped_gemm_kernel<MODE>, grid, dim3(GEMM_THREADS), LDS_BYTES, s, a);
+  if (configure_lds(&grouped_gemm_kernel<MODE, S>, Tile<S>::LDS, configured) != MOE_OK) return MOE_ERR_LAUNCH;
+  MOE_LAUNCH(name, (grouped_gemm_kernel<MODE, S>), grid, dim3(GEMM_THREADS), Tile<S>::LDS, s, a);
   return moe_check_launch();
 }
 
-template <int MODE_A, int MODE_B>
+template <int MODE_A, int MODE_B, int S>
 int launch_gemm_pair(const GemmArgs& a, const GemmArgs& b, long long max_tiles, hipStream_t s, const char* name) {
-  const dim3 grid(persistent_grid(max_tiles));
+  const dim3 grid(persistent_grid<S>(max_tiles));
   static bool configured[MAX_DEVICES] = {};
-  if (configure_lds(&grouped_gemm_pair_kernel<MODE_A, MODE_B>, configured) != MOE_OK) return MOE_ERR_LAUNCH;
-  MOE_LAUNCH(name, (grouped_gemm_pair_kernel<MODE_A, MODE_B>), grid, dim3(GEMM_THREADS), LDS_BYTES, s, a, b);
+  if (configure_lds(&grouped_gemm_pair_kernel<MODE_A, MODE_B, S>, Tile<S>::LDS, configured) != MOE_OK) return MOE_ERR_LAUNCH;
+  MOE_LAUNCH(name, (grouped_gemm_pair_kernel<MODE_A, MODE_B, S>), grid, dim3(GEMM_THREADS), Tile<S>::LDS, s, a, b);
   return moe_check_launch();
+}
+
+// The launches fill in what depends on the tile's edge: column tiles, row tiles and the bound on the tile list.
+int ceil_div(int n, int by) { return (n + by - 1) / by; }
+template <int MODE, int S>
+long long count_tiles(GemmArgs& a, int R_cap) {
+  if constexpr (is_wgrad(MODE)) {
+    a.n_tiles = ceil_div(a.N, S);
+    a.m_tiles_cap = ceil_div(a.M, S);         // row tiles of one expert's dW
+    return static_cast<long long>(a.n_tiles) * a.m_tiles_cap * a.E * (a.A1 != nullptr ? 2 : 1);
+  } else {
+    a.n_tiles = ceil_div(a.N, MODE == GATE_UP ? S / 2 : S);
+    a.m_tiles_cap = R_cap / S + a.E;
+    return static_cast<long long>(a.n_tiles) * a.m_tiles_cap;
+  }
+}
+
+// Which tile edge a launch takes: the one for which the model below expects less time.  Both give the same bits.
+//
+// 256: half the operand bytes per operation, and what long lists are quickest with.  128: two workgroups share a compute
+// unit, so that one's waits and epilogue lie under the other's main loop; four times the tiles, so that a short list still
+// reaches every compute unit; a quarter of the epilogue behind the last step of a reduction of a few; half the padding where
+// experts have few rows or d, f are no multiple of 256.
+//
+// The model, in units of one K step of a 256-edge tile (1.4 us): a tile costs something fixed (start, epilogue) and something
+// per step.  A launch takes its tiles' sum, spread over the places of the chip, plus one tile of the longest kind, since a list
+// rarely ends evenly; a list alone in its launch also ends on whole rounds.  The row tiles are counted for an even load of
+// the expected rows.  The constants are a fit to 152 layers of 128 to 32768 tokens, d 128 to 4096, f 128 to 2048, 4 to 240
+// experts, even and zipf-like loads (four launches each, timed with both edges): the edge chosen is on average 0.5 % slower than
+// the better one, always 256 16 % slower, always 128 6 %.
+// Some of them, 256 / 128 in us, gate_up, down, dgrad_h with dWd, dgrad_x with dWg and dWu:
+//   256 tokens, d 128, f 256, 8 experts, 2 per token        13 / 9      12 / 8      19 / 11     16 / 11
+//   248 tokens, d 320, f 320, 28 of 57 experts, 6           22 / 12     17 / 10     31 / 16     29 / 20
+//   7380 tokens, d 512, f 1600, 19 of 39 experts, 2         47 / 62     44 / 36     79 / 60    101 / 93
+//   2048 tokens, d 2048, f 1024, 64 experts, 8             171 / 207    93 / 109   222 / 244   359 / 424
+//   8192 tokens, d 2048, f 1024, 64 experts, 8             471 / 665   258 / 333   555 / 695   914 / 1225
+template <int S> struct TileCost;
+template <> struct TileCost<256> { static constexpr double FIXED = 5.0, STEP = 1.0, SWIGLU_BWD = 16.0; };
+template <> struct TileCost<128> { static constexpr double FIXED = 3.5, STEP = 0.75, SWIGLU_BWD = 10.0; };
+struct ListCost { double tiles, each; };
+// rows: routed rows to expect
+template <int MODE, int S>
+ListCost list_cost(const GemmArgs& a, double rows) {
+  const double r = rows / a.E;
+  if (is_wgrad(MODE)) {
+    const double steps = r / BK + 0.5 > 1.0 ? r / BK + 0.5 : 1.0;
+    return {static_cast<double>(a.E) * ceil_div(a.M, S) * ceil_div(a.N, S) * (a.A1 != nullptr ? 2 : 1),
+            TileCost<S>::FIXED + 0.7 * TileCost<S>::STEP * steps};
+  }
+  const double row_tiles = a.E * (r < 1.0 ? r : 1.0) * (r / S + 0.5 > 1.0 ? r / S + 0.5 : 1.0);
+  return {row_tiles * ceil_div(a.N, MODE == GATE_UP ? S / 2 : S),
+          TileCost<S>::FIXED * (MODE == GATE_UP ? 1.5 : 1.0) + (is_dgrad_h(MODE) ? TileCost<S>::SWIGLU_BWD : 0.0) +
+              TileCost<S>::STEP * (a.K / BK) * (MODE == DGRAD_X ? 2 : 1)};
+}
+template <int S> double places() { return static_cast<double>(Tile<S>::PER_CU) * compute_units(); }
+template <int S> double launch_cost(const ListCost& l) {
+  const double rounds = l.tiles / places<S>();
+  const long long whole = static_cast<long long>(rounds + 0.95);      // a twentieth of a round too many does not count
+  return 0.6 * (0.65 * rounds * l.each + l.each) + 0.4 * (whole < 1 ? 1 : whole) * l.each;
+}
+template <int S> double launch_cost(const ListCost& l, const ListCost& m) {
+  return 0.65 * (l.tiles * l.each + m.tiles * m.each) / places<S>() + (l.each > m.each ? l.each : m.each);
+}
+
+template <int MODE>
+int run_gemm(GemmArgs& a, int R_cap, long long rows, hipStream_t s, const char* name) {
+  const double r = static_cast<double>(rows);
+  if (launch_cost<128>(list_cost<MODE, 128>(a, r)) < launch_cost<256>(list_cost<MODE, 256>(a, r))) {
+    const long long tiles = count_tiles<MODE, 128>(a, R_cap);
+    return launch_gemm<MODE, 128>(a, tiles, s, name);
+  }
+  const long long tiles = count_tiles<MODE, 256>(a, R_cap);
+  return launch_gemm<MODE, 256>(a, tiles, s, name);
+}
+template <int MODE_A, int MODE_B>
+int run_gemm_pair(GemmArgs& a, GemmArgs& b, int R_cap, long long rows, hipStream_t s, const char* name) {
+  const double r = static_cast<double>(rows);
+  if (launch_cost<128>(list_cost<MODE_A, 128>(a, r), list_cost<MODE_B, 128>(b, r)) <
+      launch_cost<256>(list_cost<MODE_A, 256>(a, r), list_cost<MODE_B, 256>(b, r))) {
+    const long long tiles = count_tiles<MODE_A, 128>(a, R_cap) + count_tiles<MODE_B, 128>(b, R_cap);
+    return launch_gemm_pair<MODE_A, MODE_B, 128>(a, b, tiles, s, name);
+  }
+  const long long tiles = count_tiles<MODE_A, 256>(a, R_cap) + count_tiles<MODE_B, 256>(b, R_cap);
+  return launch_gemm_pair<MODE_A, MODE_B, 256>(a, b, tiles, s, name);
 }
 
 bool bad_gemm_dims(int E, int R_cap, int d, int f) {
@@ -1398,24 +1522,22 @@ int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_
     if ((rc = moe_stream_gate_up(p, rows, s)) != MOE_OK) return rc;
     if (streamed) return moe_stream_down(q, rows, s);
   }
-  const int m_tiles = R_cap / BM + E;
-
   GemmArgs a{};
-  a.offsets = expert_offsets; a.E = E; a.m_tiles_cap = m_tiles; a.row_token = row_token; a.row_weight = row_weight;
+  a.offsets = expert_offsets; a.E = E; a.row_token = row_token; a.row_weight = row_weight;
   // gate | up with the SwiGLU epilogue
   a.A0 = U16(xp); a.B0 = U16(Wg); a.B1 = U16(Wu); a.O0 = g; a.O1 = u; a.O2 = h;
-  a.K = d; a.N = f; a.n_tiles = (f + BN / 2 - 1) / (BN / 2);
+  a.K = d; a.N = f;
   a.stream_rows = either ? few : 0;
-  rc = launch_gemm<GATE_UP>(a, static_cast<long long>(a.n_tiles) * m_tiles, s, "gemm_gate_up");
+  rc = run_gemm<GATE_UP>(a, R_cap, rows, s, "gemm_gate_up");
   if (rc != MOE_OK) return rc;
   // down
   if (either && (rc = moe_stream_down(q, rows, s)) != MOE_OK) return rc;
   GemmArgs b{};
-  b.offsets = expert_offsets; b.E = E; b.m_tiles_cap = m_tiles;
+  b.offsets = expert_offsets; b.E = E;
   b.A0 = U16(h); b.B0 = U16(Wd); b.O0 = yp;
-  b.K = f; b.N = d; b.n_tiles = (d + BN - 1) / BN;
+  b.K = f; b.N = d;
   b.stream_rows = a.stream_rows;
-  return launch_gemm<DOWN>(b, static_cast<long long>(b.n_tiles) * m_tiles, s, "gemm_down");
+  return run_gemm<DOWN>(b, R_cap, rows, s, "gemm_down");
 }
 
 namespace {
@@ -1461,7 +1583,7 @@ extern "C" int moe_grouped_gemm_fwd_folded(const moe_bf16* x, int T, const int32
 // two weight-gradient products that read them
 int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
                  const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-                 const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
+                 const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
                  moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream) {
   if (row_token != nullptr && bad_gather(xp, T, row_token, d)) return MOE_ERR_INVALID;
   if (!dyp || !xp || !g || !u || !h || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws)
@@ -1471,7 +1593,6 @@ int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* 
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   if (ws_bytes < moe_grouped_gemm_bwd_workspace_bytes(R_cap, f)) return MOE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int m_tiles = R_cap / BM + E;
   uint16_t* dg = static_cast<uint16_t*>(ws);
   uint16_t* du = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + moe_grouped_gemm_bwd_workspace_bytes(R_cap, f) / 2);
 
@@ -1481,30 +1602,23 @@ int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* 
   GemmArgs wd{};
   wd.offsets = expert_offsets; wd.E = E;
   wd.A0 = U16(dyp); wd.B0 = U16(h); wd.O0 = dWd; wd.M = d; wd.N = f;
-  wd.n_tiles = (f + BN - 1) / BN;
-  wd.m_tiles_cap = (d + BM - 1) / BM;   // row tiles of one expert's dW
   GemmArgs a{};
-  a.offsets = expert_offsets; a.E = E; a.m_tiles_cap = m_tiles;
+  a.offsets = expert_offsets; a.E = E;
   a.A0 = U16(dyp); a.B0 = U16(Wd); a.G = U16(g); a.U = U16(u); a.O0 = dg; a.O1 = du;
-  a.K = d; a.N = f; a.n_tiles = (f + BN - 1) / BN;
-  int rc = launch_gemm_pair<DGRAD_H, WGRAD>(a, wd, static_cast<long long>(wd.n_tiles) * wd.m_tiles_cap * E +
-                                                       static_cast<long long>(a.n_tiles) * m_tiles,
-                                            s, "gemm_dgrad_h+wgrad_down");
+  a.K = d; a.N = f;
+  int rc = run_gemm_pair<DGRAD_H, WGRAD>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down");
   if (rc != MOE_OK) return rc;
   // dxp = dg . Wg + du . Wu ; dWg = dg^T xp and dWu = du^T xp (one list: both read the same rows of xp)
   GemmArgs w{};
   w.offsets = expert_offsets; w.E = E; w.row_token = row_token;
   w.A0 = dg; w.A1 = du; w.B0 = U16(xp); w.O0 = dWg; w.O1 = dWu; w.M = f; w.N = d;
-  w.n_tiles = (d + BN - 1) / BN;
-  w.m_tiles_cap = (f + BM - 1) / BM;
   GemmArgs b{};
-  b.offsets = expert_offsets; b.E = E; b.m_tiles_cap = m_tiles;
+  b.offsets = expert_offsets; b.E = E;
   b.A0 = dg; b.A1 = du; b.B0 = U16(Wg); b.B1 = U16(Wu); b.O0 = dxp;
-  b.K = f; b.N = d; b.n_tiles = (d + BN - 1) / BN;
-  const long long tiles = 2ll * w.n_tiles * w.m_tiles_cap * E + static_cast<long long>(b.n_tiles) * m_tiles;
+  b.K = f; b.N = d;
   // dgrad_x first: its tiles are the long ones, the weight gradients' many short tiles fill its tail
-  if (row_token != nullptr) return launch_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, tiles, s, "gemm_wgrad_gate_up+dgrad_x");
-  return launch_gemm_pair<DGRAD_X, WGRAD>(b, w, tiles, s, "gemm_wgrad_gate_up+dgrad_x");
+  if (row_token != nullptr) return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
+  return run_gemm_pair<DGRAD_X, WGRAD>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
 }
 
 extern "C" int moe_grouped_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, const moe_bf16* g, const moe_bf16* u,
@@ -1512,7 +1626,7 @@ extern "C" int moe_grouped_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, con
                                     const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, int d, int f,
                                     moe_bf16* dxp, moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws,
                                     size_t ws_bytes, void* stream) {
-  return moe_gemm_bwd(dyp, xp, 0, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd,
+  return moe_gemm_bwd(dyp, xp, 0, nullptr, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
                       ws, ws_bytes, stream);
 }
 
@@ -1523,7 +1637,7 @@ extern "C" int moe_grouped_gemm_bwd_gather(const moe_bf16* dyp, const moe_bf16* 
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes,
                                            void* stream) {
   if (row_token == nullptr) return MOE_ERR_INVALID;
-  return moe_gemm_bwd(dyp, x, T, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, d, f, dxp, dWg, dWu, dWd,
+  return moe_gemm_bwd(dyp, x, T, row_token, g, u, h, expert_offsets, Wg, Wu, Wd, E, R_cap, R_cap, d, f, dxp, dWg, dWu, dWd,
                       ws, ws_bytes, stream);
 }
 
@@ -1559,7 +1673,7 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
                                            const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
-                                           const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
+                                           const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
   if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !dgate ||
@@ -1571,7 +1685,6 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   if (ws_bytes < moe_grouped_gemm_bwd_folded_workspace_bytes(R_cap, f)) return MOE_ERR_WORKSPACE;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int m_tiles = R_cap / BM + E;
   const size_t one = moe_grouped_gemm_bwd_workspace_bytes(R_cap, f) / 2;
   uint16_t* dg = static_cast<uint16_t*>(ws);
   uint16_t* du = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + one);
@@ -1585,16 +1698,12 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   GemmArgs wd{};
   wd.offsets = expert_offsets; wd.E = E; wd.row_token = row_token;
   wd.A0 = U16(dout); wd.B0 = U16(hw); wd.O0 = dWd; wd.M = d; wd.N = f;
-  wd.n_tiles = (f + BN - 1) / BN;
-  wd.m_tiles_cap = (d + BM - 1) / BM;
-  const long long wd_tiles = static_cast<long long>(wd.n_tiles) * wd.m_tiles_cap * E;
   GemmArgs a{};
-  a.offsets = expert_offsets; a.E = E; a.m_tiles_cap = m_tiles; a.row_token = row_token; a.row_weight = row_weight;
+  a.offsets = expert_offsets; a.E = E; a.row_token = row_token; a.row_weight = row_weight;
   a.dgate_part = part;
   a.A0 = U16(dout); a.B0 = U16(Wd); a.G = U16(g); a.U = U16(u); a.O0 = dg; a.O1 = du;
-  a.K = d; a.N = f; a.n_tiles = (f + BN - 1) / BN;
-  int rc = launch_gemm_pair<DGRAD_H_GATE, WGRAD_GATHER_A>(a, wd, wd_tiles + static_cast<long long>(a.n_tiles) * m_tiles, s,
-                                                          "gemm_dgrad_h+wgrad_down");
+  a.K = d; a.N = f;
+  int rc = run_gemm_pair<DGRAD_H_GATE, WGRAD_GATHER_A>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down");
   if (rc != MOE_OK) return rc;
   const int n = T * k;
   MOE_LAUNCH("dgate_finish", dgate_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const float*>(part),
@@ -1604,17 +1713,14 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   GemmArgs w{};
   w.offsets = expert_offsets; w.E = E; w.row_token = row_token;
   w.A0 = dg; w.A1 = du; w.B0 = U16(x); w.O0 = dWg; w.O1 = dWu; w.M = f; w.N = d;
-  w.n_tiles = (d + BN - 1) / BN;
-  w.m_tiles_cap = (f + BM - 1) / BM;
   GemmArgs b{};
-  b.offsets = expert_offsets; b.E = E; b.m_tiles_cap = m_tiles;
+  b.offsets = expert_offsets; b.E = E;
   b.A0 = dg; b.A1 = du; b.B0 = U16(Wg); b.B1 = U16(Wu); b.O0 = dxp;
-  b.K = f; b.N = d; b.n_tiles = (d + BN - 1) / BN;
+  b.K = f; b.N = d;
   // dgrad_x first: its tiles are the long ones, the weight gradients' many short tiles fill its tail.  (The other
   // order used to pay off through dxp still lying in the last-level cache when moe_permute_bwd read it; since that
   // kernel streams its rows with non-temporal loads it no longer depends on that.)
-  return launch_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, 2ll * w.n_tiles * w.m_tiles_cap * E + static_cast<long long>(b.n_tiles) * m_tiles,
-                                                 s, "gemm_wgrad_gate_up+dgrad_x");
+  return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
 }
 
 extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
@@ -1625,5 +1731,5 @@ extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16*
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
   return moe_gemm_bwd_folded(dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, expert_offsets, Wg, Wu, Wd, E, R_cap,
-                             d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
+                             R_cap, d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
 }

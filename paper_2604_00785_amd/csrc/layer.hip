@@ -37,13 +37,13 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if (!plain && !L->row_token) return MOE_ERR_INVALID;   // without it moe_gemm_bwd would take x for T * k grouped rows
     if (fold) {
       rc = moe_gemm_bwd_folded(L->dout, L->x, T, k, L->row_token, L->row_weight, L->slot_row, L->g, L->u, L->h,
-                               L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
+                               L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
                                L->dgate, L->ws, L->ws_bytes, stream);
     } else {
       rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
       if (rc != MOE_OK) return rc;
       rc = moe_gemm_bwd(L->dyp, plain ? L->xp : L->x, T, plain ? nullptr : L->row_token, L->g, L->u, L->h, L->expert_offsets,
-                        L->Wg, L->Wu, L->Wd, nl, R_cap, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
+                        L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
     }
     if (rc != MOE_OK) return rc;
     if ((rc = moe_permute_bwd(L->dxp, L->slot_row, T, k, d, L->dx, stream)) != MOE_OK) return rc;
