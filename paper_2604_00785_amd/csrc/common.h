@@ -29,6 +29,22 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// Inclusive prefix sum over the 64 lanes of a wave, all of them active.  Six vector instructions that take their partner
+// through the lane permutation of the operand (rows of 16 lanes first, then lane 15 of a row for the row behind it, then lane 31
+// for the upper half), some 50 cycles; six ds_bpermute, each waiting for the one before, were some 800, and the tile lookup
+// of a grouped product scans up to eight times before its first load.
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, false);   // row_shr:1 (nothing comes in from outside the row)
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
+  return v;
+}
+// The value of a lane whose number is the same in the whole wave.
+__device__ __forceinline__ int wave_lane(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+
 static inline bool moe_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // ---- launch bookkeeping (prof.hip) ----------------------------------------

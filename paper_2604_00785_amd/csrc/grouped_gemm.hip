@@ -202,22 +202,14 @@ __device__ __forceinline__ float silu_f(float g) { return g * sigmoid_f(g); }
 
 // Row tiles of the grouped products: expert e owns ceil(rows_e / S) consecutive tile numbers (S: the tile's edge).
 // Both functions are evaluated by a whole wave (64 experts per pass) and return wave-uniform values.
-__device__ __forceinline__ int wave_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) {
-    const int u = __shfl_up(v, s, 64);
-    if (lane >= s) v += u;
-  }
-  return v;
-}
 template <int S> __device__ __forceinline__ int count_row_tiles(const int32_t* offsets, int E, int lane) {
   int total = 0;
   for (int e0 = 0; e0 < E; e0 += 64) {
     const int ee = e0 + lane;
     const int rows = ee < E ? offsets[ee + 1] - offsets[ee] : 0;
-    total += __shfl(wave_incl_scan((rows + S - 1) / S, lane), 63, 64);
+    total += wave_lane(wave_incl_scan((rows + S - 1) / S), 63);
   }
-  return __builtin_amdgcn_readfirstlane(total);
+  return total;
 }
 // Tile number `tile` of a row-grouped product -> expert, first row, column tile.  An expert's tiles are
 // numbered column tile by column tile, its row tiles innermost: the workgroups of an XCD, which take a
@@ -233,7 +225,7 @@ template <int S> __device__ __forceinline__ int count_row_tiles(const int32_t* o
 // kernel, so the lookup needs no memory access (which would otherwise sit in front of every tile's
 // first loads) and no scan.
 // (kept as six plain registers: a struct of arrays behind a reference ends up in scratch memory)
-__device__ __forceinline__ void sorted_first_tiles(int tiles0, int tiles1, int run, int lane, int& first0, int& first1) {
+__device__ __forceinline__ void sorted_first_tiles(int tiles0, int tiles1, int run, int& first0, int& first1) {
   const int r0 = tiles0 % run, r1 = tiles1 % run;
   const int cls0 = r0 == 0 ? 0 : (2 * r0 == run ? 1 : 2);
   const int cls1 = r1 == 0 ? 0 : (2 * r1 == run ? 1 : 2);
@@ -243,13 +235,13 @@ __device__ __forceinline__ void sorted_first_tiles(int tiles0, int tiles1, int r
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
     const int mine0 = cls0 == c ? tiles0 : 0;
-    const int inc0 = wave_incl_scan(mine0, lane);
+    const int inc0 = wave_incl_scan(mine0);
     if (cls0 == c) first0 = base + inc0 - mine0;
-    base += __shfl(inc0, 63, 64);
+    base += wave_lane(inc0, 63);
     const int mine1 = cls1 == c ? tiles1 : 0;
-    const int inc1 = wave_incl_scan(mine1, lane);
+    const int inc1 = wave_incl_scan(mine1);
     if (cls1 == c) first1 = base + inc1 - mine1;
-    base += __shfl(inc1, 63, 64);
+    base += wave_lane(inc1, 63);
   }
 }
 constexpr int LANE_EXPERTS_MAX = 128;
@@ -263,11 +255,11 @@ __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first,
   if (!hit) return false;
   const int l = __ffsll(hit) - 1;
   e = h * 64 + l;
-  const int q = tile - __shfl(first, l, 64);
-  const int rt = __shfl(row_tiles, l, 64);
+  const int q = tile - wave_lane(first, l);
+  const int rt = wave_lane(row_tiles, l);
   nt = q / rt;
-  m0 = __shfl(lo, l, 64) + (q - nt * rt) * S;
-  m_end = __shfl(hi, l, 64);
+  m0 = wave_lane(lo, l) + (q - nt * rt) * S;
+  m_end = wave_lane(hi, l);
   return true;
 }
 template <int S>
@@ -285,20 +277,20 @@ __device__ __forceinline__ void find_tile(const int32_t* offsets, int E, int lo0
     const int lo = ee < E ? offsets[ee] : 0, hi = ee < E ? offsets[ee + 1] : 0;
     const int row_tiles = (hi - lo + S - 1) / S;
     const int tiles = row_tiles * n_tiles;
-    const int inc = wave_incl_scan(tiles, lane);
+    const int inc = wave_incl_scan(tiles);
     const int excl = base + inc - tiles;
     const unsigned long long hit = __ballot(tiles > 0 && excl <= tile && tile < excl + tiles);
     if (hit) {
       const int l = __ffsll(hit) - 1;
       e = e0 + l;
-      const int q = tile - __shfl(excl, l, 64);
-      const int rt = __shfl(row_tiles, l, 64);
+      const int q = tile - wave_lane(excl, l);
+      const int rt = wave_lane(row_tiles, l);
       nt = q / rt;
-      m0 = __shfl(lo, l, 64) + (q - nt * rt) * S;
-      m_end = __shfl(hi, l, 64);
+      m0 = wave_lane(lo, l) + (q - nt * rt) * S;
+      m_end = wave_lane(hi, l);
       return;
     }
-    base += __shfl(inc, 63, 64);
+    base += wave_lane(inc, 63);
   }
 }
 
@@ -383,8 +375,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       const int e0 = tid0 & 63, e1 = 64 + (tid0 & 63);
       if (e0 < a.E) { lo0 = a.offsets[e0]; hi0 = a.offsets[e0 + 1]; }
       if (e1 < a.E) { lo1 = a.offsets[e1]; hi1 = a.offsets[e1 + 1]; }
-      sorted_first_tiles((hi0 - lo0 + S - 1) / S * a.n_tiles, (hi1 - lo1 + S - 1) / S * a.n_tiles, gridDim.x >> 3,
-                         tid0 & 63, first0, first1);
+      sorted_first_tiles((hi0 - lo0 + S - 1) / S * a.n_tiles, (hi1 - lo1 + S - 1) / S * a.n_tiles, gridDim.x >> 3, first0, first1);
     }
   }
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<size_t>(LDS_PTR(lds)));

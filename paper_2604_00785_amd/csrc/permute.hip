@@ -127,12 +127,7 @@ __global__ __launch_bounds__(PERM_THREADS) void permute_place_kernel(const int32
       tots[j] = tot;
       s += tot;
     }
-    int inc = s;
-#pragma unroll
-    for (int d = 1; d < MOE_WAVE; d <<= 1) {
-      const int o = __shfl_up(inc, d, MOE_WAVE);
-      if (lane >= d) inc += o;
-    }
+    const int inc = wave_incl_scan(s);
     int run = inc - s;
 #pragma unroll
     for (int j = 0; j < MOE_MAX_EXPERTS / MOE_WAVE; ++j) {

@@ -279,12 +279,7 @@ __global__ __launch_bounds__(RS_THREADS) void route_small_kernel(const float* __
       total += c;
     }
   }
-  int inc = total;
-#pragma unroll
-  for (int d = 1; d < MOE_WAVE; d <<= 1) {
-    const int o = __shfl_up(inc, d, MOE_WAVE);
-    if (lane >= d) inc += o;
-  }
+  const int inc = wave_incl_scan(total);
   if (lane == MOE_WAVE - 1 && w < MOE_MAX_EXPERTS / MOE_WAVE) s_sum[w] = inc;
   __syncthreads();
   if (tid < e_count) {

@@ -27,14 +27,6 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 __device__ __forceinline__ float st_sigmoid(float g) {
   return __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
 }
-__device__ __forceinline__ int st_incl_scan(int v, int lane) {
-#pragma unroll
-  for (int s = 1; s < 64; s <<= 1) {
-    const int u = __shfl_up(v, s, 64);
-    if (lane >= s) v += u;
-  }
-  return v;
-}
 __device__ __forceinline__ int sfirst(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 struct StTile { int e, m0, m_end, col; };
@@ -56,11 +48,11 @@ __device__ __forceinline__ bool st_find_tile(const int32_t* __restrict__ offsets
   for (int c = 0; c < MOE_MAX_EXPERTS / 64; ++c) {
     inc[c] = 0;
     if (c * 64 < E) {
-      inc[c] = total + st_incl_scan((hi[c] - lo[c] + ST_ROWS - 1) / ST_ROWS, lane);
-      total = __shfl(inc[c], 63, 64);
+      inc[c] = total + wave_incl_scan((hi[c] - lo[c] + ST_ROWS - 1) / ST_ROWS);
+      total = wave_lane(inc[c], 63);
     }
   }
-  total = sfirst(total) * ncol;
+  total *= ncol;
   const int per_xcd = (total + 7) >> 3;
   const int b = blockIdx.x;
   const int q = (b & 7) * per_xcd + (b >> 3);
@@ -74,11 +66,11 @@ __device__ __forceinline__ bool st_find_tile(const int32_t* __restrict__ offsets
       if (hit) {
         const int l = __ffsll(hit) - 1;
         t.e = c * 64 + l;
-        const int r = sfirst(__shfl(rt, l, 64));
-        const int in = q - sfirst(__shfl(excl, l, 64)) * ncol;
+        const int r = wave_lane(rt, l);
+        const int in = q - wave_lane(excl, l) * ncol;
         t.col = in / r;
-        t.m0 = sfirst(__shfl(lo[c], l, 64)) + (in - t.col * r) * ST_ROWS;
-        t.m_end = sfirst(__shfl(hi[c], l, 64));
+        t.m0 = wave_lane(lo[c], l) + (in - t.col * r) * ST_ROWS;
+        t.m_end = wave_lane(hi[c], l);
         return true;
       }
     }
