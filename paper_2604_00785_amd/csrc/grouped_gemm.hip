@@ -320,7 +320,7 @@ struct TileState {
   int e, m0, m_end, nt, n0;     // expert, first output row, end of the valid rows, column tile, first output column
   int r0;                       // first of this wave's rows inside the tile
   int m_wave;                   // end of the valid rows that are this wave's
-  int nv;                       // 32-row groups of this wave's rows that hold a valid row (the others issue no MFMA)
+  int nv;                       // 32-row groups that every wave works on, 1 .. HALF / 32 (the others issue no load and no MFMA)
   bool second;                  // tile of the second weight gradient of a pair
   int nk, nk_phase;             // K steps in total / in the first K phase
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
@@ -414,15 +414,15 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   m_end = __builtin_amdgcn_readfirstlane(m_end);
   const int n0 = nt * (MODE == GATE_UP ? HALF : S);
   t.e = e; t.m0 = m0; t.m_end = m_end; t.nt = nt; t.n0 = n0; t.second = second;
-  // The tile's 32-row groups that hold a valid row are shared out evenly: the upper waves take the larger half, so
-  // that a ragged tile keeps both pairs of waves busy for half the time instead of one for all of it.
+  // The tile's 32-row groups that hold a valid row are shared out evenly between the two pairs of waves, the last of an odd
+  // number together with a dead one: a ragged tile keeps both pairs busy for half the time instead of one for all of it, and
+  // rows of dead groups are not loaded (but for that one).
   int nv = HALF / 32, r0 = wm * HALF, m_wave = m_end;
   if constexpr (!is_wgrad(MODE)) {
     int groups = (m_end - m0 + 31) >> 5;
     groups = groups > S / 32 ? S / 32 : groups;
-    const int upper = (groups + 1) >> 1;
-    nv = __builtin_amdgcn_readfirstlane(wm == 0 ? upper : groups - upper);
-    r0 = wm * 32 * upper;
+    nv = __builtin_amdgcn_readfirstlane((groups + 1) >> 1);
+    r0 = wm * 32 * nv;
     m_wave = m_end < m0 + r0 + 32 * nv ? m_end : m0 + r0 + 32 * nv;
     r0 = __builtin_amdgcn_readfirstlane(r0);
     m_wave = __builtin_amdgcn_readfirstlane(m_wave);
@@ -431,9 +431,10 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
 
   // ---------------- operand sources -------------------------------------------
   // Per K step and operand tile a wave issues NL direct-to-LDS loads of 1 KB each:
-  //  K-contiguous source ([row][k]): load i of wave w fills tile rows 8 (NL w + i) .. + 8;
+  //  K-contiguous source ([row][k]): load i of wave w fills LDS rows 8 (NL w + i) .. + 8;
   //    lane l -> row + l/8, physical piece l%8, i.e. logical piece kc_logical_piece(row, l%8).
-  //    The base advances by 64 elements per step.
+  //    The base advances by 64 elements per step.  B: these are the tile's rows.  A: they hold its rows 32 i + 8 w .. + 8, so that
+  //    the first 2 nv loads of every wave bring the rows of the 2 nv live groups, and the others are left out.
   //  n-contiguous source ([k][n]): load i of wave w fills the KN_RPL (2 or 4) k rows from KN_RPL (NL w + i) on;
   //    with P = KN_PIECES (32 or 16) lane l -> k row + l/P, physical piece l%P = logical piece kn_piece(k row, l%P).
   //    The base advances by 64 rows per step.
@@ -496,7 +497,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     if (gathered) abase = reinterpret_cast<const char*>(a.A0);   // lane offsets carry the token row
 #pragma unroll
     for (int i = 0; i < NL; ++i) {
-      const int row = (wave * NL + i) * 8 + (lane >> 3);
+      const int row = i * 32 + wave * 8 + (lane >> 3);
       const int chunk = kc_logical_piece(row, lane & 7);
       int r = row;
       if (m0 + r > m_end - 1) r = m_end - 1 - m0;
@@ -651,8 +652,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   //    16 g .. 16 g + 15 take k rows 8 g .. of the sub-step.  The k-row swizzle XORs bits 1-2 of the block
   //    number (counted over the whole row), so the address of block b is base[b / 2] + 32 (b & 1); the second half of a
   //    fragment lies 4 k rows further, sub-step 1 32 k rows.
-  // The addresses of a row-grouped A operand carry the wave's first row r0, which depends on the tile (a multiple of 32,
-  // so the rotation of the pieces does not see it).
+  //  The row-grouped A operand is kept as eight rows per wave of every 32-row group (see the loads): row 32 i + 8 w + s lies
+  //    at LDS row 8 (NL w + i) + s, so block b begins at LDS rows 16 NL (b & 1) + 8 (b / 2) and its second half 8 NL rows further.
+  //    Its addresses carry the wave's first row r0, which depends on the tile (a multiple of 32, that is 8 LDS rows).
   uint32_t fa_base[TL::SETS][4], fb_base[TL::SETS][4];
 #pragma unroll
   for (int st = 0; st < TL::SETS; ++st) {
@@ -662,7 +664,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       const int i16 = lane & 15;
       // [row][k]
       const int pc = ((x & 1) * 4 + (lane >> 4) + (lane & 7)) & 7;   // sub-step x & 1; the block is an immediate offset
-      const uint32_t kc_a = org + i16 * 128 + pc * 16;   // + 128 r0 of the tile, see main_loop
+      const uint32_t kc_a = org + (i16 >> 3) * (NL * 1024) + (lane & 7) * 128 + pc * 16;   // + 32 r0 of the tile, see main_loop
       const uint32_t kc_b = org + (wn * HALF + i16) * 128 + pc * 16;
       // [k][n]
       const int krow = (lane >> 4) * 8 + (i16 >> 2);
@@ -693,7 +695,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         constexpr int half = OP % 2;
         fa[SET][blk].h[half] = lds_read_tr_b64<SA % SPS * TILE_BYTES + SUB * 32 * TL::KN_ROW + half * 4 * TL::KN_ROW + (blk & 1) * 32>(fa_base[SA / SPS][blk >> 1]);
       } else {
-        fa[SET][blk].v = lds_read_b128<SA % SPS * TILE_BYTES + blk * 2048>(fa_base[SA / SPS][SUB]);
+        fa[SET][blk].v = lds_read_b128<SA % SPS * TILE_BYTES + (blk & 1) * 2 * NL * 1024 + (blk >> 1) * 1024>(fa_base[SA / SPS][SUB]);
       }
     } else {
       constexpr int OB = OP - A_OPS;
@@ -716,25 +718,26 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
 
   // One 32-deep sub-step: the live MFMAs of fragment set SET, and between them (one per gap) the read
-  // instructions of the next sub-step and, in a step that loads (LOADS), the wave's NL loads of one
+  // instructions of the next sub-step and, in a step that loads, the wave's LOADS loads of one
   // tile.  Gap g is the place after MFMA g: reads take the even gaps 0, 2, .. (every gap when they would not fit
-  // otherwise), M0 is set in gap 1, loads take gaps 3, 7, .., 4 NL - 1; what does not fit behind
+  // otherwise), M0 is set in gap 1, loads take gaps 3, 7, .., 4 LOADS - 1; what does not fit behind
   // the last live MFMA follows it.
+  constexpr auto a_loads = [](int nv) { return is_wgrad(MODE) ? NL : 2 * nv; };   // A loads per wave and step
   auto sub_step = [&](auto set_tag, auto nv_tag, auto nreads_tag, auto reader, auto loads_tag, auto set_m0_fn, auto loader)
       __attribute__((always_inline)) {
     constexpr int SET = decltype(set_tag)::value, NV = decltype(nv_tag)::value;
     constexpr int NREADS = decltype(nreads_tag)::value;
-    constexpr bool LOADS = decltype(loads_tag)::value != 0;
+    constexpr int LOADS = decltype(loads_tag)::value;   // how many, 0: none
     constexpr int ML = 2 * NB * NV;                     // live MFMAs: blocks i < 2 NV, all j
     constexpr int RSTRIDE = 2 * NREADS > NB * NB ? 1 : 2;
-    constexpr int LAST_LOAD = 4 * NL - 1;
+    constexpr int LAST_LOAD = 4 * LOADS - 1;
     constexpr int LAST_GAP = (NREADS - 1) * RSTRIDE > LAST_LOAD ? (NREADS - 1) * RSTRIDE : LAST_LOAD;
     constexpr int SLOTS = ML > LAST_GAP + 1 ? ML : LAST_GAP + 1;
     static_for<SLOTS>([&](auto g_tag) {
       constexpr int g = decltype(g_tag)::value;
       if constexpr (g < ML) mma(IC<SET>{}, IC<g / NB>{}, IC<g % NB>{});
       if constexpr (g % RSTRIDE == 0 && g / RSTRIDE < NREADS) reader(IC<g / RSTRIDE>{});
-      if constexpr (LOADS) {
+      if constexpr (LOADS > 0) {
         if constexpr (g == 1) set_m0_fn();
         if constexpr (g >= 3 && g <= LAST_LOAD && (g - 3) % 4 == 0) loader(IC<(g - 3) / 4>{});
       }
@@ -751,7 +754,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     using NextA = IC<slot_of_a((P + 1) % NSLOT)>;
     using NextB = IC<slot_of_b((P + 1) % NSLOT)>;
     constexpr int LA = slot_of_a((P + 2) % NSLOT);
-    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
+    constexpr int ALOADS = a_loads(NV);
+    constexpr int NREADS = 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
     if constexpr (KIND == 2 && GATHER_A) {
       // the tokens of A(kt+2) were fetched a step ago and are covered by that step's wait; those of A(kt+3)
       // are requested before the loads of A(kt+2), the only ones this step's wait leaves in flight
@@ -760,19 +764,19 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     }
     sub_step(IC<0>{}, nv_tag, IC<NREADS>{},
              [&](auto op) __attribute__((always_inline)) { read_op(SA{}, SB{}, IC<1>{}, IC<1>{}, nv_tag, op); },
-             IC<KIND == 2 ? 1 : 0>{},
+             IC<KIND == 2 ? ALOADS : 0>{},
              [&]() __attribute__((always_inline)) { set_m0<LA * TILE_BYTES>(lds_fill); },
              [&](auto i) __attribute__((always_inline)) { a_part(t, kt + 2, i, sp_tag); });
     if constexpr (KIND == 2) a_end(t, kt + 2);
     lds_wait<0>();
     if constexpr (KIND >= 1) {
-      if constexpr (KIND == 2) wait_vm<NL>(); else wait_vm<0>();   // this wave's loads of A(kt+2) may stay in flight
+      if constexpr (KIND == 2) wait_vm<ALOADS>(); else wait_vm<0>();   // this wave's loads of A(kt+2) may stay in flight
       wg_barrier();
     }
     if constexpr (KIND == 2 && GATHER_B) apply_tok(t, t.tokn);   // fetched a step ago, older than the loads of A(kt+2)
     sub_step(IC<1>{}, nv_tag, IC<KIND >= 1 ? NREADS : 0>{},
              [&](auto op) __attribute__((always_inline)) { read_op(NextA{}, NextB{}, IC<0>{}, IC<0>{}, nv_tag, op); },
-             IC<KIND == 2 ? 1 : 0>{},
+             IC<KIND == 2 ? NL : 0>{},
              [&]() __attribute__((always_inline)) { set_m0<SA::value * TILE_BYTES>(lds_fill); },
              [&](auto i) __attribute__((always_inline)) { b_part(t, kt + 2, i, sp_tag); });
     if constexpr (KIND == 2) {
@@ -798,7 +802,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
     set_m0_rt(slot_m0(t, 2 * kt));
     asm volatile("s_nop 0" ::: "memory");
-    static_for<NL>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
+    if constexpr (is_wgrad(MODE)) {
+      static_for<NL>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
+    } else {
+      static_for<HALF / 32>([&](auto g) {
+        constexpr int i = 2 * decltype(g)::value;
+        if (i < 2 * t.nv) { a_part(t, kt, IC<i>{}, IC<2>{}); a_part(t, kt, IC<i + 1>{}, IC<2>{}); }
+      });
+    }
     a_end(t, kt);
   };
   auto b_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
@@ -852,8 +863,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     if constexpr (!A_KN) {
 #pragma unroll
       for (int st = 0; st < TL::SETS; ++st) {
-        fa_base[st][0] += (t.r0 - fa_r0) * 128;
-        fa_base[st][1] += (t.r0 - fa_r0) * 128;
+        fa_base[st][0] += (t.r0 - fa_r0) * 32;
+        fa_base[st][1] += (t.r0 - fa_r0) * 32;
       }
       fa_r0 = t.r0;
     }
@@ -861,11 +872,11 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     // The tile's first loads are awaited; those of step 1 may stay in flight (the last of a gathered operand only: both
     // steps of the other one come first).  Stores of the epilogue before are in flight too; as loads complete in order
     // among themselves, the waits here and in the steps hold wherever the stores lie between them.
-    if (t.nk <= 1) wait_vm<0>(); else if (GATHER_A || GATHER_B) wait_vm<NL>(); else wait_vm<2 * NL>();
+    constexpr int NV = decltype(nv_tag)::value;
+    if (t.nk <= 1) wait_vm<0>(); else if (GATHER_A || GATHER_B) wait_vm<NL>(); else wait_vm<a_loads(NV) + NL>();
     wg_barrier();
     // ---- first fragments: sub-step 0 of step 0, from the slots of phase p0
-    constexpr int NV = decltype(nv_tag)::value;
-    constexpr int NREADS = NV == 0 ? 0 : 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
+    constexpr int NREADS = 2 * NV * A_OPS_PER_BLK + NB * B_OPS_PER_BLK;
     auto first_reads = [&](auto phase_tag) __attribute__((always_inline)) {
       constexpr int P = decltype(phase_tag)::value;
       static_for<NREADS>([&](auto op) { read_op(IC<slot_of_a(P)>{}, IC<slot_of_b(P)>{}, IC<0>{}, IC<0>{}, nv_tag, op); });
@@ -896,24 +907,18 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     step(t, t.nk - 1, IC<2>{}, IC<0>{}, nv_tag, IC<0>{});
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the last MFMAs have written before the accumulators are read
   };
-  // one copy of the loop per number of live 32-row groups: a wave whose 128 rows all lie past the
-  // expert's end only keeps the loads and barriers going
+  // one copy of the loop per number of live 32-row groups
   auto run_main = [&](TileState& t) __attribute__((always_inline)) {
     if constexpr (is_wgrad(MODE)) {
       main_loop(t, IC<HALF / 32>{});
     } else if constexpr (S == 128) {
-      switch (t.nv) {
-        case 2: main_loop(t, IC<2>{}); break;
-        case 1: main_loop(t, IC<1>{}); break;
-        default: main_loop(t, IC<0>{}); break;
-      }
+      if (t.nv == 2) main_loop(t, IC<2>{}); else main_loop(t, IC<1>{});
     } else {
       switch (t.nv) {
         case 4: main_loop(t, IC<4>{}); break;
         case 3: main_loop(t, IC<3>{}); break;
         case 2: main_loop(t, IC<2>{}); break;
-        case 1: main_loop(t, IC<1>{}); break;
-        default: main_loop(t, IC<0>{}); break;
+        default: main_loop(t, IC<1>{}); break;
       }
     }
   };
