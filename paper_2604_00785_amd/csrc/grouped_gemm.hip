@@ -26,7 +26,7 @@
 //
 // The two operand tiles of a step (32 KB each) live in a ring of five LDS slots (160 KB, all
 // there is): A(t) in slot 2t mod 5, B(t) in slot (2t+1) mod 5, so two and a half steps are
-// resident.  Step t loads A(t+2) during its first 32-deep sub-step, into the slot B(t-1) left;
+// resident (a small tile that holds all of an expert's few rows has a ring of its own, see few_rows_loop).  Step t loads A(t+2) during its first 32-deep sub-step, into the slot B(t-1) left;
 // its barrier follows that sub-step: behind it the tiles of step t+1 are complete (the wave's own
 // loads of A(t+2) may still be in flight) and every wave is done with A(t), whose slot B(t+2) is
 // loaded into during the second sub-step.  Fragments are double-buffered in registers: the reads
@@ -79,6 +79,9 @@ template <int S> struct Tile {
   static constexpr int SLOTS_PER_SET = 65536 / BYTES; // slots that an LDS read's immediate offset reaches
   static constexpr int SETS = (NSLOT + SLOTS_PER_SET - 1) / SLOTS_PER_SET;
 };
+// few_rows_loop: up to 64 rows, RING steps of one 16 KB slot for B and 8 KB for A behind the B slots
+constexpr int FEW_ROWS = 64, FEW_RING = 3, FEW_A_BYTES = FEW_ROWS * BK * 2;
+static_assert(FEW_RING * (Tile<128>::BYTES + FEW_A_BYTES) <= Tile<128>::LDS);
 constexpr int LOAD_BIAS = 4096;                       // see dma16_imm
 constexpr int slot_of_a(int p) { return (2 * p) % NSLOT; }       // p = ring phase of the step
 constexpr int slot_of_b(int p) { return (2 * p + 1) % NSLOT; }
@@ -179,6 +182,9 @@ template <int OFF> __device__ __forceinline__ int load_i32(uint32_t voff, const 
   asm volatile("global_load_dword %0, %1, %2 offset:%3" : "=v"(v) : "v"(voff), "s"(sbase), "n"(OFF) : "memory");
   return v;
 }
+// A scalar base that the compiler may just have brought back from a vector register (it keeps what it has no scalar registers for
+// there): five wait states lie between that and a load that uses it, which the compiler sees to for its own loads only.
+__device__ __forceinline__ void settle(const char*& sbase) { asm volatile("s_nop 4" : "+s"(sbase)::"memory"); }
 template <int N> __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() {
@@ -248,7 +254,7 @@ constexpr int LANE_EXPERTS_MAX = 128;
 // One half (experts 64 h .. 64 h + 63, one per lane) of the register-resident lookup.
 template <int S>
 __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first, int n_tiles, int tile, int& e, int& m0,
-                                               int& m_end, int& nt) {
+                                               int& m_end, int& nt, int& rt) {
   const int row_tiles = (hi - lo + S - 1) / S;
   const int tiles = row_tiles * n_tiles;
   const unsigned long long hit = __ballot(tiles > 0 && first <= tile && tile < first + tiles);
@@ -256,7 +262,7 @@ __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first,
   const int l = __ffsll(hit) - 1;
   e = h * 64 + l;
   const int q = tile - wave_lane(first, l);
-  const int rt = wave_lane(row_tiles, l);
+  rt = wave_lane(row_tiles, l);
   nt = q / rt;
   m0 = wave_lane(lo, l) + (q - nt * rt) * S;
   m_end = wave_lane(hi, l);
@@ -264,11 +270,12 @@ __device__ __forceinline__ bool find_tile_half(int h, int lo, int hi, int first,
 }
 template <int S>
 __device__ __forceinline__ void find_tile(const int32_t* offsets, int E, int lo0, int hi0, int first0, int lo1, int hi1,
-                                          int first1, int n_tiles, int tile, int lane, int& e, int& m0, int& m_end, int& nt) {
-  e = 0; m0 = 0; m_end = 0; nt = 0;
+                                          int first1, int n_tiles, int tile, int lane, int& e, int& m0, int& m_end, int& nt,
+                                          int& rt) {
+  e = 0; m0 = 0; m_end = 0; nt = 0; rt = 0;
   if (E <= LANE_EXPERTS_MAX) {
-    if (find_tile_half<S>(0, lo0, hi0, first0, n_tiles, tile, e, m0, m_end, nt)) return;
-    find_tile_half<S>(1, lo1, hi1, first1, n_tiles, tile, e, m0, m_end, nt);
+    if (find_tile_half<S>(0, lo0, hi0, first0, n_tiles, tile, e, m0, m_end, nt, rt)) return;
+    find_tile_half<S>(1, lo1, hi1, first1, n_tiles, tile, e, m0, m_end, nt, rt);
     return;
   }
   int base = 0;
@@ -284,7 +291,7 @@ __device__ __forceinline__ void find_tile(const int32_t* offsets, int E, int lo0
       const int l = __ffsll(hit) - 1;
       e = e0 + l;
       const int q = tile - wave_lane(excl, l);
-      const int rt = wave_lane(row_tiles, l);
+      rt = wave_lane(row_tiles, l);
       nt = q / rt;
       m0 = wave_lane(lo, l) + (q - nt * rt) * S;
       m_end = wave_lane(hi, l);
@@ -321,6 +328,7 @@ struct TileState {
   int r0;                       // first of this wave's rows inside the tile
   int m_wave;                   // end of the valid rows that are this wave's
   int nv;                       // 32-row groups that every wave works on, 1 .. HALF / 32 (the others issue no load and no MFMA)
+  bool few;                     // tiles of 128: takes few_rows_loop
   bool second;                  // tile of the second weight gradient of a pair
   int nk, nk_phase;             // K steps in total / in the first K phase
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
@@ -382,6 +390,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // M0 base of this wave's loads: the middle of its share of tile slot 0 (immediates reach -4096 .. +3072)
   const uint32_t lds_fill = __builtin_amdgcn_readfirstlane(lds0 + wave * TL::SHARE + NL / 2 * 1024);
 
+  // few_rows_loop: the same for its A tiles, 2 KB of a wave each
+  const uint32_t few_a = __builtin_amdgcn_readfirstlane(lds0 + FEW_RING * TILE_BYTES + wave * 2048 + NL / 2 * 1024);
+
   const int lane = tid0 & 63;
   // k row (of a [64 k][S n] tile) that load i of this wave fills from this lane
   auto kn_load_row = [&](int i, int lane) __attribute__((always_inline)) { return (wave * NL + i) * TL::KN_RPL + lane / TL::KN_PIECES; };
@@ -392,7 +403,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   int tid = tid0;
   asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
-  int e, m0, m_end, nt;
+  int e, m0, m_end, nt, rt = 0;
   bool second = false;
   if constexpr (is_wgrad(MODE)) {
     nt = tile % a.n_tiles;
@@ -404,7 +415,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     m0 = mi * S;                        // output row of dW
     m_end = a.M;
   } else {
-    find_tile<S>(a.offsets, a.E, lo0, hi0, first0, lo1, hi1, first1, a.n_tiles, tile, lane, e, m0, m_end, nt);
+    find_tile<S>(a.offsets, a.E, lo0, hi0, first0, lo1, hi1, first1, a.n_tiles, tile, lane, e, m0, m_end, nt, rt);
     nt = __builtin_amdgcn_readfirstlane(nt);
   }
   // tile coordinates are wave-uniform: keep them in scalar registers, so that everything derived
@@ -428,6 +439,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     m_wave = __builtin_amdgcn_readfirstlane(m_wave);
   }
   t.nv = nv; t.r0 = r0; t.m_wave = m_wave;
+  t.few = S == 128 && !is_wgrad(MODE) && nv == 1 && rt == 1 && total <= static_cast<int>(gridDim.x);
 
   // ---------------- operand sources -------------------------------------------
   // Per K step and operand tile a wave issues NL direct-to-LDS loads of 1 KB each:
@@ -795,13 +807,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // What a tile waits for between main loops counts where tiles are short: a training step of 2048 tokens (d 2048, f 1024, 64
   // experts, 4 steps per weight gradient) 885 -> 868 us, the forward of 4001 tokens over 128 experts of f 512 328 -> 322 us;
   // at 1024 rows per expert and more the chip is power-limited and the step takes as long as before (0-1.5 % less).
-  auto spare_slot = [&](const TileState& t) __attribute__((always_inline)) { return (2 * t.p0 + 4) % NSLOT; };
-  auto slot_m0 = [&](const TileState& t, int unit) __attribute__((always_inline)) {   // units 0..3: A(0), B(0), A(1), B(1)
-    return lds_fill + ((2 * t.p0 + unit) % NSLOT) * TILE_BYTES;
-  };
-  auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
-    set_m0_rt(slot_m0(t, 2 * kt));
-    asm volatile("s_nop 0" ::: "memory");
+  // A tile with few rows always starts at the first slot of its ring; slots 2 and 4 are what its steps 0 and 1 leave free.
+  auto spare_slot = [&](const TileState& t) __attribute__((always_inline)) { return t.few ? 2 : (2 * t.p0 + 4) % NSLOT; };
+  auto spare_slot2 = [&](const TileState& t) __attribute__((always_inline)) { return t.few ? 4 : (2 * t.p0 + 3) % NSLOT; };
+  auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {   // kt: 0 or 1
+    int at = lds_fill + (2 * t.p0 + 2 * kt) % NSLOT * TILE_BYTES;
+    if (t.few) at = few_a + kt * FEW_A_BYTES;
+    set_m0_rt(__builtin_amdgcn_readfirstlane(at));
+    settle(t.sa_next);
     if constexpr (is_wgrad(MODE)) {
       static_for<NL>([&](auto i) { a_part(t, kt, i, IC<2>{}); });
     } else {
@@ -813,8 +826,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     a_end(t, kt);
   };
   auto b_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {
-    set_m0_rt(slot_m0(t, 2 * kt + 1));
-    asm volatile("s_nop 0" ::: "memory");
+    const int slot = t.few ? kt : (2 * t.p0 + 2 * kt + 1) % NSLOT;
+    set_m0_rt(__builtin_amdgcn_readfirstlane(lds_fill + slot * TILE_BYTES));
+    settle(t.sb_next);
     static_for<NL>([&](auto i) { b_part(t, kt, i, IC<2>{}); });
     b_end(t, kt);
   };
@@ -826,13 +840,15 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // steps that do not exist, repeat its last row.
       int tk[3][NL];
       const int last = t.k_hi - t.k_lo - 1;
+      const char* tok = reinterpret_cast<const char*>(t.row_tok);
+      settle(tok);
       static_for<3>([&](auto s_tag) {
         constexpr int s = decltype(s_tag)::value;
         static_for<NL>([&](auto i_tag) {
           constexpr int i = decltype(i_tag)::value;
           int r = s * BK + kn_load_row(i, lane);
           if (r > last) r = last;
-          tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, t.row_tok);
+          tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, reinterpret_cast<const int32_t*>(tok));
         });
       });
       if constexpr (GATHER_B) a_unit(t, 0); else b_unit(t, 0);
@@ -850,13 +866,13 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       b_unit(t, 0);
       a_unit(t, 0);
       if (t.nk > 1) {
-        if constexpr (!is_dgrad_h(MODE)) b_unit(t, 1);
+        if (!is_dgrad_h(MODE) || t.few) b_unit(t, 1);
         a_unit(t, 1);
       }
     }
   };
   auto last_first_loads = [&](TileState& t) __attribute__((always_inline)) {
-    if constexpr (is_dgrad_h(MODE)) { if (t.nk > 1) b_unit(t, 1); }
+    if constexpr (is_dgrad_h(MODE)) { if (t.nk > 1 && !t.few) b_unit(t, 1); }
   };
   auto main_loop = [&](TileState& t, auto nv_tag) __attribute__((always_inline)) {
     if (t.nk <= 0) return;
@@ -907,12 +923,81 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     step(t, t.nk - 1, IC<2>{}, IC<0>{}, nv_tag, IC<0>{});
     asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");   // the last MFMAs have written before the accumulators are read
   };
+  // The main loop of a small tile that holds all of an expert's at most 64 rows, in a list with no more tiles than workgroups.  It
+  // shares its weights with nobody, has little to multiply, and what it waits for is the latency of memory: in the ring above a
+  // step's B tile is requested one step before it is awaited; the rows that are not there make room for FEW_RING steps of B and A,
+  // all but one of them in flight.  The loop is kept plain (slots are computed, fragments are read in front of the products
+  // that use them): there is time for it.
+  // Not for what is left of an expert after whole tiles, nor in tiles of 256: those share their weights with the expert's other
+  // tiles, and taking more than their part of the memory's bandwidth slows the others down (2048 tokens, d 2048, f 1024, 64
+  // experts, forward and backward: 901 -> 921 us when they had such a ring too).  Nor in longer lists, which wait for bandwidth
+  // rather than latency (501 tokens of the same layer, forward: 192 -> 197 us on one card, 212 -> 202 us on another).
+  // Without / with, us: forward of 597 tokens, d 2240, f 192, 41 experts, 1 per token 57.8 / 50.2; of 146 tokens, d 256, f 1216, 33
+  // experts, 6 per token 42.3 / 40.5; forward and backward of 453 tokens, d 3072, f 128, 3 of 38 experts 100 / 96.8.
+  auto few_rows_loop = [&](TileState& t) __attribute__((always_inline)) {
+    constexpr int STEP_LOADS = 2 + NL;
+    constexpr int NREADS = 2 + NB * B_OPS_PER_BLK;       // per 32-deep sub-step
+    const int i16 = lane & 15;
+    // row 32 i + 8 w + s of the tile lies at LDS row 8 (2 w + i) + s (see the loads; i is 0 or 1)
+    const uint32_t a_lane = lds0 + FEW_RING * TILE_BYTES + (i16 >> 3) * 2048 + (lane & 7) * 128 + t.r0 * 32;
+    const uint32_t a_sub0 = a_lane + (((lane >> 4) + (lane & 7)) & 7) * 16, a_sub1 = a_lane + ((4 + (lane >> 4) + (lane & 7)) & 7) * 16;
+    asm volatile("s_nop 7" ::: "memory");   // the accumulators were cleared by vector-ALU writes
+    int cur = 0, nxt = 2;                   // slots of step kt and of step kt + 2
+#pragma clang loop unroll(disable)
+    for (int kt = 0; kt < t.nk; ++kt) {
+      asm volatile("" : "+s"(kt));          // one copy of the body: two would keep the accumulators in different registers
+      // this step's tiles are here (requests complete in order; stores of the epilogue before only make the wait longer) ...
+      if (kt + 1 < t.nk) wait_vm<STEP_LOADS>(); else wait_vm<0>();
+      wg_barrier();                         // ... those of the other waves too, and every wave is done with step kt - 1, whose slot
+      if (kt + 2 < t.nk) {                  // is requested anew
+        set_m0_rt(__builtin_amdgcn_readfirstlane(lds_fill + nxt * TILE_BYTES));
+        settle(t.sb_next);
+        static_for<NL>([&](auto i) { b_part(t, kt + 2, i, IC<0>{}); });
+        b_end(t, kt + 2);
+        set_m0_rt(__builtin_amdgcn_readfirstlane(few_a + nxt * FEW_A_BYTES));
+        settle(t.sa_next);
+        static_for<2>([&](auto i) { a_part(t, kt + 2, i, IC<0>{}); });
+        a_end(t, kt + 2);
+      }
+      uint32_t a_at[2] = {a_sub0 + cur * FEW_A_BYTES, a_sub1 + cur * FEW_A_BYTES}, b_at[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) b_at[x] = fb_base[0][x] + cur * TILE_BYTES;
+      static_for<2>([&](auto s_tag) {
+        constexpr int SUB = decltype(s_tag)::value;
+        static_for<2>([&](auto b_tag) {
+          constexpr int blk = decltype(b_tag)::value;
+          fa[SUB][blk].v = lds_read_b128<blk * 4096>(a_at[SUB]);
+        });
+        static_for<NB>([&](auto b_tag) {
+          constexpr int blk = decltype(b_tag)::value;
+          if constexpr (B_KN) {
+            static_for<2>([&](auto h_tag) {
+              constexpr int half = decltype(h_tag)::value;
+              fb[SUB][blk].h[half] = lds_read_tr_b64<SUB * 32 * TL::KN_ROW + half * 4 * TL::KN_ROW + (blk & 1) * 32>(b_at[blk >> 1]);
+            });
+          } else {
+            fb[SUB][blk].v = lds_read_b128<blk * 2048>(b_at[SUB]);
+          }
+        });
+      });
+      static_for<2>([&](auto s_tag) {
+        constexpr int SUB = decltype(s_tag)::value;
+        lds_wait<SUB == 0 ? NREADS : 0>();      // the reads of the other sub-step may be under way
+        static_for<2>([&](auto i) { static_for<NB>([&](auto j) { mma(IC<SUB>{}, i, j); }); });
+      });
+      cur = cur + 1 == FEW_RING ? 0 : cur + 1;
+      nxt = nxt + 1 == FEW_RING ? 0 : nxt + 1;
+      // the last MFMAs have written before the accumulators are read, or moved, which the compiler may do where paths join and
+      // without a wait, since it does not know the statements above for what they are
+      asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");
+    }
+  };
   // one copy of the loop per number of live 32-row groups
   auto run_main = [&](TileState& t) __attribute__((always_inline)) {
     if constexpr (is_wgrad(MODE)) {
       main_loop(t, IC<HALF / 32>{});
     } else if constexpr (S == 128) {
-      if (t.nv == 2) main_loop(t, IC<2>{}); else main_loop(t, IC<1>{});
+      if (t.few) few_rows_loop(t); else if (t.nv == 2) main_loop(t, IC<2>{}); else main_loop(t, IC<1>{});
     } else {
       switch (t.nv) {
         case 4: main_loop(t, IC<4>{}); break;
@@ -954,8 +1039,8 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
 
   // what the epilogue needs of a tile whose successor is set up already (and its first loads in flight: slot, and for the
-  // SwiGLU derivative the one before it, is what they leave free)
-  struct Finished { int e, m0, n0, r0, m_wave, slot; bool second; };
+  // SwiGLU derivative slot2, is what they leave free)
+  struct Finished { int e, m0, n0, r0, m_wave, slot, slot2; bool second; };
   auto epilogue = [&](const Finished& t) __attribute__((always_inline)) {
     const ArgPtr ae = reload_args<ARG>();     // the epilogue reads its arguments afresh
     int tid = tid0;                           // laundered as in setup_tile
@@ -1098,7 +1183,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
           *reinterpret_cast<u32x4*>(buf + UOFF + so) = pu[p];
         }
       };
-      char* const bufs[2] = {stage, lds + (t.slot + NSLOT - 1) % NSLOT * TILE_BYTES + wave * TL::SHARE};
+      char* const bufs[2] = {stage, lds + t.slot2 * TILE_BYTES + wave * TL::SHARE};
       int qoff[NB];                 // offsets of the lane's quads in a part's buffer: the same for every part
 #pragma unroll
       for (int j = 0; j < NB; ++j) qoff[j] = static_cast<int>(quad_addr(l16, j) - stage);
@@ -1274,7 +1359,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       if constexpr (MODE == GATE_UP || MODE == DGRAD_H_GATE) {
         if (weighted) fetch_row_weights(cur, a.row_weight);
       }
-      Finished done{cur.e, cur.m0, cur.n0, cur.r0, cur.m_wave, 0, cur.second};
+      Finished done{cur.e, cur.m0, cur.n0, cur.r0, cur.m_wave, 0, 4, cur.second};
       tile += gridDim.x;
       const bool more = tile < total;
       if (more) {
@@ -1282,6 +1367,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         place = place + 1 == run ? 0 : place + 1;
         setup_tile(list_entry(), cur);
         done.slot = __builtin_amdgcn_readfirstlane(spare_slot(cur));
+        if constexpr (is_dgrad_h(MODE)) done.slot2 = __builtin_amdgcn_readfirstlane(spare_slot2(cur));
       }
       if constexpr (MODE == GATE_UP || MODE == DGRAD_H_GATE) {
         // (a use that the compiler sees: left to the epilogue, its wait would cover the first loads too)
