@@ -46,6 +46,7 @@ def kernel_work(cfg, R):
         "permute_rows": ("hbm", row * (T + R)),
         "combine": ("hbm", row * (R + T)),
         "combine_bwd": ("hbm", row * (T + R) + row * R),
+        "combine+bwd": ("hbm", 2 * row * (T + R)),               # both in one pass over yp
         "permute_bwd": ("hbm", row * (R + T)),
         "route": ("hbm", 4.0 * T * cfg.E + 8.0 * T * k),
         "route_count": ("hbm", 4.0 * T * cfg.E + 8.0 * T * k),   # routing with the per-chunk expert counts as a by-product

@@ -6,7 +6,8 @@
 // every load and store is a full, coalesced row segment, the k source rows are
 // summed in slot order in fp32, and the token's own row (out / dout) is touched
 // exactly once.  No atomics, so results are reproducible.
-#include "common.h"
+#include <type_traits>
+#include "gemm.h"
 
 namespace {
 // A routed row is read once per kernel: the load is marked non-temporal, so that the rows stream through the
@@ -36,13 +37,115 @@ __device__ __forceinline__ uint4 scale8(const uint4& v, float w) {
                     pack_bf16(w * bf16lo(v.z), w * bf16hi(v.z)), pack_bf16(w * bf16lo(v.w), w * bf16hi(v.w)));
 }
 
+// Sum over the wave, in every lane, in the order of a butterfly with partners lane ^ 1, ^ 2, ^ 4, ..: by then all lanes of the
+// smaller unit agree, so a mirrored partner is as good, and the partners come through lane permutations, not through LDS.
+__device__ __forceinline__ float wave_sum(float v) {
+  auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
+  };
+  v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
+  v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
+  v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
+  v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);   // rows 0 + 1, 2 + 3
+  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
+}
+
+// The next SLOTS slots of a token that have a local row, in slot order: mask holds those not yet taken (one bit per lane, lane i holds
+// slot i's row), and what is taken leaves it.  Where fewer are left the first is repeated, so that every row can be loaded
+// without a test; live says which count.
+template <int SLOTS> struct SlotGroup {
+  int lane[SLOTS], row[SLOTS];
+  bool live[SLOTS];
+  __device__ __forceinline__ SlotGroup(uint64_t& mask, int my_row) {
+#pragma unroll
+    for (int s = 0; s < SLOTS; ++s) {
+      live[s] = mask != 0;
+      lane[s] = s == 0 || live[s] ? __builtin_ctzll(mask) : lane[0];
+      mask &= mask - 1;
+      row[s] = wave_lane(my_row, lane[s]);
+    }
+  }
+};
+
 // out[t] = sum_i w[t,i] * src[slot_row[t,i]]   (WEIGHTED)  or  sum_i src[slot_row[t,i]]
-// The token's slot rows and weights are fetched once (lane i holds slot i); the row loads of two
-// slots are in flight together; the sum still runs in slot order.
-template <int VPT, bool WEIGHTED>
+// A wave owns 64 VPT pieces of a token's row at a time (blockIdx.y: of every gridDim.y-th such part).  The token's slot rows and
+// weights are fetched once (lane i holds slot i); the row loads of SLOTS slots are in flight together, without a branch between
+// them (a lane without a piece reads the row's last one); the sum runs in slot order.
+// PART: also dgate[t, i] = sum over c of part[slot_row[t, i] * strips + c], what the grouped products leave of the gradient of a
+// folded gate weight (in the order of dgate_finish, the kernel of its own that larger passes have for it).
+template <int VPT, int SLOTS, bool WEIGHTED, bool PART>
 __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ slot_row,
                                                       const float* __restrict__ topk_w, int T, int k, int chunks,
-                                                      uint4* __restrict__ out) {
+                                                      uint4* __restrict__ out, const float* __restrict__ part, int strips,
+                                                      float* __restrict__ dgate) {
+  const int lane = threadIdx.x % MOE_WAVE;
+  const int t = blockIdx.x * (256 / MOE_WAVE) + threadIdx.x / MOE_WAVE;
+  if (t >= T) return;
+  for (int c0 = blockIdx.y * (MOE_WAVE * VPT); c0 < chunks; c0 += gridDim.y * (MOE_WAVE * VPT)) {
+    float acc[VPT][8];
+    int piece[VPT];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+      piece[j] = min(c0 + j * MOE_WAVE + lane, chunks - 1);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) acc[j][q] = 0.f;
+    }
+    for (int i0 = 0; i0 < k; i0 += MOE_WAVE) {
+      const int kk = min(k - i0, MOE_WAVE);
+      int my_row = -1;
+      float my_w = 0.f;
+      if (lane < kk) {
+        my_row = slot_row[static_cast<size_t>(t) * k + i0 + lane];
+        if (WEIGHTED) my_w = topk_w[static_cast<size_t>(t) * k + i0 + lane];
+      }
+      uint64_t mask = __ballot(my_row >= 0);
+      while (mask != 0) {
+        const SlotGroup<SLOTS> g(mask, my_row);
+        uint4 v[SLOTS][VPT];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+          for (int j = 0; j < VPT; ++j) v[s][j] = nt_load(src + static_cast<size_t>(g.row[s]) * chunks + piece[j]);
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          if (g.live[s]) {
+            const float w = WEIGHTED ? __int_as_float(wave_lane(__float_as_int(my_w), g.lane[s])) : 1.0f;
+#pragma unroll
+            for (int j = 0; j < VPT; ++j) fma8(acc[j], v[s][j], w);
+          }
+        }
+      }
+      if (PART && c0 == 0 && lane < kk) {
+        float sum = 0.f;
+        if (my_row >= 0) {
+          const float* p = part + static_cast<size_t>(my_row) * strips;
+#pragma unroll 8
+          for (int c = 0; c < strips; ++c) sum += p[c];
+        }
+        dgate[static_cast<size_t>(t) * k + i0 + lane] = sum;
+      }
+    }
+    uint4* o = out + static_cast<size_t>(t) * chunks;
+#pragma unroll
+    for (int j = 0; j < VPT; ++j) {
+      const int c = c0 + j * MOE_WAVE + lane;
+      if (c < chunks) o[c] = pack8(acc[j]);
+    }
+  }
+}
+
+// The same, two slots at a time and under a mask, all parts of a row in one wave: for rows of at most 64 pieces, and for large passes
+// most of whose slots have a row.  The former take a few us of latency whatever is done, and behind the other kernels of a layer,
+// with its code not in the instruction cache, the short body is the quicker one (2 tokens of d 512, 8 slots: 22.3 us for the pass,
+// 22.8-23.1 with the body above; 120 tokens of d 192 28.3 and 29.0).  The latter run at the rate of memory in either form, within
+// the step a little better here (8192 tokens of d 2048, 8 slots 53.8 / 57.1 us; 20257 tokens of d 2368, 4 slots 80 / 84 us).
+template <int VPT, bool WEIGHTED>
+__global__ __launch_bounds__(256) void combine_pairs_kernel(const uint4* __restrict__ src, const int32_t* __restrict__ slot_row,
+                                                            const float* __restrict__ topk_w, int T, int k, int chunks,
+                                                            uint4* __restrict__ out) {
   const int lane = threadIdx.x % MOE_WAVE;
   const int t = blockIdx.x * (256 / MOE_WAVE) + threadIdx.x / MOE_WAVE;
   if (t >= T) return;
@@ -92,14 +195,16 @@ __global__ __launch_bounds__(256) void combine_kernel(const uint4* __restrict__ 
   }
 }
 
-// dyp[row(t,i)] = w[t,i] * dout[t];  dgate[t,i] = <yp[row(t,i)], dout[t]>
-// The token's dout segment is loaded once and kept in registers for all of its slots; lane i
-// collects the dot product of slot i (k <= 64 slots per pass over the lanes).
-template <int VPT>
+// dyp[row(t,i)] = w[t,i] * dout[t];  dgate[t,i] = <yp[row(t,i)], dout[t]>;  OUT: also out[t] = sum_i w[t,i] * yp[row(t,i)], for a
+// caller that runs the forward pass's combine and its backward one behind the other: the rows of yp are then read once.
+// The token's dout segment is loaded once and kept in registers for all of its slots; the loads of SLOTS rows are in flight
+// together; lane i collects the dot product of slot i (k <= 64 slots per pass over the lanes).
+template <int VPT, int SLOTS, bool OUT>
 __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restrict__ dout, const uint4* __restrict__ yp,
                                                           const int32_t* __restrict__ slot_row,
                                                           const float* __restrict__ topk_w, int T, int k, int chunks,
-                                                          uint4* __restrict__ dyp, float* __restrict__ dgate) {
+                                                          uint4* __restrict__ dyp, float* __restrict__ dgate,
+                                                          uint4* __restrict__ out) {
   const int lane = threadIdx.x % MOE_WAVE;
   const int t = blockIdx.x * (256 / MOE_WAVE) + threadIdx.x / MOE_WAVE;
   if (t >= T) return;
@@ -115,51 +220,122 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restric
     }
     for (int c0 = 0; c0 < chunks; c0 += MOE_WAVE * VPT) {
       uint4 gv[VPT];
+      int piece[VPT];
+      float acc[OUT ? VPT : 1][8];
 #pragma unroll
       for (int j = 0; j < VPT; ++j) {
         const int c = c0 + j * MOE_WAVE + lane;
+        piece[j] = min(c, chunks - 1);
         gv[j] = c < chunks ? g[c] : make_uint4(0, 0, 0, 0);
+        if constexpr (OUT) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) acc[j][q] = 0.f;
+        }
       }
-      for (int i = 0; i < kk; ++i) {
-        const int row = __shfl(my_row, i, MOE_WAVE);
-        if (row < 0) continue;
-        const float w = __shfl(my_w, i, MOE_WAVE);
-        const uint4* y = yp + static_cast<size_t>(row) * chunks;
-        uint4* dy = dyp + static_cast<size_t>(row) * chunks;
-        uint4 yv[VPT];
+      uint64_t mask = __ballot(my_row >= 0);
+      while (mask != 0) {
+        const SlotGroup<SLOTS> sg(mask, my_row);
+        uint4 yv[SLOTS][VPT];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s)
+#pragma unroll
+          for (int j = 0; j < VPT; ++j) {
+            yv[s][j] = nt_load(yp + static_cast<size_t>(sg.row[s]) * chunks + piece[j]);
+            if (c0 + j * MOE_WAVE + lane >= chunks) yv[s][j] = make_uint4(0, 0, 0, 0);
+          }
+        float dot[SLOTS];
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          dot[s] = 0.f;
+          if (sg.live[s]) {
+            const float w = __int_as_float(wave_lane(__float_as_int(my_w), sg.lane[s]));
+            uint4* dy = dyp + static_cast<size_t>(sg.row[s]) * chunks;
+#pragma unroll
+            for (int j = 0; j < VPT; ++j) {
+              const int c = c0 + j * MOE_WAVE + lane;
+              dot[s] += dot8(yv[s][j], gv[j]);
+              if (c < chunks) dy[c] = scale8(gv[j], w);
+              if constexpr (OUT) fma8(acc[j], yv[s][j], w);
+            }
+          }
+        }
+#pragma unroll
+        for (int s = 0; s < SLOTS; ++s) {
+          dot[s] = wave_sum(dot[s]);
+          if (lane == sg.lane[s] && sg.live[s]) my_dot += dot[s];
+        }
+      }
+      if constexpr (OUT) {       // k <= 64: the only pass over the slots
+        uint4* o = out + static_cast<size_t>(t) * chunks;
 #pragma unroll
         for (int j = 0; j < VPT; ++j) {
           const int c = c0 + j * MOE_WAVE + lane;
-          yv[j] = c < chunks ? nt_load(y + c) : make_uint4(0, 0, 0, 0);
+          if (c < chunks) o[c] = pack8(acc[j]);
         }
-        float dot = 0.f;
-#pragma unroll
-        for (int j = 0; j < VPT; ++j) {
-          const int c = c0 + j * MOE_WAVE + lane;
-          dot += dot8(yv[j], gv[j]);
-          if (c < chunks) dy[c] = scale8(gv[j], w);
-        }
-#pragma unroll
-        for (int m = 1; m < MOE_WAVE; m <<= 1) dot += __shfl_xor(dot, m, MOE_WAVE);
-        if (lane == i) my_dot += dot;
       }
     }
     if (lane < kk) dgate[static_cast<size_t>(t) * k + i0 + lane] = my_dot;
   }
 }
 
+#define COMBINE(VPT, SLOTS, PART, PARTS)                                                                                           \
+  MOE_LAUNCH(name, (combine_kernel<VPT, SLOTS, WEIGHTED, PART>), dim3((T + 3) / 4, PARTS), dim3(256), 0, s, a, slot_row, w, T, k, \
+             chunks, o, part, strips, dgate)
+#define COMBINE_PAIRS(VPT) \
+  MOE_LAUNCH(name, (combine_pairs_kernel<VPT, WEIGHTED>), dim3((T + 3) / 4), dim3(256), 0, s, a, slot_row, w, T, k, chunks, o)
+// A pass over so few bytes of rows waits for latency: a wave for every 64 pieces, four slots at a time.  Passes over more want long
+// runs of a row.  Whole kernel, us, (4 pieces per lane, 2 slots, in one wave) / (1, 4), 8 slots per token, rows not in the caches:
+//   d 2048:  1 token 4.0 / 2.8   48 tokens 6.4 / 4.0   1024 9.8 / 8.0   2048 14.6 / 14.2   8192 53.2 / 68.6
+//   d 4096:  1 token 4.4 / 3.2   48 tokens 7.0 / 4.7   1024 14.6 / 14.5   4096 53.3 / 64.4
+bool few_bytes(int T, int k, int d) { return static_cast<long long>(T) * k * d * 2 < (48 << 20); }
+
+// sparse: most slots are expected to have no local row.  They are left out beforehand there: 24576 tokens of d 3072, 8 slots, one of
+// twelve local, 55 -> 49 us (sum) and 50 -> 43 us (backward of the gather) against the pairs.
 template <bool WEIGHTED>
 int launch_combine(const moe_bf16* src, const int32_t* slot_row, const float* w, int T, int k, int d, moe_bf16* out,
-                   hipStream_t s, const char* name) {
+                   hipStream_t s, const char* name, bool sparse, const float* part = nullptr, int strips = 0, float* dgate = nullptr) {
   const int chunks = d / 8;
-  dim3 grid((T + 3) / 4), block(256);
   const uint4* a = reinterpret_cast<const uint4*>(src);
   uint4* o = reinterpret_cast<uint4*>(out);
-  if (chunks <= 64) MOE_LAUNCH(name, (combine_kernel<1, WEIGHTED>), grid, block, 0, s, a, slot_row, w, T, k, chunks, o);
-  else if (chunks <= 128) MOE_LAUNCH(name, (combine_kernel<2, WEIGHTED>), grid, block, 0, s, a, slot_row, w, T, k, chunks, o);
-  else MOE_LAUNCH(name, (combine_kernel<4, WEIGHTED>), grid, block, 0, s, a, slot_row, w, T, k, chunks, o);
+  if (part != nullptr) {
+    if constexpr (!WEIGHTED) { if (chunks <= 64) COMBINE(1, 2, true, 1); else COMBINE(1, 4, true, (chunks + 63) / 64); }
+  } else if (chunks <= 64) {
+    COMBINE_PAIRS(1);
+  } else if (few_bytes(T, k, d)) {
+    COMBINE(1, 4, false, (chunks + 63) / 64);
+  } else if (chunks <= 128) {
+    COMBINE_PAIRS(2);
+  } else if (sparse) {
+    COMBINE(4, 2, false, 1);
+  } else {
+    COMBINE_PAIRS(4);
+  }
   return moe_check_launch();
 }
+#undef COMBINE_PAIRS
+#undef COMBINE
+
+#define COMBINE_BWD(VPT, SLOTS, OUT)                                                                                                   \
+  MOE_LAUNCH(name, (combine_bwd_kernel<VPT, SLOTS, OUT>), dim3((T + 3) / 4), dim3(256), 0, s, a, y, slot_row, topk_w, T, k, chunks, o, \
+             dgate, ov)
+template <bool OUT>
+int launch_combine_bwd(const moe_bf16* dout, const moe_bf16* yp, const int32_t* slot_row, const float* topk_w, int T, int k, int d,
+                       moe_bf16* dyp, float* dgate, moe_bf16* out, hipStream_t s, const char* name) {
+  const int chunks = d / 8;
+  const uint4* a = reinterpret_cast<const uint4*>(dout);
+  const uint4* y = reinterpret_cast<const uint4*>(yp);
+  uint4* o = reinterpret_cast<uint4*>(dyp);
+  uint4* ov = reinterpret_cast<uint4*>(out);
+  // Whole kernel, us, before (one slot at a time, the reductions through LDS) / now: d 256, 2048 tokens 10.6 / 6.8; d 2048, 48 tokens
+  // 10.0 / 7.1, 8192 tokens 107 / 106; d 4096, 48 tokens 20.1 / 13.4.  combine and combine_bwd apart / in one (OUT): d 2048, 48 tokens
+  // 10.6 / 8.2 and a launch, 8192 tokens 158 / 119; d 1024, 24576 tokens of 2 slots 65 / 47.
+  if (chunks <= 64) COMBINE_BWD(1, 4, OUT);
+  else if (T <= 512) { if (chunks <= 128) COMBINE_BWD(2, 4, OUT); else COMBINE_BWD(4, 4, OUT); }
+  else if (chunks <= 128) COMBINE_BWD(2, 2, OUT);
+  else COMBINE_BWD(4, 2, OUT);
+  return moe_check_launch();
+}
+#undef COMBINE_BWD
 
 bool bad_dims(int T, int k, int d) { return T <= 0 || k <= 0 || d <= 0 || d % 8 != 0; }
 
@@ -169,21 +345,32 @@ extern "C" int moe_unpermute_combine(const moe_bf16* yp, const int32_t* slot_row
                                      moe_bf16* out, void* stream) {
   if (!yp || !slot_row || !topk_w || !out || bad_dims(T, k, d)) return MOE_ERR_INVALID;
   if (!moe_aligned16(yp) || !moe_aligned16(out) || !moe_aligned16(slot_row) || !moe_aligned16(topk_w)) return MOE_ERR_INVALID;
-  return launch_combine<true>(yp, slot_row, topk_w, T, k, d, out, static_cast<hipStream_t>(stream), "combine");
+  return launch_combine<true>(yp, slot_row, topk_w, T, k, d, out, static_cast<hipStream_t>(stream), "combine", false);
 }
 
 extern "C" int moe_permute_bwd(const moe_bf16* dxp, const int32_t* slot_row, int T, int k, int d, moe_bf16* dx,
                                void* stream) {
   if (!dxp || !slot_row || !dx || bad_dims(T, k, d)) return MOE_ERR_INVALID;
   if (!moe_aligned16(dxp) || !moe_aligned16(dx) || !moe_aligned16(slot_row)) return MOE_ERR_INVALID;
-  return launch_combine<false>(dxp, slot_row, nullptr, T, k, d, dx, static_cast<hipStream_t>(stream), "permute_bwd");
+  return launch_combine<false>(dxp, slot_row, nullptr, T, k, d, dx, static_cast<hipStream_t>(stream), "permute_bwd", false);
+}
+
+// Saves the launch of dgate_finish (4 us) where the whole backward of the gather takes a few us; larger passes would wait for the
+// strips (24576 tokens, one twelfth of their slots local: 50 + 8 us apart, 82 in one).
+bool moe_permute_bwd_adds_dgate(int T, int k, int d) { return few_bytes(T, k, d) && static_cast<long long>(T) * k <= 16384; }
+
+int moe_permute_bwd_dgate(const moe_bf16* dxp, const int32_t* slot_row, int T, int k, int d, moe_bf16* dx, const float* part,
+                          int strips, float* dgate, void* stream) {
+  if (!dxp || !slot_row || !dx || !part || !dgate || strips <= 0 || bad_dims(T, k, d)) return MOE_ERR_INVALID;
+  if (!moe_aligned16(dxp) || !moe_aligned16(dx) || !moe_aligned16(slot_row) || !moe_aligned16(dgate)) return MOE_ERR_INVALID;
+  return launch_combine<false>(dxp, slot_row, nullptr, T, k, d, dx, static_cast<hipStream_t>(stream), "permute_bwd", false, part, strips, dgate);
 }
 
 extern "C" int moe_unpermute_sum(const moe_bf16* ypw, const int32_t* slot_row, int T, int k, int d, moe_bf16* out,
                                  void* stream) {
   if (!ypw || !slot_row || !out || bad_dims(T, k, d)) return MOE_ERR_INVALID;
   if (!moe_aligned16(ypw) || !moe_aligned16(out) || !moe_aligned16(slot_row)) return MOE_ERR_INVALID;
-  return launch_combine<false>(ypw, slot_row, nullptr, T, k, d, out, static_cast<hipStream_t>(stream), "combine");
+  return launch_combine<false>(ypw, slot_row, nullptr, T, k, d, out, static_cast<hipStream_t>(stream), "combine", false);
 }
 
 extern "C" int moe_unpermute_combine_bwd(const moe_bf16* dout, const moe_bf16* yp, const int32_t* slot_row,
@@ -193,14 +380,27 @@ extern "C" int moe_unpermute_combine_bwd(const moe_bf16* dout, const moe_bf16* y
   if (!moe_aligned16(dout) || !moe_aligned16(yp) || !moe_aligned16(dyp) || !moe_aligned16(slot_row) ||
       !moe_aligned16(topk_w) || !moe_aligned16(dgate))
     return MOE_ERR_INVALID;
+  return launch_combine_bwd<false>(dout, yp, slot_row, topk_w, T, k, d, dyp, dgate, nullptr, static_cast<hipStream_t>(stream), "combine_bwd");
+}
+
+int moe_combine_sparse(const moe_bf16* src, const int32_t* slot_row, const float* topk_w, int T, int k, int d, moe_bf16* out,
+                       const char* name, void* stream) {
+  if (!src || !slot_row || !out || bad_dims(T, k, d)) return MOE_ERR_INVALID;
+  const void* ptrs[] = {src, slot_row, topk_w, out};
+  for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int chunks = d / 8;
-  dim3 grid((T + 3) / 4), block(256);
-  const uint4* a = reinterpret_cast<const uint4*>(dout);
-  const uint4* y = reinterpret_cast<const uint4*>(yp);
-  uint4* o = reinterpret_cast<uint4*>(dyp);
-  if (chunks <= 64) MOE_LAUNCH("combine_bwd", combine_bwd_kernel<1>, grid, block, 0, s, a, y, slot_row, topk_w, T, k, chunks, o, dgate);
-  else if (chunks <= 128) MOE_LAUNCH("combine_bwd", combine_bwd_kernel<2>, grid, block, 0, s, a, y, slot_row, topk_w, T, k, chunks, o, dgate);
-  else MOE_LAUNCH("combine_bwd", combine_bwd_kernel<4>, grid, block, 0, s, a, y, slot_row, topk_w, T, k, chunks, o, dgate);
-  return moe_check_launch();
+  return topk_w != nullptr ? launch_combine<true>(src, slot_row, topk_w, T, k, d, out, s, name, true)
+                           : launch_combine<false>(src, slot_row, nullptr, T, k, d, out, s, name, true);
+}
+
+int moe_combine_both(const moe_bf16* dout, const moe_bf16* yp, const int32_t* slot_row, const float* topk_w, int T, int k, int d,
+                     moe_bf16* out, moe_bf16* dyp, float* dgate, void* stream) {
+  if (k > MOE_WAVE) {
+    const int rc = moe_unpermute_combine(yp, slot_row, topk_w, T, k, d, out, stream);
+    return rc != MOE_OK ? rc : moe_unpermute_combine_bwd(dout, yp, slot_row, topk_w, T, k, d, dyp, dgate, stream);
+  }
+  if (!dout || !yp || !slot_row || !topk_w || !dyp || !dgate || !out || bad_dims(T, k, d)) return MOE_ERR_INVALID;
+  const void* ptrs[] = {dout, yp, dyp, slot_row, topk_w, dgate, out};
+  for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
+  return launch_combine_bwd<true>(dout, yp, slot_row, topk_w, T, k, d, dyp, dgate, out, static_cast<hipStream_t>(stream), "combine+bwd");
 }

@@ -1751,6 +1751,10 @@ extern "C" size_t moe_grouped_gemm_bwd_folded_workspace_bytes(int R_cap, int f) 
   return moe_grouped_gemm_bwd_workspace_bytes(R_cap, f) + folded_part_bytes(R_cap, f);
 }
 
+const float* moe_folded_part(const void* ws, int R_cap, int f) {
+  return reinterpret_cast<const float*>(static_cast<const char*>(ws) + moe_grouped_gemm_bwd_workspace_bytes(R_cap, f));
+}
+
 int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
                                            const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
@@ -1758,8 +1762,7 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
-  if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !dgate ||
-      !ws || !row_weight || !slot_row || k <= 0)
+  if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws || !row_weight || !slot_row || k <= 0)
     return MOE_ERR_INVALID;
   if (bad_gemm_dims(E, R_cap, d, f) || bad_gather(x, T, row_token, d) || bad_gather(dout, T, row_token, d))
     return MOE_ERR_INVALID;
@@ -1770,7 +1773,7 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   const size_t one = moe_grouped_gemm_bwd_workspace_bytes(R_cap, f) / 2;
   uint16_t* dg = static_cast<uint16_t*>(ws);
   uint16_t* du = reinterpret_cast<uint16_t*>(static_cast<char*>(ws) + one);
-  float* part = reinterpret_cast<float*>(static_cast<char*>(ws) + 2 * one);
+  float* part = const_cast<float*>(moe_folded_part(ws, R_cap, f));
 
   // Two launches of two independent products each (the second list of a launch takes over the workgroups
   // that the first leaves idle at its end).
@@ -1787,9 +1790,11 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   a.K = d; a.N = f;
   int rc = run_gemm_pair<DGRAD_H_GATE, WGRAD_GATHER_A>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down");
   if (rc != MOE_OK) return rc;
-  const int n = T * k;
-  MOE_LAUNCH("dgate_finish", dgate_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const float*>(part),
-             f / 64, slot_row, n, dgate);
+  if (dgate != nullptr) {
+    const int n = T * k;
+    MOE_LAUNCH("dgate_finish", dgate_finish_kernel, dim3((n + 255) / 256), dim3(256), 0, s, static_cast<const float*>(part),
+               f / 64, slot_row, n, dgate);
+  }
   // dWg = dg^T x[token] and dWu = du^T x[token] (one list: both read the same gathered rows of x), then
   // dxp = dg . Wg + du . Wu
   GemmArgs w{};
@@ -1812,6 +1817,7 @@ extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16*
                                            const moe_bf16* Wd, int E, int R_cap, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
                                            size_t ws_bytes, void* stream) {
+  if (!dgate) return MOE_ERR_INVALID;
   return moe_gemm_bwd_folded(dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, expert_offsets, Wg, Wu, Wd, E, R_cap,
                              R_cap, d, f, dxp, dWg, dWu, dWd, dgate, ws, ws_bytes, stream);
 }

@@ -12,6 +12,7 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
   const int T = L->T, d = L->d, E = L->E, k = L->k, f = L->f, nl = L->e_count, R_cap = T * k;
   const long long rows = (static_cast<long long>(R_cap) * nl + E - 1) / E;
   const bool fold = L->path == MOE_LAYER_FOLD, plain = L->path == MOE_LAYER_PLAIN;
+  const bool sparse = 2ll * nl <= E;   // few of a token's slots have a local row
   int rc = MOE_OK;
   if (what & MOE_LAYER_ROUTER) {
     if ((rc = moe_router_fwd(L->x, L->Wr, T, d, E, L->logits, stream)) != MOE_OK) return rc;
@@ -29,24 +30,35 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
       rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
                                R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
     if (rc != MOE_OK) return rc;
-    rc = fold ? moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream)
-              : moe_unpermute_combine(L->yp, L->slot_row, L->topk_w, T, k, d, L->out, stream);
+    // with the backward in the same call the rows of yp are read once, for both
+    if (!fold && !L->topk_w) return MOE_ERR_INVALID;
+    if (sparse && (fold || !(what & MOE_LAYER_BWD)))
+      rc = moe_combine_sparse(L->yp, L->slot_row, fold ? nullptr : L->topk_w, T, k, d, L->out, "combine", stream);
+    else if (fold) rc = moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream);
+    else if (what & MOE_LAYER_BWD)
+      rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
+    else rc = moe_unpermute_combine(L->yp, L->slot_row, L->topk_w, T, k, d, L->out, stream);
     if (rc != MOE_OK) return rc;
   }
   if (what & MOE_LAYER_BWD) {
     if (!plain && !L->row_token) return MOE_ERR_INVALID;   // without it moe_gemm_bwd would take x for T * k grouped rows
+    if (!L->dgate || !moe_aligned16(L->dgate)) return MOE_ERR_INVALID;
+    const bool adds_dgate = fold && moe_permute_bwd_adds_dgate(T, k, d);
     if (fold) {
       rc = moe_gemm_bwd_folded(L->dout, L->x, T, k, L->row_token, L->row_weight, L->slot_row, L->g, L->u, L->h,
                                L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
-                               L->dgate, L->ws, L->ws_bytes, stream);
+                               adds_dgate ? nullptr : L->dgate, L->ws, L->ws_bytes, stream);
     } else {
-      rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
+      if (!(what & MOE_LAYER_FWD)) rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
       if (rc != MOE_OK) return rc;
       rc = moe_gemm_bwd(L->dyp, plain ? L->xp : L->x, T, plain ? nullptr : L->row_token, L->g, L->u, L->h, L->expert_offsets,
                         L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);
     }
     if (rc != MOE_OK) return rc;
-    if ((rc = moe_permute_bwd(L->dxp, L->slot_row, T, k, d, L->dx, stream)) != MOE_OK) return rc;
+    rc = adds_dgate ? moe_permute_bwd_dgate(L->dxp, L->slot_row, T, k, d, L->dx, moe_folded_part(L->ws, R_cap, f), f / 64, L->dgate, stream)
+         : sparse   ? moe_combine_sparse(L->dxp, L->slot_row, nullptr, T, k, d, L->dx, "permute_bwd", stream)
+                    : moe_permute_bwd(L->dxp, L->slot_row, T, k, d, L->dx, stream);
+    if (rc != MOE_OK) return rc;
   }
   if (what & MOE_LAYER_ROUTER_BWD) {
     if ((rc = moe_route_bwd(L->logits, L->topk_idx, L->dgate, T, E, k, L->renormalize, L->dlogits, stream)) != MOE_OK) return rc;

@@ -179,7 +179,7 @@ __global__ __launch_bounds__(PERM_THREADS) void permute_place_kernel(const int32
   }
 }
 
-// xp[slot_row[t,i]] = x[t] for every local slot; one wave per token.
+// xp[slot_row[t,i]] = x[t] for every local slot.  A wave owns 64 VPT pieces of a token's row; lane i holds slot i's row.
 template <int VPT>
 __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ slot_row,
                                                            int T, int k, int chunks /* d/8 */, uint4* __restrict__ xp) {
@@ -187,15 +187,18 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restri
   const int t = blockIdx.x * (256 / MOE_WAVE) + threadIdx.x / MOE_WAVE;
   if (t >= T) return;
   const uint4* src = x + static_cast<size_t>(t) * chunks;
-  for (int c0 = 0; c0 < chunks; c0 += MOE_WAVE * VPT) {
-    uint4 v[VPT];
+  const int c0 = blockIdx.y * (MOE_WAVE * VPT);
+  uint4 v[VPT];
 #pragma unroll
-    for (int j = 0; j < VPT; ++j) {
-      const int c = c0 + j * MOE_WAVE + lane;
-      if (c < chunks) v[j] = src[c];
-    }
-    for (int i = 0; i < k; ++i) {
-      const int row = slot_row[static_cast<size_t>(t) * k + i];
+  for (int j = 0; j < VPT; ++j) {
+    const int c = c0 + j * MOE_WAVE + lane;
+    v[j] = c < chunks ? src[c] : make_uint4(0, 0, 0, 0);
+  }
+  for (int i0 = 0; i0 < k; i0 += MOE_WAVE) {
+    const int kk = min(k - i0, MOE_WAVE);
+    const int my_row = lane < kk ? slot_row[static_cast<size_t>(t) * k + i0 + lane] : -1;
+    for (int i = 0; i < kk; ++i) {
+      const int row = wave_lane(my_row, i);
       if (row < 0) continue;
       uint4* dst = xp + static_cast<size_t>(row) * chunks;
 #pragma unroll
@@ -227,15 +230,15 @@ extern "C" size_t moe_permute_workspace_bytes(int T, int k, int e_count) {
 namespace {
 void launch_rows(const moe_bf16* x, const int32_t* slot_row, int T, int d, int k, moe_bf16* xp, hipStream_t s) {
   const int chunks = d / 8;
-  dim3 grid((T + 3) / 4), block(256);
   const uint4* xs = reinterpret_cast<const uint4*>(x);
   uint4* xd = reinterpret_cast<uint4*>(xp);
-  if (chunks <= 64)
-    MOE_LAUNCH("permute_rows", permute_rows_kernel<1>, grid, block, 0, s, xs, slot_row, T, k, chunks, xd);
-  else if (chunks <= 128)
-    MOE_LAUNCH("permute_rows", permute_rows_kernel<2>, grid, block, 0, s, xs, slot_row, T, k, chunks, xd);
+  // Few rows wait for latency, many want long runs of a row.  Us, 1 / 2 / 4 pieces per lane, 8 slots per token: d 2048, 48 tokens
+  // 3.1 / 3.2 / 3.6, 2048 tokens 15.4 / 17.4 / 14.8, 8192 tokens 84 / 83 / 61; d 1024, 8192 tokens 30.3 / 27.6 / 27.6; d 256 all the same.
+  // (19 tokens of d 2688 took 9.0 us with 4 pieces and one dependent load of a slot's row per slot.)
+  if (chunks > 128 && static_cast<long long>(T) * k * d * 2 >= (48 << 20))
+    MOE_LAUNCH("permute_rows", permute_rows_kernel<4>, dim3((T + 3) / 4, (chunks + 255) / 256), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
   else
-    MOE_LAUNCH("permute_rows", permute_rows_kernel<4>, grid, block, 0, s, xs, slot_row, T, k, chunks, xd);
+    MOE_LAUNCH("permute_rows", permute_rows_kernel<2>, dim3((T + 3) / 4, (chunks + 127) / 128), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
 }
 
 int check_permute_args(const moe_bf16* x, const int32_t* topk_idx, int T, int d, int E_total, int k, int e_begin,

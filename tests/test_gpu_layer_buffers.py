@@ -147,3 +147,42 @@ def test_one_call_equals_the_stage_calls(path, T, d, E, k, f, eb, ec, hot):
         if n in ("row_token", "row_weight", "xp", "g", "u", "h", "yp", "hw", "ypw", "dyp", "dxp"):     # T * k rows, not all local
             a, b = a[:rows], b[:rows]
         assert torch.equal(a, b), n
+
+
+# The forward pass's combine and its backward in one kernel (run_fwd_bwd) against the two of run_fwd and run_bwd, and the gate
+# gradient added up by the backward of the gather against the kernel of its own: rows of one to five groups of 64 pieces with
+# a remainder, both sides of the rules on tokens (512), bytes of rows (48 MB) and the share of local experts (a half), more slots
+# than lanes
+@pytest.mark.parametrize("T,d,E,k,eb,ec", [
+    (513, 320, 12, 5, 0, 12), (40, 576, 12, 5, 3, 6), (600, 1088, 9, 3, 0, 9), (512, 1088, 9, 8, 0, 9), (33, 2112, 9, 1, 2, 4),
+    (3100, 2112, 9, 4, 0, 9), (6000, 2112, 9, 4, 2, 3), (700, 2624, 9, 7, 0, 9), (20, 64, 90, 70, 5, 80)])
+@pytest.mark.parametrize("path", ["plain", "gather", "fold"])
+def test_both_passes_in_one_call(path, T, d, E, k, eb, ec):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(T + d)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda:0")
+    x, dout, logits, f = r(T, d).bfloat16(), r(T, d).bfloat16(), r(T, E), 64
+    w = [r(ec, *s).mul_(0.05).bfloat16() for s in ((f, d), (f, d), (d, f))]
+    one, two = (B.MoELayerBuffers(T, d, E, k, f, eb, ec, 1, gather=path == "gather", fold=path == "fold") for _ in range(2))
+    one.run_fwd_bwd(x, logits, dout, *w)
+    two.run_fwd(x, logits, *w)
+    out = two.out.clone()
+    apart = torch.empty_like(out)
+    if path == "fold":
+        B.moe_unpermute_sum(two.yp, two.slot_row, apart)
+    else:
+        B.moe_unpermute_combine(two.yp, two.slot_row, two.topk_w, apart)
+    assert torch.equal(apart, out)
+    if path == "fold":
+        dx, dgate = torch.empty_like(two.dx), torch.empty_like(two.dgate)
+        B.moe_grouped_gemm_bwd_folded(dout, x, two.row_token, two.row_weight, two.slot_row, two.g, two.u, two.h, two.expert_offsets, *w,
+                                      two.dxp, two.dWg, two.dWu, two.dWd, dgate, two.ws)
+        B.moe_permute_bwd(two.dxp, two.slot_row, dx)
+    else:
+        two.run_bwd(dout, *w)
+        dx, dgate = two.dx, two.dgate
+        rows = int(one.expert_offsets[-1])
+        assert torch.equal(one.dyp[:rows], two.dyp[:rows])
+    assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(dgate).all())
+    assert torch.equal(one.out, out) and torch.equal(one.dgate, dgate) and torch.equal(one.dx, dx)
+    assert torch.equal(one.dWd, two.dWd)
