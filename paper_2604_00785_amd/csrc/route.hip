@@ -2,12 +2,16 @@
 //
 // A group of G lanes (G a power of two, 8..64) owns one token and keeps
 // ceil(E/G) logits per lane in registers.  Selection runs on the logits (the
-// softmax is monotone): each logit becomes a 64-bit key
-//   (order-preserving image of the fp32 value) << 32 | (0xFFFFFFFF - expert)
-// so that an unsigned maximum picks the largest value and, among equal values,
-// the lowest expert id.  k rounds of a butterfly maximum over the group pick the
-// k winners; the owner of a winner retires its key.  Gates are exp(l - max)
+// softmax is monotone): each becomes a 32-bit key, the order-preserving image of
+// the fp32 value.  k rounds pick the k winners: the maximum over the group, then
+// the lowest expert id among the lanes' keys that equal it, which the owner
+// retires; the value comes back out of the key.  Gates are exp(l - max)
 // divided by the sum over all experts, or over the winners when renormalising.
+//
+// What bounds it is the vector ALU (large passes) and the chain of rounds (small ones): a round is some 50 instructions, all of them
+// single ones whose partners come through lane permutations.  With 64-bit keys (value and id in one maximum) it was some 110, every
+// compare and select doubled, and the value went through LDS.  Routing launch before -> now, us (between events),
+// 8 winners: 24576 tokens of 240 experts 34.1 -> 28.1, 8192 of 64 10.7 -> 8.5, 501 of 64 9.8 -> 8.2, 48 of 64 in one workgroup 10.0 -> 9.1.
 //
 // When the index generation of Stages 2-3 follows in the same call, a workgroup routes a chunk of
 // tokens (one or more passes of 256 / G tokens) and counts its winners per local expert straight from
@@ -23,31 +27,30 @@ __device__ __forceinline__ uint32_t ordered_bits(float v) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int mask) {
-  uint32_t lo = static_cast<uint32_t>(v), hi = static_cast<uint32_t>(v >> 32);
-  lo = __shfl_xor(lo, mask, MOE_WAVE);
-  hi = __shfl_xor(hi, mask, MOE_WAVE);
-  return (static_cast<uint64_t>(hi) << 32) | lo;
+__device__ __forceinline__ float from_ordered_bits(uint32_t u) {
+  return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
 }
 
-// The maximum of a 64-bit key over a group of G lanes, in every lane of the group.  Partners inside a row
-// of 16 lanes come through DPP lane permutations (no LDS round trip): neighbour, other pair of the quad,
-// then the mirrored lane of the 8- and 16-lane halves (by then all lanes of the smaller unit agree, so the
-// mirror is as good as the XOR partner); beyond a row, through the crossbar.
-template <int CTRL> __device__ __forceinline__ uint64_t dpp_u64(uint64_t v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(v)), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(static_cast<uint32_t>(v >> 32)), CTRL, 0xF, 0xF, false);
-  return (static_cast<uint64_t>(static_cast<uint32_t>(hi)) << 32) | static_cast<uint32_t>(lo);
+// Reduction of v by op over a group of G lanes, in every lane of the group.  Partners inside a row of 16 lanes come through DPP lane
+// permutations (neighbour, other pair of the quad, then the mirrored lane of the 8- and 16-lane halves: by then all lanes of the
+// smaller unit agree, so the mirror is as good as the XOR partner), beyond a row through the exchange of rows or halves.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false));
 }
-template <int G> __device__ __forceinline__ uint64_t group_max_u64(uint64_t best) {
-  auto take = [&](uint64_t o) { best = o > best ? o : best; };
-  if constexpr (G >= 2) take(dpp_u64<0xB1>(best));     // quad_perm [1,0,3,2]
-  if constexpr (G >= 4) take(dpp_u64<0x4E>(best));     // quad_perm [2,3,0,1]
-  if constexpr (G >= 8) take(dpp_u64<0x141>(best));    // row_half_mirror
-  if constexpr (G >= 16) take(dpp_u64<0x140>(best));   // row_mirror
-  if constexpr (G >= 32) take(shfl_xor_u64(best, 16));
-  if constexpr (G >= 64) take(shfl_xor_u64(best, 32));
-  return best;
+template <int G, typename Op> __device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
+  if constexpr (G >= 2) v = op(v, dpp_u32<0xB1>(v));     // quad_perm [1,0,3,2]
+  if constexpr (G >= 4) v = op(v, dpp_u32<0x4E>(v));     // quad_perm [2,3,0,1]
+  if constexpr (G >= 8) v = op(v, dpp_u32<0x141>(v));    // row_half_mirror
+  if constexpr (G >= 16) v = op(v, dpp_u32<0x140>(v));   // row_mirror
+  if constexpr (G >= 32) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op(r[0], r[1]);
+  }
+  if constexpr (G >= 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = op(r[0], r[1]);
+  }
+  return v;
 }
 
 // Selection and gates of one token by a group of G lanes (gl: lane inside the group): val[j] is the logit of expert
@@ -55,12 +58,13 @@ template <int G> __device__ __forceinline__ uint64_t group_max_u64(uint64_t best
 template <int G, int VPL>
 __device__ __forceinline__ void route_token(const float (&val)[VPL], int gl, int E, int k, int renormalize, int (&my_idx)[VPL],
                                             float (&my_w)[VPL]) {
-  uint64_t key[VPL];
+  const auto larger = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a > b ? a : b; };
+  const auto smaller = [](uint32_t a, uint32_t b) __attribute__((always_inline)) { return a < b ? a : b; };
+  uint32_t key[VPL];
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
-    const int e = gl + j * G;
-    // padding keys lie below every real key (real keys have a non-zero low word or high bit)
-    key[j] = e < E ? (static_cast<uint64_t>(ordered_bits(val[j])) << 32) | (0xFFFFFFFFu - static_cast<uint32_t>(e)) : 0;
+    // 0 is for padding and retired keys; the lowest bit pattern, a negative NaN, goes one up
+    key[j] = gl + j * G < E ? larger(ordered_bits(val[j]), 1u) : 0u;
   }
   float my_val[VPL];
 #pragma unroll
@@ -68,22 +72,21 @@ __device__ __forceinline__ void route_token(const float (&val)[VPL], int gl, int
   // full-softmax denominator pieces need the row maximum, which is winner 0
   float row_max = 0.f;
   for (int i = 0; i < k; ++i) {
-    uint64_t best = key[0];
+    uint32_t best = key[0];
 #pragma unroll
-    for (int j = 1; j < VPL; ++j) best = key[j] > best ? key[j] : best;
-    best = group_max_u64<G>(best);
-    const int e = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(best));
-    // the owner retires the key and publishes the value
-    float v = 0.f;
+    for (int j = 1; j < VPL; ++j) best = larger(best, key[j]);
+    best = group_reduce<G>(best, larger);
+    uint32_t id = 0xFFFFFFFFu;            // the lane's lowest expert with that key
 #pragma unroll
-    for (int j = 0; j < VPL; ++j) {
-      if (gl + j * G == e) { v = val[j]; key[j] = 0; }
-    }
-    // exactly one lane of the group holds v != 0-initialised; share it
-    const int owner = e % G;
-    v = __shfl(v, static_cast<int>(threadIdx.x) / G * G % MOE_WAVE + owner, MOE_WAVE);
+    for (int j = VPL - 1; j >= 0; --j) id = key[j] == best ? static_cast<uint32_t>(gl + j * G) : id;
+    const int e = static_cast<int>(group_reduce<G>(id, smaller));
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) key[j] = gl + j * G == e ? 0u : key[j];
+    const float v = from_ordered_bits(best);
     if (i == 0) row_max = v;
-    if (gl == i % G) {
+    if (k <= G) {
+      if (gl == i) { my_idx[0] = e; my_val[0] = v; }
+    } else if (gl == i % G) {
 #pragma unroll
       for (int j = 0; j < VPL; ++j)
         if (j == i / G) { my_idx[j] = e; my_val[j] = v; }
