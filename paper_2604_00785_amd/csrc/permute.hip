@@ -84,20 +84,34 @@ __global__ __launch_bounds__(PERM_THREADS) void permute_place_kernel(const int32
   const int p = tid / cols;
   for (int cg = tid % cols; cg < ncol; cg += (parts == 1 ? PERM_THREADS : (1 << 30))) {
     int bef[4] = {0, 0, 0, 0}, tot[4] = {0, 0, 0, 0};
+    // Batches of loads that are all in flight together, the last one filled up with its last row: a remainder taken one by one waits
+    // for the fabric once per row (128 experts, 250 chunks: 31 rows per thread, 15 of them so; 18.0 -> 10.6 us for the launch).
+    constexpr int BATCH4 = 16, BATCH1 = 8;
     if (vec == 4) {
-#pragma unroll 16
-      for (int q = p; q < nblocks; q += parts) {
-        const int4 v = *reinterpret_cast<const int4*>(hist + static_cast<size_t>(q) * e_count + cg * 4);
-        const int m = q < b ? -1 : 0;
-        tot[0] += v.x; tot[1] += v.y; tot[2] += v.z; tot[3] += v.w;
-        bef[0] += v.x & m; bef[1] += v.y & m; bef[2] += v.z & m; bef[3] += v.w & m;
+      for (int q0 = p; q0 < nblocks; q0 += BATCH4 * parts) {
+        int4 v[BATCH4];
+#pragma unroll
+        for (int u = 0; u < BATCH4; ++u)
+          v[u] = *reinterpret_cast<const int4*>(hist + static_cast<size_t>(min(q0 + u * parts, nblocks - 1)) * e_count + cg * 4);
+#pragma unroll
+        for (int u = 0; u < BATCH4; ++u) {
+          const int q = q0 + u * parts;
+          const int in = q < nblocks ? -1 : 0, m = q < b ? -1 : 0;    // b < nblocks
+          tot[0] += v[u].x & in; tot[1] += v[u].y & in; tot[2] += v[u].z & in; tot[3] += v[u].w & in;
+          bef[0] += v[u].x & m; bef[1] += v[u].y & m; bef[2] += v[u].z & m; bef[3] += v[u].w & m;
+        }
       }
     } else {
-#pragma unroll 8
-      for (int q = p; q < nblocks; q += parts) {
-        const int v = hist[static_cast<size_t>(q) * e_count + cg];
-        tot[0] += v;
-        bef[0] += q < b ? v : 0;
+      for (int q0 = p; q0 < nblocks; q0 += BATCH1 * parts) {
+        int v[BATCH1];
+#pragma unroll
+        for (int u = 0; u < BATCH1; ++u) v[u] = hist[static_cast<size_t>(min(q0 + u * parts, nblocks - 1)) * e_count + cg];
+#pragma unroll
+        for (int u = 0; u < BATCH1; ++u) {
+          const int q = q0 + u * parts;
+          tot[0] += q < nblocks ? v[u] : 0;
+          bef[0] += q < b ? v[u] : 0;
+        }
       }
     }
     for (int j = 0; j < vec; ++j) {
