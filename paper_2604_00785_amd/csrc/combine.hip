@@ -6,7 +6,6 @@
 // every load and store is a full, coalesced row segment, the k source rows are
 // summed in slot order in fp32, and the token's own row (out / dout) is touched
 // exactly once.  No atomics, so results are reproducible.
-#include <type_traits>
 #include "gemm.h"
 
 namespace {
@@ -35,22 +34,6 @@ __device__ __forceinline__ float dot8(const uint4& a, const uint4& b) {
 __device__ __forceinline__ uint4 scale8(const uint4& v, float w) {
   return make_uint4(pack_bf16(w * bf16lo(v.x), w * bf16hi(v.x)), pack_bf16(w * bf16lo(v.y), w * bf16hi(v.y)),
                     pack_bf16(w * bf16lo(v.z), w * bf16hi(v.z)), pack_bf16(w * bf16lo(v.w), w * bf16hi(v.w)));
-}
-
-// Sum over the wave, in every lane, in the order of a butterfly with partners lane ^ 1, ^ 2, ^ 4, ..: by then all lanes of the
-// smaller unit agree, so a mirrored partner is as good, and the partners come through lane permutations, not through LDS.
-__device__ __forceinline__ float wave_sum(float v) {
-  auto dpp = [](float x, auto ctrl) __attribute__((always_inline)) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xF, 0xF, false));
-  };
-  v += dpp(v, std::integral_constant<int, 0xB1>{});    // quad_perm [1,0,3,2]
-  v += dpp(v, std::integral_constant<int, 0x4E>{});    // quad_perm [2,3,0,1]
-  v += dpp(v, std::integral_constant<int, 0x141>{});   // row_half_mirror
-  v += dpp(v, std::integral_constant<int, 0x140>{});   // row_mirror
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);   // rows 0 + 1, 2 + 3
-  const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(h[0]) + __uint_as_float(h[1]);
 }
 
 // The next SLOTS slots of a token that have a local row, in slot order: mask holds those not yet taken (one bit per lane, lane i holds
@@ -261,7 +244,7 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restric
         }
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
-          dot[s] = wave_sum(dot[s]);
+          dot[s] = group_sum<MOE_WAVE>(dot[s]);
           if (lane == sg.lane[s] && sg.live[s]) my_dot += dot[s];
         }
       }

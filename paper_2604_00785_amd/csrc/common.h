@@ -45,6 +45,38 @@ __device__ __forceinline__ int wave_incl_scan(int v) {
 // The value of a lane whose number is the same in the whole wave.
 __device__ __forceinline__ int wave_lane(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 
+// Reduction of v by op over a group of G lanes, in every lane of the group.  Partners inside a row of 16 lanes come through DPP lane
+// permutations (neighbour, other pair of the quad, then the mirrored lane of the 8- and 16-lane halves: by then all lanes of the
+// smaller unit agree, so the mirror is as good as the XOR partner), beyond a row through the exchange of rows or halves.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
+  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false));
+}
+template <int G, typename Op> __device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
+  if constexpr (G >= 2) v = op(v, dpp_u32<0xB1>(v));     // quad_perm [1,0,3,2]
+  if constexpr (G >= 4) v = op(v, dpp_u32<0x4E>(v));     // quad_perm [2,3,0,1]
+  if constexpr (G >= 8) v = op(v, dpp_u32<0x141>(v));    // row_half_mirror
+  if constexpr (G >= 16) v = op(v, dpp_u32<0x140>(v));   // row_mirror
+  if constexpr (G >= 32) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = op(r[0], r[1]);
+  }
+  if constexpr (G >= 64) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = op(r[0], r[1]);
+  }
+  return v;
+}
+template <int G> __device__ __forceinline__ float group_sum(float v) {   // the sums of a butterfly with partners lane ^ 1, ^ 2, ^ 4, ..
+  return __uint_as_float(group_reduce<G>(__float_as_uint(v), [](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
+}
+template <int G> __device__ __forceinline__ float group_max(float v) {
+  return __uint_as_float(group_reduce<G>(__float_as_uint(v), [](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+
 static inline bool moe_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
 // ---- launch bookkeeping (prof.hip) ----------------------------------------

@@ -31,28 +31,6 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t u) {
   return __uint_as_float((u & 0x80000000u) ? u & 0x7FFFFFFFu : ~u);
 }
 
-// Reduction of v by op over a group of G lanes, in every lane of the group.  Partners inside a row of 16 lanes come through DPP lane
-// permutations (neighbour, other pair of the quad, then the mirrored lane of the 8- and 16-lane halves: by then all lanes of the
-// smaller unit agree, so the mirror is as good as the XOR partner), beyond a row through the exchange of rows or halves.
-template <int CTRL> __device__ __forceinline__ uint32_t dpp_u32(uint32_t v) {
-  return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, 0xF, 0xF, false));
-}
-template <int G, typename Op> __device__ __forceinline__ uint32_t group_reduce(uint32_t v, Op op) {
-  if constexpr (G >= 2) v = op(v, dpp_u32<0xB1>(v));     // quad_perm [1,0,3,2]
-  if constexpr (G >= 4) v = op(v, dpp_u32<0x4E>(v));     // quad_perm [2,3,0,1]
-  if constexpr (G >= 8) v = op(v, dpp_u32<0x141>(v));    // row_half_mirror
-  if constexpr (G >= 16) v = op(v, dpp_u32<0x140>(v));   // row_mirror
-  if constexpr (G >= 32) {
-    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
-    v = op(r[0], r[1]);
-  }
-  if constexpr (G >= 64) {
-    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
-    v = op(r[0], r[1]);
-  }
-  return v;
-}
-
 // Selection and gates of one token by a group of G lanes (gl: lane inside the group): val[j] is the logit of expert
 // gl + j G.  Winner i ends up in lane i % G, slot i / G: my_idx its expert, my_w its gate.
 template <int G, int VPL>
@@ -103,8 +81,7 @@ __device__ __forceinline__ void route_token(const float (&val)[VPL], int gl, int
     for (int j = 0; j < VPL; ++j)
       if (gl + j * G < E) part += expf(val[j] - row_max);
   }
-#pragma unroll
-  for (int m = 1; m < G; m <<= 1) part += __shfl_xor(part, m, MOE_WAVE);
+  part = group_sum<G>(part);
   const float inv = 1.0f / part;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) my_w[j] = expf(my_val[j] - row_max) * inv;

@@ -171,16 +171,14 @@ __global__ __launch_bounds__(256) void route_bwd_kernel(const float* __restrict_
     m = fmaxf(m, val[j]);
     if (e < E) dp[e] = 0.f;
   }
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) m = fmaxf(m, __shfl_xor(m, s, MOE_WAVE));
+  m = group_max<G>(m);
   float p[VPL], sum = 0.f;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) {
     p[j] = gl + j * G < E ? expf(val[j] - m) : 0.f;
     sum += p[j];
   }
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) sum += __shfl_xor(sum, s, MOE_WAVE);
+  sum = group_sum<G>(sum);
   const float inv = 1.0f / sum;
 #pragma unroll
   for (int j = 0; j < VPL; ++j) p[j] *= inv;
@@ -193,8 +191,8 @@ __global__ __launch_bounds__(256) void route_bwd_kernel(const float* __restrict_
     S += s_i;
     dot += dgate[static_cast<size_t>(tt) * k + i] * s_i;
   }
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) { S += __shfl_xor(S, s, MOE_WAVE); dot += __shfl_xor(dot, s, MOE_WAVE); }
+  S = group_sum<G>(S);
+  dot = group_sum<G>(dot);
   // renormalised: w_i = s_i / S, dL/ds_i = (dgate_i - sum_j dgate_j w_j) / S ; otherwise dL/ds_i = dgate_i
   const float invS = renormalize ? 1.0f / S : 1.0f;
   const float shift = renormalize ? dot * invS : 0.f;
@@ -207,8 +205,7 @@ __global__ __launch_bounds__(256) void route_bwd_kernel(const float* __restrict_
     dp[e] = ds;                          // a token's experts are distinct
     c += ds * s_i;
   }
-#pragma unroll
-  for (int s = 1; s < G; s <<= 1) c += __shfl_xor(c, s, MOE_WAVE);
+  c = group_sum<G>(c);
   __syncthreads();
   if (live) {
 #pragma unroll
@@ -533,7 +530,18 @@ __global__ __launch_bounds__(256) void router_bwd_dw_reduce_kernel(const float* 
   const size_t i = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
   if (i >= n) return;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  for (int c = 0; c < chunks; ++c) s += *reinterpret_cast<const f32x4*>(part + static_cast<size_t>(c) * n + i);
+  // in chunk order, sixteen loads in flight (104 chunks of 48 experts, d 320: 28.8 us one after the other, 11.8 us so; 71 chunks of 99
+  // experts, d 2240: 24.7 and 14.1)
+  constexpr int BATCH = 16;
+  for (int c0 = 0; c0 < chunks; c0 += BATCH) {
+    f32x4 v[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) v[u] = *reinterpret_cast<const f32x4*>(part + static_cast<size_t>(min(c0 + u, chunks - 1)) * n + i);
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      if (c0 + u < chunks) s += v[u];
+    }
+  }
   *reinterpret_cast<f32x4*>(dWr + i) = s;
 }
 
