@@ -14,7 +14,7 @@
 //           table that stays in L2 instead of by a kernel of its own.  It then recounts its pairs,
 //           derives each wave's first row per expert, and ranks pairs inside a batch by the
 //           popcount of the lower lanes that chose the same expert -> slot_row, row_token.
-//   rows    one wave per token copies x[t] to its (up to k) grouped rows with
+//   rows    a wave copies 64 or 256 pieces of x[t] to the token's (up to k) grouped rows with
 //           16-byte accesses: x is read once, xp is written in full rows.
 #include "perm_common.h"
 
