@@ -7,17 +7,25 @@
 // rows (a token's experts are distinct, so no expert has more rows than there are tokens).  A rank's share may hold the
 // large experts: where R_cap allows more rows and only the expected number is small, both kernels are launched and look
 // at the number of rows on the device; the one that it is not for ends at once.
-// Forward pass, tiled / streaming, in us, other weights in every pass:
+// Forward pass, tiled / streaming, in us, other weights in every pass (the tiled side picks its tile size; both sides' results
+// have the same bits):
 //                                             rows per expert  even load    zipf load
-//   d 2048, f 1024, 64 experts, 8 per token           4          182 / 167    164 / 130
-//                                                     8          184 / 172    171 / 161
-//                                                    10          186 / 186    174 / 178
-//   d 1088, f 576, 96 experts, 4 per token            8          106 /  89     80 /  75
-//   d 512, f 256, 128 experts, 8 per token            8           57 /  52     57 /  51
-//   d 1024, f 512, 128 experts, 2 per token           6          109 /  95     70 /  63
-//   d 2048, f 1024, 64 experts, 1 per token           6          169 / 159     95 / 101
-//   d 2048, f 1024, the 20 of 240 experts that zipf makes the largest, 8 per token: 32 tokens 93 / 81; the same weights in
-//   every pass: 32 tokens 67 / 67, 48 tokens 70 / 83, 128 tokens 78 / 134
+//   d 2048, f 1024, 64 experts, 8 per token           1/8         59 /  33     58 /  32
+//                                                     4          173 / 173    141 / 130
+//                                                     6          189 / 186    156 / 152
+//                                                     8          179 / 179    160 / 170
+//                                                    10          160 / 179    150 / 174
+//   d 1088, f 576, 96 experts, 4 per token            3           88 /  81     54 /  43
+//                                                     8           94 /  90     71 /  78
+//                                                    12           95 /  96     84 /  92
+//   d 512, f 256, 128 experts, 8 per token            2           34 /  34     32 /  26
+//                                                     8           47 /  49     45 /  43
+//                                                    12           42 /  47     42 /  44
+//   d 1024, f 512, 128 experts, 2 per token           6           97 /  96     59 /  59
+//   d 2048, f 1024, 64 experts, 1 per token           6          160 / 164     93 / 108
+//   d 2048, f 1024, the 20 of 240 experts that zipf makes the largest, 8 per token: 32 tokens 67 / 52 and 80 / 77
+// At 6 to 8 rows per expert the order changes with load and shape (tiles up to 16 %, streaming up to 6 % ahead), by nothing known
+// on the host; from 10 on the tiles are ahead.
 constexpr int STREAM_ROWS = 8, STREAM_TOKENS = 32;
 
 // One grouped product out[r] = act[r] . W[e]^T (weights [N][K], K contiguous), or the pair gate/up with the
