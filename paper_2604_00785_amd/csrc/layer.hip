@@ -4,6 +4,20 @@
 // whole layer, from which the expected number of local rows follows, and of tokens, which no expert's rows exceed.
 #include "gemm.h"
 
+namespace {
+bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t p = reinterpret_cast<uintptr_t>(a), q = reinterpret_cast<uintptr_t>(b);
+  return p < q + b_bytes && q < p + a_bytes;
+}
+// Whether the combine and its backward may be one kernel: not where the forward pass writes what the backward reads (the gradient of
+// half the squared output is the output itself) or writes again.
+bool combine_in_one(const moe_layer* L) {
+  const size_t row = static_cast<size_t>(L->d) * sizeof(moe_bf16), out = L->T * row;
+  return !overlap(L->out, out, L->dout, out) && !overlap(L->out, out, L->dyp, out * L->k) &&
+         !overlap(L->out, out, L->dgate, static_cast<size_t>(L->T) * L->k * sizeof(float));
+}
+}  // namespace
+
 extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
   if (!L || (what & ~(MOE_LAYER_ROUTER | MOE_LAYER_FWD | MOE_LAYER_BWD | MOE_LAYER_ROUTER_BWD))) return MOE_ERR_INVALID;
   if (L->path < MOE_LAYER_PLAIN || L->path > MOE_LAYER_FOLD) return MOE_ERR_INVALID;
@@ -13,6 +27,7 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
   const long long rows = (static_cast<long long>(R_cap) * nl + E - 1) / E;
   const bool fold = L->path == MOE_LAYER_FOLD, plain = L->path == MOE_LAYER_PLAIN;
   const bool sparse = 2ll * nl <= E;   // few of a token's slots have a local row
+  const bool both = !fold && (what & MOE_LAYER_FWD) && (what & MOE_LAYER_BWD) && combine_in_one(L);
   int rc = MOE_OK;
   if (what & MOE_LAYER_ROUTER) {
     if ((rc = moe_router_fwd(L->x, L->Wr, T, d, E, L->logits, stream)) != MOE_OK) return rc;
@@ -32,11 +47,9 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if (rc != MOE_OK) return rc;
     // with the backward in the same call the rows of yp are read once, for both
     if (!fold && !L->topk_w) return MOE_ERR_INVALID;
-    if (sparse && (fold || !(what & MOE_LAYER_BWD)))
-      rc = moe_combine_sparse(L->yp, L->slot_row, fold ? nullptr : L->topk_w, T, k, d, L->out, "combine", stream);
+    if (both) rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
+    else if (sparse) rc = moe_combine_sparse(L->yp, L->slot_row, fold ? nullptr : L->topk_w, T, k, d, L->out, "combine", stream);
     else if (fold) rc = moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream);
-    else if (what & MOE_LAYER_BWD)
-      rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
     else rc = moe_unpermute_combine(L->yp, L->slot_row, L->topk_w, T, k, d, L->out, stream);
     if (rc != MOE_OK) return rc;
   }
@@ -49,7 +62,7 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
                                L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd,
                                adds_dgate ? nullptr : L->dgate, L->ws, L->ws_bytes, stream);
     } else {
-      if (!(what & MOE_LAYER_FWD)) rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
+      if (!both) rc = moe_unpermute_combine_bwd(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->dyp, L->dgate, stream);
       if (rc != MOE_OK) return rc;
       rc = moe_gemm_bwd(L->dyp, plain ? L->xp : L->x, T, plain ? nullptr : L->row_token, L->g, L->u, L->h, L->expert_offsets,
                         L->Wg, L->Wu, L->Wd, nl, R_cap, rows, d, f, L->dxp, L->dWg, L->dWu, L->dWd, L->ws, L->ws_bytes, stream);

@@ -186,3 +186,23 @@ def test_both_passes_in_one_call(path, T, d, E, k, eb, ec):
     assert bool(torch.isfinite(out.float()).all()) and bool(torch.isfinite(dgate).all())
     assert torch.equal(one.out, out) and torch.equal(one.dgate, dgate) and torch.equal(one.dx, dx)
     assert torch.equal(one.dWd, two.dWd)
+
+
+# A loss of half the squared output: the gradient handed in is the output buffer itself, read by the backward after the forward pass
+# of the same call has written it (rows of one to five groups of 64 pieces, few and many tokens)
+@pytest.mark.parametrize("T,d", [(600, 320), (40, 1088), (700, 2112)])
+@pytest.mark.parametrize("path", ["plain", "gather", "fold"])
+def test_the_output_as_its_own_gradient(path, T, d):
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(T + d)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda:0")
+    E, k, f = 9, 4, 64
+    x, logits = r(T, d).bfloat16(), r(T, E)
+    w = [r(E, *s).mul_(0.05).bfloat16() for s in ((f, d), (f, d), (d, f))]
+    one, two = (B.MoELayerBuffers(T, d, E, k, f, gather=path == "gather", fold=path == "fold") for _ in range(2))
+    one.out.fill_(7.0)                       # what an earlier pass may have left there
+    one.run_fwd_bwd(x, logits, one.out, *w)
+    two.run_fwd(x, logits, *w)
+    two.run_bwd(two.out, *w)
+    for n in ("out", "dx", "dgate", "dWg", "dWu", "dWd"):
+        assert torch.equal(getattr(one, n), getattr(two, n)), n
