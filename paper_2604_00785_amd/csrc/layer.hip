@@ -10,8 +10,11 @@ bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   return p < q + b_bytes && q < p + a_bytes;
 }
 // Whether the combine and its backward may be one kernel: not where the forward pass writes what the backward reads (the gradient of
-// half the squared output is the output itself) or writes again.
+// half the squared output is the output itself) or writes again, and not where the backward will be refused and the forward pass
+// is to be complete nevertheless.
 bool combine_in_one(const moe_layer* L) {
+  for (const void* p : {static_cast<const void*>(L->dout), static_cast<const void*>(L->dyp), static_cast<const void*>(L->dgate)})
+    if (!p || !moe_aligned16(p)) return false;
   const size_t row = static_cast<size_t>(L->d) * sizeof(moe_bf16), out = L->T * row;
   return !overlap(L->out, out, L->dout, out) && !overlap(L->out, out, L->dyp, out * L->k) &&
          !overlap(L->out, out, L->dgate, static_cast<size_t>(L->T) * L->k * sizeof(float));

@@ -1,5 +1,7 @@
 """The layer's own buffers, checked once and written down for the native call: a buffer that is replaced, resized or taken
 away afterwards counts as it would have at the first call."""
+import struct
+
 import pytest
 import torch
 
@@ -206,3 +208,31 @@ def test_the_output_as_its_own_gradient(path, T, d):
     two.run_bwd(two.out, *w)
     for n in ("out", "dx", "dgate", "dWg", "dWu", "dWd"):
         assert torch.equal(getattr(one, n), getattr(two, n)), n
+
+
+# Both passes in one call, a buffer that only the backward uses missing or misaligned: the call is refused, and the forward pass in
+# front of it is complete (few and more than 64 slots)
+@pytest.mark.parametrize("name", ["dout", "dyp", "dgate", "dxp", "dWd"])
+@pytest.mark.parametrize("value", [0, 4])
+@pytest.mark.parametrize("path,T,E,k", [("plain", 300, 9, 4), ("gather", 300, 9, 4), ("gather", 20, 90, 70), ("fold", 300, 9, 4)])
+def test_a_refused_backward_leaves_the_forward_pass(path, T, E, k, name, value):
+    if path == "fold" and name == "dyp":
+        return                                      # not used there
+    L, d, f = B.MoELayerBuffers, 1088, 64
+    gen = torch.Generator(device="cuda:0")
+    gen.manual_seed(T + k)
+    r = lambda *s: torch.randn(*s, generator=gen, device="cuda:0")
+    x, dout, logits = r(T, d).bfloat16(), r(T, d).bfloat16(), r(T, E)
+    w = [r(E, *s).mul_(0.05).bfloat16() for s in ((f, d), (f, d), (d, f))]
+    m = L(T, d, E, k, f, gather=path == "gather", fold=path == "fold")
+    m.run_fwd(x, logits, *w)
+    want = m.out.clone()
+    m.run_fwd_bwd(x, logits, dout, *w)
+    blob, at = m._plans[L._FWD + L._BWD][:2]
+    place = L._SIZES.size + (8 if name == "dout" else L._ARGS.size + 8 * L._ORDER.index(name))
+    pointer = struct.unpack_from("=Q", blob, place)[0]
+    struct.pack_into("=Q", blob, place, pointer + value if value else 0)
+    m.out.fill_(7.0)
+    assert B.load().moe_layer_run(at, L._FWD + L._BWD, B._stream()) == -1
+    torch.cuda.synchronize()
+    assert torch.equal(m.out, want)
