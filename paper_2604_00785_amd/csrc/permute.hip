@@ -16,6 +16,7 @@
 //           popcount of the lower lanes that chose the same expert -> slot_row, row_token.
 //   rows    a wave copies 64 or 256 pieces of x[t] to the token's (up to k) grouped rows with
 //           16-byte accesses: x is read once, xp is written in full rows.
+#include <algorithm>
 #include "perm_common.h"
 
 namespace {
@@ -193,7 +194,8 @@ __global__ __launch_bounds__(PERM_THREADS) void permute_place_kernel(const int32
   }
 }
 
-// xp[slot_row[t,i]] = x[t] for every local slot.  A wave owns 64 VPT pieces of a token's row; lane i holds slot i's row.
+// xp[slot_row[t,i]] = x[t] for every local slot.  A wave owns 64 VPT pieces of a token's row (of every gridDim.y-th such part);
+// lane i holds slot i's row.
 template <int VPT>
 __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restrict__ x, const int32_t* __restrict__ slot_row,
                                                            int T, int k, int chunks /* d/8 */, uint4* __restrict__ xp) {
@@ -201,24 +203,25 @@ __global__ __launch_bounds__(256) void permute_rows_kernel(const uint4* __restri
   const int t = blockIdx.x * (256 / MOE_WAVE) + threadIdx.x / MOE_WAVE;
   if (t >= T) return;
   const uint4* src = x + static_cast<size_t>(t) * chunks;
-  const int c0 = blockIdx.y * (MOE_WAVE * VPT);
-  uint4 v[VPT];
+  for (int c0 = blockIdx.y * (MOE_WAVE * VPT); c0 < chunks; c0 += gridDim.y * (MOE_WAVE * VPT)) {
+    uint4 v[VPT];
 #pragma unroll
-  for (int j = 0; j < VPT; ++j) {
-    const int c = c0 + j * MOE_WAVE + lane;
-    v[j] = c < chunks ? src[c] : make_uint4(0, 0, 0, 0);
-  }
-  for (int i0 = 0; i0 < k; i0 += MOE_WAVE) {
-    const int kk = min(k - i0, MOE_WAVE);
-    const int my_row = lane < kk ? slot_row[static_cast<size_t>(t) * k + i0 + lane] : -1;
-    for (int i = 0; i < kk; ++i) {
-      const int row = wave_lane(my_row, i);
-      if (row < 0) continue;
-      uint4* dst = xp + static_cast<size_t>(row) * chunks;
+    for (int j = 0; j < VPT; ++j) {
+      const int c = c0 + j * MOE_WAVE + lane;
+      v[j] = c < chunks ? src[c] : make_uint4(0, 0, 0, 0);
+    }
+    for (int i0 = 0; i0 < k; i0 += MOE_WAVE) {
+      const int kk = min(k - i0, MOE_WAVE);
+      const int my_row = lane < kk ? slot_row[static_cast<size_t>(t) * k + i0 + lane] : -1;
+      for (int i = 0; i < kk; ++i) {
+        const int row = wave_lane(my_row, i);
+        if (row < 0) continue;
+        uint4* dst = xp + static_cast<size_t>(row) * chunks;
 #pragma unroll
-      for (int j = 0; j < VPT; ++j) {
-        const int c = c0 + j * MOE_WAVE + lane;
-        if (c < chunks) dst[c] = v[j];
+        for (int j = 0; j < VPT; ++j) {
+          const int c = c0 + j * MOE_WAVE + lane;
+          if (c < chunks) dst[c] = v[j];
+        }
       }
     }
   }
@@ -249,10 +252,12 @@ void launch_rows(const moe_bf16* x, const int32_t* slot_row, int T, int d, int k
   // Few rows wait for latency, many want long runs of a row.  Us, 1 / 2 / 4 pieces per lane, 8 slots per token: d 2048, 48 tokens
   // 3.1 / 3.2 / 3.6, 2048 tokens 15.4 / 17.4 / 14.8, 8192 tokens 84 / 83 / 61; d 1024, 8192 tokens 30.3 / 27.6 / 27.6; d 256 all the same.
   // (19 tokens of d 2688 took 9.0 us with 4 pieces and one dependent load of a slot's row per slot.)
+  // A grid has at most 65535 parts along y; the waves go on from there.
+  const auto grid = [&](int pieces) { return dim3((T + 3) / 4, std::min((chunks + pieces - 1) / pieces, 65535)); };
   if (chunks > 128 && static_cast<long long>(T) * k * d * 2 >= (48 << 20))
-    MOE_LAUNCH("permute_rows", permute_rows_kernel<4>, dim3((T + 3) / 4, (chunks + 255) / 256), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
+    MOE_LAUNCH("permute_rows", permute_rows_kernel<4>, grid(256), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
   else
-    MOE_LAUNCH("permute_rows", permute_rows_kernel<2>, dim3((T + 3) / 4, (chunks + 127) / 128), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
+    MOE_LAUNCH("permute_rows", permute_rows_kernel<2>, grid(128), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
 }
 
 int check_permute_args(const moe_bf16* x, const int32_t* topk_idx, int T, int d, int E_total, int k, int e_begin,

@@ -204,6 +204,20 @@ def test_permute_then_combine_is_identity():
     assert torch.equal(buf.out.view(torch.int16), x.view(torch.int16))
 
 
+def test_permute_rows_longer_than_a_grid():
+    """One row of more parts of 256 pieces (of 16 bytes) than a grid may have along y (65535)."""
+    d = (65535 * 256 + 70) * 8
+    print(f"permute rows d={d}", flush=True)
+    x = torch.randint(-30000, 30000, (1, d), dtype=torch.int16, device=DEV).view(torch.bfloat16)
+    xp = torch.zeros(1, d, dtype=torch.bfloat16, device=DEV)
+    z = lambda *s: torch.zeros(*s, dtype=torch.int32, device=DEV)
+    off, tok, slot = z(2), z(1), z(1, 1)
+    ws = torch.zeros(B.moe_permute_workspace_bytes(1, 1, 1), dtype=torch.uint8, device=DEV)
+    B.moe_permute(x, z(1, 1), 1, 0, 1, off, tok, slot, xp, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(xp.view(torch.int16), x.view(torch.int16))
+
+
 # ----------------------------------------------------------------------------- grouped GEMMs, isolated
 @pytest.mark.parametrize("counts,d,f", [
     ([64, 64, 64, 64], 128, 256),                 # whole tiles only partly filled
