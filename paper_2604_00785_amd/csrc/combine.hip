@@ -6,6 +6,7 @@
 // are few: every load and store is a full, coalesced row segment, the k source rows are
 // summed in slot order in fp32, and the token's own row (out / dout) is touched
 // exactly once.  No atomics, so results are reproducible.
+#include <type_traits>
 #include "gemm.h"
 
 namespace {
@@ -201,43 +202,43 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restric
       my_row = slot_row[static_cast<size_t>(t) * k + i0 + lane];
       my_w = topk_w[static_cast<size_t>(t) * k + i0 + lane];
     }
-    for (int c0 = 0; c0 < chunks; c0 += MOE_WAVE * VPT) {
+    const uint64_t live = __ballot(my_row >= 0);
+    // WHOLE: every lane has all of its pieces.  A row's ragged end is loaded under a mask: lanes that repeat its last piece would cost
+    // as much as lanes that have one (d 768, 16384 tokens of 1 slot 18.8 / 14.3 us).
+    auto part = [&](int c0, auto whole_tag) __attribute__((always_inline)) {
+      constexpr bool WHOLE = decltype(whole_tag)::value;
       uint4 gv[VPT];
-      int piece[VPT];
+      bool has[VPT];
       float acc[OUT ? VPT : 1][8];
 #pragma unroll
       for (int j = 0; j < VPT; ++j) {
-        const int c = c0 + j * MOE_WAVE + lane;
-        piece[j] = min(c, chunks - 1);
-        gv[j] = c < chunks ? g[c] : make_uint4(0, 0, 0, 0);
+        has[j] = WHOLE || c0 + j * MOE_WAVE + lane < chunks;
+        gv[j] = has[j] ? g[c0 + j * MOE_WAVE + lane] : make_uint4(0, 0, 0, 0);
         if constexpr (OUT) {
 #pragma unroll
           for (int q = 0; q < 8; ++q) acc[j][q] = 0.f;
         }
       }
-      uint64_t mask = __ballot(my_row >= 0);
+      uint64_t mask = live;
       while (mask != 0) {
         const SlotGroup<SLOTS> sg(mask, my_row);
         uint4 yv[SLOTS][VPT];
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s)
 #pragma unroll
-          for (int j = 0; j < VPT; ++j) {
-            yv[s][j] = nt_load(yp + static_cast<size_t>(sg.row[s]) * chunks + piece[j]);
-            if (c0 + j * MOE_WAVE + lane >= chunks) yv[s][j] = make_uint4(0, 0, 0, 0);
-          }
+          for (int j = 0; j < VPT; ++j)
+            yv[s][j] = has[j] ? nt_load(yp + static_cast<size_t>(sg.row[s]) * chunks + c0 + j * MOE_WAVE + lane) : make_uint4(0, 0, 0, 0);
         float dot[SLOTS];
 #pragma unroll
         for (int s = 0; s < SLOTS; ++s) {
           dot[s] = 0.f;
           if (sg.live[s]) {
             const float w = __int_as_float(wave_lane(__float_as_int(my_w), sg.lane[s]));
-            uint4* dy = dyp + static_cast<size_t>(sg.row[s]) * chunks;
+            uint4* dy = dyp + static_cast<size_t>(sg.row[s]) * chunks + c0 + lane;
 #pragma unroll
             for (int j = 0; j < VPT; ++j) {
-              const int c = c0 + j * MOE_WAVE + lane;
               dot[s] += dot8(yv[s][j], gv[j]);
-              if (c < chunks) dy[c] = scale8(gv[j], w);
+              if (has[j]) dy[j * MOE_WAVE] = scale8(gv[j], w);
               if constexpr (OUT) fma8(acc[j], yv[s][j], w);
             }
           }
@@ -249,14 +250,15 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restric
         }
       }
       if constexpr (OUT) {       // k <= 64: the only pass over the slots
-        uint4* o = out + static_cast<size_t>(t) * chunks;
+        uint4* o = out + static_cast<size_t>(t) * chunks + c0 + lane;
 #pragma unroll
-        for (int j = 0; j < VPT; ++j) {
-          const int c = c0 + j * MOE_WAVE + lane;
-          if (c < chunks) o[c] = pack8(acc[j]);
-        }
+        for (int j = 0; j < VPT; ++j)
+          if (has[j]) o[j * MOE_WAVE] = pack8(acc[j]);
       }
-    }
+    };
+    int c0 = 0;
+    for (; c0 + MOE_WAVE * VPT <= chunks; c0 += MOE_WAVE * VPT) part(c0, std::true_type{});
+    if (c0 < chunks) part(c0, std::false_type{});
     if (lane < kk) dgate[static_cast<size_t>(t) * k + i0 + lane] = my_dot;
   }
 }
@@ -266,10 +268,16 @@ __global__ __launch_bounds__(256) void combine_bwd_kernel(const uint4* __restric
              chunks, o, part, strips, dgate)
 #define COMBINE_PAIRS(VPT) \
   MOE_LAUNCH(name, (combine_pairs_kernel<VPT, WEIGHTED>), dim3((T + 3) / 4), dim3(256), 0, s, a, slot_row, w, T, k, chunks, o)
-// A pass over so few bytes of rows waits for latency: a wave for every 64 pieces, four slots at a time.  Passes over more want long
-// runs of a row.  Whole kernel, us, (4 pieces per lane, 2 slots, in one wave) / (1, 4), 8 slots per token, rows not in the caches:
-//   d 2048:  1 token 4.0 / 2.8   48 tokens 6.4 / 4.0   1024 9.8 / 8.0   2048 14.6 / 14.2   8192 53.2 / 68.6
-//   d 4096:  1 token 4.4 / 3.2   48 tokens 7.0 / 4.7   1024 14.6 / 14.5   4096 53.3 / 64.4
+// A pass over so few bytes of rows is bound by latency or by loads in flight, not by the rate of memory.  With few waves: one for every
+// 64 pieces, four slots at a time.  With more of them, fewer slots or rows of several pieces per lane: one for every 128 pieces, two
+// slots at a time, since what a wave loads for slots that are not there (it repeats the first) then counts, and the waves alone keep
+// enough in flight.  Whole kernel, us, (pairs of slots, all of a row in one wave) / (1 piece per lane, 4 slots) / (2, 2):
+//   8 slots  d 2048:  40 tokens  6.1 / 4.2 / 5.5   1000 tokens   9.7 /  8.2 /  9.1   2048 (more than 48 MB) 15.1 / 16.3 / 14.9
+//   6 slots  d 1536:  40 tokens  4.3 / 3.2 / 3.7   1000 tokens   6.7 /  6.1 /  7.0   2048  9.4 / 10.0 /  9.1
+//   2 slots  d 2048:  40 tokens  3.4 / 2.8 / 2.9   1000 tokens   4.5 /  4.7 /  4.4   2048  6.9 /  7.5 /  6.4   4096 10.8 / 13.1 / 11.0
+//   2 slots  d 768:                                1000 tokens   3.4 /  3.5 /  3.6   8192  8.4 / 10.8 /  8.4
+//   1 slot   d 2048:  40 tokens  3.2 / 2.7 / 2.7   1000 tokens   3.9 /  3.9 /  3.6   8192 15.5 / 18.1 / 14.4
+// (393 sizes, 1 to 8 slots, d 128 to 4096: the form chosen is at most 2.4 % behind the pairs and on average 8 % ahead of them.)
 bool few_bytes(int T, int k, int d) { return static_cast<long long>(T) * k * d * 2 < (48 << 20); }
 
 // sparse: most slots are expected to have no local row.  They are left out beforehand there: 24576 tokens of d 3072, 8 slots, one of
@@ -280,12 +288,16 @@ int launch_combine(const moe_bf16* src, const int32_t* slot_row, const float* w,
   const int chunks = d / 8;
   const uint4* a = reinterpret_cast<const uint4*>(src);
   uint4* o = reinterpret_cast<uint4*>(out);
+  const bool few = few_bytes(T, k, d);
+  const long long waves = static_cast<long long>(T) * ((chunks + 63) / 64), long_rows = (chunks + 255) / 256;
   if (part != nullptr) {
     if constexpr (!WEIGHTED) { if (chunks <= 64) COMBINE(1, 2, true, 1); else COMBINE(1, 4, true, (chunks + 63) / 64); }
   } else if (chunks <= 64) {
     COMBINE_PAIRS(1);
-  } else if (few_bytes(T, k, d)) {
+  } else if (few && waves <= (k > 2 ? 4096 : 1536) * long_rows) {
     COMBINE(1, 4, false, (chunks + 63) / 64);
+  } else if (few && (sparse || k == 1 || (chunks > 128 && waves <= 8192 * long_rows))) {
+    COMBINE(2, 2, false, (chunks + 127) / 128);
   } else if (chunks <= 128) {
     COMBINE_PAIRS(2);
   } else if (sparse) {
@@ -309,13 +321,19 @@ int launch_combine_bwd(const moe_bf16* dout, const moe_bf16* yp, const int32_t* 
   const uint4* y = reinterpret_cast<const uint4*>(yp);
   uint4* o = reinterpret_cast<uint4*>(dyp);
   uint4* ov = reinterpret_cast<uint4*>(out);
-  // Whole kernel, us, before (one slot at a time, the reductions through LDS) / now: d 256, 2048 tokens 10.6 / 6.8; d 2048, 48 tokens
-  // 10.0 / 7.1, 8192 tokens 107 / 106; d 4096, 48 tokens 20.1 / 13.4.  combine and combine_bwd apart / in one (OUT): d 2048, 48 tokens
-  // 10.6 / 8.2 and a launch, 8192 tokens 158 / 119; d 1024, 24576 tokens of 2 slots 65 / 47.
-  if (chunks <= 64) COMBINE_BWD(1, 4, OUT);
-  else if (T <= 512) { if (chunks <= 128) COMBINE_BWD(2, 4, OUT); else COMBINE_BWD(4, 4, OUT); }
-  else if (chunks <= 128) COMBINE_BWD(2, 2, OUT);
-  else COMBINE_BWD(4, 2, OUT);
+  // Slots in flight.  What is loaded for slots that are not there costs as much as for those that are, and rows of several pieces per
+  // lane and many waves keep enough in flight by themselves.  combine_bwd, us, 1 / 2 / 4 slots in flight:
+  //   1 slot   d 512, 40 tokens 2.7 / 2.7 / 2.9   d 320, 16384 tokens  8.4 /  8.7 / 10.0   d 2560,  4096 tokens 11.6 / 11.6 / 14.1
+  //   2 slots  d 512, 40 tokens 2.8 / 2.8 / 3.0   d 320, 16384 tokens 11.4 / 11.0 / 12.3   d  768,  8192 tokens 11.4 / 12.8 / 14.3
+  //   3 slots                                     d 128, 32768 tokens 21.4 / 20.1 / 19.4   d  768, 16384 tokens 30.5 / 31.5 / 32.7
+  //   8 slots  d 512, 40 tokens 4.0 / 4.1 / 4.0   d 128, 32768 tokens 43.0 / 34.5 / 33.1   d 2048,  8192 tokens  103 /  103 /  103
+  // Before (one slot at a time, the reductions through LDS): 3.0, 8.8, 11.9; 3.4, 12.2, 11.8; 23.3, 30.7; 6.3, 48.2, 106 for these.
+  // combine and combine_bwd apart / in one (OUT): d 2048, 48 tokens 10.6 / 8.2 and a launch, 8192 tokens 158 / 119; d 1024, 24576
+  // tokens of 2 slots 65 / 47.
+  const int slots = k == 1 || (k < 4 && chunks > 64 && T > 2048) ? 1 : k == 2 || (chunks > 64 && T > 512) ? 2 : 4;
+  if (chunks <= 64) { if (slots == 1) COMBINE_BWD(1, 1, OUT); else if (slots == 2) COMBINE_BWD(1, 2, OUT); else COMBINE_BWD(1, 4, OUT); }
+  else if (chunks <= 128) { if (slots == 1) COMBINE_BWD(2, 1, OUT); else if (slots == 2) COMBINE_BWD(2, 2, OUT); else COMBINE_BWD(2, 4, OUT); }
+  else { if (slots == 1) COMBINE_BWD(4, 1, OUT); else if (slots == 2) COMBINE_BWD(4, 2, OUT); else COMBINE_BWD(4, 4, OUT); }
   return moe_check_launch();
 }
 #undef COMBINE_BWD

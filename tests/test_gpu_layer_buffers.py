@@ -153,11 +153,12 @@ def test_one_call_equals_the_stage_calls(path, T, d, E, k, f, eb, ec, hot):
 
 # The forward pass's combine and its backward in one kernel (run_fwd_bwd) against the two of run_fwd and run_bwd, and the gate
 # gradient added up by the backward of the gather against the kernel of its own: rows of one to five groups of 64 pieces with
-# a remainder, both sides of the rules on tokens (512), bytes of rows (48 MB) and the share of local experts (a half), more slots
-# than lanes
+# a remainder, both sides of the rules on tokens (512, 2048), slots, bytes of rows (48 MB) and the share of local experts (a half),
+# more slots than lanes
 @pytest.mark.parametrize("T,d,E,k,eb,ec", [
     (513, 320, 12, 5, 0, 12), (40, 576, 12, 5, 3, 6), (600, 1088, 9, 3, 0, 9), (512, 1088, 9, 8, 0, 9), (33, 2112, 9, 1, 2, 4),
-    (3100, 2112, 9, 4, 0, 9), (6000, 2112, 9, 4, 2, 3), (700, 2624, 9, 7, 0, 9), (20, 64, 90, 70, 5, 80)])
+    (3100, 2112, 9, 4, 0, 9), (6000, 2112, 9, 4, 2, 3), (700, 2624, 9, 7, 0, 9), (20, 64, 90, 70, 5, 80),
+    (2049, 576, 9, 1, 0, 9), (2049, 1088, 9, 2, 0, 9), (600, 1088, 9, 2, 0, 9), (600, 320, 9, 2, 0, 9)])
 @pytest.mark.parametrize("path", ["plain", "gather", "fold"])
 def test_both_passes_in_one_call(path, T, d, E, k, eb, ec):
     gen = torch.Generator(device="cuda:0")

@@ -190,6 +190,17 @@ def test_combine_and_backward(T, E, k, d, eb, ec):
     H.assert_close(dgate.cpu().numpy().astype(np.float64), rdgate, "dgate", 1e-4)
 
 
+# one to five slots, tokens and widths on both sides of the rules for the pieces per lane and the slots in flight; rows that end
+# inside a part of 64 pieces, at one, and in a last part of few
+@pytest.mark.parametrize("T,E,k,d,eb,ec", [
+    (700, 6, 1, 576, 0, 6), (1537, 6, 1, 1088, 0, 6), (2049, 6, 1, 72, 0, 6),       # one slot: 1 and 2 pieces per lane, short rows
+    (700, 6, 2, 576, 0, 6), (2049, 6, 2, 576, 1, 5), (2049, 9, 2, 1096, 0, 9), (40, 6, 2, 264, 2, 3),
+    (2049, 6, 3, 520, 0, 6), (900, 6, 3, 2056, 0, 6), (600, 9, 5, 1032, 0, 9), (2100, 9, 4, 1536, 2, 6),
+])
+def test_combine_forms(T, E, k, d, eb, ec):
+    test_combine_and_backward(T, E, k, d, eb, ec)
+
+
 def test_permute_then_combine_is_identity():
     T, E, k, d = 512, 16, 4, 512
     rng = np.random.default_rng(9)
