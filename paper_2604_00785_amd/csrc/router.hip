@@ -525,14 +525,15 @@ __global__ __launch_bounds__(256) void router_bwd_dw_partial_kernel(const float*
   }
 }
 
+// In chunk order, BATCH loads in flight, the last batch filled up with the last chunk.  Us, one after the other / 16: 104 chunks of 48
+// experts, d 320 28.8 / 11.8; 71 chunks of 99 experts, d 2240 24.7 / 14.1.  Where there are no 16 chunks the repeated loads cost
+// more than they save (the whole router backward of 256 tokens, d 4096, 240 experts, one chunk: 36.3 / 38.2).
+template <int BATCH>
 __global__ __launch_bounds__(256) void router_bwd_dw_reduce_kernel(const float* __restrict__ part, int chunks,
                                                                    size_t n, float* __restrict__ dWr) {
   const size_t i = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
   if (i >= n) return;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  // in chunk order, sixteen loads in flight (104 chunks of 48 experts, d 320: 28.8 us one after the other, 11.8 us so; 71 chunks of 99
-  // experts, d 2240: 24.7 and 14.1)
-  constexpr int BATCH = 16;
   for (int c0 = 0; c0 < chunks; c0 += BATCH) {
     f32x4 v[BATCH];
 #pragma unroll
@@ -605,8 +606,10 @@ extern "C" int moe_router_bwd(const moe_bf16* x, const float* Wr, const float* d
   {
     const size_t n = static_cast<size_t>(E) * d;
     dim3 grid(static_cast<unsigned>((n / 4 + 255) / 256)), block(256);
-    MOE_LAUNCH("router_bwd_dw_reduce", router_bwd_dw_reduce_kernel, grid, block, 0, s, static_cast<const float*>(ws),
-               chunks, n, dWr);
+    const float* part = static_cast<const float*>(ws);
+    if (chunks == 1) MOE_LAUNCH("router_bwd_dw_reduce", router_bwd_dw_reduce_kernel<1>, grid, block, 0, s, part, chunks, n, dWr);
+    else if (chunks <= 4) MOE_LAUNCH("router_bwd_dw_reduce", router_bwd_dw_reduce_kernel<4>, grid, block, 0, s, part, chunks, n, dWr);
+    else MOE_LAUNCH("router_bwd_dw_reduce", router_bwd_dw_reduce_kernel<16>, grid, block, 0, s, part, chunks, n, dWr);
   }
   return moe_check_launch();
 }

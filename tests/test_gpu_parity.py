@@ -480,6 +480,12 @@ def test_router_bwd(T, d, E):
     assert torch.equal(dWr, dWr2)
 
 
+# 1, 4, 5, 16 and 18 chunks of tokens: the batches in which their partial sums of dWr are added
+@pytest.mark.parametrize("T", [256, 1024, 1025, 4096, 4400])
+def test_router_bwd_chunks(T):
+    test_router_bwd(T, 64, 7)
+
+
 @pytest.mark.parametrize("gather", [False, True, "fold"])
 def test_drop_in_block_router_to_gradients(gather):
     """Router -> route on the device's own logits -> ... -> dgate -> dlogits -> dWr, dx: the chain a
