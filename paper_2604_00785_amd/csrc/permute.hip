@@ -17,6 +17,7 @@
 //   rows    a wave copies 64 or 256 pieces of x[t] to the token's (up to k) grouped rows with
 //           16-byte accesses: x is read once, xp is written in full rows.
 #include <algorithm>
+#include <type_traits>
 #include "perm_common.h"
 
 namespace {
@@ -86,35 +87,38 @@ __global__ __launch_bounds__(PERM_THREADS) void permute_place_kernel(const int32
   for (int cg = tid % cols; cg < ncol; cg += (parts == 1 ? PERM_THREADS : (1 << 30))) {
     int bef[4] = {0, 0, 0, 0}, tot[4] = {0, 0, 0, 0};
     // Batches of loads that are all in flight together, the last one filled up with its last row: a remainder taken one by one waits
-    // for the fabric once per row (128 experts, 250 chunks: 31 rows per thread, 15 of them so; 18.0 -> 10.6 us for the launch).
-    constexpr int BATCH4 = 16, BATCH1 = 8;
-    if (vec == 4) {
-      for (int q0 = p; q0 < nblocks; q0 += BATCH4 * parts) {
-        int4 v[BATCH4];
+    // for the fabric once per row (128 experts, 250 chunks: 31 rows per thread, 15 of them so; 18.0 -> 10.6 us for the launch).  A table
+    // with a row or four per thread takes a short batch: 16 loads of the same row cost it 0.2-0.4 us.
+    auto add_up = [&](auto vec_tag, auto batch_tag) __attribute__((always_inline)) {
+      constexpr int VEC = decltype(vec_tag)::value, BATCH = decltype(batch_tag)::value;
+      for (int q0 = p; q0 < nblocks; q0 += BATCH * parts) {
+        int v[BATCH][VEC];
 #pragma unroll
-        for (int u = 0; u < BATCH4; ++u)
-          v[u] = *reinterpret_cast<const int4*>(hist + static_cast<size_t>(min(q0 + u * parts, nblocks - 1)) * e_count + cg * 4);
+        for (int u = 0; u < BATCH; ++u) {
+          const int32_t* row = hist + static_cast<size_t>(min(q0 + u * parts, nblocks - 1)) * e_count + cg * VEC;
+          if constexpr (VEC == 4) {
+            const int4 x = *reinterpret_cast<const int4*>(row);
+            v[u][0] = x.x; v[u][1] = x.y; v[u][2] = x.z; v[u][3] = x.w;
+          } else {
+            v[u][0] = *row;
+          }
+        }
 #pragma unroll
-        for (int u = 0; u < BATCH4; ++u) {
+        for (int u = 0; u < BATCH; ++u) {
           const int q = q0 + u * parts;
           const int in = q < nblocks ? -1 : 0, m = q < b ? -1 : 0;    // b < nblocks
-          tot[0] += v[u].x & in; tot[1] += v[u].y & in; tot[2] += v[u].z & in; tot[3] += v[u].w & in;
-          bef[0] += v[u].x & m; bef[1] += v[u].y & m; bef[2] += v[u].z & m; bef[3] += v[u].w & m;
+#pragma unroll
+          for (int j = 0; j < VEC; ++j) { tot[j] += v[u][j] & in; bef[j] += v[u][j] & m; }
         }
       }
-    } else {
-      for (int q0 = p; q0 < nblocks; q0 += BATCH1 * parts) {
-        int v[BATCH1];
-#pragma unroll
-        for (int u = 0; u < BATCH1; ++u) v[u] = hist[static_cast<size_t>(min(q0 + u * parts, nblocks - 1)) * e_count + cg];
-#pragma unroll
-        for (int u = 0; u < BATCH1; ++u) {
-          const int q = q0 + u * parts;
-          tot[0] += q < nblocks ? v[u] : 0;
-          bef[0] += q < b ? v[u] : 0;
-        }
-      }
-    }
+    };
+    const auto sum_columns = [&](auto vec_tag, auto longest) __attribute__((always_inline)) {
+      if (nblocks <= parts) add_up(vec_tag, std::integral_constant<int, 1>{});
+      else if (nblocks <= 4 * parts) add_up(vec_tag, std::integral_constant<int, 4>{});
+      else add_up(vec_tag, longest);
+    };
+    if (vec == 4) sum_columns(std::integral_constant<int, 4>{}, std::integral_constant<int, 16>{});
+    else sum_columns(std::integral_constant<int, 1>{}, std::integral_constant<int, 8>{});
     for (int j = 0; j < vec; ++j) {
       part_before[p * e_count + cg * vec + j] = bef[j];
       part_total[p * e_count + cg * vec + j] = tot[j];

@@ -215,6 +215,13 @@ def test_permute_then_combine_is_identity():
     assert torch.equal(buf.out.view(torch.int16), x.view(torch.int16))
 
 
+# the count table read in batches of one, four and sixteen (eight) rows per thread, with four columns per thread and with one
+@pytest.mark.parametrize("T,E,k", [(300, 33, 3), (1000, 33, 3), (3000, 33, 3), (500, 64, 8), (600, 64, 8), (2048, 64, 8), (3000, 64, 8),
+                                   (100, 512, 4), (500, 512, 4), (2000, 512, 4)])
+def test_permute_tables(T, E, k):
+    test_permute(T, E, k, 64, 0, E)
+
+
 def test_permute_rows_longer_than_a_grid():
     """One row of more parts of 256 pieces (of 16 bytes) than a grid may have along y (65535)."""
     d = (65535 * 256 + 70) * 8
