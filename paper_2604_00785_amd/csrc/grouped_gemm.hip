@@ -183,8 +183,10 @@ template <int OFF> __device__ __forceinline__ int load_i32(uint32_t voff, const 
   return v;
 }
 // A scalar base that the compiler may just have brought back from a vector register (it keeps what it has no scalar registers for
-// there): five wait states lie between that and a load that uses it, which the compiler sees to for its own loads only.
-__device__ __forceinline__ void settle(const char*& sbase) { asm volatile("s_nop 4" : "+s"(sbase)::"memory"); }
+// there): five wait states lie between that and a load that uses it, which the compiler sees to for its own loads only.  Here the scalar
+// unit writes the base once more, in place, and no wait is needed behind that.  It stands in front of every group of loads above.
+// (Five wait states in front of each load instead: 2-4 % of a large training step.)
+template <typename T> __device__ __forceinline__ void settle(T*& sbase) { asm volatile("s_mov_b64 %0, %0" : "+s"(sbase)::"memory"); }
 template <int N> __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
 template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() {
@@ -625,6 +627,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   auto fetch_tok = [&](TileState& t, int kt, int (&tk)[NL]) __attribute__((always_inline)) {
     if constexpr (GATHER_B || GATHER_A) {
       if (t.k_lo + (kt + 1) * BK > t.k_hi) {
+        settle(t.row_tok);
         const int last = t.k_hi - t.k_lo - 1;
 #pragma unroll
         for (int i = 0; i < NL; ++i) {
@@ -634,6 +637,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
         }
       } else {
         const int32_t* base = t.row_tok + static_cast<size_t>(kt) * BK;
+        settle(base);
         static_for<NL>([&](auto i_tag) {
           constexpr int i = decltype(i_tag)::value;
           tk[i] = load_i32<i * TL::KN_RPL * 4>(tok_voff, base);
@@ -777,7 +781,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     sub_step(IC<0>{}, nv_tag, IC<NREADS>{},
              [&](auto op) __attribute__((always_inline)) { read_op(SA{}, SB{}, IC<1>{}, IC<1>{}, nv_tag, op); },
              IC<KIND == 2 ? ALOADS : 0>{},
-             [&]() __attribute__((always_inline)) { set_m0<LA * TILE_BYTES>(lds_fill); },
+             [&]() __attribute__((always_inline)) { set_m0<LA * TILE_BYTES>(lds_fill); settle(t.sa_next); },
              [&](auto i) __attribute__((always_inline)) { a_part(t, kt + 2, i, sp_tag); });
     if constexpr (KIND == 2) a_end(t, kt + 2);
     lds_wait<0>();
@@ -789,7 +793,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     sub_step(IC<1>{}, nv_tag, IC<KIND >= 1 ? NREADS : 0>{},
              [&](auto op) __attribute__((always_inline)) { read_op(NextA{}, NextB{}, IC<0>{}, IC<0>{}, nv_tag, op); },
              IC<KIND == 2 ? NL : 0>{},
-             [&]() __attribute__((always_inline)) { set_m0<SA::value * TILE_BYTES>(lds_fill); },
+             [&]() __attribute__((always_inline)) { set_m0<SA::value * TILE_BYTES>(lds_fill); settle(t.sb_next); },
              [&](auto i) __attribute__((always_inline)) { b_part(t, kt + 2, i, sp_tag); });
     if constexpr (KIND == 2) {
       b_end(t, kt + 2);
@@ -820,7 +824,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     } else {
       static_for<HALF / 32>([&](auto g) {
         constexpr int i = 2 * decltype(g)::value;
-        if (i < 2 * t.nv) { a_part(t, kt, IC<i>{}, IC<2>{}); a_part(t, kt, IC<i + 1>{}, IC<2>{}); }
+        if (i == 0 || i < 2 * t.nv) { a_part(t, kt, IC<i>{}, IC<2>{}); a_part(t, kt, IC<i + 1>{}, IC<2>{}); }
       });
     }
     a_end(t, kt);
@@ -840,15 +844,14 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
       // steps that do not exist, repeat its last row.
       int tk[3][NL];
       const int last = t.k_hi - t.k_lo - 1;
-      const char* tok = reinterpret_cast<const char*>(t.row_tok);
-      settle(tok);
+      settle(t.row_tok);
       static_for<3>([&](auto s_tag) {
         constexpr int s = decltype(s_tag)::value;
         static_for<NL>([&](auto i_tag) {
           constexpr int i = decltype(i_tag)::value;
           int r = s * BK + kn_load_row(i, lane);
           if (r > last) r = last;
-          tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, reinterpret_cast<const int32_t*>(tok));
+          tk[s][i] = load_i32<0>(static_cast<uint32_t>(r) * 4u, t.row_tok);
         });
       });
       if constexpr (GATHER_B) a_unit(t, 0); else b_unit(t, 0);
