@@ -330,7 +330,8 @@ struct TileState {
   int r0;                       // first of this wave's rows inside the tile
   int m_wave;                   // end of the valid rows that are this wave's
   int nv;                       // 32-row groups that every wave works on, 1 .. HALF / 32 (the others issue no load and no MFMA)
-  bool few;                     // tiles of 128: takes few_rows_loop
+  bool few;                     // tiles of 128: takes few_rows_loop, whose ring lies across the slots of the other tiles and the shares of
+                                // the waves: only in a list with no more tiles than workgroups, the first of its launch
   bool second;                  // tile of the second weight gradient of a pair
   int nk, nk_phase;             // K steps in total / in the first K phase
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
@@ -811,9 +812,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   // What a tile waits for between main loops counts where tiles are short: a training step of 2048 tokens (d 2048, f 1024, 64
   // experts, 4 steps per weight gradient) 885 -> 868 us, the forward of 4001 tokens over 128 experts of f 512 328 -> 322 us;
   // at 1024 rows per expert and more the chip is power-limited and the step takes as long as before (0-1.5 % less).
-  // A tile with few rows always starts at the first slot of its ring; slots 2 and 4 are what its steps 0 and 1 leave free.
-  auto spare_slot = [&](const TileState& t) __attribute__((always_inline)) { return t.few ? 2 : (2 * t.p0 + 4) % NSLOT; };
-  auto spare_slot2 = [&](const TileState& t) __attribute__((always_inline)) { return t.few ? 4 : (2 * t.p0 + 3) % NSLOT; };
+  // A tile with few rows is the only one of its workgroup's list (see TileState::few): there is no epilogue before it.
+  auto spare_slot = [&](const TileState& t) __attribute__((always_inline)) { return (2 * t.p0 + 4) % NSLOT; };
+  auto spare_slot2 = [&](const TileState& t) __attribute__((always_inline)) { return (2 * t.p0 + 3) % NSLOT; };
   auto a_unit = [&](TileState& t, int kt) __attribute__((always_inline)) {   // kt: 0 or 1
     int at = lds_fill + (2 * t.p0 + 2 * kt) % NSLOT * TILE_BYTES;
     if (t.few) at = few_a + kt * FEW_A_BYTES;
@@ -949,7 +950,7 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
 #pragma clang loop unroll(disable)
     for (int kt = 0; kt < t.nk; ++kt) {
       asm volatile("" : "+s"(kt));          // one copy of the body: two would keep the accumulators in different registers
-      // this step's tiles are here (requests complete in order; stores of the epilogue before only make the wait longer) ...
+      // this step's tiles are here (requests complete in order) ...
       if (kt + 1 < t.nk) wait_vm<STEP_LOADS>(); else wait_vm<0>();
       wg_barrier();                         // ... those of the other waves too, and every wave is done with step kt - 1, whose slot
       if (kt + 2 < t.nk) {                  // is requested anew
