@@ -1536,10 +1536,16 @@ template <int S> double launch_cost(const ListCost& l, const ListCost& m) {
   return 0.65 * (l.tiles * l.each + m.tiles * m.each) / places<S>() + (l.each > m.each ? l.each : m.each);
 }
 
+// edge: null, or in: the edge to take (0: the rule's), out: the edge taken
+bool take_small(int* edge, double small, double large) {
+  const bool is_small = edge != nullptr && *edge != 0 ? *edge == 128 : small < large;
+  if (edge != nullptr) *edge = is_small ? 128 : 256;
+  return is_small;
+}
 template <int MODE>
-int run_gemm(GemmArgs& a, int R_cap, long long rows, hipStream_t s, const char* name) {
+int run_gemm(GemmArgs& a, int R_cap, long long rows, hipStream_t s, const char* name, int* edge) {
   const double r = static_cast<double>(rows);
-  if (launch_cost<128>(list_cost<MODE, 128>(a, r)) < launch_cost<256>(list_cost<MODE, 256>(a, r))) {
+  if (take_small(edge, launch_cost<128>(list_cost<MODE, 128>(a, r)), launch_cost<256>(list_cost<MODE, 256>(a, r)))) {
     const long long tiles = count_tiles<MODE, 128>(a, R_cap);
     return launch_gemm<MODE, 128>(a, tiles, s, name);
   }
@@ -1547,15 +1553,20 @@ int run_gemm(GemmArgs& a, int R_cap, long long rows, hipStream_t s, const char* 
   return launch_gemm<MODE, 256>(a, tiles, s, name);
 }
 template <int MODE_A, int MODE_B>
-int run_gemm_pair(GemmArgs& a, GemmArgs& b, int R_cap, long long rows, hipStream_t s, const char* name) {
+int run_gemm_pair(GemmArgs& a, GemmArgs& b, int R_cap, long long rows, hipStream_t s, const char* name, int* edge) {
   const double r = static_cast<double>(rows);
-  if (launch_cost<128>(list_cost<MODE_A, 128>(a, r), list_cost<MODE_B, 128>(b, r)) <
-      launch_cost<256>(list_cost<MODE_A, 256>(a, r), list_cost<MODE_B, 256>(b, r))) {
+  if (take_small(edge, launch_cost<128>(list_cost<MODE_A, 128>(a, r), list_cost<MODE_B, 128>(b, r)),
+                 launch_cost<256>(list_cost<MODE_A, 256>(a, r), list_cost<MODE_B, 256>(b, r)))) {
     const long long tiles = count_tiles<MODE_A, 128>(a, R_cap) + count_tiles<MODE_B, 128>(b, R_cap);
     return launch_gemm_pair<MODE_A, MODE_B, 128>(a, b, tiles, s, name);
   }
   const long long tiles = count_tiles<MODE_A, 256>(a, R_cap) + count_tiles<MODE_B, 256>(b, R_cap);
   return launch_gemm_pair<MODE_A, MODE_B, 256>(a, b, tiles, s, name);
+}
+bool bad_edges(const int* edges) {
+  if (edges == nullptr) return false;
+  for (int i = 0; i < 2; ++i) if (edges[i] != 0 && edges[i] != 128 && edges[i] != 256) return true;
+  return false;
 }
 
 bool bad_gemm_dims(int E, int R_cap, int d, int f) {
@@ -1586,18 +1597,19 @@ extern "C" size_t moe_workspace_bytes(int T, int E, int k, int d, int f) {
 }
 
 // xp grouped rows, or (row_token not null) the token rows themselves, gathered by the GEMM's loads
-int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets, const moe_bf16* Wg,
+extern "C" int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_weight, const int32_t* expert_offsets, const moe_bf16* Wg,
                  const moe_bf16* Wu, const moe_bf16* Wd, int E, int R_cap, long long rows, int most, int d, int f,
-                 moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream) {
+                 moe_bf16* g, moe_bf16* u, moe_bf16* h, moe_bf16* yp, void* stream, int* edges) {
   if (!xp || !expert_offsets || !Wg || !Wu || !Wd || !g || !u || !h || !yp) return MOE_ERR_INVALID;
-  if (bad_gemm_dims(E, R_cap, d, f)) return MOE_ERR_INVALID;
+  if (bad_gemm_dims(E, R_cap, d, f) || bad_edges(edges)) return MOE_ERR_INVALID;
   const void* ptrs[] = {xp, expert_offsets, Wg, Wu, Wd, g, u, h, yp};
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
   hipStream_t s = static_cast<hipStream_t>(stream);
   // Few rows for certain: the streaming kernels.  Few rows expected, but not for certain (a rank's share of the experts): both,
   // and on the device one of the two finds that the rows are not for it (see small_gemm.h).
   const int few = STREAM_ROWS * E;
-  const bool streamed = R_cap <= few || most <= STREAM_TOKENS, either = !streamed && rows <= few;
+  const bool tiled = edges != nullptr && (edges[0] != 0 || edges[1] != 0);
+  const bool streamed = !tiled && (R_cap <= few || most <= STREAM_TOKENS), either = !tiled && !streamed && rows <= few;
   int rc = MOE_OK;
   StreamFwdArgs p{}, q{};
   if (streamed || either) {
@@ -1614,7 +1626,7 @@ int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_
   a.A0 = U16(xp); a.B0 = U16(Wg); a.B1 = U16(Wu); a.O0 = g; a.O1 = u; a.O2 = h;
   a.K = d; a.N = f;
   a.stream_rows = either ? few : 0;
-  rc = run_gemm<GATE_UP>(a, R_cap, rows, s, "gemm_gate_up");
+  rc = run_gemm<GATE_UP>(a, R_cap, rows, s, "gemm_gate_up", edges);
   if (rc != MOE_OK) return rc;
   // down
   if (either && (rc = moe_stream_down(q, rows, s)) != MOE_OK) return rc;
@@ -1623,7 +1635,7 @@ int moe_gemm_fwd(const moe_bf16* xp, const int32_t* row_token, const float* row_
   b.A0 = U16(h); b.B0 = U16(Wd); b.O0 = yp;
   b.K = f; b.N = d;
   b.stream_rows = a.stream_rows;
-  return run_gemm<DOWN>(b, R_cap, rows, s, "gemm_down");
+  return run_gemm<DOWN>(b, R_cap, rows, s, "gemm_down", edges != nullptr ? edges + 1 : nullptr);
 }
 
 namespace {
@@ -1667,11 +1679,11 @@ extern "C" int moe_grouped_gemm_fwd_folded(const moe_bf16* x, int T, const int32
 
 // xp grouped rows, or (row_token not null) the token rows themselves, gathered by the loads of the
 // two weight-gradient products that read them
-int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
+extern "C" int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* row_token, const moe_bf16* g, const moe_bf16* u,
                  const moe_bf16* h, const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
                  const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp, moe_bf16* dWg,
-                 moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream) {
-  if (row_token != nullptr && bad_gather(xp, T, row_token, d)) return MOE_ERR_INVALID;
+                 moe_bf16* dWu, moe_bf16* dWd, void* ws, size_t ws_bytes, void* stream, int* edges) {
+  if ((row_token != nullptr && bad_gather(xp, T, row_token, d)) || bad_edges(edges)) return MOE_ERR_INVALID;
   if (!dyp || !xp || !g || !u || !h || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws)
     return MOE_ERR_INVALID;
   if (bad_gemm_dims(E, R_cap, d, f)) return MOE_ERR_INVALID;
@@ -1692,7 +1704,7 @@ int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* 
   a.offsets = expert_offsets; a.E = E;
   a.A0 = U16(dyp); a.B0 = U16(Wd); a.G = U16(g); a.U = U16(u); a.O0 = dg; a.O1 = du;
   a.K = d; a.N = f;
-  int rc = run_gemm_pair<DGRAD_H, WGRAD>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down");
+  int rc = run_gemm_pair<DGRAD_H, WGRAD>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down", edges);
   if (rc != MOE_OK) return rc;
   // dxp = dg . Wg + du . Wu ; dWg = dg^T xp and dWu = du^T xp (one list: both read the same rows of xp)
   GemmArgs w{};
@@ -1703,8 +1715,9 @@ int moe_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, int T, const int32_t* 
   b.A0 = dg; b.A1 = du; b.B0 = U16(Wg); b.B1 = U16(Wu); b.O0 = dxp;
   b.K = f; b.N = d;
   // dgrad_x first: its tiles are the long ones, the weight gradients' many short tiles fill its tail
-  if (row_token != nullptr) return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
-  return run_gemm_pair<DGRAD_X, WGRAD>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
+  int* edge = edges != nullptr ? edges + 1 : nullptr;
+  if (row_token != nullptr) return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x", edge);
+  return run_gemm_pair<DGRAD_X, WGRAD>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x", edge);
 }
 
 extern "C" int moe_grouped_gemm_bwd(const moe_bf16* dyp, const moe_bf16* xp, const moe_bf16* g, const moe_bf16* u,
@@ -1759,16 +1772,16 @@ const float* moe_folded_part(const void* ws, int R_cap, int f) {
   return reinterpret_cast<const float*>(static_cast<const char*>(ws) + moe_grouped_gemm_bwd_workspace_bytes(R_cap, f));
 }
 
-int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
+extern "C" int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
                                            const int32_t* row_token, const float* row_weight, const int32_t* slot_row,
                                            const moe_bf16* g, const moe_bf16* u, const moe_bf16* hw,
                                            const int32_t* expert_offsets, const moe_bf16* Wg, const moe_bf16* Wu,
                                            const moe_bf16* Wd, int E, int R_cap, long long rows, int d, int f, moe_bf16* dxp,
                                            moe_bf16* dWg, moe_bf16* dWu, moe_bf16* dWd, float* dgate, void* ws,
-                                           size_t ws_bytes, void* stream) {
+                                           size_t ws_bytes, void* stream, int* edges) {
   if (!dout || !g || !u || !hw || !expert_offsets || !Wg || !Wu || !Wd || !dxp || !dWg || !dWu || !dWd || !ws || !row_weight || !slot_row || k <= 0)
     return MOE_ERR_INVALID;
-  if (bad_gemm_dims(E, R_cap, d, f) || bad_gather(x, T, row_token, d) || bad_gather(dout, T, row_token, d))
+  if (bad_gemm_dims(E, R_cap, d, f) || bad_gather(x, T, row_token, d) || bad_gather(dout, T, row_token, d) || bad_edges(edges))
     return MOE_ERR_INVALID;
   const void* ptrs[] = {dout, x, g, u, hw, expert_offsets, Wg, Wu, Wd, dxp, dWg, dWu, dWd, dgate, ws, row_weight, slot_row};
   for (const void* p : ptrs) if (!moe_aligned16(p)) return MOE_ERR_INVALID;
@@ -1792,7 +1805,7 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   a.dgate_part = part;
   a.A0 = U16(dout); a.B0 = U16(Wd); a.G = U16(g); a.U = U16(u); a.O0 = dg; a.O1 = du;
   a.K = d; a.N = f;
-  int rc = run_gemm_pair<DGRAD_H_GATE, WGRAD_GATHER_A>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down");
+  int rc = run_gemm_pair<DGRAD_H_GATE, WGRAD_GATHER_A>(a, wd, R_cap, rows, s, "gemm_dgrad_h+wgrad_down", edges);
   if (rc != MOE_OK) return rc;
   if (dgate != nullptr) {
     const int n = T * k;
@@ -1811,7 +1824,8 @@ int moe_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,
   // dgrad_x first: its tiles are the long ones, the weight gradients' many short tiles fill its tail.  (The other
   // order used to pay off through dxp still lying in the last-level cache when moe_permute_bwd read it; since that
   // kernel streams its rows with non-temporal loads it no longer depends on that.)
-  return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x");
+  return run_gemm_pair<DGRAD_X, WGRAD_GATHER>(b, w, R_cap, rows, s, "gemm_wgrad_gate_up+dgrad_x",
+                                              edges != nullptr ? edges + 1 : nullptr);
 }
 
 extern "C" int moe_grouped_gemm_bwd_folded(const moe_bf16* dout, const moe_bf16* x, int T, int k,

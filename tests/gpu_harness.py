@@ -2,6 +2,7 @@
 the HIP path through the binding, bring results back as numpy, compare."""
 from __future__ import annotations
 
+import ctypes
 from typing import Dict
 
 import numpy as np
@@ -9,6 +10,46 @@ import torch
 
 from paper_2604_00785_amd import binding as B
 from paper_2604_00785_amd import workloads as W
+
+class AtEdge:
+    """The library with the products of every grouped call launched on tiles of one edge, whatever the rule would take and
+    without the streaming kernels: stands in for ``binding.load()``.  Which edge a launch ran with comes back from it."""
+
+    def __init__(self, edge: int):
+        self.lib, self.edge, self.launches = B.load(), edge, 0
+        P, I, L = ctypes.c_void_p, ctypes.c_int, ctypes.c_longlong
+        self.lib.moe_gemm_fwd.argtypes = [P] * 7 + [I, I, L, I, I, I] + [P] * 6
+        self.lib.moe_gemm_bwd.argtypes = [P, P, I] + [P] * 8 + [I, I, L, I, I] + [P] * 5 + [ctypes.c_size_t, P, P]
+        self.lib.moe_gemm_bwd_folded.argtypes = [P, P, I, I] + [P] * 10 + [I, I, L, I, I] + [P] * 6 + [ctypes.c_size_t, P, P]
+
+    def __getattr__(self, name):
+        return getattr(self.lib, name)
+
+    def _run(self, name, *args):
+        edges = (ctypes.c_int * 2)(self.edge, self.edge)
+        rc = getattr(self.lib, name)(*args, ctypes.addressof(edges))
+        assert rc == 0 and list(edges) == [self.edge] * 2, (name, rc, list(edges))
+        self.launches += 2
+        return rc
+
+    def moe_grouped_gemm_fwd(self, xp, off, Wg, Wu, Wd, E, R, d, f, *out):
+        return self._run("moe_gemm_fwd", xp, None, None, off, Wg, Wu, Wd, E, R, R, R, d, f, *out)
+
+    def moe_grouped_gemm_fwd_gather(self, x, T, row_token, off, Wg, Wu, Wd, E, R, d, f, *out):
+        return self._run("moe_gemm_fwd", x, row_token, None, off, Wg, Wu, Wd, E, R, R, T, d, f, *out)
+
+    def moe_grouped_gemm_fwd_folded(self, x, T, row_token, row_weight, off, Wg, Wu, Wd, E, R, d, f, *out):
+        return self._run("moe_gemm_fwd", x, row_token, row_weight, off, Wg, Wu, Wd, E, R, R, T, d, f, *out)
+
+    def moe_grouped_gemm_bwd(self, dyp, xp, g, u, h, off, Wg, Wu, Wd, E, R, d, f, *rest):
+        return self._run("moe_gemm_bwd", dyp, xp, 0, None, g, u, h, off, Wg, Wu, Wd, E, R, R, d, f, *rest)
+
+    def moe_grouped_gemm_bwd_gather(self, dyp, x, T, row_token, g, u, h, off, Wg, Wu, Wd, E, R, d, f, *rest):
+        return self._run("moe_gemm_bwd", dyp, x, T, row_token, g, u, h, off, Wg, Wu, Wd, E, R, R, d, f, *rest)
+
+    def moe_grouped_gemm_bwd_folded(self, dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, off, Wg, Wu, Wd, E, R, d, f, *rest):
+        return self._run("moe_gemm_bwd_folded", dout, x, T, k, row_token, row_weight, slot_row, g, u, hw, off, Wg, Wu, Wd, E, R, R, d, f, *rest)
+
 
 REL_TOL = 2e-2        # max |gpu - ref| / max |ref| per tensor: bf16 inputs, fp32 accumulation
 GATE_TOL = 1e-5       # relative, fp32 softmax against the fp64 oracle

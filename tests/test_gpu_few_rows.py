@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import gpu_harness as H
 import test_gpu_parity as P
 from paper_2604_00785_amd import binding as B
 
@@ -90,13 +91,18 @@ def test_streamed_products_have_the_bits_of_the_tiled(T, d, E, k, f, form):
 
 
 # A list of many tiles whose experts' sizes are in no order: several rounds of runs taken from both ends, and (more than 128
-# experts) in index order
+# experts) in index order, at either tile edge
 @pytest.mark.parametrize("E,d,f", [(96, 1024, 1024), (72, 512, 2048), (140, 1024, 512)])
-def test_many_rounds_of_uneven_experts(E, d, f):
+@pytest.mark.parametrize("edge", [128, 256])
+def test_many_rounds_of_uneven_experts(E, d, f, edge, monkeypatch):
     rng = np.random.default_rng(E)
     counts = np.concatenate([[1100, 520, 513, 300, 257, 256, 255, 0, 0, 0], rng.integers(1, 30, E - 10)])
     rng.shuffle(counts)
-    assert 256 * 2 < sum(-(-c // 256) for c in counts) * (f // 128) and sum(-(-c // 256) for c in counts) <= 3 * E
+    row_tiles = sum(-(-c // edge) for c in counts)
+    workgroups = 256 * 256 // edge
+    assert 2 * workgroups < row_tiles * (f // (edge // 2)) and row_tiles <= 3 * E      # of gate/up: more than two rounds, both ends
+    lib = H.AtEdge(edge)
+    monkeypatch.setattr(B, "load", lambda: lib)
     P.test_grouped_gemm_fwd_bwd_isolated([int(c) for c in counts], d, f)
 
 
