@@ -328,11 +328,14 @@ int launch_combine_bwd(const moe_bf16* dout, const moe_bf16* yp, const int32_t* 
   //   3 slots                                     d 128, 32768 tokens 21.4 / 20.1 / 19.4   d  768, 16384 tokens 30.5 / 31.5 / 32.7
   //   8 slots  d 512, 40 tokens 4.0 / 4.1 / 4.0   d 128, 32768 tokens 43.0 / 34.5 / 33.1   d 2048,  8192 tokens  103 /  103 /  103
   // Before (one slot at a time, the reductions through LDS): 3.0, 8.8, 11.9; 3.4, 12.2, 11.8; 23.3, 30.7; 6.3, 48.2, 106 for these.
+  // Three pieces per lane for rows that mostly fill the third: d 1536, 1 slot, 8192 tokens 15.1 (four pieces) / 13.8, before 14.0; 8 slots,
+  // 40 tokens 6.5 / 5.0 (d 1088, 2 slots, 8192 tokens 17.4 / 17.8).
   // combine and combine_bwd apart / in one (OUT): d 2048, 48 tokens 10.6 / 8.2 and a launch, 8192 tokens 158 / 119; d 1024, 24576
   // tokens of 2 slots 65 / 47.
   const int slots = k == 1 || (k < 4 && chunks > 64 && T > 2048) ? 1 : k == 2 || (chunks > 64 && T > 512) ? 2 : 4;
   if (chunks <= 64) { if (slots == 1) COMBINE_BWD(1, 1, OUT); else if (slots == 2) COMBINE_BWD(1, 2, OUT); else COMBINE_BWD(1, 4, OUT); }
   else if (chunks <= 128) { if (slots == 1) COMBINE_BWD(2, 1, OUT); else if (slots == 2) COMBINE_BWD(2, 2, OUT); else COMBINE_BWD(2, 4, OUT); }
+  else if (chunks > 160 && chunks <= 192) { if (slots == 1) COMBINE_BWD(3, 1, OUT); else if (slots == 2) COMBINE_BWD(3, 2, OUT); else COMBINE_BWD(3, 4, OUT); }
   else { if (slots == 1) COMBINE_BWD(4, 1, OUT); else if (slots == 2) COMBINE_BWD(4, 2, OUT); else COMBINE_BWD(4, 4, OUT); }
   return moe_check_launch();
 }

@@ -196,6 +196,7 @@ def test_combine_and_backward(T, E, k, d, eb, ec):
     (700, 6, 1, 576, 0, 6), (1537, 6, 1, 1088, 0, 6), (2049, 6, 1, 72, 0, 6),       # one slot: 1 and 2 pieces per lane, short rows
     (700, 6, 2, 576, 0, 6), (2049, 6, 2, 576, 1, 5), (2049, 9, 2, 1096, 0, 9), (40, 6, 2, 264, 2, 3),
     (2049, 6, 3, 520, 0, 6), (900, 6, 3, 2056, 0, 6), (600, 9, 5, 1032, 0, 9), (2100, 9, 4, 1536, 2, 6),
+    (600, 6, 1, 1536, 0, 6), (300, 9, 8, 1528, 0, 9), (2049, 6, 2, 1544, 0, 6),     # three pieces per lane and the next more
 ])
 def test_combine_forms(T, E, k, d, eb, ec):
     test_combine_and_backward(T, E, k, d, eb, ec)
