@@ -333,7 +333,8 @@ int moe_router_bwd(const moe_bf16* x, const float* Wr, const float* dlogits, int
  * moe_router_bwd).  `path` chooses the calls: MOE_LAYER_PLAIN (xp is materialised, dyp is used), MOE_LAYER_GATHER
  * (rows gathered by the products, no xp), MOE_LAYER_FOLD (gate weights folded: h and yp hold hw and ypw; no xp, no
  * dyp, row_weight is used).  Sizes, buffers and errors are those of the calls; pointers that the chosen stages and
- * path do not use may be NULL.  A stage that fails leaves the stages before it enqueued.
+ * path do not use may be NULL.  A stage that fails leaves the stages before it enqueued.  With FWD and BWD in one call
+ * `dout` may be `out` (the gradient of half the squared output): the backward reads what the forward has written.
  */
 enum { MOE_LAYER_PLAIN = 0, MOE_LAYER_GATHER = 1, MOE_LAYER_FOLD = 2 };
 enum { MOE_LAYER_ROUTER = 1, MOE_LAYER_FWD = 2, MOE_LAYER_BWD = 4, MOE_LAYER_ROUTER_BWD = 8 };

@@ -2,7 +2,7 @@
 // derivative of the Stage-4 gather, which is the same reduction with unit weights.
 //
 // The paper maps one thread to one output element (forward) or one routed row
-// (backward).  Here one wave owns a token, or 64 pieces (16 B) of its row where tokens
+// (backward).  Here one wave owns a token, or 64 or 128 pieces (16 B) of its row where tokens
 // are few: every load and store is a full, coalesced row segment, the k source rows are
 // summed in slot order in fp32, and the token's own row (out / dout) is touched
 // exactly once.  No atomics, so results are reproducible.

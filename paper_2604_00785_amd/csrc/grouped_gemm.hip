@@ -26,7 +26,8 @@
 //
 // The two operand tiles of a step (32 KB each) live in a ring of five LDS slots (160 KB, all
 // there is): A(t) in slot 2t mod 5, B(t) in slot (2t+1) mod 5, so two and a half steps are
-// resident (a small tile that holds all of an expert's few rows has a ring of its own, see few_rows_loop).  Step t loads A(t+2) during its first 32-deep sub-step, into the slot B(t-1) left;
+// resident (a small tile that holds all of an expert's few rows has a ring of its own, see few_rows_loop).
+// Step t loads A(t+2) during its first 32-deep sub-step, into the slot B(t-1) left;
 // its barrier follows that sub-step: behind it the tiles of step t+1 are complete (the wave's own
 // loads of A(t+2) may still be in flight) and every wave is done with A(t), whose slot B(t+2) is
 // loaded into during the second sub-step.  Fragments are double-buffered in registers: the reads
@@ -63,7 +64,7 @@ namespace {
 constexpr int BK = 64;
 constexpr int GEMM_THREADS = 256;
 constexpr int NSLOT = 5;                              // ring of operand tile slots
-// What follows from the edge S of the output tile, 256 or 128 (see tile_edge()).  Four waves as 2 x 2 in either case.
+// What follows from the edge S of the output tile, 256 or 128 (see TileCost).  Four waves as 2 x 2 in either case.
 template <int S> struct Tile {
   static_assert(S == 256 || S == 128);
   static constexpr int BYTES = S * BK * 2;            // one operand tile: 32 or 16 KB
@@ -1501,7 +1502,9 @@ long long count_tiles(GemmArgs& a, int R_cap) {
 // rarely ends evenly; a list alone in its launch also ends on whole rounds.  The row tiles are counted for an even load of
 // the expected rows.  The constants are a fit to 152 layers of 128 to 32768 tokens, d 128 to 4096, f 128 to 2048, 4 to 240
 // experts, even and zipf-like loads (four launches each, timed with both edges): the edge chosen is on average 0.5 % slower than
-// the better one, always 256 16 % slower, always 128 6 %.
+// the better one, always 256 16 % slower, always 128 6 %.  Where it is wrong: a share of the experts that holds the large ones of
+// a skewed load (the first 59 of 237 experts, d 1536, f 448, some 39000 rows where 11228 were expected: gate_up 164 / 200 us and dgrad_h 330 / 360
+// with 128 taken), and widths of 192 to 320 under more than 1500 rows per expert (gate_up 171 / 184, dgrad_h 50 / 57 with 128 taken).
 // Some of them, 256 / 128 in us, gate_up, down, dgrad_h with dWd, dgrad_x with dWg and dWu:
 //   256 tokens, d 128, f 256, 8 experts, 2 per token        13 / 9      12 / 8      19 / 11     16 / 11
 //   248 tokens, d 320, f 320, 28 of 57 experts, 6           22 / 12     17 / 10     31 / 16     29 / 20
