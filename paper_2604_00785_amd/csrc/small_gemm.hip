@@ -90,7 +90,7 @@ __device__ __forceinline__ void st_fwd_tile(const StreamFwdArgs& a, const StTile
   const int i16 = lane & 15, g4 = lane >> 4;
   const int K = a.K;
   const int n0 = t.col * (16 * NBC);
-  const int np = K / ST_KB, nb = (np + PIECES - 1) / PIECES;
+  const int np = K / ST_KB, nb = (np + PIECES - 1) / PIECES, first = first_k_step(t.e, K);
 
   f32x4_t acc[FR];
 #pragma unroll
@@ -115,8 +115,9 @@ __device__ __forceinline__ void st_fwd_tile(const StreamFwdArgs& a, const StTile
   auto load = [&](int s, int kb) __attribute__((always_inline)) {
 #pragma unroll
     for (int q = 0; q < PIECES; ++q) {
-      const int p = kb * PIECES + q;
-      const size_t ko = static_cast<size_t>(p < np ? p : np - 1) * (ST_KB * 2);
+      int p = kb * PIECES + q;
+      p = first + (p < np ? p : np - 1);
+      const size_t ko = static_cast<size_t>(p < np ? p : p - np) * (ST_KB * 2);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
