@@ -56,6 +56,7 @@
 #include <type_traits>
 #include <utility>
 #include "common.h"
+#include "dma.h"
 #include "gemm.h"
 #include "small_gemm.h"
 
@@ -90,7 +91,6 @@ constexpr int slot_of_b(int p) { return (2 * p + 1) % NSLOT; }
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
-#define LDS_PTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 template <int N> using IC = std::integral_constant<int, N>;
 template <typename F, int... I> __device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
@@ -169,10 +169,6 @@ template <int OFF> __device__ __forceinline__ s16x4 lds_read_tr_b64(uint32_t add
 template <int OFF> __device__ __forceinline__ void set_m0(uint32_t lds_base) {
   asm volatile("s_add_i32 m0, %0, %1" :: "s"(lds_base), "n"(OFF) : "memory", "scc");
 }
-__device__ __forceinline__ void set_m0_rt(uint32_t lds_addr) { asm volatile("s_mov_b32 m0, %0" :: "s"(lds_addr) : "memory"); }
-template <int OFF> __device__ __forceinline__ void dma16_imm(uint32_t voff, const char* sbase) {
-  asm volatile("global_load_lds_dwordx4 %0, %1 offset:%2" :: "v"(voff), "s"(sbase), "n"(OFF) : "memory");
-}
 // the same with a 64-bit address per lane (used once per tile at most, for rows past an expert's end)
 template <int OFF> __device__ __forceinline__ void dma16_lane_imm(const char* p) {
   asm volatile("global_load_lds_dwordx4 %0, off offset:%1" :: "v"(p), "n"(OFF) : "memory");
@@ -183,13 +179,6 @@ template <int OFF> __device__ __forceinline__ int load_i32(uint32_t voff, const 
   asm volatile("global_load_dword %0, %1, %2 offset:%3" : "=v"(v) : "v"(voff), "s"(sbase), "n"(OFF) : "memory");
   return v;
 }
-// A scalar base that the compiler may just have brought back from a vector register (it keeps what it has no scalar registers for
-// there): five wait states lie between that and a load that uses it, which the compiler sees to for its own loads only.  Here the scalar
-// unit writes the base once more, in place, and no wait is needed behind that.  It stands in front of every group of loads above.
-// (Five wait states in front of each load instead: 2-4 % of a large training step.)
-template <typename T> __device__ __forceinline__ void settle(T*& sbase) { asm volatile("s_mov_b64 %0, %0" : "+s"(sbase)::"memory"); }
-template <int N> __device__ __forceinline__ void lds_wait() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }
-template <int N> __device__ __forceinline__ void wait_vm() { asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory"); }
 __device__ __forceinline__ void wg_barrier() {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_barrier();

@@ -3,6 +3,8 @@
 // the language boundary per stage, and what the grouped products by themselves do not know: the number of experts of the
 // whole layer, from which the expected number of local rows follows, and of tokens, which no expert's rows exceed.
 #include "gemm.h"
+#include "perm_common.h"
+#include "small_gemm.h"
 
 namespace {
 bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
@@ -18,6 +20,31 @@ bool combine_in_one(const moe_layer* L) {
   const size_t row = static_cast<size_t>(L->d) * sizeof(moe_bf16), out = L->T * row;
   return !overlap(L->out, out, L->dout, out) && !overlap(L->out, out, L->dyp, out * L->k) &&
          !overlap(L->out, out, L->dgate, static_cast<size_t>(L->T) * L->k * sizeof(float));
+}
+// Whether the forward pass may take the kernels that do several of its stages (moe_route_gate_up): a small call, rows gathered, that none of
+// the stages would refuse, and no output of theirs lies where another workgroup still reads (the stages by themselves have
+// read their inputs when the next one writes).
+bool fwd_in_two(const moe_layer* L) {
+  if (L->path == MOE_LAYER_PLAIN || !moe_small_layer_fits(L->T, L->E, L->k)) return false;
+  if (moe_check_permute_args(nullptr, L->topk_idx, L->T, L->d, L->E, L->k, L->e_begin, L->e_count, L->expert_offsets, L->row_token,
+                             L->slot_row, nullptr, L->ws, L->ws_bytes) != MOE_OK) return false;
+  if (L->d % 64 != 0 || L->f <= 0 || L->f % 64 != 0 || static_cast<unsigned long long>(L->T) * L->d * sizeof(moe_bf16) > 0xFFFFFFFFull - 65536)
+    return false;
+  const void* used[] = {L->logits, L->topk_w, L->x, L->Wg, L->Wu, L->Wd, L->g, L->u, L->h, L->yp};
+  if (L->path == MOE_LAYER_FOLD && (!L->row_weight || !moe_aligned16(L->row_weight))) return false;
+  for (const void* p : used) if (!p || !moe_aligned16(p)) return false;
+  const size_t pairs = static_cast<size_t>(L->T) * L->k, logits = sizeof(float) * L->T * L->E, rows = pairs * L->f * sizeof(moe_bf16);
+  const void* words[] = {L->topk_idx, L->topk_w, L->row_token, L->slot_row, L->row_weight};
+  for (const void* p : words) if (p && overlap(L->logits, logits, p, 4 * pairs)) return false;
+  for (const void* p : {L->g, L->u, L->h}) if (overlap(L->logits, logits, p, rows)) return false;
+  return !overlap(L->logits, logits, L->expert_offsets, sizeof(int32_t) * (L->e_count + 1));
+}
+bool down_and_combine_in_one(const moe_layer* L) {
+  if (!moe_down_combine_fits(L->T, L->k) || !L->out || !moe_aligned16(L->out)) return false;
+  const size_t pairs = static_cast<size_t>(L->T) * L->k, out = sizeof(moe_bf16) * L->T * L->d;
+  return !overlap(L->out, out, L->h, pairs * L->f * sizeof(moe_bf16)) && !overlap(L->out, out, L->yp, pairs * L->d * sizeof(moe_bf16)) &&
+         !overlap(L->out, out, L->Wd, sizeof(moe_bf16) * L->e_count * L->d * L->f) && !overlap(L->out, out, L->topk_idx, 4 * pairs) &&
+         !overlap(L->out, out, L->slot_row, 4 * pairs) && !overlap(L->out, out, L->topk_w, 4 * pairs);
 }
 }  // namespace
 
@@ -36,21 +63,37 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if ((rc = moe_router_fwd(L->x, L->Wr, T, d, E, L->logits, stream)) != MOE_OK) return rc;
   }
   if (what & MOE_LAYER_FWD) {
-    rc = moe_route_permute(L->logits, plain ? L->x : nullptr, T, d, E, k, L->renormalize, L->e_begin, nl, L->topk_idx, L->topk_w,
-                           L->expert_offsets, L->row_token, L->slot_row, fold ? L->row_weight : nullptr,
-                           plain ? L->xp : nullptr, L->ws, L->ws_bytes, stream);
-    if (rc != MOE_OK) return rc;
-    if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
-    if (plain)
-      rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, T, d, f, L->g, L->u, L->h,
-                        L->yp, stream);
-    else
-      rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
-                               R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
-    if (rc != MOE_OK) return rc;
+    bool combined = false;
+    if (fwd_in_two(L)) {
+      hipStream_t s = static_cast<hipStream_t>(stream);
+      if ((rc = moe_route_gate_up(L, rows, s)) != MOE_OK) return rc;
+      combined = !both && down_and_combine_in_one(L);
+      if (combined) {
+        rc = moe_down_combine(L, s);
+      } else {
+        StreamFwdArgs q{};
+        q.A = L->h; q.offsets = L->expert_offsets; q.B0 = L->Wd; q.O0 = L->yp; q.E = nl; q.K = f; q.N = d; q.max_rows = R_cap;
+        rc = moe_stream_down(q, rows, s);
+      }
+      if (rc != MOE_OK) return rc;
+    } else {
+      rc = moe_route_permute(L->logits, plain ? L->x : nullptr, T, d, E, k, L->renormalize, L->e_begin, nl, L->topk_idx, L->topk_w,
+                             L->expert_offsets, L->row_token, L->slot_row, fold ? L->row_weight : nullptr,
+                             plain ? L->xp : nullptr, L->ws, L->ws_bytes, stream);
+      if (rc != MOE_OK) return rc;
+      if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
+      if (plain)
+        rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, T, d, f, L->g, L->u, L->h,
+                          L->yp, stream);
+      else
+        rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
+                                 R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
+      if (rc != MOE_OK) return rc;
+    }
     // with the backward in the same call the rows of yp are read once, for both
     if (!fold && !L->topk_w) return MOE_ERR_INVALID;
-    if (both) rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
+    if (combined) rc = MOE_OK;
+    else if (both) rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
     else if (sparse) rc = moe_combine_sparse(L->yp, L->slot_row, fold ? nullptr : L->topk_w, T, k, d, L->out, "combine", stream);
     else if (fold) rc = moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream);
     else rc = moe_unpermute_combine(L->yp, L->slot_row, L->topk_w, T, k, d, L->out, stream);

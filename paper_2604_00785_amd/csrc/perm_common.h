@@ -29,6 +29,18 @@ __device__ __forceinline__ uint64_t same_expert_mask(int e, int nbits) {
   return e >= 0 ? m : 0ull;
 }
 
+// Besides, the mask of lanes whose expert is a smaller one: the same ballots, from the highest bit down.
+__device__ __forceinline__ uint64_t same_expert_mask(int e, int nbits, uint64_t& smaller) {
+  uint64_t m = __ballot(e >= 0);
+  smaller = 0;
+  for (int b = nbits - 1; b >= 0; --b) {
+    const uint64_t set = __ballot((e >> b) & 1);
+    if ((e >> b) & 1) { smaller |= m & ~set; m &= set; } else { m &= ~set; }
+  }
+  if (e < 0) { smaller = 0; m = 0; }
+  return m;
+}
+
 // Adds this wave's share of a chunk to cnt[] (the wave's own LDS row): local(i) is the local expert
 // of the chunk's pair i, or -1.  The lowest lane of every group of equal experts adds the group's
 // size: one writer per expert and batch, no atomic.
@@ -54,6 +66,12 @@ inline int perm_max_chunks(int e_count) {
   const int by_cells = 16384 / e_count;
   return by_cells < 256 ? 256 : (by_cells > 4096 ? 4096 : by_cells);
 }
+
+// MOE_OK, or what moe_route_permute answers to these arguments (permute.hip); bits of a local expert's number.
+int moe_check_permute_args(const moe_bf16* x, const int32_t* topk_idx, int T, int d, int E_total, int k, int e_begin, int e_count,
+                           const int32_t* expert_offsets, const int32_t* row_token, const int32_t* slot_row, const moe_bf16* xp,
+                           const void* ws, size_t ws_bytes);
+int moe_expert_bits(int e_count);
 
 // Launches Stage 1 with the per-chunk expert counts as a by-product (route.hip); hist has room for hist_cells
 // counts.  Returns false if the shape does not fit the fused kernel (the caller then routes and counts with

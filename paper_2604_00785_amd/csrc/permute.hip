@@ -248,6 +248,27 @@ extern "C" size_t moe_permute_workspace_bytes(int T, int k, int e_count) {
   return (rows * e_count * sizeof(int32_t) + 16 + 255) & ~static_cast<size_t>(255);
 }
 
+int moe_check_permute_args(const moe_bf16* x, const int32_t* topk_idx, int T, int d, int E_total, int k, int e_begin,
+                       int e_count, const int32_t* expert_offsets, const int32_t* row_token, const int32_t* slot_row,
+                       const moe_bf16* xp, const void* ws, size_t ws_bytes) {
+  // xp == NULL: index generation only (for callers that let the GEMMs gather the rows); x is not read then
+  if (!topk_idx || !expert_offsets || !row_token || !slot_row || !ws || (xp && !x)) return MOE_ERR_INVALID;
+  if (T <= 0 || d <= 0 || d % 8 != 0 || E_total <= 0 || k <= 0 || k > E_total) return MOE_ERR_INVALID;
+  if (e_begin < 0 || e_count <= 0 || e_begin + e_count > E_total || e_count > MOE_MAX_EXPERTS) return MOE_ERR_INVALID;
+  if (static_cast<long long>(T) * k > 0x7FFFFFFFll / 2) return MOE_ERR_INVALID;
+  if ((xp && (!moe_aligned16(x) || !moe_aligned16(xp))) || !moe_aligned16(ws) || !moe_aligned16(topk_idx) ||
+      !moe_aligned16(slot_row) || !moe_aligned16(row_token) || !moe_aligned16(expert_offsets))
+    return MOE_ERR_INVALID;
+  if (ws_bytes < moe_permute_workspace_bytes(T, k, e_count)) return MOE_ERR_WORKSPACE;
+  return MOE_OK;
+}
+
+int moe_expert_bits(int e_count) {
+  int nbits = 0;
+  while ((1 << nbits) < e_count) ++nbits;
+  return nbits;
+}
+
 namespace {
 void launch_rows(const moe_bf16* x, const int32_t* slot_row, int T, int d, int k, moe_bf16* xp, hipStream_t s) {
   const int chunks = d / 8;
@@ -264,35 +285,14 @@ void launch_rows(const moe_bf16* x, const int32_t* slot_row, int T, int d, int k
     MOE_LAUNCH("permute_rows", permute_rows_kernel<2>, grid(128), dim3(256), 0, s, xs, slot_row, T, k, chunks, xd);
 }
 
-int check_permute_args(const moe_bf16* x, const int32_t* topk_idx, int T, int d, int E_total, int k, int e_begin,
-                       int e_count, const int32_t* expert_offsets, const int32_t* row_token, const int32_t* slot_row,
-                       const moe_bf16* xp, const void* ws, size_t ws_bytes) {
-  // xp == NULL: index generation only (for callers that let the GEMMs gather the rows); x is not read then
-  if (!topk_idx || !expert_offsets || !row_token || !slot_row || !ws || (xp && !x)) return MOE_ERR_INVALID;
-  if (T <= 0 || d <= 0 || d % 8 != 0 || E_total <= 0 || k <= 0 || k > E_total) return MOE_ERR_INVALID;
-  if (e_begin < 0 || e_count <= 0 || e_begin + e_count > E_total || e_count > MOE_MAX_EXPERTS) return MOE_ERR_INVALID;
-  if (static_cast<long long>(T) * k > 0x7FFFFFFFll / 2) return MOE_ERR_INVALID;
-  if ((xp && (!moe_aligned16(x) || !moe_aligned16(xp))) || !moe_aligned16(ws) || !moe_aligned16(topk_idx) ||
-      !moe_aligned16(slot_row) || !moe_aligned16(row_token) || !moe_aligned16(expert_offsets))
-    return MOE_ERR_INVALID;
-  if (ws_bytes < moe_permute_workspace_bytes(T, k, e_count)) return MOE_ERR_WORKSPACE;
-  return MOE_OK;
-}
-
-int expert_bits(int e_count) {
-  int nbits = 0;
-  while ((1 << nbits) < e_count) ++nbits;
-  return nbits;
-}
-
 int permute_impl(const moe_bf16* x, const int32_t* topk_idx, const float* topk_w, int T, int d, int E_total, int k,
                  int e_begin, int e_count, int32_t* expert_offsets, int32_t* row_token, int32_t* slot_row,
                  float* row_weight, moe_bf16* xp, void* ws, size_t ws_bytes, void* stream) {
-  const int bad = check_permute_args(x, topk_idx, T, d, E_total, k, e_begin, e_count, expert_offsets, row_token, slot_row,
+  const int bad = moe_check_permute_args(x, topk_idx, T, d, E_total, k, e_begin, e_count, expert_offsets, row_token, slot_row,
                                      xp, ws, ws_bytes);
   if (bad != MOE_OK) return bad;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int n = T * k, nbits = expert_bits(e_count);
+  const int n = T * k, nbits = moe_expert_bits(e_count);
   const int chunk = perm_chunk_pairs(n, e_count), nb = (n + chunk - 1) / chunk;
   int32_t* hist = static_cast<int32_t*>(ws);
   MOE_LAUNCH("permute_count", permute_count_kernel, dim3(nb), dim3(PERM_THREADS), 0, s, topk_idx, n, e_begin, e_count,
@@ -313,11 +313,11 @@ extern "C" int moe_route_permute(const float* logits, const moe_bf16* x, int T, 
                                  moe_bf16* xp, void* ws, size_t ws_bytes, void* stream) {
   if (!logits || !topk_w || !moe_aligned16(logits) || !moe_aligned16(topk_w)) return MOE_ERR_INVALID;
   if (row_weight && !moe_aligned16(row_weight)) return MOE_ERR_INVALID;
-  const int bad = check_permute_args(x, topk_idx, T, d, E_total, k, e_begin, e_count, expert_offsets, row_token, slot_row,
+  const int bad = moe_check_permute_args(x, topk_idx, T, d, E_total, k, e_begin, e_count, expert_offsets, row_token, slot_row,
                                      xp, ws, ws_bytes);
   if (bad != MOE_OK) return bad;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int n = T * k, nbits = expert_bits(e_count);
+  const int n = T * k, nbits = moe_expert_bits(e_count);
   if (moe_launch_route_small(logits, T, E_total, k, renormalize != 0, e_begin, e_count, nbits, topk_idx, topk_w,
                              expert_offsets, row_token, slot_row, row_weight, s)) {
     if (xp) launch_rows(x, slot_row, T, d, k, xp, s);

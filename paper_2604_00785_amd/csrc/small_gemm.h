@@ -56,3 +56,10 @@ struct StreamFwdArgs {
 // rows: rows to expect (only shapes the launch, not the results)
 int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s);
 int moe_stream_down(const StreamFwdArgs& a, long long rows, hipStream_t s);
+
+// A layer's forward pass with at most 64 (token, slot) pairs, rows gathered: Stages 1 to 3 with gate_up in one kernel, and, for a few
+// tokens, down with the combine in another.  The caller has checked the arguments.
+bool moe_small_layer_fits(int T, int E, int k);
+int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s);   // rows: to expect
+bool moe_down_combine_fits(int T, int k);
+int moe_down_combine(const moe_layer* L, hipStream_t s);

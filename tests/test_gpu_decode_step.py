@@ -1,0 +1,69 @@
+"""The forward pass of a few tokens, whose layer call takes kernels that do several stages each: the bits of the stages one by one.
+Sizes on both sides of what those kernels hold: 64 pairs, 16 tokens, two passes of a wave's 8, 4, 2 or 1 lane groups, 4 tokens and 8
+slots for down with the combine, one expert, shares of the experts, odd numbers of column tiles, reductions of any length."""
+import pytest
+import torch
+
+from paper_2604_00785_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("T,d,E,k,f,eb,ec,renorm", [
+    (1, 2048, 64, 8, 1024, 0, 64, 1),
+    (2, 2048, 64, 8, 2048, 0, 64, 1),         # reductions that begin at a step of the expert's in both products
+    (4, 1088, 96, 8, 576, 0, 96, 0),          # two passes of four tokens; the last call of down with the combine
+    (5, 1088, 96, 8, 576, 0, 96, 1),          # ... the first without
+    (4, 576, 20, 9, 192, 0, 20, 1),           # nine slots: not in one kernel
+    (3, 64, 5, 5, 64, 1, 3, 0),               # a share, one step per reduction, four column tiles
+    (4, 320, 8, 1, 448, 0, 8, 1),
+    (1, 192, 1, 1, 128, 0, 1, 1),             # one expert
+    (16, 256, 8, 4, 128, 0, 8, 1),            # 64 pairs, 16 rows of one expert possible
+    (16, 320, 12, 4, 192, 5, 1, 0),           # one local expert of many
+    (17, 320, 12, 3, 192, 0, 12, 1),          # 17 tokens
+    (13, 320, 12, 5, 192, 0, 12, 1),          # 65 pairs
+    (4, 512, 240, 8, 128, 60, 120, 1),        # two passes of two tokens
+    (5, 512, 240, 8, 128, 0, 240, 1),         # ... a third would be needed
+    (2, 448, 300, 8, 64, 299, 1, 0),          # two passes of one token, no or one local row
+    (1, 128, 512, 64, 64, 0, 512, 1),         # 64 slots
+    (2, 128, 130, 8, 64, 129, 1, 1),
+])
+@pytest.mark.parametrize("fold", [False, True])
+@pytest.mark.parametrize("load", ["even", "equal"])
+def test_forward_of_few_tokens(T, d, E, k, f, eb, ec, renorm, fold, load):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T * 1000 + d + E)
+    bf = lambda *s, std=1.0: torch.randn(*s, generator=gen, device=DEV).mul_(std).bfloat16()
+    x, logits = bf(T, d), torch.randn(T, E, generator=gen, device=DEV)
+    if load == "equal":                        # every token has the same experts, and ties among the logits
+        logits[:] = (logits[:1] * 2).round()
+    w = bf(ec, f, d, std=0.03), bf(ec, f, d, std=0.03), bf(ec, d, f, std=0.03)
+    layer = B.MoELayerBuffers(T, d, E, k, f, eb, ec, renorm, DEV, gather=not fold, fold=fold)
+    for again in range(2):                     # the second pass finds what the first one left
+        layer.run_fwd(x, logits, *w)
+    z = lambda *s, dt=torch.int32: torch.zeros(*s, dtype=dt, device=DEV)
+    o = {"topk_idx": z(T, k), "topk_w": z(T, k, dt=torch.float32), "expert_offsets": z(ec + 1), "row_token": z(T * k), "slot_row": z(T, k)}
+    o.update({n: z(T * k, c, dt=torch.bfloat16) for n, c in (("g", f), ("u", f), ("h", f), ("yp", d))}, out=z(T, d, dt=torch.bfloat16))
+    ws = z(max(B.moe_workspace_bytes(T, E, k, d, f), 256), dt=torch.uint8)
+    rw = z(T * k, dt=torch.float32) if fold else None
+    B.moe_route_permute(logits, None, k, renorm, eb, ec, o["topk_idx"], o["topk_w"], o["expert_offsets"], o["row_token"], o["slot_row"],
+                        rw, None, ws)
+    guhy = [o[n] for n in ("g", "u", "h", "yp")]
+    if fold:
+        B.moe_grouped_gemm_fwd_folded(x, o["row_token"], rw, o["expert_offsets"], *w, *guhy)
+        B.moe_unpermute_sum(o["yp"], o["slot_row"], o["out"])
+    else:
+        B.moe_grouped_gemm_fwd_gather(x, o["row_token"], o["expert_offsets"], *w, *guhy)
+        B.moe_unpermute_combine(o["yp"], o["slot_row"], o["topk_w"], o["out"])
+    rows = int(o["expert_offsets"][-1])
+    assert rows == int((o["slot_row"] >= 0).sum())
+    if fold:
+        assert torch.equal(layer.row_weight[:rows], rw[:rows])
+    for n, want in o.items():
+        got = getattr(layer, n)
+        if n in ("row_token", "g", "u", "h", "yp"):   # rows behind the last are nobody's
+            got, want = got[:rows], want[:rows]
+        assert torch.equal(got.view(want.shape), want), n
+        if want.is_floating_point():
+            assert bool(torch.isfinite(want).all()), n
