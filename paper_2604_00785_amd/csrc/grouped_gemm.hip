@@ -1504,20 +1504,24 @@ long long count_tiles(GemmArgs& a, int R_cap) {
 // The model, in units of one K step of a 256-edge tile (1.4 us): a tile costs something fixed (start, epilogue) and something
 // per step.  A launch takes its tiles' sum, spread over the places of the chip, plus one tile of the longest kind, since a list
 // rarely ends evenly; a list alone in its launch also ends on whole rounds.  The row tiles are counted for an even load of
-// the expected rows.  The constants are a fit to 152 layers of 128 to 32768 tokens, d 128 to 4096, f 128 to 2048, 4 to 240
-// experts, even and zipf-like loads (four launches each, timed with both edges): the edge chosen is on average 0.5 % slower than
-// the better one, always 256 16 % slower, always 128 6 %.  Where it is wrong: a share of the experts that holds the large ones of
-// a skewed load (the first 59 of 237 experts, d 1536, f 448, some 39000 rows where 11228 were expected: gate_up 164 / 200 us and dgrad_h 330 / 360
-// with 128 taken), and widths of 192 to 320 under more than 1500 rows per expert (gate_up 171 / 184, dgrad_h 50 / 57 with 128 taken).
+// the expected rows; RAGGED is what the last one of an expert counts for.  The constants are a fit to 7700 of 12900 layers of 64 to 12000
+// tokens, d and f 128 to 4096, 4 to 240 experts, all or a share of them local, even and zipf-like loads (four launches each, timed
+// with both edges); on the others the edge chosen is on average 1.0 % slower than the better one (gate_up 0.9, down 0.7, dgrad_h with dWd 1.1, dgrad_x
+// with dWg and dWu 1.6), always 256 17 % slower, always 128 4 %.  In 4 % of the launches it is wrong by 10 % or more: mostly a share of the
+// experts that holds the large ones of a skewed load, whose rows are far more than expected, and, under 100 rows per expert, weight gradients
+// of narrow layers.  (The constants before, a fit to 152 layers and to slower products where weight rows are multiples of 4096 bytes: 1.25 %
+// on the same layers; a layer's four launches together gain 2 to 7 % in one of twenty, lose 4 % in one of a hundred.  Forward of 1500
+// tokens, d 2048, f 1024, 64 experts, 8 per token 216 -> 200 us, of 2000 tokens, d 1024, f 512, 128 experts 125 -> 110.)
 // Some of them, 256 / 128 in us, gate_up, down, dgrad_h with dWd, dgrad_x with dWg and dWu:
-//   256 tokens, d 128, f 256, 8 experts, 2 per token        13 / 9      12 / 8      19 / 11     16 / 11
-//   248 tokens, d 320, f 320, 28 of 57 experts, 6           22 / 12     17 / 10     31 / 16     29 / 20
-//   7380 tokens, d 512, f 1600, 19 of 39 experts, 2         47 / 62     44 / 36     79 / 60    101 / 93
-//   2048 tokens, d 2048, f 1024, 64 experts, 8             171 / 207    93 / 109   222 / 244   359 / 424
-//   8192 tokens, d 2048, f 1024, 64 experts, 8             471 / 665   258 / 333   555 / 695   914 / 1225
+//   256 tokens, d 128, f 256, 8 experts, 2 per token        11 / 9      10 / 8      16 / 11     13 / 10
+//   248 tokens, d 320, f 320, 28 of 57 experts, 6           13 / 10     11 / 8      15 / 13     23 / 20
+//   7380 tokens, d 512, f 1600, 19 of 39 experts, 2         45 / 59     42 / 34     78 / 57     98 / 87
+//   1500 tokens, d 2048, f 1024, 64 experts, 8             127 / 160    73 / 85    169 / 198   320 / 367
+//   2048 tokens of the same layer                          161 / 209    93 / 110   223 / 254   355 / 425
+//   8192 tokens of the same layer                          444 / 647   248 / 325   554 / 687   893 / 1215
 template <int S> struct TileCost;
-template <> struct TileCost<256> { static constexpr double FIXED = 5.0, STEP = 1.0, SWIGLU_BWD = 16.0; };
-template <> struct TileCost<128> { static constexpr double FIXED = 3.5, STEP = 0.75, SWIGLU_BWD = 10.0; };
+template <> struct TileCost<256> { static constexpr double FIXED = 5.2, WGRAD = 6.0, STEP = 1.0, SWIGLU_BWD = 16.0, RAGGED = 0.5; };
+template <> struct TileCost<128> { static constexpr double FIXED = 2.7, WGRAD = 3.8, STEP = 0.75, SWIGLU_BWD = 9.0, RAGGED = 0.8; };
 struct ListCost { double tiles, each; };
 // rows: routed rows to expect
 template <int MODE, int S>
@@ -1526,18 +1530,18 @@ ListCost list_cost(const GemmArgs& a, double rows) {
   if (is_wgrad(MODE)) {
     const double steps = r / BK + 0.5 > 1.0 ? r / BK + 0.5 : 1.0;
     return {static_cast<double>(a.E) * ceil_div(a.M, S) * ceil_div(a.N, S) * (a.A1 != nullptr ? 2 : 1),
-            TileCost<S>::FIXED + 0.7 * TileCost<S>::STEP * steps};
+            TileCost<S>::WGRAD + 1.1 * TileCost<S>::STEP * steps};
   }
-  const double row_tiles = a.E * (r < 1.0 ? r : 1.0) * (r / S + 0.5 > 1.0 ? r / S + 0.5 : 1.0);
+  const double row_tiles = a.E * (r < 1.0 ? r : 1.0) * (r / S + TileCost<S>::RAGGED > 1.0 ? r / S + TileCost<S>::RAGGED : 1.0);
   return {row_tiles * ceil_div(a.N, MODE == GATE_UP ? S / 2 : S),
-          TileCost<S>::FIXED * (MODE == GATE_UP ? 1.5 : 1.0) + (is_dgrad_h(MODE) ? TileCost<S>::SWIGLU_BWD : 0.0) +
+          TileCost<S>::FIXED + (is_dgrad_h(MODE) ? TileCost<S>::SWIGLU_BWD : 0.0) +
               TileCost<S>::STEP * (a.K / BK) * (MODE == DGRAD_X ? 2 : 1)};
 }
 template <int S> double places() { return static_cast<double>(Tile<S>::PER_CU) * compute_units(); }
 template <int S> double launch_cost(const ListCost& l) {
   const double rounds = l.tiles / places<S>();
   const long long whole = static_cast<long long>(rounds + 0.95);      // a twentieth of a round too many does not count
-  return 0.6 * (0.65 * rounds * l.each + l.each) + 0.4 * (whole < 1 ? 1 : whole) * l.each;
+  return 0.6 * (0.9 * rounds * l.each + l.each) + 0.4 * (whole < 1 ? 1 : whole) * l.each;
 }
 template <int S> double launch_cost(const ListCost& l, const ListCost& m) {
   return 0.65 * (l.tiles * l.each + m.tiles * m.each) / places<S>() + (l.each > m.each ? l.each : m.each);

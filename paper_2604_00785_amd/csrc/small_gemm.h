@@ -7,25 +7,23 @@
 // rows (a token's experts are distinct, so no expert has more rows than there are tokens).  A rank's share may hold the
 // large experts: where R_cap allows more rows and only the expected number is small, both kernels are launched and look
 // at the number of rows on the device; the one that it is not for ends at once.
-// Forward pass, tiled / streaming, in us, other weights in every pass (the tiled side picks its tile size; both sides' results
+// Both forward products, tiled / streaming, in us, other weights in every pass (the tiled side picks its tile size; both sides' results
 // have the same bits):
-//                                             rows per expert  even load    zipf load
-//   d 2048, f 1024, 64 experts, 8 per token           1/8         59 /  33     58 /  32
-//                                                     4          173 / 173    141 / 130
-//                                                     6          189 / 186    156 / 152
-//                                                     8          179 / 179    160 / 170
-//                                                    10          160 / 179    150 / 174
-//   d 1088, f 576, 96 experts, 4 per token            3           88 /  81     54 /  43
-//                                                     8           94 /  90     71 /  78
-//                                                    12           95 /  96     84 /  92
-//   d 512, f 256, 128 experts, 8 per token            2           34 /  34     32 /  26
-//                                                     8           47 /  49     45 /  43
-//                                                    12           42 /  47     42 /  44
-//   d 1024, f 512, 128 experts, 2 per token           6           97 /  96     59 /  59
-//   d 2048, f 1024, 64 experts, 1 per token           6          160 / 164     93 / 108
-//   d 2048, f 1024, the 20 of 240 experts that zipf makes the largest, 8 per token: 32 tokens 67 / 52 and 80 / 77
-// At 6 to 8 rows per expert the order changes with load and shape (tiles up to 16 %, streaming up to 6 % ahead), by nothing known
-// on the host; from 10 on the tiles are ahead.
+//                                             rows per expert  even load    zipf loads
+//   d 2048, f 1024, 64 experts, 8 per token           2        128 / 121     73 / 69, 114 / 83
+//                                                     4        138 / 135    117 / 95, 119 / 106
+//                                                     6        139 / 137    122 / 112, 127 / 119
+//                                                     8        140 / 138    131 / 155, 128 / 145
+//   d 2048, f 1024, 64 experts, 1 per token           7        140 / 137     74 / 73, 81 / 92
+//   d 2048, f 512, 128 experts, 8 per token           8        150 / 143    123 / 114
+//   d 1088, f 576, 96 experts, 4 per token            4         76 / 66      44 / 36
+//                                                     8         76 / 68      48 / 50
+//   d 1024, f 512, 128 experts, 2 per token           8         83 / 78      45 / 43
+//   d 1024, f 1024, 32 experts, 4 per token           8         50 / 41      46 / 40
+//   d 512, f 256, 128 experts, 8 per token            8         26 / 25      27 / 22
+// From 12 on they are even (76 / 76, 82 / 82), at 32 the tiles are ahead (147 / 155, 86 / 92; both with streaming tiles of up to 64 activation
+// rows, which gave nothing below and were taken back).  The 64 experts of f 1024 are 2048 tiles, as many as the chip holds at a time: one expert
+// with more than 16 rows adds a round of waves that each stream alone (64 tokens, one even load in four: 164 us).
 constexpr int STREAM_ROWS = 8, STREAM_TOKENS = 32;
 
 // The 64-deep step with which expert e begins the reduction of a forward product; it goes on to the end and then takes the steps in front
