@@ -335,6 +335,7 @@ int moe_router_bwd(const moe_bf16* x, const float* Wr, const float* dlogits, int
  * dyp, row_weight is used).  Sizes, buffers and errors are those of the calls; pointers that the chosen stages and
  * path do not use may be NULL.  A stage that fails leaves the stages before it enqueued.  With FWD and BWD in one call
  * `dout` may be `out` (the gradient of half the squared output): the backward reads what the forward has written.
+ * A forward pass of few tokens runs several stages in one kernel, with the results of the calls one by one.
  */
 enum { MOE_LAYER_PLAIN = 0, MOE_LAYER_GATHER = 1, MOE_LAYER_FOLD = 2 };
 enum { MOE_LAYER_ROUTER = 1, MOE_LAYER_FWD = 2, MOE_LAYER_BWD = 4, MOE_LAYER_ROUTER_BWD = 8 };

@@ -248,7 +248,7 @@ int launch_fwd_any(const StreamFwdArgs& a, long long rows, hipStream_t s, const 
 // ---- A decoding step of a few sequences in two launches -------------------------------------------------------------------
 // At most 64 (token, slot) pairs.  The layer is then four kernels of a few us (routing, gate_up, down, combine) that each wait for
 // the one before and reach their rate of memory late; here every wave of gate_up routes the tokens by itself, and down also combines.
-// Forward pass in four / two launches (both stream through LDS), us: 1 token of d 4096, f 2048, 8 of 64 experts, 2 per token 20 / 13.6; 2 tokens of
+// Forward pass in four launches that stream through registers / in two that stream through LDS, us: 1 token of d 4096, f 2048, 8 of 64 experts, 2 per token 20 / 13.6; 2 tokens of
 // d 1088, f 576, 96 experts, 4 per token 22.8 / 15.2; 4 of d 512, f 256, 128 experts, 8 per token 20.5 / 15.4; d 2048, f 1024, 64 experts, 8
 // per token: 1, 2, 3, 4 tokens 34 / 29.8, 49 / 43, 65 / 61, 80 / 72.
 
