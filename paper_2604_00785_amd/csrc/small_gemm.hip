@@ -417,11 +417,10 @@ int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s) {
                          L->T, L->E, L->k, L->renormalize != 0, L->e_begin, moe_expert_bits(L->e_count)};
   StreamFwdArgs a{};
   a.A = L->x; a.B0 = L->Wg; a.B1 = L->Wu; a.O0 = L->g; a.O1 = L->u; a.O2 = L->h; a.E = L->e_count; a.K = L->d; a.N = L->f;
-  // the lane groups of moe_route (same bits)
-  if (L->E <= 8) launch_route_gate_up<8, 1>(r, a, rows, s);
-  else if (L->E <= 16) launch_route_gate_up<8, 2>(r, a, rows, s);
-  else if (L->E <= 32) launch_route_gate_up<8, 4>(r, a, rows, s);
-  else if (L->E <= 64) launch_route_gate_up<8, 8>(r, a, rows, s);
+  // the lane groups of moe_route (same bits).  Up to 64 experts one variant with eight logits per lane, those past the last expert left out:
+  // with four per lane (17 to 32 experts) the streaming behind the routing took twice as long (2 tokens of d 2432, f 640, 21
+  // experts: 35.1 us, 20.7 so, 25.7 in four launches), for a reason not found in its code.
+  if (L->E <= 64) launch_route_gate_up<8, 8>(r, a, rows, s);
   else if (L->E <= 128) launch_route_gate_up<16, 8>(r, a, rows, s);
   else if (L->E <= 256) launch_route_gate_up<32, 8>(r, a, rows, s);
   else launch_route_gate_up<64, 8>(r, a, rows, s);
