@@ -323,7 +323,7 @@ struct TileState {
   bool few;                     // tiles of 128: takes few_rows_loop, whose ring lies across the slots of the other tiles and the shares of
                                 // the waves: only in a list with no more tiles than workgroups, the first of its launch
   bool second;                  // tile of the second weight gradient of a pair
-  int nk, nk_phase;             // K steps in total / in the first K phase, or in front of the wrap of a rotated reduction
+  int nk, nk_phase;             // K steps in total / in the first K phase
   int nmain, p0;                // steps in front of the last three; ring phase of step 0
   int k_lo, k_hi;               // weight gradients: the expert's row range is the reduction
   bool last_partial;            // weight gradients: the last step holds fewer than 64 rows
@@ -332,7 +332,7 @@ struct TileState {
   int tokn[Tile<S>::NL];        // gathered operand: tokens of the lane's reduction rows of a coming step
   const char* sa_next;          // scalar bases of the next A / B tile to load (LOAD_BIAS low)
   const char* sb_next;
-  const char* sa_phase1;        // DGRAD_X: bases of the second K phase; ROTATED: of the reduction's beginning, which its last steps are
+  const char* sa_phase1;        // DGRAD_X: bases of the second K phase
   const char* sb_phase1;
   size_t a_step, b_step;        // bytes per step
   const int32_t* row_tok;       // gathered operand: token of the expert's first reduction row onwards
@@ -353,7 +353,6 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
 
   constexpr bool A_KN = is_wgrad(MODE);                                           // stored [k][m]
   constexpr bool B_KN = (is_wgrad(MODE) || is_dgrad_h(MODE) || MODE == DGRAD_X);  // stored [k][n]
-  constexpr bool ROTATED = (MODE == GATE_UP || MODE == DOWN);                      // see first_k_step
   constexpr bool GATHER_B = (MODE == WGRAD_GATHER);
   constexpr bool GATHER_A = (MODE == WGRAD_GATHER_A);
 
@@ -552,12 +551,6 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   t.sa_phase1 = nullptr;
   t.sb_phase1 = nullptr;
   if constexpr (MODE == DGRAD_X) { t.sa_phase1 = scalarize(abase + a_phase - LOAD_BIAS); t.sb_phase1 = scalarize(bbase + b_phase - LOAD_BIAS); }
-  if constexpr (ROTATED) {
-    const int first = first_k_step(e, a.K);
-    t.sa_phase1 = t.sa_next; t.sb_phase1 = t.sb_next;
-    t.sa_next += first * a_step; t.sb_next += first * b_step;
-    nk_phase = nk - first;
-  }
   t.a_step = a_step; t.b_step = b_step; t.k_lo = k_lo; t.k_hi = k_hi; t.row_tok = row_tok; t.nk = nk; t.nk_phase = nk_phase;
   t.last_partial = is_wgrad(MODE) && ((k_hi - k_lo) % BK) != 0;
   // The last three steps of a tile are copies of their own: the last step that loads (it loads the tile's last
@@ -607,13 +600,13 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
   };
   auto a_end = [&](TileState& t, int kt) __attribute__((always_inline)) {
     t.sa_next += t.a_step;
-    if constexpr (MODE == DGRAD_X || ROTATED) {
+    if constexpr (MODE == DGRAD_X) {
       if (kt + 1 == t.nk_phase) t.sa_next = t.sa_phase1;
     }
   };
   auto b_end = [&](TileState& t, int kt) __attribute__((always_inline)) {
     t.sb_next += t.b_step;
-    if constexpr (MODE == DGRAD_X || ROTATED) {
+    if constexpr (MODE == DGRAD_X) {
       if (kt + 1 == t.nk_phase) t.sb_next = t.sb_phase1;
     }
   };

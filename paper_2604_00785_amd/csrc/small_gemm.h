@@ -26,15 +26,6 @@
 // with more than 16 rows adds a round of waves that each stream alone (64 tokens, one even load in four: 164 us).
 constexpr int STREAM_ROWS = 8, STREAM_TOKENS = 32;
 
-// The 64-deep step with which expert e begins the reduction of a forward product; it goes on to the end and then takes the steps in front
-// of it.  Where a weight row is a multiple of 4096 bytes, workgroups that run in step would otherwise all read the same 128 bytes of
-// their rows' 4096 at a time, and those lie in a fraction of the memory channels.  By the expert alone, so that every kernel and
-// tile size sums a row in the same order.  Weights read by gate_up (E 64), TB/s, from the beginning -> rotated: K 2048, 64 rows per expert
-// 4.25 -> 5.33, 192 rows 3.75 -> 4.49; K 4096 4.32 -> 5.82 and 3.89 -> 4.98; from 264 rows on, where the matrix pipe bounds, no
-// difference.  With other K nothing is to be gained (1024, 1536, 1792, 2304, 3072, 3584: 4.8 to 5.3 either way), nor in the products
-// with weights stored [K][N], whose steps read whole rows.
-__device__ __forceinline__ int first_k_step(int e, int K) { return K % 2048 == 0 ? e * 11 % 32 : 0; }
-
 // One grouped product out[r] = act[r] . W[e]^T (weights [N][K], K contiguous), or the pair gate/up with the
 // SwiGLU epilogue.  E, K, N as in GemmArgs; row_token / row_weight may be null.
 struct StreamFwdArgs {

@@ -14,7 +14,7 @@
 // TB/s.  Same card, whole forward pass, d 2048, f 1024, 64 experts, registers -> LDS: one token 34 -> 30 us with the kernels below, 16 tokens
 // 137-150 -> 132 us, 48 tokens 152 -> 147 us; 24 tokens of d 1088, f 576, 96 experts 59 -> 54 us.)
 //
-// A wave takes the WHOLE reduction in its order (see first_k_step) and so gives the bits of the tiled kernel: a row's result does not depend
+// A wave takes the WHOLE reduction in its order and so gives the bits of the tiled kernel: a row's result does not depend
 // on how many rows the call has.  Splitting the reduction over four waves rounds differently; it was 2-6 % faster at 8 to 32
 // tokens of d 2048, f 1024, 64 experts, 10 % with 8 experts of d 4096, and up to 15 % slower elsewhere (narrow experts,
 // skewed loads).
@@ -90,17 +90,16 @@ typedef const __attribute__((address_space(3))) bf16x8_t* LdsFrag;
 __device__ __forceinline__ uint32_t st_lane_piece(int lane) { return static_cast<uint32_t>(((lane & 7) - (lane >> 3)) & 7) * 16u; }
 
 // Streams the FR fragments of 16 weight rows at wb (lane offsets wl of rows 0-7 and 8-15) against the activation rows at xb (xl; XL = 1:
-// eight rows stand for all sixteen) and adds the products to acc: np pieces of the reduction, beginning with piece `first`.
+// eight rows stand for all sixteen) and adds the products to acc: np pieces of the reduction.
 // RING - 1 pieces are in flight; nobody but the wave touches its ring, so there is no barrier.
 template <int FR, int XL, int RING>
 __device__ __forceinline__ void st_stream(const char* const (&wb)[FR], const uint32_t (&wl)[2], const char* xb, const uint32_t (&xl)[XL],
-                                          int np, int first, const char* ring, f32x4_t (&acc)[FR]) {
+                                          int np, const char* ring, f32x4_t (&acc)[FR]) {
   constexpr int LOADS = 2 * FR + XL, BYTES = st_piece_bytes<FR, XL>();
   const int lane = threadIdx.x & 63, i16 = lane & 15, g4 = lane >> 4;
   const uint32_t lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<size_t>(LDS_PTR(ring))));
   auto load = [&](int p, int slot) __attribute__((always_inline)) {
-    p += first;
-    const int ko = (p < np ? p : p - np) * (ST_KB * 2);
+    const int ko = p * (ST_KB * 2);
     uint32_t at = lds + slot * BYTES;
     auto rows = [&](const char* base, const uint32_t* off, int n) __attribute__((always_inline)) {
       base += ko;
@@ -155,7 +154,7 @@ __device__ __forceinline__ void st_fwd_tile(const StreamFwdArgs& a, const StTile
   const int i16 = lane & 15, g4 = lane >> 4;
   const int K = a.K;
   const int n0 = t.col * (16 * NBC);
-  const int np = K / ST_KB, first = first_k_step(t.e, K);
+  const int np = K / ST_KB;
 
   f32x4_t acc[FR];
 #pragma unroll
@@ -179,7 +178,7 @@ __device__ __forceinline__ void st_fwd_tile(const StreamFwdArgs& a, const StTile
     xl[i] = row * static_cast<uint32_t>(K) * 2u + st_lane_piece(lane);
   }
   const char* xb = reinterpret_cast<const char*>(a.A + (row_token != nullptr ? 0 : static_cast<size_t>(t.m0) * K));
-  st_stream<FR, 2, RING>(wb, wl, xb, xl, np, first, lds + wave * (RING * st_piece_bytes<FR, 2>()), acc);
+  st_stream<FR, 2, RING>(wb, wl, xb, xl, np, lds + wave * (RING * st_piece_bytes<FR, 2>()), acc);
   __syncthreads();                                      // every wave is done with its ring
   f32x4_t* const part = reinterpret_cast<f32x4_t*>(lds);
   // the fragments' sums meet in LDS, where a lane of the epilogue finds its neighbouring columns
@@ -371,7 +370,7 @@ __global__ __launch_bounds__(ST_DOWN_SLOTS * MOE_WAVE) void down_combine_kernel(
                             static_cast<uint32_t>((8 + (lane >> 3)) * a.K) * 2u + st_lane_piece(lane)};
     const uint32_t xl[1] = {st_lane_piece(lane)};
     st_stream<1, 1, ST_DOWN_RING>(wb, wl, reinterpret_cast<const char*>(a.h + static_cast<size_t>(row) * a.K), xl, a.K / ST_KB,
-                                  first_k_step(e, a.K), lds + slot * (ST_DOWN_RING * st_piece_bytes<1, 1>()), acc);
+                                  lds + slot * (ST_DOWN_RING * st_piece_bytes<1, 1>()), acc);
     if (i16 == 0) {
       typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
       const u32x2 y = {pack_bf16(acc[0][0], acc[0][1]), pack_bf16(acc[0][2], acc[0][3])};
