@@ -22,8 +22,8 @@ bool combine_in_one(const moe_layer* L) {
          !overlap(L->out, out, L->dgate, static_cast<size_t>(L->T) * L->k * sizeof(float));
 }
 // Whether the forward pass may take the kernels that do several of its stages (moe_route_gate_up): a small call, rows gathered, that none of
-// the stages would refuse, and no output of theirs lies where another workgroup still reads (the stages by themselves have
-// read their inputs when the next one writes).
+// the stages would refuse, and no output of one stage lies where another workgroup still reads for a stage before it, or over an output of
+// a later stage (the stages by themselves have read their inputs when the next one writes, and the later one's results stay).
 bool fwd_in_two(const moe_layer* L) {
   if (L->path == MOE_LAYER_PLAIN || !moe_small_layer_fits(L->T, L->E, L->k)) return false;
   if (moe_check_permute_args(nullptr, L->topk_idx, L->T, L->d, L->E, L->k, L->e_begin, L->e_count, L->expert_offsets, L->row_token,
@@ -33,18 +33,28 @@ bool fwd_in_two(const moe_layer* L) {
   const void* used[] = {L->logits, L->topk_w, L->x, L->Wg, L->Wu, L->Wd, L->g, L->u, L->h, L->yp};
   if (L->path == MOE_LAYER_FOLD && (!L->row_weight || !moe_aligned16(L->row_weight))) return false;
   for (const void* p : used) if (!p || !moe_aligned16(p)) return false;
-  const size_t pairs = static_cast<size_t>(L->T) * L->k, logits = sizeof(float) * L->T * L->E, rows = pairs * L->f * sizeof(moe_bf16);
-  const void* words[] = {L->topk_idx, L->topk_w, L->row_token, L->slot_row, L->row_weight};
-  for (const void* p : words) if (p && overlap(L->logits, logits, p, 4 * pairs)) return false;
-  for (const void* p : {L->g, L->u, L->h}) if (overlap(L->logits, logits, p, rows)) return false;
-  return !overlap(L->logits, logits, L->expert_offsets, sizeof(int32_t) * (L->e_count + 1));
+  const size_t pairs = static_cast<size_t>(L->T) * L->k, rows = pairs * L->f * sizeof(moe_bf16);
+  const size_t weights = sizeof(moe_bf16) * L->e_count * L->f * L->d;
+  struct Range { const void* p; size_t bytes; };
+  const Range routed[] = {{L->topk_idx, 4 * pairs}, {L->topk_w, 4 * pairs}, {L->row_token, 4 * pairs}, {L->slot_row, 4 * pairs},
+                          {L->path == MOE_LAYER_FOLD ? L->row_weight : L->topk_w, 4 * pairs},
+                          {L->expert_offsets, sizeof(int32_t) * (L->e_count + 1)}};
+  const Range logits = {L->logits, sizeof(float) * L->T * L->E}, products[] = {{L->g, rows}, {L->u, rows}, {L->h, rows}};
+  const Range read[] = {logits, {L->x, sizeof(moe_bf16) * L->T * L->d}, {L->Wg, weights}, {L->Wu, weights}};
+  const auto meet = [](const Range& a, const Range& b) { return overlap(a.p, a.bytes, b.p, b.bytes); };
+  for (const Range& o : routed) {
+    for (const Range& q : products) if (meet(o, q)) return false;
+    for (const Range& q : read) if (meet(o, q)) return false;
+  }
+  for (const Range& o : products) if (meet(o, logits)) return false;
+  return true;
 }
 bool down_and_combine_in_one(const moe_layer* L) {
   if (!moe_down_combine_fits(L->T, L->k) || !L->out || !moe_aligned16(L->out)) return false;
   const size_t pairs = static_cast<size_t>(L->T) * L->k, out = sizeof(moe_bf16) * L->T * L->d;
   return !overlap(L->out, out, L->h, pairs * L->f * sizeof(moe_bf16)) && !overlap(L->out, out, L->yp, pairs * L->d * sizeof(moe_bf16)) &&
-         !overlap(L->out, out, L->Wd, sizeof(moe_bf16) * L->e_count * L->d * L->f) && !overlap(L->out, out, L->topk_idx, 4 * pairs) &&
-         !overlap(L->out, out, L->slot_row, 4 * pairs) && !overlap(L->out, out, L->topk_w, 4 * pairs);
+         !overlap(L->out, out, L->Wd, sizeof(moe_bf16) * L->e_count * L->d * L->f) && !overlap(L->out, out, L->slot_row, 4 * pairs) &&
+         !overlap(L->out, out, L->expert_offsets, sizeof(int32_t) * (L->e_count + 1)) && !overlap(L->out, out, L->topk_w, 4 * pairs);
 }
 }  // namespace
 

@@ -341,10 +341,10 @@ __global__ __launch_bounds__(256 / FR) void route_gate_up_kernel(StRouteArgs r, 
 // of f 512 47.0 / 45.9).  Two waves per tile and rings of three pieces in gate_up beyond 512 tiles: 71.3 us with 4 tokens of d 2048.
 struct StDownArgs {
   const uint16_t *h, *Wd;
-  const int32_t *topk_idx, *slot_row;
+  const int32_t *offsets, *slot_row;
   const float* topk_w;          // null: rows of h carry their weights
   uint16_t *yp, *out;
-  int T, k, e_begin, K, N;
+  int T, k, E, K, N;
 };
 constexpr int ST_DOWN_SLOTS = 8, ST_DOWN_RING = 6;
 __global__ __launch_bounds__(ST_DOWN_SLOTS * MOE_WAVE) void down_combine_kernel(StDownArgs a) {
@@ -357,13 +357,20 @@ __global__ __launch_bounds__(ST_DOWN_SLOTS * MOE_WAVE) void down_combine_kernel(
   const int per = 8 * a.T, col = blockIdx.x / per * 8 + (blockIdx.x & 7), t = blockIdx.x % per >> 3;
   if (col >= a.N / 16) return;
   const int n0 = col * 16, pair = t * a.k + slot;
+  const int end = lane < a.E ? a.offsets[lane + 1] : 0x7FFFFFFF;
   const int row = sfirst(a.slot_row[pair]);
   if (lane == 0) {
     s_row[slot] = row;
     s_w[slot] = a.topk_w != nullptr ? a.topk_w[pair] : 1.f;
   }
   if (row >= 0) {
-    const int e = sfirst(a.topk_idx[pair]) - a.e_begin;
+    // the row's expert, from what the stages read: a caller may have laid topk_idx, which none reads behind the routing, under their results
+    int e = __builtin_popcountll(__ballot(end <= row));
+    for (int x0 = MOE_WAVE; x0 < a.E; x0 += MOE_WAVE) {
+      const int x = x0 + lane;
+      e += __builtin_popcountll(__ballot(x < a.E && a.offsets[x + 1] <= row));
+    }
+    e = sfirst(e);
     f32x4_t acc[1] = {f32x4_t{0.f, 0.f, 0.f, 0.f}};
     const char* const wb[1] = {reinterpret_cast<const char*>(a.Wd + (static_cast<size_t>(e) * a.N + n0) * a.K)};
     const uint32_t wl[2] = {static_cast<uint32_t>((lane >> 3) * a.K) * 2u + st_lane_piece(lane),
@@ -429,8 +436,8 @@ int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s) {
 bool moe_down_combine_fits(int T, int k) { return T <= 4 && k <= ST_DOWN_SLOTS; }
 
 int moe_down_combine(const moe_layer* L, hipStream_t s) {
-  const StDownArgs a = {L->h, L->Wd, L->topk_idx, L->slot_row, L->path == MOE_LAYER_FOLD ? nullptr : L->topk_w, L->yp, L->out,
-                        L->T, L->k, L->e_begin, L->f, L->d};
+  const StDownArgs a = {L->h, L->Wd, L->expert_offsets, L->slot_row, L->path == MOE_LAYER_FOLD ? nullptr : L->topk_w, L->yp, L->out,
+                        L->T, L->k, L->e_count, L->f, L->d};
   const int cols = (L->d / 16 + 7) / 8 * 8;
   MOE_LAUNCH("down+combine", down_combine_kernel, dim3(cols * L->T), dim3(L->k * MOE_WAVE), 0, s, a);
   return moe_check_launch();

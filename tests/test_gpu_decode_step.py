@@ -67,3 +67,39 @@ def test_forward_of_few_tokens(T, d, E, k, f, eb, ec, renorm, fold, load):
         assert torch.equal(got.view(want.shape), want), n
         if want.is_floating_point():
             assert bool(torch.isfinite(want).all()), n
+
+
+# Buffers that share memory where the stages one by one allow it, since one of them is done with when the other is written: `a` is laid at
+# the start of `b`.  1 to 4 tokens take both kernels of several stages, 16 the first, unless the memory that is shared forbids it.
+@pytest.mark.parametrize("T", [1, 4, 16])
+@pytest.mark.parametrize("a,b", [
+    ("topk_idx", "g"), ("topk_idx", "u"), ("topk_idx", "h"), ("topk_idx", "yp"), ("topk_idx", "out"), ("topk_idx", "row_token"),
+    ("topk_idx", "slot_row"), ("topk_w", "g"), ("topk_w", "h"), ("topk_w", "yp"), ("row_token", "yp"), ("row_weight", "yp"), ("row_weight", "topk_w"),
+    ("row_token", "out"), ("expert_offsets", "out"), ("logits", "topk_idx"), ("logits", "h"), ("logits", "yp"), ("logits", "out"), ("x", "out"), ("x", "yp")])
+@pytest.mark.parametrize("fold", [False, True])
+def test_buffers_that_share_memory(T, a, b, fold):
+    if not fold and (a == "topk_w" or "row_weight" in (a, b)):
+        return                                  # the combine reads topk_w; there is no row_weight
+    E, k, d, f = 24, 4, 320, 192
+    if (a, b) == ("logits", "topk_idx"):
+        E = 4                                   # as long as topk_idx
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T)
+    bf = lambda *s, std=1.0: torch.randn(*s, generator=gen, device=DEV).mul_(std).bfloat16()
+    x, logits = bf(T, d), torch.randn(T, E, generator=gen, device=DEV)
+    w = bf(E, f, d, std=0.05), bf(E, f, d, std=0.05), bf(E, d, f, std=0.05)
+    layers = [B.MoELayerBuffers(T, d, E, k, f, 0, E, 1, DEV, gather=not fold, fold=fold) for _ in range(2)]
+    layers[0].run_fwd(x, logits, *w)
+    m, given = layers[1], {"x": x, "logits": logits}
+    room = getattr(m, b).view(-1).view(torch.uint8)
+    old = given.get(a, getattr(m, a, None))
+    laid = room[:old.numel() * old.element_size()].view(old.dtype).view(old.shape)
+    for again in range(2):
+        if a in given:
+            laid.copy_(given[a])
+            m.run_fwd(*[laid if n == a else given[n] for n in ("x", "logits")], *w)
+        else:
+            setattr(m, a, laid)
+            m.run_fwd(x, logits, *w)
+        torch.cuda.synchronize()
+        assert torch.equal(m.out, layers[0].out)
