@@ -21,11 +21,10 @@ bool combine_in_one(const moe_layer* L) {
   return !overlap(L->out, out, L->dout, out) && !overlap(L->out, out, L->dyp, out * L->k) &&
          !overlap(L->out, out, L->dgate, static_cast<size_t>(L->T) * L->k * sizeof(float));
 }
-// Whether the forward pass may take the kernels that do several of its stages (moe_route_gate_up): a small call, rows gathered, that none of
-// the stages would refuse, and no output of one stage lies where another workgroup still reads for a stage before it, or over an output of
-// a later stage (the stages by themselves have read their inputs when the next one writes, and the later one's results stay).
-bool fwd_in_two(const moe_layer* L) {
-  if (L->path == MOE_LAYER_PLAIN || !moe_small_layer_fits(L->T, L->E, L->k)) return false;
+// Whether the forward pass is one that kernels for several of its stages may take: a small call, rows gathered, that none of the stages
+// would refuse.
+bool few_gathered(const moe_layer* L) {
+  if (L->path == MOE_LAYER_PLAIN || L->T > MOE_JOIN_TOKENS) return false;
   if (moe_check_permute_args(nullptr, L->topk_idx, L->T, L->d, L->E, L->k, L->e_begin, L->e_count, L->expert_offsets, L->row_token,
                              L->slot_row, nullptr, L->ws, L->ws_bytes) != MOE_OK) return false;
   if (L->d % 64 != 0 || L->f <= 0 || L->f % 64 != 0 || static_cast<unsigned long long>(L->T) * L->d * sizeof(moe_bf16) > 0xFFFFFFFFull - 65536)
@@ -33,6 +32,12 @@ bool fwd_in_two(const moe_layer* L) {
   const void* used[] = {L->logits, L->topk_w, L->x, L->Wg, L->Wu, L->Wd, L->g, L->u, L->h, L->yp};
   if (L->path == MOE_LAYER_FOLD && (!L->row_weight || !moe_aligned16(L->row_weight))) return false;
   for (const void* p : used) if (!p || !moe_aligned16(p)) return false;
+  return true;
+}
+// Routing with gate_up: worth it, and no output of one lies where another workgroup still reads for the other, or over the other's outputs
+// (the stages by themselves have read their inputs when the next one writes, and the later one's results stay).
+bool route_and_gate_up_in_one(const moe_layer* L) {
+  if (!moe_route_gate_up_fits(L->T, L->E, L->k, L->e_count, L->f)) return false;
   const size_t pairs = static_cast<size_t>(L->T) * L->k, rows = pairs * L->f * sizeof(moe_bf16);
   const size_t weights = sizeof(moe_bf16) * L->e_count * L->f * L->d;
   struct Range { const void* p; size_t bytes; };
@@ -49,8 +54,9 @@ bool fwd_in_two(const moe_layer* L) {
   for (const Range& o : products) if (meet(o, logits)) return false;
   return true;
 }
-bool down_and_combine_in_one(const moe_layer* L) {
-  if (!moe_down_combine_fits(L->T, L->k) || !L->out || !moe_aligned16(L->out)) return false;
+// down with the combine: worth it, and `out` lies nowhere that another workgroup still reads.
+bool down_and_combine_in_one(const moe_layer* L, long long rows) {
+  if (!moe_down_combine_fits(L->T, L->k, L->d, L->f, rows) || !L->out || !moe_aligned16(L->out)) return false;
   const size_t pairs = static_cast<size_t>(L->T) * L->k, out = sizeof(moe_bf16) * L->T * L->d;
   return !overlap(L->out, out, L->h, pairs * L->f * sizeof(moe_bf16)) && !overlap(L->out, out, L->yp, pairs * L->d * sizeof(moe_bf16)) &&
          !overlap(L->out, out, L->Wd, sizeof(moe_bf16) * L->e_count * L->d * L->f) && !overlap(L->out, out, L->slot_row, 4 * pairs) &&
@@ -73,36 +79,42 @@ extern "C" int moe_layer_run(const moe_layer* L, int what, void* stream) {
     if ((rc = moe_router_fwd(L->x, L->Wr, T, d, E, L->logits, stream)) != MOE_OK) return rc;
   }
   if (what & MOE_LAYER_FWD) {
-    bool combined = false;
-    if (fwd_in_two(L)) {
-      hipStream_t s = static_cast<hipStream_t>(stream);
-      if ((rc = moe_route_gate_up(L, rows, s)) != MOE_OK) return rc;
-      combined = !both && down_and_combine_in_one(L);
-      if (combined) {
-        rc = moe_down_combine(L, s);
-      } else {
-        StreamFwdArgs q{};
-        q.A = L->h; q.offsets = L->expert_offsets; q.B0 = L->Wd; q.O0 = L->yp; q.E = nl; q.K = f; q.N = d; q.max_rows = R_cap;
-        rc = moe_stream_down(q, rows, s);
-      }
-      if (rc != MOE_OK) return rc;
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    const bool few = few_gathered(L), front = few && route_and_gate_up_in_one(L);
+    const bool back = few && !both && down_and_combine_in_one(L, rows);
+    if (front) {
+      rc = moe_route_gate_up(L, rows, s);
     } else {
       rc = moe_route_permute(L->logits, plain ? L->x : nullptr, T, d, E, k, L->renormalize, L->e_begin, nl, L->topk_idx, L->topk_w,
                              L->expert_offsets, L->row_token, L->slot_row, fold ? L->row_weight : nullptr,
                              plain ? L->xp : nullptr, L->ws, L->ws_bytes, stream);
-      if (rc != MOE_OK) return rc;
-      if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
-      if (plain)
-        rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, T, d, f, L->g, L->u, L->h,
-                          L->yp, stream);
-      else
-        rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
-                                 R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
+    }
+    if (rc != MOE_OK) return rc;
+    if (fold && (!L->row_weight || !moe_aligned16(L->row_weight))) return MOE_ERR_INVALID;
+    StreamFwdArgs p{}, q{};
+    p.offsets = q.offsets = L->expert_offsets; p.E = q.E = nl; p.max_rows = q.max_rows = R_cap;
+    if (back && !front) {
+      p.A = L->x; p.row_token = L->row_token; p.row_weight = fold ? L->row_weight : nullptr;
+      p.B0 = L->Wg; p.B1 = L->Wu; p.O0 = L->g; p.O1 = L->u; p.O2 = L->h; p.K = d; p.N = f;
+      rc = moe_stream_gate_up(p, rows, s);
       if (rc != MOE_OK) return rc;
     }
+    if (back) {
+      rc = moe_down_combine(L, s);
+    } else if (front) {
+      q.A = L->h; q.B0 = L->Wd; q.O0 = L->yp; q.K = f; q.N = d;
+      rc = moe_stream_down(q, rows, s);
+    } else if (plain) {
+      rc = moe_gemm_fwd(L->xp, nullptr, nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl, R_cap, rows, T, d, f, L->g, L->u, L->h,
+                        L->yp, stream);
+    } else {
+      rc = moe_gemm_fwd_gather(L->x, T, L->row_token, fold ? L->row_weight : nullptr, L->expert_offsets, L->Wg, L->Wu, L->Wd, nl,
+                               R_cap, rows, d, f, L->g, L->u, L->h, L->yp, stream);
+    }
+    if (rc != MOE_OK) return rc;
     // with the backward in the same call the rows of yp are read once, for both
     if (!fold && !L->topk_w) return MOE_ERR_INVALID;
-    if (combined) rc = MOE_OK;
+    if (back) rc = MOE_OK;
     else if (both) rc = moe_combine_both(L->dout, L->yp, L->slot_row, L->topk_w, T, k, d, L->out, L->dyp, L->dgate, stream);
     else if (sparse) rc = moe_combine_sparse(L->yp, L->slot_row, fold ? nullptr : L->topk_w, T, k, d, L->out, "combine", stream);
     else if (fold) rc = moe_unpermute_sum(L->yp, L->slot_row, T, k, d, L->out, stream);

@@ -46,9 +46,12 @@ struct StreamFwdArgs {
 int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s);
 int moe_stream_down(const StreamFwdArgs& a, long long rows, hipStream_t s);
 
-// A layer's forward pass with at most 64 (token, slot) pairs, rows gathered: Stages 1 to 3 with gate_up in one kernel, and, for a few
-// tokens, down with the combine in another.  The caller has checked the arguments.
-bool moe_small_layer_fits(int T, int E, int k);
-int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s);   // rows: to expect
-bool moe_down_combine_fits(int T, int k);
+// A few tokens' forward pass, rows gathered: Stages 1 to 3 with gate_up in one kernel, down with the combine in another, each where it is
+// faster than its parts (the rules stand at the kernels).  The caller has checked the arguments; at MOE_JOIN_TOKENS and below the products
+// stream.
+constexpr int MOE_JOIN_TOKENS = 8;
+static_assert(MOE_JOIN_TOKENS <= STREAM_TOKENS);
+bool moe_route_gate_up_fits(int T, int E, int k, int e_count, int f);
+int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s);   // rows: to expect, here and below
+bool moe_down_combine_fits(int T, int k, int d, int f, long long rows);
 int moe_down_combine(const moe_layer* L, hipStream_t s);

@@ -244,16 +244,16 @@ int launch_fwd_any(const StreamFwdArgs& a, long long rows, hipStream_t s, const 
   return launch_fwd<GATE_UP, 4, 2>(a, s, name);
 }
 
-// ---- A decoding step of a few sequences in two launches -------------------------------------------------------------------
-// At most 64 (token, slot) pairs.  The layer is then four kernels of a few us (routing, gate_up, down, combine) that each wait for
-// the one before and reach their rate of memory late; here every wave of gate_up routes the tokens by itself, and down also combines.
-// Forward pass in four launches that stream through registers / in two that stream through LDS, us: 1 token of d 4096, f 2048, 8 of 64 experts, 2 per token 20 / 13.6; 2 tokens of
-// d 1088, f 576, 96 experts, 4 per token 22.8 / 15.2; 4 of d 512, f 256, 128 experts, 8 per token 20.5 / 15.4; d 2048, f 1024, 64 experts, 8
-// per token: 1, 2, 3, 4 tokens 34 / 29.8, 49 / 43, 65 / 61, 80 / 72.
+// ---- A decoding step of a few sequences in fewer launches -----------------------------------------------------------------
+// The layer is then four kernels of a few us (routing, gate_up, down, combine) that each wait for the one before and reach their rate of
+// memory late; here every wave of gate_up routes the tokens by itself, and down also combines.  Forward pass in us, four launches / routing with gate_up /
+// down with the combine / both (the same products): one token of d 2048, f 1024, 64 experts, 8 per token 33.5 / 31.1 / 31.4 / 29.1; one of d 4096,
+// f 2048, 64 experts, 2 per token 37.2 / 35.1 / 32.1 / 29.7; 2 of d 1088, f 576, 96 experts, 4 per token 21.3 / 18.9 / 18.4 / 16.3; 4 of d 512, f 256,
+// 128 experts, 8 per token 20.1 / 18.7 / 17.3 / 16.1; 8 of d 2048, f 1024, 64 experts, 4 per token 77.4 / 74.2.
 
-// Stages 1 to 3 and gate_up.  A wave routes all tokens (lane groups, selection and sums of route.hip), finds the pairs' rows
-// among its 64 lanes with ballots, as the counting sort does, and takes its tile from there; the last workgroup writes what Stages 1 to 3
-// leave behind.
+// Stages 1 to 3 and gate_up, at most 64 (token, slot) pairs.  A wave routes all tokens (lane groups, selection and sums of route.hip), finds
+// the pairs' rows among its 64 lanes with ballots, as the counting sort does, and takes its tile from there; the last workgroup writes what
+// Stages 1 to 3 leave behind.
 struct StRouteArgs {
   const float* logits;
   int32_t* topk_idx;
@@ -336,9 +336,7 @@ __global__ __launch_bounds__(256 / FR) void route_gate_up_kernel(StRouteArgs r, 
 
 // down and combine.  A workgroup owns a token and 16 output columns, a wave one of the token's slots: it streams the 16 rows of its
 // expert's Wd against the slot's row of h.  The rows of yp are rounded to bf16 (and written) as down does and added in slot order as combine
-// does.  Weights of an expert that several tokens chose are read by each of them: up to four tokens that costs less than the
-// launch (4 tokens, down and combine apart / in one, us: d 512, 128 experts 18.7 / 15.4; d 2048 76.8 / 73.9, with a zipf load 54.6 / 55.3; 128 experts
-// of f 512 47.0 / 45.9).  Two waves per tile and rings of three pieces in gate_up beyond 512 tiles: 71.3 us with 4 tokens of d 2048.
+// does.  Weights of an expert that several tokens chose are read by each of them.
 struct StDownArgs {
   const uint16_t *h, *Wd;
   const int32_t *offsets, *slot_row;
@@ -402,6 +400,7 @@ template <int G, int VPL>
 void launch_route_gate_up(const StRouteArgs& r, const StreamFwdArgs& a, long long rows, hipStream_t s) {
   const int n = r.T * r.k, ncol = a.N / 32;
   const dim3 grid((((n < a.E ? n : a.E) * ncol + 7) & ~7) + 1);
+  // (the deeper ring leaves room for 768 workgroups at a time, the other for 1024: 4 tokens of d 2048 73.9 us with rings of four, 71.3 of three)
   if (st_expected_tiles(rows, a.E, ncol) <= 512)
     MOE_LAUNCH("route+gate_up", (route_gate_up_kernel<G, VPL, 2, 4>), grid, dim3(128), 0, s, r, a);
   else
@@ -409,9 +408,20 @@ void launch_route_gate_up(const StRouteArgs& r, const StreamFwdArgs& a, long lon
 }
 }  // namespace
 
-bool moe_small_layer_fits(int T, int E, int k) {
+// Every workgroup repeats the selection: `rounds` winners one after the other, in each round of workgroups that the chip holds at a time.  Beyond
+// some 8000 of rounds times workgroups that costs more than the launch.  Forward pass in us, apart / joined: 2 tokens, 32 of 294 experts each, d 128,
+// f 1920 (64 rounds, 3840 workgroups) 42 / 133; 4 tokens, 16 of 174, d 320, f 2048 (32, 4096) 37 / 91; 1 token, 64 of 512, d 1024, f 512 (64, 1024)
+// 76 / 104; 8 tokens, 8 of 64, d 2048, f 1024 (8, 2048) 118 / 115; 5 tokens, 8 of 126, 31 local, d 128, f 1920 (16, 1860) 20 / 35.  On 16400 calls
+// of 1 to 16 tokens, 4 to 512 experts, d 128 to 4096, f 128 to 2560, even loads and all tokens alike, those that the rule takes gain 9 % on
+// average, one in 450 loses 5 % or more (the worst 17 %); without the bounds one in 18 did, up to two thirds of its speed.  Beyond 8 tokens a third
+// are slower (2 % faster on average).
+bool moe_route_gate_up_fits(int T, int E, int k, int e_count, int f) {
+  static_assert(MOE_JOIN_TOKENS <= ST_ROWS, "no expert may have more rows than a tile");
+  if (E > MOE_MAX_EXPERTS || T > MOE_JOIN_TOKENS || T * k > MOE_WAVE) return false;
   const int G = E <= 64 ? 8 : E <= 128 ? 16 : E <= 256 ? 32 : 64;   // lanes of a token, as in moe_route
-  return E <= MOE_MAX_EXPERTS && T <= ST_ROWS && T * k <= MOE_WAVE && T <= 2 * (MOE_WAVE / G);
+  const int rounds = (T * G + MOE_WAVE - 1) / MOE_WAVE * k;
+  const long long workgroups = static_cast<long long>(T * k < e_count ? T * k : e_count) * (f / 32);
+  return rounds <= 10 && rounds * workgroups <= 8192;
 }
 
 int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s) { return launch_fwd_any<true>(a, rows, s, "gemm_gate_up"); }
@@ -425,7 +435,8 @@ int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s) {
   a.A = L->x; a.B0 = L->Wg; a.B1 = L->Wu; a.O0 = L->g; a.O1 = L->u; a.O2 = L->h; a.E = L->e_count; a.K = L->d; a.N = L->f;
   // the lane groups of moe_route (same bits).  Up to 64 experts one variant with eight logits per lane, those past the last expert left out:
   // with four per lane (17 to 32 experts) the streaming behind the routing took twice as long (2 tokens of d 2432, f 640, 21
-  // experts: 35.1 us, 20.7 so, 25.7 in four launches), for a reason not found in its code.
+  // experts: 35.1 us, 20.7 so, 25.7 in four launches), for a reason not found in its code.  The other variants do not: on the calls above that the rule takes, joined is
+  // 1.08, 1.09, 1.09 and 1.14 times as fast as apart with lane groups of 8, 16, 32 and 64, and one in 250 or fewer is slower by 5 % or more.
   if (L->E <= 64) launch_route_gate_up<8, 8>(r, a, rows, s);
   else if (L->E <= 128) launch_route_gate_up<16, 8>(r, a, rows, s);
   else if (L->E <= 256) launch_route_gate_up<32, 8>(r, a, rows, s);
@@ -433,7 +444,17 @@ int moe_route_gate_up(const moe_layer* L, long long rows, hipStream_t s) {
   return moe_check_launch();
 }
 
-bool moe_down_combine_fits(int T, int k) { return T <= 4 && k <= ST_DOWN_SLOTS; }
+// The rings fill a compute unit's LDS, so one workgroup per compute unit: a second round of them, or weights read by each of several tokens, cost
+// more than the launch.  And few workgroups with many slots bring all weights through few compute units (rows: to expect, so rows / T local
+// slots per token).  Forward pass in us, apart / joined, routing joined in both: 4 tokens of d 4096, f 2048, 64 experts, 2 per token (1024 workgroups) 76 / 80, all tokens
+// alike 36 / 48; 4 of d 3392, f 1920, 4 per token, 4 experts (848) 37 / 51; 4 of d 1024, f 512, 64 experts, 8 per token (256) 28.5 / 24.9; 1 of d 192, f 2432, 11
+// experts, 8 per token (12) 23.8 / 30.4; 1 of d 2048, f 2048, 240 experts, 120 local, 8 per token (128) 34.2 / 30.5.  On the same calls: 18 % gained
+// on average where the rule takes it, one in 280 loses 5 % or more (the worst 11 %); without the bounds on workgroups one in 11 did, up to a third
+// of its speed.
+bool moe_down_combine_fits(int T, int k, int d, int f, long long rows) {
+  const long long workgroups = static_cast<long long>(T) * (d / 16);
+  return T <= 4 && k <= ST_DOWN_SLOTS && workgroups <= 256 && (rows * f <= 8192ll * T || workgroups >= 128);
+}
 
 int moe_down_combine(const moe_layer* L, hipStream_t s) {
   const StDownArgs a = {L->h, L->Wd, L->expert_offsets, L->slot_row, L->path == MOE_LAYER_FOLD ? nullptr : L->topk_w, L->yp, L->out,

@@ -1,5 +1,5 @@
 """The forward pass of a few tokens, whose layer call takes kernels that do several stages each: the bits of the stages one by one.
-Sizes on both sides of what those kernels hold: 64 pairs, 16 tokens, two passes of a wave's 8, 4, 2 or 1 lane groups, 4 tokens and 8
+Sizes on both sides of what those kernels take: 64 pairs, 8 tokens, ten winners of a wave one after the other, 4 tokens and 8
 slots for down with the combine, one expert, shares of the experts, odd numbers of column tiles, reductions of any length."""
 import pytest
 import torch
@@ -103,3 +103,32 @@ def test_buffers_that_share_memory(T, a, b, fold):
             m.run_fwd(x, logits, *w)
         torch.cuda.synchronize()
         assert torch.equal(m.out, layers[0].out)
+
+
+# Which of the two kernels a call takes, on both sides of the rules: selections in a row times workgroups for the first, one workgroup per compute
+# unit and not all weights through a few of them for the second; each without the other
+@pytest.mark.parametrize("T,d,E,k,f,ec,front,back", [
+    (1, 2048, 64, 8, 1024, 64, True, True),
+    (2, 128, 294, 32, 1920, 294, False, False),       # 64 winners in a row, 3840 workgroups
+    (4, 320, 174, 16, 2048, 174, False, False),
+    (1, 64, 64, 10, 128, 64, True, False), (1, 64, 64, 11, 128, 64, False, False),
+    (8, 64, 64, 8, 512, 64, True, False), (8, 64, 64, 8, 576, 64, False, False), (9, 64, 8, 1, 64, 8, False, False),
+    (4, 64, 240, 5, 128, 240, True, True), (4, 64, 240, 6, 128, 240, False, True),      # two passes of two tokens
+    (4, 1024, 8, 2, 128, 8, True, True), (4, 1088, 8, 2, 128, 8, True, False), (5, 64, 8, 2, 128, 8, True, False),
+    (1, 128, 64, 8, 1024, 64, True, True), (1, 128, 64, 8, 1088, 64, True, False), (1, 128, 64, 8, 1088, 32, True, True),
+])
+@pytest.mark.parametrize("fold", [False, True])
+def test_which_kernels_a_call_takes(T, d, E, k, f, ec, front, back, fold):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(T + d + E)
+    bf = lambda *s, std=1.0: torch.randn(*s, generator=gen, device=DEV).mul_(std).bfloat16()
+    layer = B.MoELayerBuffers(T, d, E, k, f, 0, ec, 1, DEV, gather=not fold, fold=fold)
+    B.moe_prof_enable(True)
+    try:
+        layer.run_fwd(bf(T, d), torch.randn(T, E, generator=gen, device=DEV), bf(ec, f, d, std=0.05), bf(ec, f, d, std=0.05), bf(ec, d, f, std=0.05))
+        torch.cuda.synchronize()
+        names = {n for n, _, _ in B.moe_prof_read()}
+    finally:
+        B.moe_prof_enable(False)
+    assert ("route+gate_up" in names, "down+combine" in names) == (front, back), names
+    assert len(names) == 4 - front - back
