@@ -234,14 +234,27 @@ int launch_fwd(const StreamFwdArgs& a, hipStream_t s, const char* name) {
 // Under an even load rows * E / (rows + E) experts, roughly, have a row.
 long long st_expected_tiles(long long rows, int E, int ncol) { return rows * E / (rows + E) * ncol; }
 // With few tiles for the 256 compute units two waves share a tile and each keeps three pieces in flight; beyond that one wave takes a
-// tile with one piece in flight, and eight of them on a compute unit overlap (20 KB of LDS each).  Forward pass in us, two waves and rings of
-// four pieces / one wave and rings of two: 102 tiles (6 tokens, 8 of 64 experts of d 4096, f 2048, 2 per token) 19.7 / 22.5; 512 tiles (16
-// tokens, d 512, f 256, 128 experts) 28.5 / 30.3; 864 (24 tokens, d 1088, f 576, 96 experts) 57.8 / 54.1; 877 (6 tokens, d 2048) 96.6 / 93.0;
-// 2050 (64 tokens, d 2048) 161 / 148.  One wave and rings of three or four pieces: 157 and 150 at 64 tokens.
+// tile with two pieces in flight, and five of them on a compute unit overlap (30 KB of LDS each).  The number of tiles is that of an even
+// load; a skewed one uses fewer experts, so the second variant must do for few tiles too: rings of two pieces, eight waves on a compute
+// unit, are up to 3 % faster at 770 to 1540 tiles of an even load, and 11 tokens of d 4096, f 2048, 61 experts, 1 per token, zipf load, took 91 us
+// with them and 69 us before.  6300 calls of 1 to 64 tokens, gate_up in each variant, forward time over the best one's, mean and 95th percentile:
+//                          even load: 2 waves, 4 pieces | 1, 2 | 1, 3     zipf load
+//   128 to 255 tiles           1.01 1.04 | 1.27 1.55 | 1.05 1.13     1.00 1.03 | 1.29 1.60 | 1.06 1.15
+//   256 to 383                 1.02 1.04 | 1.17 1.31 | 1.01 1.03     1.01 1.05 | 1.21 1.46 | 1.03 1.12
+//   384 to 512                 1.02 1.05 | 1.08 1.17 | 1.00 1.02     1.02 1.05 | 1.16 1.38 | 1.02 1.09
+//   513 to 768                 1.03 1.06 | 1.04 1.07 | 1.01 1.04     1.02 1.05 | 1.10 1.27 | 1.01 1.05
+//   769 to 1536                1.03 1.07 | 1.01 1.07 | 1.03 1.07     1.03 1.07 | 1.05 1.23 | 1.01 1.05
+//   from 1537                  1.01 1.07 | 1.04 1.08 | 1.01 1.03     1.04 1.11 | 1.02 1.09 | 1.02 1.06
+// (down: the same order, half the differences.)  Where weight rows are multiples of 4096 bytes, waves that run in step read the same few bytes of each,
+// which lie in a fraction of the memory channels; more pieces in flight spread over more of them (from 513 tiles on 1.01 | 1.03 | 1.03 for an even load,
+// 1.02 | 1.07 | 1.02 for a zipf load).  d 2048, f 1024, 64 experts, 8 per token, gate_up in the three variants, forward in us: 16 tokens
+// 151 / 163 / 159, 48 tokens 165 / 177 / 172, 64 tokens 176 / 203 / 182, with a zipf load 156 / 178 / 161 (48 tokens with the same kernels: 147 to 177,
+// by where the weights lie in memory).  The rule is 0.9 % off the best of five variants on average
+// in gate_up and 0.5 % in down, 7 % and 4 % off in one call of a hundred (the line at 512 tiles and rings of two: 1.7 and 1.0 %, 21 and 11 %).
 template <bool GATE_UP>
 int launch_fwd_any(const StreamFwdArgs& a, long long rows, hipStream_t s, const char* name) {
-  if (st_expected_tiles(rows, a.E, a.N / (GATE_UP ? 32 : 64)) <= 512) return launch_fwd<GATE_UP, 2, 4>(a, s, name);
-  return launch_fwd<GATE_UP, 4, 2>(a, s, name);
+  if (st_expected_tiles(rows, a.E, a.N / (GATE_UP ? 32 : 64)) < 384 || a.K % 2048 == 0) return launch_fwd<GATE_UP, 2, 4>(a, s, name);
+  return launch_fwd<GATE_UP, 4, 3>(a, s, name);
 }
 
 // ---- A decoding step of a few sequences in fewer launches -----------------------------------------------------------------

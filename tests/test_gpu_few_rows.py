@@ -123,3 +123,16 @@ def test_one_launch_routing_passes(T, E, k, eb, ec, renorm, gate):
 @pytest.mark.parametrize("renorm,gate", [(0, False), (1, True)])
 def test_one_launch_routing(T, E, k, eb, ec, renorm, gate):
     P.test_route_permute_one_call(T, E, k, eb, ec, renorm, gate)
+
+
+# Both variants of the streaming products on either side of their rule (384 expected tiles; weight rows of a multiple of 4096 bytes), in
+# reductions of 1, 2, 3 and more steps than a ring has pieces: the bits of the tiled kernel
+@pytest.mark.parametrize("d,f", [(2048, 1024), (1984, 1024), (2112, 960), (64, 1024), (128, 1024), (192, 1024), (2048, 64), (2048, 128), (2048, 192),
+                                 (4096, 2048)])
+@pytest.mark.parametrize("form", ["gather", "fold"])
+def test_variants_of_the_streamed_products(d, f, form):
+    T, E, k = 24, 24, 1
+    rows = T * k
+    tiles = rows * E // (rows + E)
+    assert min(abs(tiles * (f // 32) - 384), abs(tiles * (d // 64) - 384)) <= 24 or (d, f) == (4096, 2048)
+    test_streamed_products_have_the_bits_of_the_tiled(T, d, E, k, f, form)
