@@ -427,14 +427,14 @@ void launch_route_gate_up(const StRouteArgs& r, const StreamFwdArgs& a, long lon
 // 76 / 104; 8 tokens, 8 of 64, d 2048, f 1024 (8, 2048) 118 / 115; 5 tokens, 8 of 126, 31 local, d 128, f 1920 (16, 1860) 20 / 35.  On 16400 calls
 // of 1 to 16 tokens, 4 to 512 experts, d 128 to 4096, f 128 to 2560, even loads and all tokens alike, those that the rule takes gain 9 % on
 // average, one in 450 loses 5 % or more (the worst 17 %); without the bounds one in 18 did, up to two thirds of its speed.  Beyond 8 tokens a third
-// are slower (2 % faster on average).
+// are slower (2 % faster on average).  More than two passes of the lane groups over the tokens: 8 tokens, 1 of 266, 33 local, d 1984, f 1728 19.7 / 23.4.
 bool moe_route_gate_up_fits(int T, int E, int k, int e_count, int f) {
   static_assert(MOE_JOIN_TOKENS <= ST_ROWS, "no expert may have more rows than a tile");
   if (E > MOE_MAX_EXPERTS || T > MOE_JOIN_TOKENS || T * k > MOE_WAVE) return false;
   const int G = E <= 64 ? 8 : E <= 128 ? 16 : E <= 256 ? 32 : 64;   // lanes of a token, as in moe_route
-  const int rounds = (T * G + MOE_WAVE - 1) / MOE_WAVE * k;
+  const int passes = (T * G + MOE_WAVE - 1) / MOE_WAVE, rounds = passes * k;
   const long long workgroups = static_cast<long long>(T * k < e_count ? T * k : e_count) * (f / 32);
-  return rounds <= 10 && rounds * workgroups <= 8192;
+  return passes <= 2 && rounds <= 10 && rounds * workgroups <= 8192;
 }
 
 int moe_stream_gate_up(const StreamFwdArgs& a, long long rows, hipStream_t s) { return launch_fwd_any<true>(a, rows, s, "gemm_gate_up"); }

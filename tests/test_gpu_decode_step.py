@@ -114,6 +114,7 @@ def test_buffers_that_share_memory(T, a, b, fold):
     (1, 64, 64, 10, 128, 64, True, False), (1, 64, 64, 11, 128, 64, False, False),
     (8, 64, 64, 8, 512, 64, True, False), (8, 64, 64, 8, 576, 64, False, False), (9, 64, 8, 1, 64, 8, False, False),
     (4, 64, 240, 5, 128, 240, True, True), (4, 64, 240, 6, 128, 240, False, True),      # two passes of two tokens
+    (5, 64, 240, 1, 128, 240, False, False), (2, 64, 300, 1, 128, 300, True, True), (3, 64, 300, 1, 128, 300, False, True),   # a third pass
     (4, 1024, 8, 2, 128, 8, True, True), (4, 1088, 8, 2, 128, 8, True, False), (5, 64, 8, 2, 128, 8, True, False),
     (1, 128, 64, 8, 1024, 64, True, True), (1, 128, 64, 8, 1088, 64, True, False), (1, 128, 64, 8, 1088, 32, True, True),
 ])
