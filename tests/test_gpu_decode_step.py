@@ -4,6 +4,7 @@ slots for down with the combine, one expert, shares of the experts, odd numbers 
 import pytest
 import torch
 
+import test_gpu_layer_buffers as L
 from paper_2604_00785_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -133,3 +134,50 @@ def test_which_kernels_a_call_takes(T, d, E, k, f, ec, front, back, fold):
         B.moe_prof_enable(False)
     assert ("route+gate_up" in names, "down+combine" in names) == (front, back), names
     assert len(names) == 4 - front - back
+
+
+# Logits at the ends of the fp32 range and NaNs through the first kernel: the routing arrays of the stage by itself, bit for bit
+ENDS = [float("inf"), -float("inf"), 3.4028235e38, -3.4028235e38, 1e-45, -1e-45, 0.0, -0.0, 1.0, -1.0]
+
+
+@pytest.mark.parametrize("T,E,k", [(7, 7, 7), (7, 16, 9), (7, 31, 9), (8, 64, 8), (4, 100, 9), (8, 128, 5), (2, 256, 9), (1, 512, 9)])
+@pytest.mark.parametrize("nan", [False, True])
+@pytest.mark.parametrize("fold", [False, True])
+def test_logits_at_the_ends_of_the_range(T, E, k, nan, fold):
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(E + k)
+    values = torch.tensor(ENDS, device=DEV)
+    if nan:
+        bits = [0x7FC00000, 0xFFC00000, 0xFFFFFFFF, 0xFFFFFFFE, 0x7F800001, 0xFF800000, 0x3F800000]
+        values = torch.tensor([b - (1 << 32) if b >> 31 else b for b in bits], dtype=torch.int32, device=DEV).view(torch.float32)
+    logits = values.view(torch.int32)[torch.randint(0, len(values), (T, E), generator=gen, device=DEV)].view(torch.float32)
+    d = f = 64
+    eb, ec = (1, E - 2) if E > 7 else (0, E)
+    x = torch.randn(T, d, generator=gen, device=DEV).bfloat16()
+    w = [torch.randn(ec, 64, 64, generator=gen, device=DEV).mul_(0.05).bfloat16() for _ in range(3)]
+    layer = B.MoELayerBuffers(T, d, E, k, f, eb, ec, 0, DEV, gather=not fold, fold=fold)
+    B.moe_prof_enable(True)
+    try:
+        layer.run_fwd(x, logits, *w)
+        torch.cuda.synchronize()
+        assert "route+gate_up" in {n for n, _, _ in B.moe_prof_read()}
+    finally:
+        B.moe_prof_enable(False)
+    z = lambda *s, dt=torch.int32: torch.zeros(*s, dtype=dt, device=DEV)
+    o = {"topk_idx": z(T, k), "topk_w": z(T, k, dt=torch.float32), "expert_offsets": z(ec + 1), "row_token": z(T * k), "slot_row": z(T, k)}
+    B.moe_route_permute(logits, None, k, 0, eb, ec, *[o[n] for n in o], z(T * k, dt=torch.float32) if fold else None, None, z(1 << 20, dt=torch.uint8))
+    rows = int(o["expert_offsets"][-1])
+    for n, want in o.items():
+        got = getattr(layer, n)
+        if n == "row_token":
+            got, want = got[:rows], want[:rows]
+        assert torch.equal(got.view(torch.int32), want.view(torch.int32)), n
+    assert int(o["topk_idx"].min()) >= 0 and int(o["topk_idx"].max()) < E
+
+
+# The refused backward of test_gpu_layer_buffers.py behind a forward pass of few tokens: both kernels, the first alone (8 tokens)
+@pytest.mark.parametrize("name", ["dout", "dyp", "dgate", "dxp", "dWd"])
+@pytest.mark.parametrize("value", [0, 4])
+@pytest.mark.parametrize("path,T,E,k", [("gather", 1, 24, 4), ("gather", 8, 24, 4), ("fold", 1, 24, 4), ("fold", 8, 24, 4)])
+def test_a_refused_backward_leaves_the_forward_pass_of_few_tokens(path, T, E, k, name, value):
+    L.test_a_refused_backward_leaves_the_forward_pass(path, T, E, k, name, value)

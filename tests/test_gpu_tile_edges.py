@@ -120,3 +120,10 @@ def test_tile_sizes_give_the_same_bits(counts, d, f, form, monkeypatch):
     for other in others:
         for n, a, b in zip(names, other, large):
             assert torch.equal(a.view(torch.int32 if n == "dgate" else torch.int16), b.view(torch.int32 if n == "dgate" else torch.int16)), n
+
+
+# Reductions of 32 and 64 steps and of weight rows that are multiples of 4096 bytes, beside tiles that hold all rows of an expert
+@pytest.mark.parametrize("counts,d,f", [([70, 1, 0, 130, 300], 2048, 64), ([65, 3, 257], 64, 2048), ([40, 129], 4096, 128)])
+@pytest.mark.parametrize("form", ["plain", "gather", "fold"])
+def test_tile_sizes_give_the_same_bits_in_long_reductions(counts, d, f, form, monkeypatch):
+    test_tile_sizes_give_the_same_bits(counts, d, f, form, monkeypatch)
