@@ -42,6 +42,8 @@
  *   Not checked (preconditions): logits finite; topk_idx values in [0, E) and
  *   distinct within a token; expert_offsets non-decreasing, starting at 0 and
  *   ending at most at R_cap.
+ * - A row of g, u, h and yp is a function of its token, its expert's weights and its gate weight alone, bit for bit:
+ *   not of the expert's number, of e_begin and e_count, nor of the other rows of the call.
  * - Calls on different streams may overlap as long as their buffers (including
  *   workspaces) do not.
  */

@@ -724,8 +724,9 @@ __device__ __forceinline__ int gemm_tile_list(const GemmArgs& a, int first_tile)
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(wfrag), "v"(afrag));
   };
 
-  // One 32-deep sub-step: the live MFMAs of fragment set SET, in 2 x 2 blocks of accumulators so that every product shares an operand
-  // with the one before it, now the weights and now the rows.  The chip runs at its power limit here, and operands that were read a
+  // One 32-deep sub-step: the live MFMAs of fragment set SET, in 2 x 2 blocks of accumulators so that within a block every product shares an operand
+  // with the one before it, now the weights and now the rows; from one block to the next of the same pair of rows neither is shared (12 of the 63 steps of a
+  // whole wave's piece).  The chip runs at its power limit here, and operands that were read a
   // moment ago cost less than new ones: with nothing but these MFMAs 1.007 us per K step in this order, 1.041 row by row (one operand held for
   // eight), 1.081 in scattered order; with the loop's reads, loads and barriers 1.225 / 1.256 us, the clock 1.82 / 1.78 GHz.
   // Products of 65536 rows, d 2048, f 1024, 64 experts, row by row -> 2 x 2: gate_up 440 -> 434 us, down of 2048 steps 422 -> 419, dgrad_x 419 -> 412,
@@ -1497,21 +1498,21 @@ long long count_tiles(GemmArgs& a, int R_cap) {
 // The model, in units of one K step of a 256-edge tile (1.4 us): a tile costs something fixed (start, epilogue) and something
 // per step.  A launch takes its tiles' sum, spread over the places of the chip, plus one tile of the longest kind, since a list
 // rarely ends evenly; a list alone in its launch also ends on whole rounds.  The row tiles are counted for an even load of
-// the expected rows; RAGGED is what the last one of an expert counts for.  The constants are a fit to 7700 of 12900 layers of 64 to 12000
+// the expected rows; RAGGED is what the last one of an expert counts for.  The constants are a fit to 7700 layers of 64 to 12000
 // tokens, d and f 128 to 4096, 4 to 240 experts, all or a share of them local, even and zipf-like loads (four launches each, timed
-// with both edges); on the others the edge chosen is on average 1.0 % slower than the better one (gate_up 0.9, down 0.7, dgrad_h with dWd 1.1, dgrad_x
-// with dWg and dWu 1.6), always 256 17 % slower, always 128 4 %.  In 4 % of the launches it is wrong by 10 % or more: mostly a share of the
-// experts that holds the large ones of a skewed load, whose rows are far more than expected, and, under 100 rows per expert, weight gradients
-// of narrow layers.  (The constants before, a fit to 152 layers and to slower products where weight rows are multiples of 4096 bytes: 1.25 %
-// on the same layers; a layer's four launches together gain 2 to 7 % in one of twenty, lose 4 % in one of a hundred.  Forward of 1500
-// tokens, d 2048, f 1024, 64 experts, 8 per token 216 -> 200 us, of 2000 tokens, d 1024, f 512, 128 experts 125 -> 110.)
+// with both edges).  On 26900 others the edge chosen is on average 1.05 % slower than the better one (gate_up 0.8, down 0.7, dgrad_h with dWd 1.05, dgrad_x
+// with dWg and dWu 1.6), always 256 17 % slower, always 128 4 %; constants fitted to these themselves reach 1.0 %.  In 4 % of the launches it is wrong by
+// 10 % or more: under 100 rows per expert weight gradients of narrow layers, and a share of the
+// experts that holds the large ones of a skewed load, whose rows are far more than expected.  (The constants before, a fit to 152 layers, are 1.23 % off
+// on the same 26900, 10 % or more in 5 %; a layer's four launches together gain 2 to 7 % over them in one of twenty, lose 4 % in one of a hundred.)
 // Some of them, 256 / 128 in us, gate_up, down, dgrad_h with dWd, dgrad_x with dWg and dWu:
 //   256 tokens, d 128, f 256, 8 experts, 2 per token        11 / 9      10 / 8      16 / 11     13 / 10
-//   248 tokens, d 320, f 320, 28 of 57 experts, 6           13 / 10     11 / 8      15 / 13     23 / 20
-//   7380 tokens, d 512, f 1600, 19 of 39 experts, 2         45 / 59     42 / 34     78 / 57     98 / 87
-//   1500 tokens, d 2048, f 1024, 64 experts, 8             127 / 160    73 / 85    169 / 198   320 / 367
-//   2048 tokens of the same layer                          161 / 209    93 / 110   223 / 254   355 / 425
-//   8192 tokens of the same layer                          444 / 647   248 / 325   554 / 687   893 / 1215
+//   248 tokens, d 320, f 320, 28 of 57 experts, 6           13 / 11     11 / 9      15 / 13     23 / 19
+//   7380 tokens, d 512, f 1600, 19 of 39 experts, 2         44 / 58     42 / 34     77 / 57     97 / 89
+//   2000 tokens, d 1024, f 512, 128 experts, 8              76 / 83     43 / 46     85 / 112   152 / 164
+//   1500 tokens, d 2048, f 1024, 64 experts, 8             156 / 166    72 / 84    165 / 196   312 / 361
+//   2048 tokens of the same layer                          163 / 204    91 / 110   222 / 245   350 / 422
+//   8192 tokens of the same layer                          470 / 646   263 / 324   557 / 683   876 / 1214
 template <int S> struct TileCost;
 template <> struct TileCost<256> { static constexpr double FIXED = 5.2, WGRAD = 6.0, STEP = 1.0, SWIGLU_BWD = 16.0, RAGGED = 0.5; };
 template <> struct TileCost<128> { static constexpr double FIXED = 2.7, WGRAD = 3.8, STEP = 0.75, SWIGLU_BWD = 9.0, RAGGED = 0.8; };

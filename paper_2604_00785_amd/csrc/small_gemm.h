@@ -7,23 +7,28 @@
 // rows (a token's experts are distinct, so no expert has more rows than there are tokens).  A rank's share may hold the
 // large experts: where R_cap allows more rows and only the expected number is small, both kernels are launched and look
 // at the number of rows on the device; the one that it is not for ends at once.
-// Both forward products, tiled / streaming, in us, other weights in every pass (the tiled side picks its tile size; both sides' results
+// Forward pass in us, tiled / streaming, other weights in every pass (the tiled side picks its tile size; both sides' results
 // have the same bits):
 //                                             rows per expert  even load    zipf loads
-//   d 2048, f 1024, 64 experts, 8 per token           2        128 / 121     73 / 69, 114 / 83
-//                                                     4        138 / 135    117 / 95, 119 / 106
-//                                                     6        139 / 137    122 / 112, 127 / 119
-//                                                     8        140 / 138    131 / 155, 128 / 145
-//   d 2048, f 1024, 64 experts, 1 per token           7        140 / 137     74 / 73, 81 / 92
-//   d 2048, f 512, 128 experts, 8 per token           8        150 / 143    123 / 114
-//   d 1088, f 576, 96 experts, 4 per token            4         76 / 66      44 / 36
-//                                                     8         76 / 68      48 / 50
-//   d 1024, f 512, 128 experts, 2 per token           8         83 / 78      45 / 43
-//   d 1024, f 1024, 32 experts, 4 per token           8         50 / 41      46 / 40
-//   d 512, f 256, 128 experts, 8 per token            8         26 / 25      27 / 22
-// From 12 on they are even (76 / 76, 82 / 82), at 32 the tiles are ahead (147 / 155, 86 / 92; both with streaming tiles of up to 64 activation
-// rows, which gave nothing below and were taken back).  The 64 experts of f 1024 are 2048 tiles, as many as the chip holds at a time: one expert
-// with more than 16 rows adds a round of waves that each stream alone (64 tokens, one even load in four: 164 us).
+//   d 2048, f 1024, 64 experts, 8 per token           2        159 / 150    112 / 99, 108 / 93
+//                                                     4        171 / 161    143 / 125, 143 / 120
+//                                                     6        173 / 164    149 / 135, 150 / 135
+//                                                     8        174 / 166    152 / 142, 153 / 142
+//                                                    12        176 / 168    159 / 170, 163 / 172
+//                                                    16        178 / 184    169 / 183, 173 / 188
+//   d 2048, f 1024, 64 experts, 1 per token           7        175 / 167     92 / 95, 93 / 96
+//   d 2048, f 512, 128 experts, 8 per token           8        186 / 177    153 / 139, 156 / 139
+//   d 1088, f 576, 96 experts, 4 per token            4         87 / 84      55 / 50, 54 / 46
+//                                                     8         89 / 88      69 / 69, 64 / 70
+//   d 1024, f 512, 128 experts, 2 per token           8         95 / 94      54 / 57, 55 / 59
+//   d 1024, f 1024, 32 experts, 4 per token           8         58 / 47      54 / 47, 54 / 47
+//   d 512, f 256, 128 experts, 8 per token            8         46 / 44      45 / 41, 45 / 40
+//   d 2048, f 1024, 240 experts, 8 per token          4        554 / 513    239 / 244, 241 / 243
+//                                                     8        576 / 544    292 / 325, 295 / 329
+// On 10000 calls of 33 to 1024 tokens with 0.7 to 28 rows per expert streaming is 10 % faster on average with an even load at every
+// number of rows up to 10, and 30 % (one row) to 9 % (8 rows) with a zipf load.  Where all experts together are 3000 tiles or more, it is 6 % ahead
+// with an even and 6 % behind with a zipf load at 6 to 8 rows, and nothing known on the host tells them apart.  With fewer than 1600 tiles it stays ahead
+// on average up to 16 rows, with fewer than 512 up to 28; the line is not moved there.
 constexpr int STREAM_ROWS = 8, STREAM_TOKENS = 32;
 
 // One grouped product out[r] = act[r] . W[e]^T (weights [N][K], K contiguous), or the pair gate/up with the

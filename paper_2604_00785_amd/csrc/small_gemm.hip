@@ -11,8 +11,8 @@
 //
 // (Loaded from memory into the registers of the matrix instruction, whose neighbouring lanes hold different rows, each load touches 64
 // lines with 16 bytes: 64 cycles of the compute unit's one address path instead of 16, which bounded a token's products at some 4
-// TB/s.  Same card, whole forward pass, d 2048, f 1024, 64 experts, registers -> LDS: one token 34 -> 30 us with the kernels below, 16 tokens
-// 137-150 -> 132 us, 48 tokens 152 -> 147 us; 24 tokens of d 1088, f 576, 96 experts 59 -> 54 us.)
+// TB/s.  Same card, whole forward pass, d 2048, f 1024, 64 experts, 8 per token, registers -> LDS: 16 tokens 153 -> 145 us, 48 tokens 169 -> 164 us, 64 tokens with
+// a zipf load 166 -> 146 us; 24 tokens of d 1088, f 576, 96 experts 59 -> 56 us; with the joined kernels below one token 34.4 -> 29.2 us.)
 //
 // A wave takes the WHOLE reduction in its order and so gives the bits of the tiled kernel: a row's result does not depend
 // on how many rows the call has.  Splitting the reduction over four waves rounds differently; it was 2-6 % faster at 8 to 32
@@ -413,7 +413,9 @@ template <int G, int VPL>
 void launch_route_gate_up(const StRouteArgs& r, const StreamFwdArgs& a, long long rows, hipStream_t s) {
   const int n = r.T * r.k, ncol = a.N / 32;
   const dim3 grid((((n < a.E ? n : a.E) * ncol + 7) & ~7) + 1);
-  // (the deeper ring leaves room for 768 workgroups at a time, the other for 1024: 4 tokens of d 2048 73.9 us with rings of four, 71.3 of three)
+  // The deeper ring leaves room for 768 workgroups at a time, the other for 1024: from 513 to 1024 expected tiles it is 5 to 9 % slower (8 tokens, 4 each of
+  // 64 experts, d 1024, f 1024 42.2 / 39.2 us), and no faster where weight rows are multiples of 4096 bytes (4 tokens, 8 each, d 2048 75 / 75);
+  // below, even with an even load and 2 to 7 % faster where all tokens are alike.
   if (st_expected_tiles(rows, a.E, ncol) <= 512)
     MOE_LAUNCH("route+gate_up", (route_gate_up_kernel<G, VPL, 2, 4>), grid, dim3(128), 0, s, r, a);
   else
